@@ -27,6 +27,8 @@ constexpr uint32_t kHardBatch = GDPM_HARD_BATCH;  // electron hard events sample
 #define GDPM_REAL_BATCH 22
 #endif
 constexpr uint32_t kRealBatch = GDPM_REAL_BATCH;  // photon interactions sampled together
+constexpr int kAbsorb = 1 << 8;         // a photon to be absorbed where it is (in place of the
+                                        // material of a waiting interaction)
 constexpr uint32_t kRefillMin = 12;     // empty lanes a wavefront refills at once
 constexpr float kMaxEnergy = 1.0e6f;    // MeV; a larger or non-finite energy marks a
                                         // damaged record
@@ -241,6 +243,14 @@ struct RunDev {
     uint32_t* bin[2];          // their re-binning buffers (2 words per queue slot), or null
     uint32_t mask[2];          // capacity - 1
     uint32_t hard[2];          // fill above which a reservation fails
+};
+
+// arguments of the transport kernels
+struct PassArgs {
+    Ctl* ctl;
+    Tables T;
+    RunDev R;
+    int photon_waves;   // fused form: wavefronts of a workgroup that start with photons
 };
 
 }  // namespace gdpm

@@ -36,7 +36,7 @@ hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int r
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
                          const SrcHdr* hdr, int ri);
 hipError_t launch_finish(hipStream_t st, Ctl* ctl, int ri);
-size_t transport_lds_bytes(int ri, const Tables& T, int waves);
+size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds);
 hipError_t transport_lds_optin(size_t bytes);
 hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool solo, bool permuted,
                             Ctl* ctl, const Tables& T, const RunDev& R);
@@ -960,7 +960,7 @@ gdpm_status Engine::step() {
         k.rebin[ri] = !M.fixed && ((ri == 0 ? ctx->rebin_photons : ctx->rebin_electrons) || holders > 1 || lone < 0);
         if (k.rebin[ri]) tm.passes_rebinned++;
         const int tpb = ri == 0 ? k.threads_photon : k.threads;
-        k.lds[ri] = ctx->lds_tables && transport_lds_bytes(ri, T, tpb / 64) <= (size_t)ctx->max_lds;
+        k.lds[ri] = ctx->lds_tables && transport_lds_bytes(ri, T, tpb / 64, true) <= (size_t)ctx->max_lds;
         tm.passes++;
         (ri == 0 ? tm.passes_photon : tm.passes_electron)++;
     }

@@ -61,24 +61,45 @@ GDPM_DEV uint32_t mbcnt(uint64_t m) {
 GDPM_DEV uint64_t ballot(bool p) { return __ballot(p); }
 GDPM_DEV uint32_t first_lane(uint64_t m) { return (uint32_t)(__ffsll((unsigned long long)m) - 1); }
 GDPM_DEV uint32_t bcast(uint32_t v, uint32_t lane) { return __builtin_amdgcn_readlane(v, lane); }
-// device-coherent load of a counter, made wave-uniform
-GDPM_DEV uint32_t load_agent(const uint32_t* p) {
-    return __builtin_amdgcn_readfirstlane(
-        __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
 
 GDPM_DEV double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
-GDPM_DEV uint32_t wave_sum(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+
+// ---------------------------------------------------------------------------
+// address spaces: pointers that come out of structures in memory are generic to
+// the compiler, and a generic access is a FLAT instruction, which waits for every
+// outstanding vector-memory operation and for LDS.  The transport therefore
+// names the space of each access.
+// ---------------------------------------------------------------------------
+#define GDPM_GLOBAL __attribute__((address_space(1)))
+#define GDPM_LDS __attribute__((address_space(3)))
+#define GDPM_CONST __attribute__((address_space(4)))
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+template <class T>
+GDPM_DEV GDPM_GLOBAL T* global_ptr(T* p) { return (GDPM_GLOBAL T*)p; }
+// vector view of a table of float4
+GDPM_DEV const GDPM_GLOBAL f4* global_f4(const float4* p) { return (const GDPM_GLOBAL f4*)p; }
+
+// A wave-uniform pointer the compiler cannot see through: what is read from it
+// afterwards is read here (by scalar loads, from the scalar cache) instead of
+// being kept in scalar registers over the whole loop, where the job's data, the
+// tables' parameters and the generator's round keys were spilled to lanes of
+// vector registers and fetched back one v_readlane each.
+template <class T>
+GDPM_DEV T* reread(T* p) {
+    asm volatile("" : "+s"(p));
+    return p;
 }
 
 // ---------------------------------------------------------------------------
 // Philox4x32-10
 // ---------------------------------------------------------------------------
+GDPM_DEV uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+
 GDPM_DEV void philox(uint32_t k0, uint32_t k1, uint32_t& x0, uint32_t& x1, uint32_t& x2,
                      uint32_t& x3) {
 #pragma unroll
@@ -86,8 +107,8 @@ GDPM_DEV void philox(uint32_t k0, uint32_t k1, uint32_t& x0, uint32_t& x1, uint3
         // one 32x32 -> 64-bit product per multiplier
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)x0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)x2;
-        const uint32_t y0 = (uint32_t)(p1 >> 32) ^ x1 ^ k0;
-        const uint32_t y2 = (uint32_t)(p0 >> 32) ^ x3 ^ k1;
+        const uint32_t y0 = xor3((uint32_t)(p1 >> 32), x1, k0);
+        const uint32_t y2 = xor3((uint32_t)(p0 >> 32), x3, k1);
         x0 = y0;
         x1 = (uint32_t)p1;
         x2 = y2;
@@ -97,102 +118,128 @@ GDPM_DEV void philox(uint32_t k0, uint32_t k1, uint32_t& x0, uint32_t& x1, uint3
     }
 }
 
+// (2 (x >> 9) + 1) 2^-24: exact in single and double precision, inside (0, 1).
+// The fused product and sum are exact, like the two operations apart.
+GDPM_DEV float unit_float(uint32_t x) { return fmaf((float)(x >> 9), 0x1p-23f, 0x1p-24f); }
+
 // A lane's stream: key (k0, k1), counter (hist lo, hist hi, path, draw >> 2);
-// draw d is word d & 3 of its block.  A (block `blk`, next word `i`, 4 = used
-// up) is followed by at most one queued block C (blk + 1, flag `qc`).  Blocks
-// are generated with the wavefront converged: rng_topup once per iteration
-// and at the start of a batch of interactions (A has a word left and C is
-// queued: at least 5 draws, enough for a flight or an electron step, and for
-// a photon interaction, which draws at most 4 with the inverse-CDF Compton
-// sampler).  A lane that still runs out (a rejection loop of an electron hard
-// event) takes the out-of-line path, which costs a whole wavefront's Philox
-// for the few lanes in it.  Blocks are only ever generated in counter order,
-// so the draws are the same whatever is buffered.
+// draw d is word d & 3 of its block.  Blocks are only ever generated in counter
+// order, so the draws are the same whatever is buffered.
+//
+// The transport's generator keeps up to two blocks of a lane in LDS, already
+// converted to uniforms: draw d in word d & 7 of the lane's column (the words of
+// a wavefront are 64 lanes apart, so no access has a bank conflict).  Held in
+// registers, the two blocks took 8 vector registers and every draw a chain of
+// divergent branches to pick its word.  Blocks are generated with the wavefront
+// converged, and only once some lane is short of draws for its next event: then
+// every lane with room gets its next block (rng_topup), so nearly all lanes of
+// the wavefront take part, where generating each lane's block as it came due ran
+// the generator in every iteration for about half of them.
+constexpr uint32_t kRngWords = 8;    // draws buffered per lane
 struct Rng {
     uint32_t hlo, hhi, path;
-    uint32_t blk, i, skip;
-    uint32_t a0, a1, a2, a3;
-    uint32_t c0, c1, c2, c3;
-    bool qc;
+    uint32_t ctr;                    // next draw
+    uint32_t nb;                     // blocks up to nb are generated: draws below 4 nb are buffered
+    GDPM_LDS float* buf;             // the lane's column of the wavefront's LDS slice
+    // draws buffered (negative in a fresh stream that starts inside a block)
+    GDPM_DEV int left() const { return (int)(4u * nb - ctr); }
+    GDPM_DEV float peek(uint32_t ahead) const { return buf[((ctr + ahead) & (kRngWords - 1u)) * 64u]; }
+    // the next draw; the caller has made sure that it is buffered
+    GDPM_DEV float draw() {
+        const float u = peek(0u);
+        ctr += 1u;
+        return u;
+    }
+    GDPM_DEV void fill(uint32_t k0, uint32_t k1) {
+        uint32_t x0 = hlo, x1 = hhi, x2 = path, x3 = nb;
+        // the round keys are formed here, not kept in 18 scalar registers
+        asm volatile("" : "+s"(k0), "+s"(k1));
+        philox(k0, k1, x0, x1, x2, x3);
+        GDPM_LDS float* b = buf + (nb & 1u) * 256u;
+        b[0] = unit_float(x0);
+        b[64] = unit_float(x1);
+        b[128] = unit_float(x2);
+        b[192] = unit_float(x3);
+        nb += 1u;
+    }
+    // at least n <= 4 draws buffered (in the lanes that call it: a divergent branch)
+    GDPM_DEV void ensure(uint32_t n, uint32_t k0, uint32_t k1) {
+        while (left() < (int)n) fill(k0, k1);
+    }
 };
 
 // counter of the next draw
-GDPM_DEV uint32_t rng_ctr(const Rng& r) { return 4u * r.blk + r.i; }
+GDPM_DEV uint32_t rng_ctr(const Rng& r) { return r.ctr; }
 
 // position the stream at draw `ctr` (no block generated yet)
 GDPM_DEV void rng_start(Rng& r, uint32_t hlo, uint32_t hhi, uint32_t path, uint32_t ctr) {
     r.hlo = hlo;
     r.hhi = hhi;
     r.path = path;
-    r.blk = (ctr >> 2) - 1u;  // A is "used up"; the next block is ctr >> 2
-    r.i = 4u;
-    r.skip = ctr & 3u;
-    r.qc = false;
+    r.ctr = ctr;
+    r.nb = ctr >> 2;
 }
 
-__device__ __attribute__((noinline)) uint4 rng_block_slow(uint32_t k0, uint32_t k1, uint32_t hlo,
-                                                         uint32_t hhi, uint32_t path, uint32_t blk) {
-    uint32_t x0 = hlo, x1 = hhi, x2 = path, x3 = blk;
-    philox(k0, k1, x0, x1, x2, x3);
-    return make_uint4(x0, x1, x2, x3);
-}
-
-GDPM_DEV uint4 rng_block(uint32_t k0, uint32_t k1, const Rng& r, uint32_t blk) {
-    uint32_t x0 = r.hlo, x1 = r.hhi, x2 = r.path, x3 = blk;
-    philox(k0, k1, x0, x1, x2, x3);
-    return make_uint4(x0, x1, x2, x3);
-}
-
-// A used up: the next block becomes A (from the queue, else generated here,
-// inline or out of line)
-GDPM_DEV void rng_advance(Rng& r, uint32_t k0, uint32_t k1, bool inline_block) {
-    if (r.qc) {
-        r.a0 = r.c0; r.a1 = r.c1; r.a2 = r.c2; r.a3 = r.c3;
-        r.qc = false;
-    } else {
-        const uint4 b = inline_block ? rng_block(k0, k1, r, r.blk + 1u)
-                                     : rng_block_slow(k0, k1, r.hlo, r.hhi, r.path, r.blk + 1u);
-        r.a0 = b.x; r.a1 = b.y; r.a2 = b.z; r.a3 = b.w;
+// with the wavefront converged: n <= 4 draws in the lanes of `want`; every lane
+// of `live` that holds fewer than two blocks gets one in each turn (a fresh
+// stream may need two)
+GDPM_DEV void rng_topup(Rng& r, bool want, bool live, uint32_t n, uint32_t k0, uint32_t k1) {
+    while (ballot(want && r.left() < (int)n)) {
+        if (live && r.nb - (r.ctr >> 2) < 2u) r.fill(k0, k1);
     }
-    r.blk += 1u;
-    r.i = r.skip;
-    r.skip = 0u;
-}
-
-// queue the next block (C)
-GDPM_DEV void rng_queue(Rng& r, uint32_t k0, uint32_t k1) {
-    const uint4 b = rng_block(k0, k1, r, r.blk + 1u);
-    r.c0 = b.x; r.c1 = b.y; r.c2 = b.z; r.c3 = b.w;
-    r.qc = true;
-}
-
-// make sure A has a word left and C is queued
-GDPM_DEV void rng_topup(Rng& r, uint32_t k0, uint32_t k1) {
-    if (r.i == 4u) rng_advance(r, k0, k1, true);
-    if (!r.qc) rng_queue(r, k0, k1);
-}
-
-// (2 (x >> 9) + 1) 2^-24: exact in single and double precision, inside (0, 1)
-GDPM_DEV float uniform(Rng& r, uint32_t k0, uint32_t k1) {
-    if (r.i == 4u) rng_advance(r, k0, k1, false);
-    const uint32_t w = r.i;
-    const uint32_t x = w == 0u ? r.a0 : (w == 1u ? r.a1 : (w == 2u ? r.a2 : r.a3));
-    r.i = w + 1u;
-    return (float)(x >> 9) * 0x1p-23f + 0x1p-24f;
 }
 
 // path id of the secondary created in role `word` at the parent's current counter
-GDPM_DEV uint32_t spawn_path(const Rng& r, uint32_t k0, uint32_t k1, int word) {
+template <class R>
+GDPM_DEV uint32_t spawn_path(const R& r, uint32_t k0, uint32_t k1, int word) {
     uint32_t x0 = r.hlo, x1 = r.hhi, x2 = r.path, x3 = 0x80000000u | rng_ctr(r);
+    asm volatile("" : "+s"(k0), "+s"(k1));
     philox(k0, k1, x0, x1, x2, x3);
     return word == 0 ? x0 : (word == 1 ? x1 : (word == 2 ? x2 : x3));
 }
+
+// a stream held in registers, for the kernels outside the transport loops (the
+// samplers' and the source's tests)
+struct RegRng {
+    uint32_t hlo, hhi, path, ctr;
+    u4 w;
+    GDPM_DEV RegRng(uint32_t lo, uint32_t hi, uint32_t p) : hlo(lo), hhi(hi), path(p), ctr(0u), w(0u) {}
+    GDPM_DEV void ensure(uint32_t, uint32_t, uint32_t) {}
+    GDPM_DEV float draw(uint32_t k0, uint32_t k1) {
+        const uint32_t i = ctr & 3u;
+        if (i == 0u) {
+            uint32_t x0 = hlo, x1 = hhi, x2 = path, x3 = ctr >> 2;
+            philox(k0, k1, x0, x1, x2, x3);
+            w = u4{x0, x1, x2, x3};
+        }
+        ctr += 1u;
+        return unit_float(i == 0u ? w.x : (i == 1u ? w.y : (i == 2u ? w.z : w.w)));
+    }
+};
+// the samplers draw from either
+GDPM_DEV float uniform(Rng& r, uint32_t, uint32_t) { return r.draw(); }
+GDPM_DEV float uniform(RegRng& r, uint32_t k0, uint32_t k1) { return r.draw(k0, k1); }
+
+// device-coherent load of a counter, made wave-uniform
+GDPM_DEV uint32_t load_agent(const GDPM_GLOBAL uint32_t* p) {
+    return __builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(const_cast<GDPM_GLOBAL uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+template <class T>
+GDPM_DEV T atomic_add(GDPM_GLOBAL T* p, T v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+GDPM_DEV void atomic_or(GDPM_GLOBAL uint32_t* p, uint32_t v) {
+    (void)__hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+GDPM_DEV void atomic_add_f64(GDPM_GLOBAL double* p, double v) { (void)__builtin_amdgcn_global_atomic_fadd_f64(p, v); }
 
 // non-exact division through the hardware reciprocal (about 1 ulp)
 GDPM_DEV float fdiv(float a, float b) { return a * hrcp(b); }
 
 // ---------------------------------------------------------------------------
-// table lookups (linear in log2 E)
+// table lookups (linear in log2 E); a table is given by a pointer into LDS or
+// global memory
 // ---------------------------------------------------------------------------
 GDPM_DEV void grid(float lg, float lo, float inv, int n, int& i, float& t) {
     float f = (lg - lo) * inv;
@@ -201,45 +248,47 @@ GDPM_DEV void grid(float lg, float lo, float inv, int n, int& i, float& t) {
     t = f - (float)i;
 }
 
-GDPM_DEV float4 lerp4(const float4* tab, int i, float t) {
-    const float4 a = tab[i], b = tab[i + 1];
-    return make_float4(fmaf(t, b.x - a.x, a.x), fmaf(t, b.y - a.y, a.y), fmaf(t, b.z - a.z, a.z),
-                       fmaf(t, b.w - a.w, a.w));
+template <class P>
+GDPM_DEV f4 lerp4(P tab, int i, float t) {
+    const f4 a = tab[i], b = tab[i + 1];
+    return f4{fmaf(t, b.x - a.x, a.x), fmaf(t, b.y - a.y, a.y), fmaf(t, b.z - a.z, a.z), fmaf(t, b.w - a.w, a.w)};
 }
 
-GDPM_DEV float lerp1(const float* tab, int i, float t) {
+template <class P>
+GDPM_DEV float lerp1(P tab, int i, float t) {
     const float a = tab[i], b = tab[i + 1];
     return fmaf(t, b - a, a);
 }
 
-GDPM_DEV float4 elec_at(const Tables& T, const float4* etab, int m, float e) {
+// TT: Tables, in any address space
+template <class TT, class P>
+GDPM_DEV f4 elec_at(const TT& T, P etab, int m, float e) {
     int i;
     float t;
     grid(hlog2(e), T.eg_lo, T.eg_inv, T.eg_n, i, t);
     return lerp4(etab + m * T.eg_n, i, t);
 }
-GDPM_DEV float4 elec_at(const Tables& T, int m, float e) { return elec_at(T, T.elec, m, e); }
 
 // energy whose residual range is r (g/cm^2); rtab holds the material's nodes
 // followed (after all materials) by the per-material scales
-GDPM_DEV float range_inv(const Tables& T, const float* rtab, const float* rscale, int m, float r) {
+template <class TT, class P>
+GDPM_DEV float range_inv(const TT& T, P rtab, P rscale, int m, float r) {
     const float f = fminf(hsqrt(fmaxf(r, 0.0f)) * rscale[m], (float)(T.nr - 1));
     const int i = min((int)f, T.nr - 2);
     return lerp1(rtab + m * T.nr, i, f - (float)i);
 }
-GDPM_DEV float range_inv(const Tables& T, int m, float r) {
-    return range_inv(T, T.rinv, T.rinv_scale, m, r);
-}
 
 // screening A of the modified-Wentzel law for t = s / lambda_1 (t < t_iso)
-GDPM_DEV float mw_screening(const Tables& T, float tt) {
+template <class TT>
+GDPM_DEV float mw_screening(const TT& T, float tt) {
     const float f = fminf((hlog2(tt) - T.aw_lo) * T.aw_inv, (float)(T.aw_n - 1));
     const int i = min(max((int)f, 0), T.aw_n - 2);  // f < 0 extrapolates the first cell
-    return hexp2(lerp1(T.aw, i, f - (float)i));
+    return hexp2(lerp1(global_ptr(T.aw), i, f - (float)i));
 }
 
 // modified-Wentzel deflection mu = (1 - cos)/2 for t = s / lambda_1
-GDPM_DEV float mw_mu(const Tables& T, float tt, float u) {
+template <class TT>
+GDPM_DEV float mw_mu(const TT& T, float tt, float u) {
     if (!(tt < kMwIsoF)) return u;
     const float a = mw_screening(T, tt);
     return fdiv(a * u, 1.0f + a - u);
@@ -270,44 +319,51 @@ GDPM_DEV void rotate(float& u, float& v, float& w, float ct, float st, float tur
 
 GDPM_DEV int clampi(int x, int n) { return min(max(x, 0), n - 1); }
 
-GDPM_DEV int voxel_of(const Geom& G, float x, float y, float z, int& ix, int& iy, int& iz) {
-    ix = clampi((int)floorf(x * G.idx), G.nx);
-    iy = clampi((int)floorf(y * G.idy), G.ny);
-    iz = clampi((int)floorf(z * G.idz), G.nz);
-    return ix + G.nx * (iy + G.ny * iz);
+GDPM_DEV int voxel_of(float idx, float idy, float idz, int nx, int ny, int nz, float x, float y, float z, int& ix,
+                      int& iy, int& iz) {
+    ix = clampi((int)floorf(x * idx), nx);
+    iy = clampi((int)floorf(y * idy), ny);
+    iz = clampi((int)floorf(z * idz), nz);
+    return ix + nx * (iy + ny * iz);
+}
+// GG: Geom, in any address space
+template <class GG>
+GDPM_DEV int voxel_of(const GG& G, float x, float y, float z, int& ix, int& iy, int& iz) {
+    return voxel_of(G.idx, G.idy, G.idz, G.nx, G.ny, G.nz, x, y, z, ix, iy, iz);
 }
 
 GDPM_DEV uint32_t pack_vox(int ix, int iy, int iz) {
     return (uint32_t)ix | ((uint32_t)iy << 11) | ((uint32_t)iz << 22);
 }
 
-GDPM_DEV bool outside(const Geom& G, float x, float y, float z) {
-    return !(x >= 0.0f && x < G.lx && y >= 0.0f && y < G.ly && z >= 0.0f && z < G.lz);
+// x in [0, lx) and so on.  For non-negative floats the order of the values is
+// the order of their bits; a negative number's sign bit and a NaN's exponent make
+// it larger than any extent.  (A position of -0 counts as outside; a position is
+// set to a face as +0 or as a product with a non-negative index, and a sum that
+// cancels is +0.)
+template <class GG>
+GDPM_DEV bool inside(const GG& G, float x, float y, float z) {
+    const bool ix = __float_as_uint(x) < __float_as_uint(G.lx);
+    const bool iy = __float_as_uint(y) < __float_as_uint(G.ly);
+    const bool iz = __float_as_uint(z) < __float_as_uint(G.lz);
+    return ix && iy && iz;
 }
 
 // distance to the exit face of voxel (ix, iy, iz) along the direction; axis of that face
-GDPM_DEV float face_dist(const Geom& G, float x, float y, float z, float u, float v, float w,
+template <class GG>
+GDPM_DEV float face_dist(const GG& G, float x, float y, float z, float u, float v, float w,
                          int ix, int iy, int iz, int& ax) {
-    float best = 3.0e38f;
+    const float du = fdiv((float)(u > 0.0f ? ix + 1 : ix) * G.dx - x, u);
+    const float dv = fdiv((float)(v > 0.0f ? iy + 1 : iy) * G.dy - y, v);
+    const float dw = fdiv((float)(w > 0.0f ? iz + 1 : iz) * G.dz - z, w);
+    float best = u != 0.0f ? du : 3.0e38f;
     ax = 0;
-    if (u != 0.0f) {
-        const float d = fdiv((u > 0.0f ? (float)(ix + 1) : (float)ix) * G.dx - x, u);
-        best = d;
-    }
-    if (v != 0.0f) {
-        const float d = fdiv((v > 0.0f ? (float)(iy + 1) : (float)iy) * G.dy - y, v);
-        if (d < best) {
-            best = d;
-            ax = 1;
-        }
-    }
-    if (w != 0.0f) {
-        const float d = fdiv((w > 0.0f ? (float)(iz + 1) : (float)iz) * G.dz - z, w);
-        if (d < best) {
-            best = d;
-            ax = 2;
-        }
-    }
+    const bool by = v != 0.0f && dv < best;
+    best = by ? dv : best;
+    ax = by ? 1 : ax;
+    const bool bz = w != 0.0f && dw < best;
+    best = bz ? dw : best;
+    ax = bz ? 2 : ax;
     return fmaxf(best, 0.0f);
 }
 
@@ -342,6 +398,7 @@ GDPM_DEV int beamlet_of(const SourceDev& S, float u) {
 struct Primary {
     float x, y, z, u, v, w, e;
     int beamlet;
+    uint32_t draws;   // of the history's stream, taken by the source
     bool in;
 };
 
@@ -358,9 +415,9 @@ GDPM_DEV int metropolis_step(const SourceDev& S, float uj, float r, uint32_t& pr
 // chain start: a beamlet drawn with equal probability among those of nonzero
 // intensity, from the chain's own stream (history id (2^32-1) 2^32 + chain)
 GDPM_DEV uint32_t metropolis_start(const SourceDev& S, uint32_t chain, uint32_t k0, uint32_t k1) {
-    Rng r;
-    rng_start(r, chain, 0xFFFFFFFFu, 0u, 0u);
-    const float u = uniform(r, k0, k1);
+    uint32_t x0 = chain, x1 = 0xFFFFFFFFu, x2 = 0u, x3 = 0u;
+    philox(k0, k1, x0, x1, x2, x3);
+    const float u = unit_float(x0);
     return S.nz[min((int)((double)u * (double)S.n_nz), S.n_nz - 1)];
 }
 
@@ -376,14 +433,13 @@ GDPM_DEV float stratified_energy(const SourceDev& S, uint32_t i, uint32_t size, 
     return spectrum_energy(S, (float)(f0 + (double)u * (f1 - f0)));
 }
 
-// section 2.3.3: the history whose stream is r starts as phase-space record
-// h mod n: inside the phantom where it is, outside where its forward ray
+// section 2.3.3: history h starts as phase-space record h mod n: inside the phantom where it is, outside where its forward ray
 // enters (else it escapes); the record number stands in for the beamlet
-GDPM_DEV Primary phase_space_primary(const SourceDev& S, const Geom& G, const Rng& rg) {
-    const unsigned long long h = (unsigned long long)rg.hhi << 32 | rg.hlo;
+GDPM_DEV Primary phase_space_primary(const SourceDev& S, const Geom& G, unsigned long long h) {
     const unsigned long long k = h % S.n_phsp;
     const float* rec = S.phsp + 7 * k;
     Primary p;
+    p.draws = 0u;
     p.beamlet = (int)k;
     p.e = rec[6];
     p.u = rec[3];
@@ -422,23 +478,31 @@ GDPM_DEV Primary phase_space_primary(const SourceDev& S, const Geom& G, const Rn
     return p;
 }
 
-// the primary of the history whose stream is r; `chain` (Metropolis sources
-// only) holds the state of the history's chain and is advanced; rpos and
-// rsize (stratified spectra only) place the history in its round
-GDPM_DEV Primary make_primary(const SourceDev& S, const Geom& G, Rng& r, uint32_t k0, uint32_t k1,
+// the primary of history h; `chain` (Metropolis sources only) holds the state
+// of the history's chain and is advanced; rpos and rsize (stratified spectra
+// only) place the history in its round
+GDPM_DEV Primary make_primary(const SourceDev& S, const Geom& G, unsigned long long h, uint32_t k0, uint32_t k1,
                               uint32_t* chain = nullptr, uint32_t rpos = 0u, uint32_t rsize = 1u) {
-    if (S.n_phsp) return phase_space_primary(S, G, r);
+    if (S.n_phsp) return phase_space_primary(S, G, h);
     Primary p;
-    const float ue = uniform(r, k0, k1);
+    // draws 0-3 of the history's stream, path 0; a Metropolis source takes a fifth
+    uint32_t x0 = (uint32_t)h, x1 = (uint32_t)(h >> 32), x2 = 0u, x3 = 0u;
+    philox(k0, k1, x0, x1, x2, x3);
+    const float ue = unit_float(x0), u1 = unit_float(x1), u2 = unit_float(x2), u3 = unit_float(x3);
     p.e = S.strata ? stratified_energy(S, rpos, rsize, ue) : spectrum_energy(S, ue);
     int gi;
+    float ux = u2, uy = u3;
+    p.draws = 4u;
     if (chain) {
-        const float uj = uniform(r, k0, k1);
-        gi = metropolis_step(S, uj, uniform(r, k0, k1), *chain);
+        uint32_t w0 = (uint32_t)h, w1 = (uint32_t)(h >> 32), w2 = 0u, w3 = 1u;
+        philox(k0, k1, w0, w1, w2, w3);
+        gi = metropolis_step(S, u1, u2, *chain);
+        ux = u3;
+        uy = unit_float(w0);
+        p.draws = 5u;
     } else {
-        gi = beamlet_of(S, uniform(r, k0, k1));
+        gi = beamlet_of(S, u1);
     }
-    const float ux = uniform(r, k0, k1), uy = uniform(r, k0, k1);
     p.beamlet = gi;
     const BeamDev& b = S.beams[S.beam_of[gi]];
     const int j = gi - b.off;
@@ -496,6 +560,17 @@ GDPM_DEV Primary make_primary(const SourceDev& S, const Geom& G, Rng& r, uint32_
     if (ax == 2) p.z = p.w > 0.0f ? 0.0f : G.lz;
     return p;
 }
+// ---------------------------------------------------------------------------
+// arguments of the transport kernels, read from the kernel-argument segment
+// where they are needed (see reread)
+// ---------------------------------------------------------------------------
+typedef const GDPM_CONST PassArgs* Args;
+typedef const GDPM_CONST JobDev* JobPtr;
+GDPM_DEV Args pass_args() { return (Args)__builtin_amdgcn_kernarg_segment_ptr(); }
+// queue control fields that no one writes during a transport pass
+GDPM_DEV const GDPM_CONST RingCtl* ring_const(Args A, int ri) {
+    return &((const GDPM_CONST Ctl*)A->ctl)->ring[ri];
+}
 
 // ---------------------------------------------------------------------------
 // queue reservation and claiming (wave-uniform state)
@@ -512,8 +587,7 @@ struct Reservation {
     bool ok;
 };
 
-GDPM_DEV Reservation reserve(PushState& ps, RingCtl* rc, uint32_t head, uint32_t hard, uint32_t n,
-                             Ctl* ctl) {
+GDPM_DEV Reservation reserve(PushState& ps, Args A, int ri, uint32_t n) {
     Reservation r;
     r.old_next = ps.next;
     r.old_avail = ps.end - ps.next;
@@ -523,12 +597,13 @@ GDPM_DEV Reservation reserve(PushState& ps, RingCtl* rc, uint32_t head, uint32_t
         ps.next += n;
         return r;
     }
+    GDPM_GLOBAL Ctl* ctl = global_ptr(A->ctl);
     const uint32_t leader = first_lane(ballot(true));
     uint32_t base = 0;
-    if (lane_id() == leader) base = atomicAdd(&rc->tail, kPushChunk);
+    if (lane_id() == leader) base = atomic_add(&ctl->ring[ri].tail, kPushChunk);
     base = bcast(base, leader);
-    if (base + kPushChunk - head > hard) {
-        if (lane_id() == leader) atomicOr(&ctl->overflow, 1u);
+    if (base + kPushChunk - ring_const(A, ri)->head > A->R.hard[ri]) {
+        if (lane_id() == leader) atomic_or(&ctl->overflow, 1u);
         r.ok = false;
         ps.next = ps.end;
         return r;
@@ -543,33 +618,17 @@ GDPM_DEV uint32_t slot_of(const Reservation& r, uint32_t j) {
     return j < r.old_avail ? r.old_next + j : r.new_base + (j - r.old_avail);
 }
 
-GDPM_DEV void store(Particle* buf, uint32_t mask, uint32_t slot, const Particle& p) {
-    float4* d = reinterpret_cast<float4*>(buf + (slot & mask));
-    const float4* s = reinterpret_cast<const float4*>(&p);
-    d[0] = s[0];
-    d[1] = s[1];
-    d[2] = s[2];
-    d[3] = s[3];
-}
-
-GDPM_DEV Particle load(const Particle* buf, uint32_t mask, uint32_t slot) {
-    Particle p;
-    const float4* s = reinterpret_cast<const float4*>(buf + (slot & mask));
-    float4* d = reinterpret_cast<float4*>(&p);
-    d[0] = s[0];
-    d[1] = s[1];
-    d[2] = s[2];
-    d[3] = s[3];
-    return p;
+GDPM_DEV GDPM_GLOBAL f4* record_ptr(Args A, int ri, uint32_t slot) {
+    return (GDPM_GLOBAL f4*)(global_ptr(A->R.buf[ri]) + (slot & A->R.mask[ri]));
 }
 
 // mark the unused tail of this wave's reservation as empty slots
-GDPM_DEV void release(PushState& ps, Particle* buf, uint32_t mask) {
+GDPM_DEV void release(PushState& ps, Args A, int ri) {
     // by offset from ps.next: queue positions run modulo 2^32, and a reserved
     // run may straddle the wrap (then ps.end < ps.next as numbers)
     const uint32_t n = ps.end - ps.next;
     for (uint32_t o = lane_id(); o < n; o += 64u)
-        reinterpret_cast<float*>(buf + ((ps.next + o) & mask))[3] = kEmptyEnergy;
+        ((GDPM_GLOBAL float*)record_ptr(A, ri, ps.next + o))[3] = kEmptyEnergy;
     ps.next = ps.end;
 }
 
@@ -577,6 +636,9 @@ GDPM_DEV void release(PushState& ps, Particle* buf, uint32_t mask) {
 // wavefront is converged, from ballots of the lanes concerned.
 struct WaveTally {
     uint32_t events;      // flights (photon pass) or steps (electron pass)
+    uint32_t real[2];     // photons: real interactions; electrons: hard-event
+                          // candidates, hard events
+    uint32_t dep;         // FP64 tally additions
     uint32_t pushes;      // secondaries written, all jobs
     uint32_t ld, rq;      // records loaded from the queue, records handed on
     uint32_t born, died;  // records created and particles ended, current job
@@ -585,36 +647,41 @@ struct WaveTally {
                           // pair; electrons: Moller); Compton and bremsstrahlung
                           // are the rest of the real interactions and hard events
 };
+GDPM_DEV uint32_t count(bool p) { return (uint32_t)__popcll(ballot(p)); }
+
+// a queue record as loaded: the four vectors of Particle
+struct Rec {
+    f4 a, b;   // x y z e; u v w nh
+    u4 c, d;   // hlo hhi path ctr; vox a flags job
+};
+
+GDPM_DEV void write_record(GDPM_GLOBAL f4* q, const Rec& p) {
+    q[0] = p.a;
+    q[1] = p.b;
+    ((GDPM_GLOBAL u4*)q)[2] = p.c;
+    ((GDPM_GLOBAL u4*)q)[3] = p.d;
+}
 
 // Hand particles to the next pass of the same type (the record keeps the whole
 // state, random stream position included, so nothing physical changes).
-// Returns true in the lanes that wrote a record.
-GDPM_DEV bool requeue(bool active, PushState& ps, uint32_t head, Ctl* ctl, RingCtl* rc, uint32_t hard,
-                      Particle* buf, uint32_t mask, const Particle& p, WaveTally& c) {
+GDPM_DEV void requeue(bool active, PushState& ps, Args A, int ri, const Rec& p, WaveTally& c) {
     const uint64_t b = ballot(active);
     const uint32_t n = (uint32_t)__popcll(b);
-    if (n == 0) return false;
-    const Reservation res = reserve(ps, rc, head, hard, n, ctl);
-    if (res.ok) c.rq += n;
-    if (!res.ok || !active) return false;
-    store(buf, mask, slot_of(res, mbcnt(b)), p);
-    return true;
+    if (n == 0) return;
+    const Reservation res = reserve(ps, A, ri, n);
+    if (!res.ok) return;
+    c.rq += n;
+    if (active) write_record(record_ptr(A, ri, slot_of(res, mbcnt(b))), p);
 }
 
 // ---------------------------------------------------------------------------
-// the job a wavefront works on: loaded when the wavefront switches jobs and
-// held in scalar registers (a wavefront only ever holds one job's particles)
+// the job a wavefront works on (a wavefront only ever holds one job's
+// particles).  Its data are read from the job table by scalar loads where they
+// are used.
 // ---------------------------------------------------------------------------
 struct WJob {
-    Geom G;
-    const float* mumax;
-    double* tally;
-    unsigned long long nv;
-    double* hist;
-    unsigned long long hist0;
-    uint32_t k0, k1, flags;
+    JobPtr p;
     int j;
-    int ri;                          // the particle type of the pass the wavefront works in
     uint32_t tag;                    // slot | generation << 8: low half of the records' job word
     uint32_t seg_begin, seg_count;   // the job's records in the running pass
 };
@@ -630,43 +697,35 @@ GDPM_DEV T uniform_copy(const T& v) {
     return out;
 }
 
-GDPM_DEV void load_job(WJob& w, const RunDev& R, int j, int ri) {
+GDPM_DEV void load_job(WJob& w, Args A, int j, int ri) {
     j = __builtin_amdgcn_readfirstlane(j);
-    const JobDev& d = R.jobs[j];
-    w.G = uniform_copy(d.G);
-    w.mumax = uniform_copy(d.mumax);
-    w.tally = uniform_copy(d.tally);
-    w.nv = uniform_copy(d.nv);
-    w.hist = uniform_copy(d.hist);
-    w.hist0 = uniform_copy(d.hist0);
-    w.k0 = __builtin_amdgcn_readfirstlane(d.k0);
-    w.k1 = __builtin_amdgcn_readfirstlane(d.k1);
-    w.flags = __builtin_amdgcn_readfirstlane(d.flags);
+    w.p = (JobPtr)A->R.jobs + j;
     w.j = j;
-    w.ri = ri;
-    w.tag = (uint32_t)j | ((__builtin_amdgcn_readfirstlane(d.gen) & 0xFFu) << 8);
-    w.seg_begin = __builtin_amdgcn_readfirstlane(R.jc->seg_begin[ri][j]);
-    w.seg_count = __builtin_amdgcn_readfirstlane(R.jc->seg_count[ri][j]);
+    w.tag = (uint32_t)j | ((w.p->gen & 0xFFu) << 8);
+    const GDPM_CONST JobCtl* jc = (const GDPM_CONST JobCtl*)A->R.jc;
+    w.seg_begin = jc->seg_begin[ri][j];
+    w.seg_count = jc->seg_count[ri][j];
 }
 
 // first job of a wavefront: the pass input is split over the wavefronts of the
 // grid in proportion to the jobs' record counts; -1 if the pass is empty
-GDPM_DEV int first_job(const RunDev& R, uint32_t total, int ri) {
+GDPM_DEV int first_job(Args A, uint32_t total, int ri) {
     if (total == 0) return -1;
+    const GDPM_CONST JobCtl* jc = (const GDPM_CONST JobCtl*)A->R.jc;
     const uint32_t waves = gridDim.x * (blockDim.x >> 6);
-    const uint32_t w = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     const uint32_t pos = (uint32_t)(((unsigned long long)w * total + total / 2) / waves);
-    int lo = 0, hi = R.n_jobs - 1;   // last job whose segment starts at or before pos
+    int lo = 0, hi = A->R.n_jobs - 1;   // last job whose segment starts at or before pos
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (__builtin_amdgcn_readfirstlane(R.jc->seg_begin[ri][mid]) <= pos) lo = mid;
+        if (jc->seg_begin[ri][mid] <= pos) lo = mid;
         else hi = mid - 1;
     }
     return lo;
 }
 
-GDPM_DEV unsigned long long load_agent64(const unsigned long long* p) {
-    const unsigned long long v = __hip_atomic_load(const_cast<unsigned long long*>(p),
+GDPM_DEV unsigned long long load_agent64(const GDPM_GLOBAL unsigned long long* p) {
+    const unsigned long long v = __hip_atomic_load(const_cast<GDPM_GLOBAL unsigned long long*>(p),
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
@@ -674,7 +733,7 @@ GDPM_DEV unsigned long long load_agent64(const unsigned long long* p) {
 }
 
 // the next job after j (cyclically) with unclaimed records in this pass, or -1
-GDPM_DEV int next_job(const JobCtl* jc, int j, int n_jobs, int ri) {
+GDPM_DEV int next_job(const GDPM_GLOBAL JobCtl* jc, int j, int n_jobs, int ri) {
     if (n_jobs <= 1) return -1;
     const int nw = (n_jobs + 63) >> 6;
     for (int k = 0; k <= nw; ++k) {
@@ -694,17 +753,6 @@ GDPM_DEV int next_job(const JobCtl* jc, int j, int n_jobs, int ri) {
     return -1;
 }
 
-// the job's majorant table: a copy in this wavefront's LDS slice `lmw`, or the
-// global array when there is no slice
-GDPM_DEV const float* job_majorant(const WJob& W, float* lmw, int n) {
-    if (lmw == nullptr) return W.mumax;
-    for (int i = (int)lane_id(); i < n; i += 64) lmw[i] = W.mumax[i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    return lmw;
-}
-
 struct ClaimState {
     uint32_t next, end;  // claimed positions of the job's segment not yet handed out
     uint32_t seen;       // the job's claim counter as this wave last saw it
@@ -713,89 +761,58 @@ struct ClaimState {
 };
 
 // ---------------------------------------------------------------------------
-// per-lane tallies
+// tallies
 // ---------------------------------------------------------------------------
-struct LaneTally {
-    int dv;          // voxel of the pending deposit (-1 none)
-    double de;       // pending deposit (MeV)
-    double e_esc;    // escaped energy of the current job
-    double h_dep, h_esc;  // per-history accumulators (test mode)
-    uint32_t ev[7];
-};
-
-
 // deposits go to the batch slot `pb` of the particle's history; a split job's
 // particles are tallied at weight 1 and the host scales the sums by 2^-split
 // (exact: a power of two commutes with every rounding of the sum)
-GDPM_DEV void tally_flush(LaneTally& t, const WJob& W, uint32_t pb) {
-    if (t.dv >= 0 && t.de != 0.0) {
-        unsafeAtomicAdd(&W.tally[(unsigned long long)pb * W.nv + (unsigned)t.dv], t.de);
-        t.ev[EV_DEPOSITS]++;
+GDPM_DEV void add_dose(JobPtr J, uint32_t pb, int v, double de, const Rng& r) {
+    atomic_add_f64(global_ptr(J->tally) + ((unsigned long long)pb * J->nv + (unsigned)v), de);
+    if (J->hist) {
+        const unsigned long long h = ((unsigned long long)r.hhi << 32 | r.hlo) - J->hist0;
+        atomic_add_f64(global_ptr(J->hist) + 2 * h, de);
     }
-    t.dv = -1;
-    t.de = 0.0;
 }
 
-GDPM_DEV void deposit(LaneTally& t, const WJob& W, uint32_t pb, int v, float e) {
-    if (v != t.dv) tally_flush(t, W, pb);
-    t.dv = v;
-    t.de += (double)e;
-    t.h_dep += (double)e;
-}
-
-GDPM_DEV void history_flush(LaneTally& t, const WJob& W, uint32_t hlo, uint32_t hhi) {
-    if (W.hist) {
-        const unsigned long long h = ((unsigned long long)hhi << 32 | hlo) - W.hist0;
-        if (t.h_dep != 0.0) unsafeAtomicAdd(&W.hist[2 * h], t.h_dep);
-        if (t.h_esc != 0.0) unsafeAtomicAdd(&W.hist[2 * h + 1], t.h_esc);
+// energy leaving the phantom: per-history output (test mode)
+GDPM_DEV void history_escape(JobPtr J, double e, const Rng& r) {
+    if (J->hist) {
+        const unsigned long long h = ((unsigned long long)r.hhi << 32 | r.hlo) - J->hist0;
+        atomic_add_f64(global_ptr(J->hist) + 2 * h + 1, e);
     }
-    t.h_dep = 0.0;
-    t.h_esc = 0.0;
-}
-
-GDPM_DEV void tally_init(LaneTally& t) {
-    t.dv = -1;
-    t.de = 0.0;
-    t.e_esc = t.h_dep = t.h_esc = 0.0;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) t.ev[i] = 0u;
 }
 
 // fold the per-job counters into the job's (before a switch, at the end)
-GDPM_DEV void job_flush(LaneTally& t, WaveTally& c, const WJob& W, JobCtl* jc) {
-    const double esc = wave_sum(t.e_esc);
+GDPM_DEV void job_flush(double& e_esc, WaveTally& c, const WJob& W, GDPM_GLOBAL JobCtl* jc) {
+    const double esc = wave_sum(e_esc);
     if (lane_id() == 0) {
-        if (esc != 0.0) unsafeAtomicAdd(&jc->e_esc[W.j], esc);
-        if (c.born) atomicAdd(&jc->births[W.j], (unsigned long long)c.born);
-        if (c.died) atomicAdd(&jc->deaths[W.j], (unsigned long long)c.died);
+        if (esc != 0.0) atomic_add_f64(&jc->e_esc[W.j], esc);
+        if (c.born) atomic_add(&jc->births[W.j], (unsigned long long)c.born);
+        if (c.died) atomic_add(&jc->deaths[W.j], (unsigned long long)c.died);
     }
-    t.e_esc = 0.0;
+    e_esc = 0.0;
     c.pushes += c.born;
     c.born = c.died = 0u;
 }
 
 // fold the pass counters into the run's; `ri` is the pass's particle type
-GDPM_DEV void pass_finish(LaneTally& t, const WaveTally& c, Ctl* ctl, int ri) {
-    uint32_t ev[7];
-#pragma unroll
-    for (int i = 0; i < 7; ++i) ev[i] = wave_sum(t.ev[i]);
-    ev[ri == 0 ? EV_FLIGHTS : EV_ESTEPS] += c.events;
-    ev[EV_PUSHES] += c.pushes;
+GDPM_DEV void pass_finish(const WaveTally& c, GDPM_GLOBAL Ctl* ctl, int ri) {
     if (lane_id() == 0) {
-        if (c.bad) atomicAdd(&ctl->anomalies, (unsigned long long)c.bad);
-#pragma unroll
-        for (int i = 0; i < 7; ++i)
-            if (ev[i]) atomicAdd(&ctl->ev[i], (unsigned long long)ev[i]);
-        atomicAdd(&ctl->pass_ev[ri][0], (unsigned long long)c.ld);
-        atomicAdd(&ctl->pass_ev[ri][1], (unsigned long long)(c.pushes + c.rq));
-        atomicAdd(&ctl->pass_ev[ri][2], (unsigned long long)ev[EV_DEPOSITS]);
-        if (c.rq) atomicAdd(&ctl->pass_ev[ri][3], (unsigned long long)c.rq);
-        if (ri == 0) {
-            if (c.it[0]) atomicAdd(&ctl->itype[1], (unsigned long long)c.it[0]);
-            if (c.it[1]) atomicAdd(&ctl->itype[2], (unsigned long long)c.it[1]);
-        } else if (c.it[0]) {
-            atomicAdd(&ctl->itype[3], (unsigned long long)c.it[0]);
-        }
+        auto add = [](GDPM_GLOBAL unsigned long long* p, uint32_t v) {
+            if (v) atomic_add(p, (unsigned long long)v);
+        };
+        add(&ctl->anomalies, c.bad);
+        add(&ctl->ev[ri == 0 ? EV_FLIGHTS : EV_ESTEPS], c.events);
+        add(&ctl->ev[EV_PUSHES], c.pushes);
+        add(&ctl->ev[EV_DEPOSITS], c.dep);
+        add(&ctl->ev[ri == 0 ? EV_REAL : EV_HARD_CAND], c.real[0]);
+        if (ri == 1) add(&ctl->ev[EV_HARD], c.real[1]);
+        add(&ctl->pass_ev[ri][0], c.ld);
+        add(&ctl->pass_ev[ri][1], c.pushes + c.rq);
+        add(&ctl->pass_ev[ri][2], c.dep);
+        add(&ctl->pass_ev[ri][3], c.rq);
+        add(&ctl->itype[ri == 0 ? 1 : 3], c.it[0]);
+        if (ri == 0) add(&ctl->itype[2], c.it[1]);
     }
 }
 
@@ -808,7 +825,8 @@ GDPM_DEV void pass_finish(LaneTally& t, const WaveTally& c, Ctl* ctl, int ri) {
 // q = ln(eps/eps0)/ln(1/eps0), so that eps = eps0^(1 - q)); then
 // t = 1 - cos(theta) and the azimuth (in turns).  No rejection: every lane
 // of a wavefront runs the same instructions.
-GDPM_DEV void sample_compton(const Tables& T, Rng& r, uint32_t k0, uint32_t k1, float e, float& eps,
+template <class TT, class RNG>
+GDPM_DEV void sample_compton(const TT& T, RNG& r, uint32_t k0, uint32_t k1, float e, float& eps,
                              float& t, float& turns) {
     const float k = e * (1.0f / kMec2f);
     const float u = uniform(r, k0, k1);
@@ -819,7 +837,7 @@ GDPM_DEV void sample_compton(const Tables& T, Rng& r, uint32_t k0, uint32_t k1, 
     const float fu = u * (float)(T.kn_nu - 1);
     const int j = min((int)fu, T.kn_nu - 2);
     const float b = fu - (float)j;
-    const float* p = T.kn + (i * T.kn_nu + j);
+    const GDPM_GLOBAL float* p = global_ptr(T.kn) + (i * T.kn_nu + j);
     const float q0 = fmaf(b, p[1] - p[0], p[0]);
     const float q1 = fmaf(b, p[T.kn_nu + 1] - p[T.kn_nu], p[T.kn_nu]);
     const float q = fmaf(a, q1 - q0, q0);
@@ -830,12 +848,15 @@ GDPM_DEV void sample_compton(const Tables& T, Rng& r, uint32_t k0, uint32_t k1, 
 
 // Moller: eps = W/T by a 1/eps^2 proposal on [W_cc/T, 1/2] and rejection
 // eps^2 B(eps) / 2.25; then the azimuth
-GDPM_DEV void sample_moller(Rng& r, uint32_t k0, uint32_t k1, float tt, float wcc, float& eps,
+template <class RNG>
+GDPM_DEV void sample_moller(RNG& r, uint32_t k0, uint32_t k1, float tt, float wcc, float& eps,
                             float& turns) {
     const float g = 1.0f + tt * (1.0f / kMec2f), e0 = fdiv(wcc, tt);
     const float ig = hrcp(g);
     const float c1 = (g - 1.0f) * ig, c2 = (2.0f * g - 1.0f) * ig * ig;
     for (;;) {
+        // a trial takes two draws, and the azimuth after the last one a third
+        r.ensure(3u, k0, k1);
         const float ua = uniform(r, k0, k1);
         eps = fdiv(e0, 1.0f - ua * (1.0f - 2.0f * e0));
         const float ub = uniform(r, k0, k1);
@@ -848,11 +869,13 @@ GDPM_DEV void sample_moller(Rng& r, uint32_t k0, uint32_t k1, float tt, float wc
 
 // bremsstrahlung photon energy: 1/k proposal on [W_cb, T], rejection by the
 // complete-screening spectrum
-GDPM_DEV float sample_brems(Rng& r, uint32_t k0, uint32_t k1, float tt, float wcb) {
+template <class RNG>
+GDPM_DEV float sample_brems(RNG& r, uint32_t k0, uint32_t k1, float tt, float wcb) {
     const float lr = hlog2(tt) - hlog2(wcb);
     const float it = hrcp(tt);
     float kph;
     for (;;) {
+        r.ensure(2u, k0, k1);
         const float ua = uniform(r, k0, k1);
         // the hardware log2 and exp2 are within about an ulp each, so near
         // ua = 1 their product could exceed T by a few ulps and leave the
@@ -866,7 +889,8 @@ GDPM_DEV float sample_brems(Rng& r, uint32_t k0, uint32_t k1, float tt, float wc
 }
 
 // isotropic direction of the first annihilation photon (cos, then azimuth)
-GDPM_DEV void sample_iso(Rng& r, uint32_t k0, uint32_t k1, float& du, float& dv, float& dw) {
+template <class RNG>
+GDPM_DEV void sample_iso(RNG& r, uint32_t k0, uint32_t k1, float& du, float& dv, float& dw) {
     const float ct = 2.0f * uniform(r, k0, k1) - 1.0f;
     const float turns = uniform(r, k0, k1);
     const float st = hsqrt((1.0f - ct) * (1.0f + ct));
@@ -898,24 +922,19 @@ GDPM_DEV void pair_split(float e, float u, float& tm, float& tp, float& aa) {
     const float kk = e - kTwoMec2f;
     aa = e - kk;
     const float tc = u * kk;
-    if (2.0f * tc >= kk) {
-        tm = tc;
-        tp = kk - tc;
-    } else {
-        tp = kk - tc;
-        tm = kk - tp;
-    }
+    tp = kk - tc;
+    tm = 2.0f * tc >= kk ? tc : kk - tp;
 }
 
 // ---------------------------------------------------------------------------
-// secondaries of one event, pushed once per iteration with the wave converged
+// secondaries of one event, pushed with the wave converged
 // ---------------------------------------------------------------------------
 // charged: up to two; the second (a positron) shares the first one's direction
 struct PendCharged {
     int n;
     float e0, du, dv, dw;   // first particle and the common direction
     float a0;               // first particle: annihilation energy if it is a positron
-    uint32_t role, flag0;   // first particle: role word, positron flag
+    uint32_t role;          // first particle: role word
     float e1, a1;           // second particle (always the pair positron, role 1)
 };
 // photons: one (role word wb) or two back to back (roles wb, wb + 1)
@@ -925,53 +944,46 @@ struct PendPhoton {
     uint32_t wb;
 };
 
-GDPM_DEV void write_particle(Particle* buf, uint32_t mask, uint32_t slot, float x, float y, float z,
-                             float e, float u, float v, float w, uint32_t hlo, uint32_t hhi,
-                             uint32_t path, uint32_t vox, float a, uint32_t flags, uint32_t job) {
-    float4* d = reinterpret_cast<float4*>(buf + (slot & mask));
-    d[0] = make_float4(x, y, z, e);
-    d[1] = make_float4(u, v, w, -1.0f);
-    d[2] = make_float4(__uint_as_float(hlo), __uint_as_float(hhi), __uint_as_float(path), 0.0f);
-    d[3] = make_float4(__uint_as_float(vox), a, __uint_as_float(flags), __uint_as_float(job));
+// a new particle of annihilation energy a (0: an electron or a photon)
+GDPM_DEV void write_particle(GDPM_GLOBAL f4* q, float x, float y, float z, float e, float u, float v, float w,
+                             const Rng& r, uint32_t path, uint32_t vox, float a, uint32_t job) {
+    q[0] = f4{x, y, z, e};
+    q[1] = f4{u, v, w, -1.0f};
+    ((GDPM_GLOBAL u4*)q)[2] = u4{r.hlo, r.hhi, path, 0u};
+    ((GDPM_GLOBAL u4*)q)[3] = u4{vox, __float_as_uint(a), a > 0.0f ? 1u : 0u, job};
 }
 
 // secondaries inherit the job and the batch slot (`jb`) of their history
-GDPM_DEV void push_charged(PendCharged& q, PushState& ps, uint32_t head, Ctl* ctl, const RunDev& R,
-                           const WJob& W, uint32_t jb, Particle* buf, float x, float y, float z,
-                           uint32_t vox, const Rng& rng, WaveTally& c) {
+GDPM_DEV void push_charged(const PendCharged& q, PushState& ps, Args A, JobPtr J, uint32_t jb, float x, float y,
+                           float z, uint32_t vox, const Rng& rng, WaveTally& c) {
     const uint64_t b0 = ballot(q.n >= 1), b1 = ballot(q.n >= 2);
     const uint32_t n0 = (uint32_t)__popcll(b0), n = n0 + (uint32_t)__popcll(b1);
     if (n == 0) return;
-    const Reservation res = reserve(ps, &ctl->ring[1], head, R.hard[1], n, ctl);
-    if (res.ok && q.n > 0) {
-        write_particle(buf, R.mask[1], slot_of(res, mbcnt(b0)), x, y, z, q.e0, q.du, q.dv, q.dw,
-                       rng.hlo, rng.hhi, spawn_path(rng, W.k0, W.k1, (int)q.role), vox, q.a0,
-                       q.flag0, jb);
-        if (q.n > 1)
-            write_particle(buf, R.mask[1], slot_of(res, n0 + mbcnt(b1)), x, y, z, q.e1, q.du, q.dv,
-                           q.dw, rng.hlo, rng.hhi, spawn_path(rng, W.k0, W.k1, 1), vox, q.a1, 1u, jb);
-    }
-    if (res.ok) c.born += n;
-    q.n = 0;
+    const Reservation res = reserve(ps, A, 1, n);
+    if (!res.ok) return;
+    if (q.n > 0)
+        write_particle(record_ptr(A, 1, slot_of(res, mbcnt(b0))), x, y, z, q.e0, q.du, q.dv, q.dw, rng,
+                       spawn_path(rng, J->k0, J->k1, (int)q.role), vox, q.a0, jb);
+    if (q.n > 1)
+        write_particle(record_ptr(A, 1, slot_of(res, n0 + mbcnt(b1))), x, y, z, q.e1, q.du, q.dv, q.dw, rng,
+                       spawn_path(rng, J->k0, J->k1, 1), vox, q.a1, jb);
+    c.born += n;
 }
 
-GDPM_DEV void push_photons(PendPhoton& q, PushState& ps, uint32_t head, Ctl* ctl, const RunDev& R,
-                           const WJob& W, uint32_t jb, Particle* buf, float x, float y, float z,
-                           const Rng& rng, WaveTally& c) {
+GDPM_DEV void push_photons(const PendPhoton& q, PushState& ps, Args A, JobPtr J, uint32_t jb, float x, float y,
+                           float z, const Rng& rng, WaveTally& c) {
     const uint64_t b0 = ballot(q.n >= 1), b1 = ballot(q.n >= 2);
     const uint32_t n0 = (uint32_t)__popcll(b0), n = n0 + (uint32_t)__popcll(b1);
     if (n == 0) return;
-    const Reservation res = reserve(ps, &ctl->ring[0], head, R.hard[0], n, ctl);
-    if (res.ok && q.n > 0) {
-        write_particle(buf, R.mask[0], slot_of(res, mbcnt(b0)), x, y, z, q.e, q.u, q.v, q.w,
-                       rng.hlo, rng.hhi, spawn_path(rng, W.k0, W.k1, (int)q.wb), 0u, 0.0f, 0u, jb);
-        if (q.n > 1)
-            write_particle(buf, R.mask[0], slot_of(res, n0 + mbcnt(b1)), x, y, z, q.e, -q.u, -q.v,
-                           -q.w, rng.hlo, rng.hhi, spawn_path(rng, W.k0, W.k1, (int)q.wb + 1), 0u,
-                           0.0f, 0u, jb);
-    }
-    if (res.ok) c.born += n;
-    q.n = 0;
+    const Reservation res = reserve(ps, A, 0, n);
+    if (!res.ok) return;
+    if (q.n > 0)
+        write_particle(record_ptr(A, 0, slot_of(res, mbcnt(b0))), x, y, z, q.e, q.u, q.v, q.w, rng,
+                       spawn_path(rng, J->k0, J->k1, (int)q.wb), 0u, 0.0f, jb);
+    if (q.n > 1)
+        write_particle(record_ptr(A, 0, slot_of(res, n0 + mbcnt(b1))), x, y, z, q.e, -q.u, -q.v, -q.w, rng,
+                       spawn_path(rng, J->k0, J->k1, (int)q.wb + 1), 0u, 0.0f, jb);
+    c.born += n;
 }
 
 // ---------------------------------------------------------------------------
@@ -1023,27 +1035,31 @@ __global__ void k_finish(Ctl* ctl, int ri) {
 // ---------------------------------------------------------------------------
 // claiming input: positions [0, seg_count) of the job's segment
 // ---------------------------------------------------------------------------
-GDPM_DEV void claim_refill(ClaimState& cs, JobCtl* jc, const WJob& W, const Ctl* ctl) {
+GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
     if (cs.done || cs.next != cs.end) return;
     // the wave has used up its items: claim a new chunk if the job has more.
     // Chunks shrink as the segment drains (guided self-scheduling), so that the
     // last items spread over many wavefronts.  The shared counters are touched
     // once per claim, never per iteration.
+    GDPM_GLOBAL Ctl* ctl = global_ptr(A->ctl);
+    GDPM_GLOBAL JobCtl* jc = global_ptr(A->R.jc);
     const uint32_t count = W.seg_count;
     const uint32_t waves = gridDim.x * (blockDim.x >> 6);
     const uint32_t left = count - min(cs.seen, count);
-    const uint32_t chunk = min(max(left / (2u * waves), kClaimMin), W.ri == 0 ? kClaimMaxPhoton : kClaimMaxElectron);
+    const uint32_t chunk = min(max(left / (2u * waves), kClaimMin), ri == 0 ? kClaimMaxPhoton : kClaimMaxElectron);
     if (load_agent(&ctl->overflow)) {   // a queue overflowed: the run is void
         cs.done = true;
         return;
     }
     const uint32_t leader = first_lane(ballot(true));
     uint32_t base = 0;
-    if (lane_id() == leader) base = atomicAdd(&jc->claim[W.ri][W.j], chunk);
+    if (lane_id() == leader) base = atomic_add(&jc->claim[ri][W.j], chunk);
     base = bcast(base, leader);
     cs.seen = base + chunk;
     if (base >= count) {
-        if (lane_id() == leader) atomicAnd(&jc->left[W.ri][W.j >> 6], ~(1ull << (W.j & 63)));
+        if (lane_id() == leader)
+            (void)__hip_atomic_fetch_and(&jc->left[ri][W.j >> 6], ~(1ull << (W.j & 63)), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
         cs.done = true;
         return;
     }
@@ -1057,38 +1073,32 @@ GDPM_DEV void claim_refill(ClaimState& cs, JobCtl* jc, const WJob& W, const Ctl*
 constexpr uint32_t kStage = 64;
 constexpr uint32_t kStageLow = 24;   // restage when fewer staged records are left
 
-GDPM_DEV Particle load_staged(const float4* st, uint32_t k) {
-    Particle p;
-    float4* d = reinterpret_cast<float4*>(&p);
-    d[0] = st[4 * k];
-    d[1] = st[4 * k + 1];
-    d[2] = st[4 * k + 2];
-    d[3] = st[4 * k + 3];
-    return p;
-}
-
 // the queue position of input position `pos` of a pass: itself, or through the
 // permutation of a pass re-binned by job (`perm` non-null); both masked, so
 // that any value reads inside the queue
-GDPM_DEV uint32_t input_slot(const uint32_t* perm, uint32_t mask, uint32_t pos) {
+GDPM_DEV uint32_t input_slot(const GDPM_GLOBAL uint32_t* perm, uint32_t mask, uint32_t pos) {
     return (perm ? perm[pos & mask] : pos) & mask;
 }
 
 // stage the records of positions [cs.next, cs.next + kStage) (every lane: 4
 // loads of 16 bytes; lane L of load c fetches piece L % 4 of record 16 c + L / 4,
 // which lands at float4 64 c + L of the slice).  Positions past the chunk are
-// loaded too (the ring index is masked) and never used.
-GDPM_DEV void stage_records(ClaimState& cs, float4* st, const Particle* buf, uint32_t mask,
-                            uint32_t first, const uint32_t* perm) {
+// loaded too (the ring index is masked) and never used.  The loads are written
+// out because the compiler orders every later LDS access of the wavefront (table
+// lookups, draws) behind a direct-to-LDS load it knows of; nothing but
+// load_staged reads the slice, after a wait of its own.
+GDPM_DEV void stage_records(ClaimState& cs, GDPM_LDS f4* st, Args A, int ri, uint32_t first,
+                            const GDPM_GLOBAL uint32_t* perm) {
     // the refill's reads of the slice are complete before it is overwritten
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
     const uint32_t l = lane_id();
+    const uint32_t mask = A->R.mask[ri];
+#pragma unroll
     for (uint32_t c = 0; c < 4; ++c) {
         const uint32_t rec = 16u * c + (l >> 2);
-        const float4* src = reinterpret_cast<const float4*>(buf + input_slot(perm, mask, first + cs.next + rec)) +
-                            (l & 3u);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                         (__attribute__((address_space(3))) void*)(st + 64u * c), 16, 0, 0);
+        const GDPM_GLOBAL f4* src = record_ptr(A, ri, input_slot(perm, mask, first + cs.next + rec)) + (l & 3u);
+        const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(st + 64u * c));
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");
     }
     cs.st_lo = cs.next;
     cs.st_hi = cs.next + kStage;
@@ -1098,13 +1108,12 @@ GDPM_DEV void stage_records(ClaimState& cs, float4* st, const Particle* buf, uin
 // true in the lanes that loaded a record.  Lanes wait until kRefillMin of them
 // are empty (or no lane is busy): a refill stalls the wavefront on record
 // loads, so it pays to do it for several lanes at once.  With a staging slice
-// (`st`, LDS) the records come from it when they are staged.  kSolo (a
+// (kStaged: `st`, LDS) the records come from it when they are staged.  kSolo (a
 // measurement form): one particle per wavefront at a time, so the wavefront
 // executes exactly the instructions of that particle's path.
-template <bool kSolo>
-GDPM_DEV bool refill(bool active, ClaimState& cs, JobCtl* jc, const WJob& W, uint32_t begin,
-                     Ctl* ctl, const Particle* buf, uint32_t mask, const uint32_t* perm, Particle& p,
-                     WaveTally& c, float4* st) {
+template <bool kSolo, bool kStaged>
+GDPM_DEV bool refill(bool active, ClaimState& cs, Args A, const WJob& W, int ri, uint32_t begin,
+                     const GDPM_GLOBAL uint32_t* perm, Rec& p, WaveTally& c, GDPM_LDS f4* st) {
     if (cs.done) return false;
     const uint64_t need = ballot(!active);
     if (!need) return false;
@@ -1113,33 +1122,43 @@ GDPM_DEV bool refill(bool active, ClaimState& cs, JobCtl* jc, const WJob& W, uin
     } else {
         if ((uint32_t)__popcll(need) < kRefillMin && ballot(active)) return false;
     }
-    claim_refill(cs, jc, W, ctl);
+    claim_refill(cs, A, W, ri);
     const uint32_t have = cs.end - cs.next;
     const uint32_t rank = mbcnt(need);
     const uint32_t take = kSolo ? min(have, 1u) : min(have, (uint32_t)__popcll(need));
     const uint32_t first = begin + W.seg_begin;
-    const bool staged = st != nullptr && take > 0u && cs.next >= cs.st_lo &&
-                        cs.next + take <= cs.st_hi;
+    const bool staged = kStaged && take > 0u && cs.next >= cs.st_lo && cs.next + take <= cs.st_hi;
     if (staged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the staging loads have landed
     bool got = false;
     if (!active && rank < take) {
-        p = staged ? load_staged(st, cs.next + rank - cs.st_lo)
-                   : load(buf, mask, input_slot(perm, mask, first + cs.next + rank));
-        got = !record_empty(p.e);
-        if (got && (p.job & 0xFFFFu) != W.tag) {
+        if (staged) {
+            const GDPM_LDS f4* q = st + 4u * (cs.next + rank - cs.st_lo);
+            p.a = q[0];
+            p.b = q[1];
+            p.c = ((const GDPM_LDS u4*)q)[2];
+            p.d = ((const GDPM_LDS u4*)q)[3];
+        } else {
+            const GDPM_GLOBAL f4* q = record_ptr(A, ri, input_slot(perm, A->R.mask[ri], first + cs.next + rank));
+            p.a = q[0];
+            p.b = q[1];
+            p.c = ((const GDPM_GLOBAL u4*)q)[2];
+            p.d = ((const GDPM_GLOBAL u4*)q)[3];
+        }
+        got = !record_empty(p.a.w);
+        if (got && (p.d.w & 0xFFFFu) != W.tag) {
             // a record of another job (or of an earlier job in this slot) in
             // this job's segment: only a broken bookkeeping puts it there; it
             // is dropped and counted
-            atomicAdd(&ctl->anomalies, 1ull);
+            atomic_add(&global_ptr(A->ctl)->anomalies, 1ull);
             got = false;
         }
     }
     cs.next += take;
     c.ld += take;
-    if (st != nullptr && cs.next < cs.end) {
+    if (kStaged && cs.next < cs.end) {
         // positions of a pass's segment do not wrap: plain comparisons
         const uint32_t left = cs.next >= cs.st_lo && cs.next < cs.st_hi ? cs.st_hi - cs.next : 0u;
-        if (left <= kStageLow) stage_records(cs, st, buf, mask, first, perm);
+        if (left <= kStageLow) stage_records(cs, st, A, ri, first, perm);
     }
     return got;
 }
@@ -1193,10 +1212,7 @@ __global__ void __launch_bounds__(256) k_source(Ctl* ctl, RunDev R, const SrcSeg
         // copy c on stream path c (copy 0 is the unsplit primary).
         auto one = [&](uint32_t i, uint32_t* chain) {
             const unsigned long long h = sg.h0 + i;
-            Rng rng;
-            rng_start(rng, (uint32_t)h, (uint32_t)(h >> 32), 0u, 0u);
-            rng_topup(rng, k0, k1);
-            const Primary pr = make_primary(S, G, rng, k0, k1, chain, sg.rpos + i, sg.rsize);
+            const Primary pr = make_primary(S, G, h, k0, k1, chain, sg.rpos + i, sg.rsize);
             e_in += (double)pr.e;
             uint32_t vox = 0u;
             if (pr.in && ri == 1) {
@@ -1210,8 +1226,8 @@ __global__ void __launch_bounds__(256) k_source(Ctl* ctl, RunDev R, const SrcSeg
                     // the stream continues at the draw after the source's draws
                     q[0] = make_float4(pr.x, pr.y, pr.z, pr.e);
                     q[1] = make_float4(pr.u, pr.v, pr.w, -1.0f);
-                    q[2] = make_float4(__uint_as_float(rng.hlo), __uint_as_float(rng.hhi), __uint_as_float(c),
-                                       __uint_as_float(rng_ctr(rng)));
+                    q[2] = make_float4(__uint_as_float((uint32_t)h), __uint_as_float((uint32_t)(h >> 32)),
+                                       __uint_as_float(c), __uint_as_float(pr.draws));
                     q[3] = make_float4(__uint_as_float(vox), 0.0f, 0.0f, __uint_as_float(jb));
                 } else {
                     reinterpret_cast<float*>(q)[3] = kEmptyEnergy;
@@ -1257,153 +1273,151 @@ __global__ void k_commit(Ctl* ctl, int ri, const SrcHdr* hdr) {
 }
 
 // ---------------------------------------------------------------------------
-// photon pass: Woodcock tracking (section 2.1), one flight per iteration
+// LDS of a transport workgroup
 // ---------------------------------------------------------------------------
 // Interpolation tables are staged in LDS (kLds) when they fit; one workgroup
-// per CU shares them, and each wavefront keeps its job's majorant in its own
-// LDS slice.
-extern __shared__ float4 lds_tables[];
+// per CU shares them.
+extern __shared__ f4 lds_tables[];
 
-// LDS layout of a transport workgroup (float4 units): the tables (photons: the
-// cross sections, then one majorant slice of pg_n floats per wavefront;
-// electrons: the stopping and scattering data, the inverse range and its
-// scales), then one slice of kStage staged records per wavefront
-GDPM_HD uint32_t stage_offset(int ri, const Tables& T, int waves) {
-    const uint32_t floats = ri == 0 ? (uint32_t)(waves * T.pg_n)
-                                    : (uint32_t)(T.n_mat * T.nr + T.n_mat);
+// Layout (float4 units): the tables (photons: the cross sections, then the
+// majorant of the pass's job; electrons: the stopping and scattering data, the
+// inverse range and its scales), if staged; then per wavefront one slice of
+// kStage staged records (with the tables) and its lanes' generator words
+constexpr uint32_t kRingF4 = kRngWords * 64u / 4u;   // generator words of a wavefront
+template <class TT>
+GDPM_HD uint32_t tables_f4(int ri, const TT& T) {
+    const uint32_t floats = ri == 0 ? (uint32_t)T.pg_n : (uint32_t)(T.n_mat * T.nr + T.n_mat);
     const uint32_t tab = ri == 0 ? (uint32_t)(T.n_mat * T.pg_n) : (uint32_t)(T.n_mat * T.eg_n);
     return tab + (floats + 3u) / 4u;
 }
+constexpr uint32_t kSliceF4 = 4u * kStage + kRingF4;
 
+// ---------------------------------------------------------------------------
+// photon pass: Woodcock tracking (section 2.1), one flight per iteration
+// ---------------------------------------------------------------------------
 // One wavefront's share of a photon pass.  ptab: the cross sections (LDS or
-// global); lmw: the wavefront's LDS slice for its job's majorant (null: the
-// global array); stage: its LDS slice for staged records (null: none).
-template <bool kSolo, bool kPerm>
-GDPM_DEV void photon_pass(Ctl* ctl, const Tables& T, const RunDev& R, const float4* ptab, float* lmw,
-                          float4* stage) {
-    RingCtl* rc = &ctl->ring[0];
-    const uint32_t begin = rc->begin, count = rc->count;
+// global); lmaj: the job's majorant in LDS (kMajLds: a pass of one job; else it
+// is read from global memory); stage: the wavefront's LDS slice for staged
+// records (kStaged); ring: its generator words.
+template <bool kSolo, bool kPerm, bool kStaged, bool kMajLds, class PT>
+GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS f4* stage, GDPM_LDS float* ring) {
+    const GDPM_CONST RingCtl* rc = ring_const(A0, 0);
+    const uint32_t begin = rc->begin, total = rc->count;
     // a re-binned pass reads its input through the permutation (only the kPerm
     // form has that code: the passes of a lone job keep the plain reads)
-    const uint32_t* perm_in =
-        kPerm && __builtin_amdgcn_readfirstlane(rc->permuted) ? bin_perm(R.bin[0], R.mask[0]) : nullptr;
-    const bool big = !kSolo && count >= kTailMinPerLane * gridDim.x * blockDim.x;
-    Particle* bufg = R.buf[0];
-    Particle* bufe = R.buf[1];
-    const uint32_t head_g = ctl->ring[0].head, head_e = ctl->ring[1].head;
-    JobCtl* jc = R.jc;
-    const float ecut_e = R.ecut_e, ecut_g = R.ecut_g;
+    const GDPM_GLOBAL uint32_t* perm_in =
+        kPerm && rc->permuted ? global_ptr(bin_perm(A0->R.bin[0], A0->R.mask[0])) : nullptr;
+    const bool big = !kSolo && total >= kTailMinPerLane * gridDim.x * blockDim.x;
 
-    int j = first_job(R, count, 0);
+    int j = first_job(A0, total, 0);
     PushState pg{0u, 0u}, pe{0u, 0u};
-    LaneTally tl;
-    tally_init(tl);
-    WaveTally wt{0u, 0u, 0u, 0u, 0u, 0u, 0u, {0u, 0u}};
+    double e_esc = 0.0;   // escaped energy of the current job
+    WaveTally wt{};
     uint32_t iters = 0u;
-    bool last_job = false;   // no other job has records left in this pass
+    bool last_job = !kPerm;   // no other job has records left in this pass
     // one job at a time: a wavefront switches jobs with all its lanes empty
     while (j >= 0) {
         WJob W;
-        load_job(W, R, j, 0);
-        const float* mtab = job_majorant(W, lmw, T.pg_n);
+        load_job(W, A0, j, 0);
         ClaimState cs{0u, 0u, 0u, false, 0u, 0u};
         bool active = false;
         float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0;
         uint32_t pb = 0u;   // batch slot of the lane's history
         int pm = -1;        // >= 0: a real interaction waits, in a voxel of this material
         Rng rng;
+        rng.buf = ring + lane_id();
         rng_start(rng, 0u, 0u, 0u, 0u);
         int next = -1;
         for (;;) {
-            const uint32_t k0 = W.k0, k1 = W.k1;
-            const bool kerma = (W.flags & 64u) != 0u;
-            Particle p;
-            if (refill<kSolo>(active, cs, jc, W, begin, ctl, bufg, R.mask[0], perm_in, p, wt, stage)) {
-                x = p.x; y = p.y; z = p.z; e = p.e;
-                u = p.u; v = p.v; w = p.w;
-                pb = p.job >> 16;
-                rng_start(rng, p.hlo, p.hhi, p.path, p.ctr);
+            const Args A = reread(A0);
+            const JobPtr J = reread(W.p);
+            Rec p;
+            if (refill<kSolo, kStaged>(active, cs, A, W, 0, begin, perm_in, p, wt, stage)) {
+                // + 0: a position of -0 becomes +0 (see inside)
+                x = p.a.x + 0.0f; y = p.a.y + 0.0f; z = p.a.z + 0.0f; e = p.a.w;
+                u = p.b.x; v = p.b.y; w = p.b.z;
+                pb = p.d.w >> 16;
+                rng_start(rng, p.c.x, p.c.y, p.c.z, p.c.w);
                 active = true;
+                // an energy that ends the photon where it is: below the
+                // absorption energy, or non-finite (only from a damaged record)
+                pm = e < A->R.ecut_g || !(e <= kMaxEnergy) ? kAbsorb : -1;
             }
             if (!ballot(active)) {
                 if (cs.done && last_job) break;
                 if (!cs.done) continue;
             } else {
-            rng_topup(rng, k0, k1);
-            const uint64_t act0 = ballot(active);
-
-            PendCharged qe;
-            PendPhoton qg;
-            qe.n = 0;
-            qg.n = 0;
-            int ix = 0, iy = 0, iz = 0;
-            if (active && !(e <= kMaxEnergy)) {
-                // a non-finite energy can only come from a damaged record: end the
-                // particle (counted as an anomaly) rather than feed it to a
-                // rejection sampler that would never accept
-                atomicAdd(&ctl->anomalies, 1ull);
-                active = false;
-                pm = -1;
-            }
-            // energy grid cell of the flight and of a waiting interaction (the
-            // energy is unchanged in between); computed on every lane, since the
-            // grid clamps any energy, 0 and non-finite ones included, into the table
-            int gi;
-            float gt;
-            grid(hlog2(e), T.pg_lo, T.pg_inv, T.pg_n, gi, gt);
-            const float mumax = lerp1(mtab, gi, gt);
-            wt.events += (uint32_t)__popcll(ballot(active && pm < 0 && !(e < ecut_g)));
-            if (active && pm < 0) {
-                if (e < ecut_g) {
-                    const int vv = voxel_of(W.G, x, y, z, ix, iy, iz);
-                    deposit(tl, W, pb, vv, e);
-                    tally_flush(tl, W, pb);
+                const uint64_t act0 = ballot(active);
+                const bool fly = active && pm < 0;
+                rng_topup(rng, fly, active, 2u, J->k0, J->k1);
+                wt.events += count(fly);
+                // energy grid cell of the flight and of a waiting interaction
+                // (the energy is unchanged in between)
+                int gi;
+                float gt;
+                grid(hlog2(e), A->T.pg_lo, A->T.pg_inv, A->T.pg_n, gi, gt);
+                float mumax;
+                if constexpr (kMajLds) mumax = lerp1(lmaj, gi, gt);
+                else mumax = lerp1(global_ptr(J->mumax), gi, gt);
+                // The flight is computed on every lane, without branches: a lane
+                // that waits or is empty flies a distance of 0, which leaves it
+                // where it is, and only the loads and the tallies are masked.
+                const float ul = rng.peek(0u), ua = rng.peek(1u);
+                const float s = fly ? neg_ln(ul) * hrcp(mumax) : 0.0f;
+                rng.ctr += fly ? 2u : 0u;
+                x = fmaf(s, u, x);
+                y = fmaf(s, v, y);
+                z = fmaf(s, w, z);
+                const bool in = fly && inside(J->G, x, y, z);
+                int ix, iy, iz;
+                const int vv = voxel_of(J->G, x, y, z, ix, iy, iz);
+                uint32_t vx = 0u;
+                if (in) vx = global_ptr(J->G.vox)[vv];
+                if (fly && !in) {
+                    e_esc += (double)e;
+                    history_escape(J, (double)e, rng);
                     active = false;
-                } else {
-                    const float s = neg_ln(uniform(rng, k0, k1)) * hrcp(mumax);
-                    x = fmaf(s, u, x);
-                    y = fmaf(s, v, y);
-                    z = fmaf(s, w, z);
-                    if (outside(W.G, x, y, z)) {
-                        tl.e_esc += (double)e;
-                        tl.h_esc += (double)e;
-                        active = false;
-                    } else {
-                        const int vv = voxel_of(W.G, x, y, z, ix, iy, iz);
-                        const uint32_t vx = W.G.vox[vv];
-                        const float rho = voxel_density(vx);
-                        const int m = voxel_material(vx);
-                        const float4 mu = lerp4(ptab + m * T.pg_n, gi, gt);
-                        if (uniform(rng, k0, k1) * mumax < rho * mu.w) {
-                            tl.ev[EV_REAL]++;
-                            pm = m;   // the interaction waits (see below)
-                        }
-                    }
                 }
-                if (!active) {
-                        history_flush(tl, W, rng.hlo, rng.hhi);
+                {
+                    const int m = voxel_material(vx);
+                    const PT row = ptab + m * A->T.pg_n + gi;
+                    const float m0 = row[0].w, m1 = row[1].w;
+                    const float mu = fmaf(gt, m1 - m0, m0);
+                    const bool real = in && ua * mumax < voxel_density(vx) * mu;
+                    pm = real ? m : pm;   // the interaction waits (see below)
+                    wt.real[0] += count(real);
                 }
-            }
-            // Real interactions are sampled together once kRealBatch lanes have
-            // one (or the wavefront has no other live lane, or the pass has
-            // nothing left to claim): the lanes of a wavefront share their
-            // sampling code instead of a few running it each iteration.  A lane
-            // waits where it is without drawing, so each particle's draws keep
-            // their order; the voxel and the cross sections are recomputed from
-            // the same inputs (the energy grid cell from this iteration's lookup).
-            {
+                // Real interactions are sampled together once kRealBatch lanes have
+                // one (or the wavefront has no other live lane, or the pass has
+                // nothing left to claim): the lanes of a wavefront share their
+                // sampling code instead of a few running it each iteration.  A lane
+                // waits where it is without drawing, so each particle's draws keep
+                // their order; the cross sections are recomputed from the same inputs.
                 const uint64_t br = ballot(pm >= 0);
                 if (br && (cs.done || (uint32_t)__popcll(br) >= kRealBatch || br == ballot(active))) {
-                    int itype = -1;   // the interaction sampled by this lane
+                    const bool kerma = (J->flags & 64u) != 0u;
+                    const float ecut_e = A->R.ecut_e;
+                    PendCharged qe;
+                    PendPhoton qg;
+                    qe.n = 0;
+                    qg.n = 0;
+                    int itype = -1;    // the interaction sampled by this lane
+                    double dep = 0.0;  // its deposit, in the lane's voxel
+                    rng_topup(rng, pm >= 0, active, 4u, J->k0, J->k1);
+                    if (pm == kAbsorb) {
+                        if (e <= kMaxEnergy) dep = (double)e;
+                        else atomic_add(&global_ptr(A->ctl)->anomalies, 1ull);
+                        active = false;
+                        pm = -1;
+                    }
                     if (pm >= 0) {
-                        rng_topup(rng, k0, k1);
-                        const int vv = voxel_of(W.G, x, y, z, ix, iy, iz);
-                        const float4 mu = lerp4(ptab + pm * T.pg_n, gi, gt);
+                        const uint32_t k0 = J->k0, k1 = J->k1;
+                        const f4 mu = lerp4(ptab + pm * A->T.pg_n, gi, gt);
                         const float r = uniform(rng, k0, k1) * mu.w;
                         itype = r < mu.x ? 0 : (r < mu.x + mu.y ? 1 : 2);
                         if (itype == 0) {
                             float eps, t, turns;
-                            sample_compton(T, rng, k0, k1, e, eps, t, turns);
+                            sample_compton(A->T, rng, k0, k1, e, eps, t, turns);
                             const float u0 = u, v0 = v, w0 = w;
                             rotate(u, v, w, 1.0f - t, hsqrt(fmaxf(0.0f, t * (2.0f - t))), turns);
                             // exact split of E into E' and T (the unit is built without
@@ -1418,21 +1432,25 @@ GDPM_DEV void photon_pass(Ctl* ctl, const Tables& T, const RunDev& R, const floa
                                 e1 = e - te;
                             }
                             if (kerma || te <= ecut_e) {
-                                deposit(tl, W, pb, vv, te);
+                                dep = (double)te;
                             } else {
                                 float eu, ev, ew;
                                 compton_electron_dir(e, e1, u0, v0, w0, u, v, w, eu, ev, ew);
                                 qe.n = 1; qe.e0 = te; qe.du = eu; qe.dv = ev; qe.dw = ew;
-                                qe.a0 = 0.0f; qe.role = 0u; qe.flag0 = 0u;
+                                qe.a0 = 0.0f; qe.role = 0u;
                             }
                             e = e1;
+                            if (e < A->R.ecut_g) {   // absorbed where it is
+                                dep += (double)e;
+                                active = false;
+                            }
                         } else if (itype == 1) {
                             // photoelectric: the electron takes E along the photon
                             if (kerma || e <= ecut_e) {
-                                deposit(tl, W, pb, vv, e);
+                                dep = (double)e;
                             } else {
                                 qe.n = 1; qe.e0 = e; qe.du = u; qe.dv = v; qe.dw = w;
-                                qe.a0 = 0.0f; qe.role = 0u; qe.flag0 = 0u;
+                                qe.a0 = 0.0f; qe.role = 0u;
                             }
                             active = false;
                         } else {
@@ -1444,43 +1462,41 @@ GDPM_DEV void photon_pass(Ctl* ctl, const Tables& T, const RunDev& R, const floa
                             if (p_local) {
                                 float du, dv, dw;
                                 sample_iso(rng, k0, k1, du, dv, dw);
-                                deposit(tl, W, pb, vv, tp);
+                                dep = (double)tp;
                                 qg.n = 2; qg.e = 0.5f * aa; qg.u = du; qg.v = dv; qg.w = dw; qg.wb = 2u;
                             }
-                            if (e_local) deposit(tl, W, pb, vv, tm);
+                            if (e_local) dep += (double)tm;
                             qe.du = u; qe.dv = v; qe.dw = w;
                             if (!e_local) {
-                                qe.n = 1; qe.e0 = tm; qe.a0 = 0.0f; qe.role = 0u; qe.flag0 = 0u;
+                                qe.n = 1; qe.e0 = tm; qe.a0 = 0.0f; qe.role = 0u;
                                 if (!p_local) {
                                     qe.n = 2; qe.e1 = tp; qe.a1 = aa;
                                 }
                             } else if (!p_local) {
-                                qe.n = 1; qe.e0 = tp; qe.a0 = aa; qe.role = 1u; qe.flag0 = 1u;
+                                qe.n = 1; qe.e0 = tp; qe.a0 = aa; qe.role = 1u;
                             }
                             active = false;
                         }
-                        tally_flush(tl, W, pb);
-                        if (!active) history_flush(tl, W, rng.hlo, rng.hhi);
                         pm = -1;
                     }
-                    wt.it[0] += (uint32_t)__popcll(ballot(itype == 1));
-                    wt.it[1] += (uint32_t)__popcll(ballot(itype == 2));
+                    if (dep != 0.0) add_dose(J, pb, vv, dep, rng);
+                    wt.dep += count(dep != 0.0);
+                    wt.it[0] += count(itype == 1);
+                    wt.it[1] += count(itype == 2);
+                    // secondaries: electrons/positrons to queue 1, annihilation photons to queue 0
+                    const uint32_t jb = W.tag | (pb << 16);
+                    push_charged(qe, pe, A, J, jb, x, y, z, pack_vox(ix, iy, iz), rng, wt);
+                    push_photons(qg, pg, A, J, jb, x, y, z, rng, wt);
                 }
-            }
-            // secondaries: electrons/positrons to queue 1, annihilation photons to queue 0
-            wt.died += (uint32_t)__popcll(act0 & ~ballot(active));
-            const uint32_t jb = W.tag | (pb << 16);
-            push_charged(qe, pe, head_e, ctl, R, W, jb, bufe, x, y, z, pack_vox(ix, iy, iz), rng, wt);
-            push_photons(qg, pg, head_g, ctl, R, W, jb, bufg, x, y, z, rng, wt);
+                wt.died += (uint32_t)__popcll(act0 & ~ballot(active));
             }
             if (++iters > kMaxWaveIterations) {
                 // safety net, never reached in a sound run: end the particles
                 // still held (counted as anomalies) so the grid always drains
-                const uint32_t n = (uint32_t)__popcll(ballot(active));
+                const uint32_t n = count(active);
                 wt.died += n;
                 wt.bad += n;
                 active = false;
-                last_job = true;
                 break;
             }
             if (cs.done) {
@@ -1489,50 +1505,59 @@ GDPM_DEV void photon_pass(Ctl* ctl, const Tables& T, const RunDev& R, const floa
                 // early; the particles still held go to the next pass
                 int nj = -1;
                 if (!last_job) {
-                    nj = next_job(jc, W.j, R.n_jobs, 0);
+                    nj = next_job(global_ptr(A->R.jc), W.j, A->R.n_jobs, 0);
                     last_job = nj < 0;
                 }
-                if (nj >= 0 || (big && __popcll(ballot(active)) < kTailLanes)) {
-                    Particle q;
-                    q.x = x; q.y = y; q.z = z; q.e = e;
-                    q.u = u; q.v = v; q.w = w; q.nh = -1.0f;
-                    q.hlo = rng.hlo; q.hhi = rng.hhi; q.path = rng.path; q.ctr = rng_ctr(rng);
-                    q.vox = 0u; q.a = 0.0f; q.flags = 0u; q.job = W.tag | (pb << 16);
-                    if (requeue(active, pg, head_g, ctl, &ctl->ring[0], R.hard[0], bufg, R.mask[0], q, wt)) {
-                        history_flush(tl, W, rng.hlo, rng.hhi);
-                    }
-                    active = false;
+                if (nj >= 0 || (big && count(active) < kTailLanes)) {
+                    Rec q;
+                    q.a = f4{x, y, z, e};
+                    q.b = f4{u, v, w, -1.0f};
+                    q.c = u4{rng.hlo, rng.hhi, rng.path, rng_ctr(rng)};
+                    q.d = u4{0u, 0u, 0u, W.tag | (pb << 16)};
+                    requeue(active, pg, A, 0, q, wt);
                     next = nj;
                     break;
                 }
             }
         }
-        tally_flush(tl, W, pb);
-        job_flush(tl, wt, W, jc);
+        job_flush(e_esc, wt, W, global_ptr(A0->R.jc));
         j = next;
     }
     // no staging load may still be writing the slice when the wave moves on
-    if (stage != nullptr) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    release(pe, bufe, R.mask[1]);
-    release(pg, bufg, R.mask[0]);
-    pass_finish(tl, wt, ctl, 0);
+    if constexpr (kStaged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    release(pe, A0, 1);
+    release(pg, A0, 0);
+    pass_finish(wt, global_ptr(A0->ctl), 0);
 }
 
+// The kernel's arguments are read through pass_args(); the parameter only
+// declares their layout.
 template <bool kLds, bool kSolo, bool kPerm>
-__global__ void __launch_bounds__(768) k_photon(Ctl* ctl, Tables T, RunDev R) {
-    const float4* ptab = T.phot;
-    float* lmw = nullptr;
-    float4* stage = nullptr;
+__global__ void __launch_bounds__(768) k_photon(PassArgs) {
+    const Args A = pass_args();
+    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (kLds) {
+        const GDPM_CONST Tables& T = A->T;
         const int np = T.n_mat * T.pg_n;
-        for (int i = threadIdx.x; i < np; i += blockDim.x) lds_tables[i] = T.phot[i];
-        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        lmw = reinterpret_cast<float*>(lds_tables + np) + wave * T.pg_n;
-        stage = lds_tables + stage_offset(0, T, blockDim.x >> 6) + wave * (4u * kStage);
+        for (int i = threadIdx.x; i < np; i += blockDim.x) lds[i] = global_f4(T.phot)[i];
+        GDPM_LDS float* lmaj = (GDPM_LDS float*)(lds + np);
+        if constexpr (!kPerm) {
+            // a pass of one job: its majorant too
+            const int j = first_job(A, ring_const(A, 0)->count, 0);
+            if (j >= 0) {
+                const GDPM_GLOBAL float* mj = global_ptr(((JobPtr)A->R.jobs)[j].mumax);
+                for (int i = threadIdx.x; i < T.pg_n; i += blockDim.x) lmaj[i] = mj[i];
+            }
+        }
         __syncthreads();
-        ptab = lds_tables;
+        GDPM_LDS f4* slice = lds + tables_f4(0, T) + wave * kSliceF4;
+        photon_pass<kSolo, kPerm, true, !kPerm>(A, (const GDPM_LDS f4*)lds, lmaj, slice,
+                                                (GDPM_LDS float*)(slice + 4u * kStage));
+    } else {
+        photon_pass<kSolo, kPerm, false, false>(A, global_f4(A->T.phot), nullptr, nullptr,
+                                                (GDPM_LDS float*)(lds + wave * kRingF4));
     }
-    photon_pass<kSolo, kPerm>(ctl, T, R, ptab, lmw, stage);
 }
 
 // ---------------------------------------------------------------------------
@@ -1541,171 +1566,156 @@ __global__ void __launch_bounds__(768) k_photon(Ctl* ctl, Tables T, RunDev R) {
 // ---------------------------------------------------------------------------
 // One wavefront's share of an electron pass.  etab, rtab, rscale: the
 // stopping and scattering data, the inverse range and its scales (LDS or
-// global); stage: the wavefront's LDS slice for staged records (null: none).
-template <bool kSolo, bool kPerm>
-GDPM_DEV void electron_pass(Ctl* ctl, const Tables& T, const RunDev& R, const float4* etab, const float* rtab,
-                            const float* rscale, float4* stage) {
-    RingCtl* rc = &ctl->ring[1];
-    const uint32_t begin = rc->begin, count = rc->count;
-    const uint32_t* perm_in =
-        kPerm && __builtin_amdgcn_readfirstlane(rc->permuted) ? bin_perm(R.bin[1], R.mask[1]) : nullptr;
-    const bool big = !kSolo && count >= kTailMinPerLane * gridDim.x * blockDim.x;
-    Particle* bufg = R.buf[0];
-    Particle* bufe = R.buf[1];
-    const uint32_t head_g = ctl->ring[0].head, head_e = ctl->ring[1].head;
-    JobCtl* jc = R.jc;
-    const float ecut = R.ecut_e;
+// global); stage: the wavefront's LDS slice for staged records (kStaged);
+// ring: its generator words.
+template <bool kSolo, bool kPerm, bool kStaged, class PE, class PR>
+GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* stage, GDPM_LDS float* ring) {
+    const GDPM_CONST RingCtl* rc = ring_const(A0, 1);
+    const uint32_t begin = rc->begin, total = rc->count;
+    const GDPM_GLOBAL uint32_t* perm_in =
+        kPerm && rc->permuted ? global_ptr(bin_perm(A0->R.bin[1], A0->R.mask[1])) : nullptr;
+    const bool big = !kSolo && total >= kTailMinPerLane * gridDim.x * blockDim.x;
 
-    int j = first_job(R, count, 1);
+    int j = first_job(A0, total, 1);
     PushState pg{0u, 0u}, pe{0u, 0u};
-    LaneTally tl;
-    tally_init(tl);
-    WaveTally wt{0u, 0u, 0u, 0u, 0u, 0u, 0u, {0u, 0u}};
+    double e_esc = 0.0;   // escaped energy of the current job
+    WaveTally wt{};
     uint32_t iters = 0u;
-    bool last_job = false;   // no other job has records left in this pass
+    bool last_job = !kPerm;   // no other job has records left in this pass
     // one job at a time: a wavefront switches jobs with all its lanes empty
     while (j >= 0) {
         WJob W;
-        load_job(W, R, j, 1);
+        load_job(W, A0, j, 1);
         ClaimState cs{0u, 0u, 0u, false, 0u, 0u};
         bool active = false;
-        float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0, nh = -1.0f, aa = 0.0f;
+        float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0, nh = -1.0f;
+        float aa = 0.0f;    // > 0: a positron, and its annihilation energy
         int ix = 0, iy = 0, iz = 0;
-        float rho = 1.0f;   // density and material of the current voxel, reloaded
-        int mat = 0;        // when the particle enters a voxel
-        bool positron = false;
+        uint32_t vx = 0u;   // the current voxel, reloaded when the particle enters one
+        double de = 0.0;    // deposit in it, not yet tallied
         float hq = -1.0f;   // >= 0: a hard event waits; the step-start mu_h per g/cm^2
         uint32_t pb = 0u;   // batch slot of the lane's history
         Rng rng;
+        rng.buf = ring + lane_id();
         rng_start(rng, 0u, 0u, 0u, 0u);
         int next = -1;
         for (;;) {
-            const uint32_t k0 = W.k0, k1 = W.k1;
-            const bool no_ms = (W.flags & 8u) != 0u;
-            Particle p;
-            if (refill<kSolo>(active, cs, jc, W, begin, ctl, bufe, R.mask[1], perm_in, p, wt, stage)) {
-                x = p.x; y = p.y; z = p.z; e = p.e;
-                u = p.u; v = p.v; w = p.w; nh = p.nh;
-                ix = (int)(p.vox & 2047u);
-                iy = (int)((p.vox >> 11) & 2047u);
-                iz = (int)(p.vox >> 22);
-                aa = p.a;
-                positron = (p.flags & 1u) != 0u;
-                pb = p.job >> 16;
-                rng_start(rng, p.hlo, p.hhi, p.path, p.ctr);
-                const uint32_t vx = W.G.vox[ix + W.G.nx * (iy + W.G.ny * iz)];
-                rho = voxel_density(vx);
-                mat = voxel_material(vx);
+            const Args A = reread(A0);
+            const JobPtr J = reread(W.p);
+            const float ecut = A->R.ecut_e;
+            Rec p;
+            if (refill<kSolo, kStaged>(active, cs, A, W, 1, begin, perm_in, p, wt, stage)) {
+                x = p.a.x; y = p.a.y; z = p.a.z; e = p.a.w;
+                u = p.b.x; v = p.b.y; w = p.b.z; nh = p.b.w;
+                ix = (int)(p.d.x & 2047u);
+                iy = (int)((p.d.x >> 11) & 2047u);
+                iz = (int)(p.d.x >> 22);
+                aa = (p.d.z & 1u) ? __uint_as_float(p.d.y) : 0.0f;
+                pb = p.d.w >> 16;
+                rng_start(rng, p.c.x, p.c.y, p.c.z, p.c.w);
+                vx = global_ptr(J->G.vox)[ix + J->G.nx * (iy + J->G.ny * iz)];
                 active = true;
             }
             if (!ballot(active)) {
                 if (cs.done && last_job) break;
                 if (!cs.done) continue;
             } else {
-            rng_topup(rng, k0, k1);
-            const uint64_t act0 = ballot(active);
-            wt.events += (uint32_t)__popcll(ballot(active && hq < 0.0f && !(e <= ecut)));
-
-            PendCharged qe;
-            PendPhoton qg;
-            qe.n = 0;
-            qg.n = 0;
-            if (active && !(e <= kMaxEnergy)) {
-                // a non-finite energy can only come from a damaged record (see the
-                // photon pass)
-                atomicAdd(&ctl->anomalies, 1ull);
-                active = false;
-                hq = -1.0f;
-            }
-            if (active && hq < 0.0f) {
-                const int vv = ix + W.G.nx * (iy + W.G.ny * iz);
-                if (e <= ecut) {
-                    // absorption; a positron annihilates at rest into two photons
-                    deposit(tl, W, pb, vv, e);
-                    if (positron) {
-                        float du, dv, dw;
-                        sample_iso(rng, k0, k1, du, dv, dw);
-                        qg.n = 2; qg.e = 0.5f * aa; qg.u = du; qg.v = dv; qg.w = dw; qg.wb = 0u;
-                    }
+                const uint64_t act0 = ballot(active);
+                if (active && !(e <= kMaxEnergy)) {
+                    // a non-finite energy can only come from a damaged record: end the
+                    // particle (counted as an anomaly) rather than feed it to a
+                    // rejection sampler that would never accept
+                    atomic_add(&global_ptr(A->ctl)->anomalies, 1ull);
                     active = false;
-                } else {
+                    hq = -1.0f;
+                }
+                const bool step = active && hq < 0.0f && e > ecut;
+                wt.events += count(step);
+                // a step draws at most 4 numbers, the first for a fresh hard-event distance
+                rng_topup(rng, step, active, 4u, J->k0, J->k1);
+                const int vv = ix + J->G.nx * (iy + J->G.ny * iz);   // voxel of the step
+                bool crossed = false;
+                if (step) {
+                    const bool no_ms = (J->flags & 8u) != 0u;
+                    const float rho = voxel_density(vx);
+                    const int m = voxel_material(vx);
                     const float irho = hrcp(rho);
-                    const int m = mat;
-                    if (nh < 0.0f) nh = neg_ln(uniform(rng, k0, k1));
+                    if (nh < 0.0f) nh = neg_ln(rng.draw());
+                    const float xi = rng.draw();
                     const float t0 = e;
-                    const float4 q0 = elec_at(T, etab, m, t0);
+                    const f4 q0 = elec_at(A->T, etab, m, t0);
                     const float mus = rho * q0.y;
                     const float sh = mus > 0.0f ? nh * hrcp(mus) : 3.0e38f;
                     const float tfl = fmaxf(0.75f * t0, ecut);
-                    const float rfl = tfl > ecut ? elec_at(T, etab, m, tfl).x : 0.0f;
+                    const float rfl = tfl > ecut ? elec_at(A->T, etab, m, tfl).x : 0.0f;
                     const float se = (q0.x - rfl) * irho;
                     const bool hard = sh < se;
                     const float s = hard ? sh : se;
-                    const float xi = uniform(rng, k0, k1);
                     const float s1 = xi * s, s2 = s - s1;
-                    const float tend = hard ? fminf(fmaxf(range_inv(T, rtab, rscale, m, q0.x - rho * s), tfl), t0) : tfl;
+                    float tend = tfl;
+                    if (hard) tend = fminf(fmaxf(range_inv(A->T, rtab, rscale, m, q0.x - rho * s), tfl), t0);
                     // first half: to the hinge, or to the voxel face if that comes
                     // first.  Lanes that cross and lanes that reach the hinge share
                     // one move, one range lookup and one deposit.
                     int ax;
-                    float db = face_dist(W.G, x, y, z, u, v, w, ix, iy, iz, ax);
-                    bool crossed = db < s1;
+                    float db = face_dist(J->G, x, y, z, u, v, w, ix, iy, iz, ax);
+                    crossed = db < s1;
                     float travelled = db;
                     {
                         const float d1 = crossed ? db : s1;
                         x = fmaf(d1, u, x); y = fmaf(d1, v, y); z = fmaf(d1, w, z);
-                        const float t1 = fminf(fmaxf(range_inv(T, rtab, rscale, m, q0.x - rho * d1), tend), e);
-                        deposit(tl, W, pb, vv, e - t1);
+                        const float t1 =
+                            fminf(fmaxf(range_inv(A->T, rtab, rscale, m, q0.x - rho * d1), tend), e);
+                        de += (double)(e - t1);
                         e = t1;
                     }
                     if (!crossed) {
                         // hinge: modified-Wentzel deflection for the whole step
                         if (!no_ms) {
                             const float tmid = 0.5f * (t0 + tend);
-                            const float tt = s * rho * elec_at(T, etab, m, tmid).w;
-                            const float mu = mw_mu(T, tt, uniform(rng, k0, k1));
-                            const float turns = uniform(rng, k0, k1);
+                            const float tt = s * rho * elec_at(A->T, etab, m, tmid).w;
+                            const float mu = mw_mu(A->T, tt, rng.draw());
+                            const float turns = rng.draw();
                             rotate(u, v, w, 1.0f - 2.0f * mu, 2.0f * hsqrt(mu * (1.0f - mu)), turns);
                         }
                         // second half: to the step end or the face; a lane that
                         // reaches the end loses exactly the energy left above tend
-                        db = face_dist(W.G, x, y, z, u, v, w, ix, iy, iz, ax);
+                        db = face_dist(J->G, x, y, z, u, v, w, ix, iy, iz, ax);
                         crossed = db < s2;
                         travelled = s1 + db;
                         const float d2 = crossed ? db : s2;
                         x = fmaf(d2, u, x); y = fmaf(d2, v, y); z = fmaf(d2, w, z);
                         float t2 = tend;
-                        if (crossed) t2 = fminf(fmaxf(range_inv(T, rtab, rscale, m, q0.x - rho * travelled), tend), e);
-                        deposit(tl, W, pb, vv, e - t2);
+                        if (crossed)
+                            t2 = fminf(fmaxf(range_inv(A->T, rtab, rscale, m, q0.x - rho * travelled), tend), e);
+                        de += (double)(e - t2);
                         e = t2;
                     }
                     if (crossed) {
                         nh -= mus * travelled;
                         // move onto the face and into the next voxel
-                        if (ax == 0) {
-                            const int st = u > 0.0f ? 1 : -1;
-                            x = (float)(st > 0 ? ix + 1 : ix) * W.G.dx;
-                            ix += st;
-                        } else if (ax == 1) {
-                            const int st = v > 0.0f ? 1 : -1;
-                            y = (float)(st > 0 ? iy + 1 : iy) * W.G.dy;
-                            iy += st;
-                        } else {
-                            const int st = w > 0.0f ? 1 : -1;
-                            z = (float)(st > 0 ? iz + 1 : iz) * W.G.dz;
-                            iz += st;
-                        }
-                        if (ix < 0 || ix >= W.G.nx || iy < 0 || iy >= W.G.ny || iz < 0 || iz >= W.G.nz) {
+                        const bool a0 = ax == 0, a1 = ax == 1;
+                        const float da = a0 ? u : (a1 ? v : w);
+                        const int ia = a0 ? ix : (a1 ? iy : iz);
+                        const int na = a0 ? J->G.nx : (a1 ? J->G.ny : J->G.nz);
+                        const float ha = a0 ? J->G.dx : (a1 ? J->G.dy : J->G.dz);
+                        const int in = da > 0.0f ? ia + 1 : ia - 1;
+                        const float pa = (float)(da > 0.0f ? in : ia) * ha;
+                        x = a0 ? pa : x;
+                        y = a1 ? pa : y;
+                        z = a0 || a1 ? z : pa;
+                        ix = a0 ? in : ix;
+                        iy = a1 ? in : iy;
+                        iz = a0 || a1 ? iz : in;
+                        if ((unsigned)in >= (unsigned)na) {
                             // a positron takes its annihilation energy along (summed in FP64)
-                            const double out = (double)e + (positron ? (double)aa : 0.0);
-                            tl.e_esc += out;
-                            tl.h_esc += out;
+                            const double out = (double)e + (double)aa;
+                            e_esc += out;
+                            history_escape(J, out, rng);
                             active = false;
                         } else {
                             // the next voxel's density and material, needed by the next step
-                            const uint32_t vx = W.G.vox[ix + W.G.nx * (iy + W.G.ny * iz)];
-                            rho = voxel_density(vx);
-                            mat = voxel_material(vx);
+                            vx = global_ptr(J->G.vox)[ix + J->G.nx * (iy + J->G.ny * iz)];
                         }
                     } else if (hard) {
                         hq = q0.y;   // the hard event waits (see below)
@@ -1713,29 +1723,27 @@ GDPM_DEV void electron_pass(Ctl* ctl, const Tables& T, const RunDev& R, const fl
                         nh -= mus * s;
                     }
                 }
-                if (!active) {
-                        tally_flush(tl, W, pb);
-                    history_flush(tl, W, rng.hlo, rng.hhi);
-                }
-            }
-            // Hard events are rare (a few per hundred steps): run as they come,
-            // their sampling would occupy the whole wavefront for one or two
-            // lanes in most iterations.  A lane with one waits, where it is and
-            // without drawing, until kHardBatch lanes wait, the wavefront has no
-            // other live lane, or the pass has nothing left to claim; then they
-            // are sampled together.  Each particle's draws keep their order.
-            {
+                // Hard events are rare (a few per hundred steps): run as they come,
+                // their sampling would occupy the whole wavefront for one or two
+                // lanes in most iterations.  A lane with one waits, where it is and
+                // without drawing, until kHardBatch lanes wait, the wavefront has no
+                // other live lane, or the pass has nothing left to claim; then they
+                // are sampled together.  Each particle's draws keep their order.
+                PendCharged qe;
+                PendPhoton qg;
+                qe.n = 0;
+                qg.n = 0;
                 const uint64_t bh = ballot(hq >= 0.0f);
                 if (bh && (cs.done || (uint32_t)__popcll(bh) >= kHardBatch || bh == ballot(active))) {
                     int htype = -1;   // the hard event sampled by this lane
+                    wt.real[0] += (uint32_t)__popcll(bh);
+                    rng_topup(rng, hq >= 0.0f, active, 4u, J->k0, J->k1);
                     if (hq >= 0.0f) {
+                        const uint32_t k0 = J->k0, k1 = J->k1;
                         // delta scattering against the step-start majorant
                         // (mu_h grows with T; the step ended at e)
-                        const int vv = ix + W.G.nx * (iy + W.G.ny * iz);
-                        tl.ev[EV_HARD_CAND]++;
-                        const float4 q1 = elec_at(T, etab, mat, e);
+                        const f4 q1 = elec_at(A->T, etab, voxel_material(vx), e);
                         if (uniform(rng, k0, k1) * hq < q1.y) {
-                            tl.ev[EV_HARD]++;
                             htype = uniform(rng, k0, k1) * q1.y < q1.z ? 0 : 1;
                             if (htype == 0) {
                                 float eps, turns;
@@ -1751,15 +1759,15 @@ GDPM_DEV void electron_pass(Ctl* ctl, const Tables& T, const RunDev& R, const fl
                                 rotate(du, dv, dw, cd, hsqrt(fmaxf(0.0f, 1.0f - cd * cd)), turns);
                                 rotate(u, v, w, cpr, hsqrt(fmaxf(0.0f, 1.0f - cpr * cpr)), turns + 0.5f);
                                 if (wd <= ecut) {
-                                    deposit(tl, W, pb, vv, wd);
+                                    de += (double)wd;
                                 } else {
                                     qe.n = 1; qe.e0 = wd; qe.du = du; qe.dv = dv; qe.dw = dw;
-                                    qe.a0 = 0.0f; qe.role = 0u; qe.flag0 = 0u;
+                                    qe.a0 = 0.0f; qe.role = 0u;
                                 }
                                 e = tp;
                             } else {
                                 const float tt = e;
-                                const float kph = sample_brems(rng, k0, k1, tt, R.ecut_g);
+                                const float kph = sample_brems(rng, k0, k1, tt, A->R.ecut_g);
                                 float kp, el;
                                 if (2.0f * kph >= tt) {
                                     kp = kph;
@@ -1775,22 +1783,45 @@ GDPM_DEV void electron_pass(Ctl* ctl, const Tables& T, const RunDev& R, const fl
                         nh = -1.0f;
                         hq = -1.0f;
                     }
-                    wt.it[0] += (uint32_t)__popcll(ballot(htype == 0));
+                    wt.real[1] += count(htype >= 0);
+                    wt.it[0] += count(htype == 0);
                 }
-            }
-            wt.died += (uint32_t)__popcll(act0 & ~ballot(active));
-            const uint32_t jb = W.tag | (pb << 16);
-            push_charged(qe, pe, head_e, ctl, R, W, jb, bufe, x, y, z, pack_vox(ix, iy, iz), rng, wt);
-            push_photons(qg, pg, head_g, ctl, R, W, jb, bufg, x, y, z, rng, wt);
+                // Absorption, in the iteration that brings the particle below its
+                // absorption energy (a particle that has just entered a voxel, or a
+                // positron with a secondary to push, is absorbed in the next one); a
+                // positron annihilates at rest into two photons.
+                const bool absorb =
+                    active && hq < 0.0f && e <= ecut && !crossed && !(aa > 0.0f && qe.n + qg.n > 0);
+                if (absorb) {
+                    de += (double)e;
+                    if (aa > 0.0f) {
+                        float du, dv, dw;
+                        rng.ensure(2u, J->k0, J->k1);
+                        sample_iso(rng, J->k0, J->k1, du, dv, dw);
+                        qg.n = 2; qg.e = 0.5f * aa; qg.u = du; qg.v = dv; qg.w = dw; qg.wb = 0u;
+                    }
+                    active = false;
+                }
+                // the deposit of a voxel goes to the tally when the particle leaves
+                // the voxel or ends
+                const bool flush = (crossed || absorb) && de != 0.0;
+                if (flush) {
+                    add_dose(J, pb, vv, de, rng);
+                    de = 0.0;
+                }
+                wt.dep += count(flush);
+                wt.died += (uint32_t)__popcll(act0 & ~ballot(active));
+                const uint32_t jb = W.tag | (pb << 16);
+                push_charged(qe, pe, A, J, jb, x, y, z, pack_vox(ix, iy, iz), rng, wt);
+                push_photons(qg, pg, A, J, jb, x, y, z, rng, wt);
             }
             if (++iters > kMaxWaveIterations) {
                 // safety net, never reached in a sound run: end the particles
                 // still held (counted as anomalies) so the grid always drains
-                const uint32_t n = (uint32_t)__popcll(ballot(active));
+                const uint32_t n = count(active);
                 wt.died += n;
                 wt.bad += n;
                 active = false;
-                last_job = true;
                 break;
             }
             if (cs.done) {
@@ -1799,56 +1830,61 @@ GDPM_DEV void electron_pass(Ctl* ctl, const Tables& T, const RunDev& R, const fl
                 // early; the particles still held go to the next pass
                 int nj = -1;
                 if (!last_job) {
-                    nj = next_job(jc, W.j, R.n_jobs, 1);
+                    nj = next_job(global_ptr(A->R.jc), W.j, A->R.n_jobs, 1);
                     last_job = nj < 0;
                 }
-                if (nj >= 0 || (big && __popcll(ballot(active)) < kTailLanes)) {
-                    Particle q;
-                    q.x = x; q.y = y; q.z = z; q.e = e;
-                    q.u = u; q.v = v; q.w = w; q.nh = nh;
-                    q.hlo = rng.hlo; q.hhi = rng.hhi; q.path = rng.path; q.ctr = rng_ctr(rng);
-                    q.vox = pack_vox(ix, iy, iz); q.a = aa; q.flags = positron ? 1u : 0u;
-                    q.job = W.tag | (pb << 16);
-                    if (requeue(active, pe, head_e, ctl, &ctl->ring[1], R.hard[1], bufe, R.mask[1], q, wt)) {
-                        history_flush(tl, W, rng.hlo, rng.hhi);
-                    }
-                    active = false;
+                if (nj >= 0 || (big && count(active) < kTailLanes)) {
+                    Rec q;
+                    q.a = f4{x, y, z, e};
+                    q.b = f4{u, v, w, nh};
+                    q.c = u4{rng.hlo, rng.hhi, rng.path, rng_ctr(rng)};
+                    q.d = u4{pack_vox(ix, iy, iz), __float_as_uint(aa), aa > 0.0f ? 1u : 0u, W.tag | (pb << 16)};
+                    requeue(active, pe, A, 1, q, wt);
                     next = nj;
                     break;
                 }
             }
         }
-        tally_flush(tl, W, pb);
-        job_flush(tl, wt, W, jc);
+        // deposits of the particles handed on (or ended by the bound), in their voxels
+        if (de != 0.0) add_dose(W.p, pb, ix + W.p->G.nx * (iy + W.p->G.ny * iz), de, rng);
+        wt.dep += count(de != 0.0);
+        job_flush(e_esc, wt, W, global_ptr(A0->R.jc));
         j = next;
     }
     // no staging load may still be writing the slice when the wave moves on
-    if (stage != nullptr) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    release(pe, bufe, R.mask[1]);
-    release(pg, bufg, R.mask[0]);
-    pass_finish(tl, wt, ctl, 1);
+    if constexpr (kStaged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    release(pe, A0, 1);
+    release(pg, A0, 0);
+    pass_finish(wt, global_ptr(A0->ctl), 1);
+}
+
+// stage the electron tables; every thread of the workgroup takes part
+GDPM_DEV void stage_electron_tables(const GDPM_CONST Tables& T, GDPM_LDS f4* lds) {
+    const int ne = T.n_mat * T.eg_n, nr = T.n_mat * T.nr;
+    for (int i = threadIdx.x; i < ne; i += blockDim.x) lds[i] = global_f4(T.elec)[i];
+    GDPM_LDS float* lr = (GDPM_LDS float*)(lds + ne);
+    for (int i = threadIdx.x; i < nr; i += blockDim.x) lr[i] = global_ptr(T.rinv)[i];
+    for (int i = threadIdx.x; i < T.n_mat; i += blockDim.x) lr[nr + i] = global_ptr(T.rinv_scale)[i];
+    __syncthreads();
 }
 
 template <bool kLds, bool kSolo, bool kPerm>
-__global__ void __launch_bounds__(768) k_electron(Ctl* ctl, Tables T, RunDev R) {
-    const float4* etab = T.elec;
-    const float* rtab = T.rinv;
-    const float* rscale = T.rinv_scale;
-    float4* stage = nullptr;
+__global__ void __launch_bounds__(768) k_electron(PassArgs) {
+    const Args A = pass_args();
+    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (kLds) {
-        const int ne = T.n_mat * T.eg_n, nr = T.n_mat * T.nr;
-        stage = lds_tables + stage_offset(1, T, blockDim.x >> 6) +
-                __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (4u * kStage);
-        for (int i = threadIdx.x; i < ne; i += blockDim.x) lds_tables[i] = T.elec[i];
-        float* lr = reinterpret_cast<float*>(lds_tables + ne);
-        for (int i = threadIdx.x; i < nr; i += blockDim.x) lr[i] = T.rinv[i];
-        for (int i = threadIdx.x; i < T.n_mat; i += blockDim.x) lr[nr + i] = T.rinv_scale[i];
-        __syncthreads();
-        etab = lds_tables;
-        rtab = lr;
-        rscale = lr + nr;
+        const GDPM_CONST Tables& T = A->T;
+        stage_electron_tables(T, lds);
+        const GDPM_LDS float* lr = (const GDPM_LDS float*)(lds + T.n_mat * T.eg_n);
+        GDPM_LDS f4* slice = lds + tables_f4(1, T) + wave * kSliceF4;
+        electron_pass<kSolo, kPerm, true>(A, (const GDPM_LDS f4*)lds, lr, lr + T.n_mat * T.nr, slice,
+                                          (GDPM_LDS float*)(slice + 4u * kStage));
+    } else {
+        electron_pass<kSolo, kPerm, false>(A, global_f4(A->T.elec), (const GDPM_GLOBAL float*)global_ptr(A->T.rinv),
+                                           (const GDPM_GLOBAL float*)global_ptr(A->T.rinv_scale), nullptr,
+                                           (GDPM_LDS float*)(lds + wave * kRingF4));
     }
-    electron_pass<kSolo, kPerm>(ctl, T, R, etab, rtab, rscale, stage);
 }
 
 // ---------------------------------------------------------------------------
@@ -1863,21 +1899,21 @@ __global__ void __launch_bounds__(768) k_electron(Ctl* ctl, Tables T, RunDev R) 
 // is transported in the next iteration.
 // ---------------------------------------------------------------------------
 template <bool kPerm>
-__global__ void __launch_bounds__(768) k_transport(Ctl* ctl, Tables T, RunDev R, int photon_waves) {
-    const int ne = T.n_mat * T.eg_n, nr = T.n_mat * T.nr;
+__global__ void __launch_bounds__(768) k_transport(PassArgs) {
+    const Args A = pass_args();
+    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float4* stage = lds_tables + stage_offset(1, T, blockDim.x >> 6) + wave * (4u * kStage);
-    for (int i = threadIdx.x; i < ne; i += blockDim.x) lds_tables[i] = T.elec[i];
-    float* lr = reinterpret_cast<float*>(lds_tables + ne);
-    for (int i = threadIdx.x; i < nr; i += blockDim.x) lr[i] = T.rinv[i];
-    for (int i = threadIdx.x; i < T.n_mat; i += blockDim.x) lr[nr + i] = T.rinv_scale[i];
-    __syncthreads();
+    const GDPM_CONST Tables& T = A->T;
+    stage_electron_tables(T, lds);
+    const GDPM_LDS float* lr = (const GDPM_LDS float*)(lds + T.n_mat * T.eg_n);
+    GDPM_LDS f4* slice = lds + tables_f4(1, T) + wave * kSliceF4;
+    GDPM_LDS float* ring = (GDPM_LDS float*)(slice + 4u * kStage);
     for (int k = 0; k < 2; ++k) {
-        const bool photons = ((int)wave < photon_waves) == (k == 0);
+        const bool photons = ((int)wave < A->photon_waves) == (k == 0);
         if (photons)
-            photon_pass<false, kPerm>(ctl, T, R, T.phot, nullptr, stage);
+            photon_pass<false, kPerm, true, false>(A, global_f4(A->T.phot), nullptr, slice, ring);
         else
-            electron_pass<false, kPerm>(ctl, T, R, lds_tables, lr, lr + nr, stage);
+            electron_pass<false, kPerm, true>(A, (const GDPM_LDS f4*)lds, lr, lr + T.n_mat * T.nr, slice, ring);
     }
 }
 
@@ -2139,9 +2175,7 @@ __global__ void k_test_sample(Tables T, int which, float e, float p1, float p2, 
                               uint32_t k1, int n, float* out1, float* out2) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    Rng r;
-    rng_start(r, (uint32_t)i, 0u, 0u, 0u);
-    rng_topup(r, k0, k1);
+    RegRng r((uint32_t)i, 0u, 0u);
     float a = 0.0f, b = 0.0f;
     if (which == 0) {
         float eps, t, turns;
@@ -2197,10 +2231,7 @@ __global__ void k_test_sample(Tables T, int which, float e, float p1, float p2, 
 GDPM_DEV void test_source_one(const SourceDev& S, const Geom& G, uint32_t k0, uint32_t k1,
                               unsigned long long hist0, int i, int n, float* out, uint32_t* chain) {
     const unsigned long long h = hist0 + i;
-    Rng r;
-    rng_start(r, (uint32_t)h, (uint32_t)(h >> 32), 0u, 0u);
-    rng_topup(r, k0, k1);
-    const Primary p = make_primary(S, G, r, k0, k1, chain, (uint32_t)i, (uint32_t)n);
+    const Primary p = make_primary(S, G, h, k0, k1, chain, (uint32_t)i, (uint32_t)n);
     float* o = out + 8 * (size_t)i;
     o[0] = p.e;
     o[1] = p.in ? (float)p.beamlet : -1.0f;
@@ -2240,12 +2271,12 @@ __global__ void k_test_lookup(Tables T, int which, int m, const float* in, float
         int gi;
         float gt;
         grid(hlog2(x), T.pg_lo, T.pg_inv, T.pg_n, gi, gt);
-        r = lerp4(T.phot + m * T.pg_n, gi, gt).w;
+        r = lerp4(global_f4(T.phot) + m * T.pg_n, gi, gt).w;
     } else if (which >= 1 && which <= 4) {
-        const float4 q = elec_at(T, m, x);
+        const f4 q = elec_at(T, global_f4(T.elec), m, x);
         r = which == 1 ? q.x : (which == 2 ? q.y : (which == 3 ? q.z : q.w));
     } else if (which == 5) {
-        r = range_inv(T, m, x);
+        r = range_inv(T, global_ptr(T.rinv), global_ptr(T.rinv_scale), m, x);
     } else if (which == 6) {
         r = mw_screening(T, x);
     }
@@ -2269,9 +2300,11 @@ hipError_t launch_finish(hipStream_t st, Ctl* ctl, int ri) {
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(1), 0, st, ctl, ri);
     return hipGetLastError();
 }
-// LDS bytes the table staging of a pass needs with `waves` wavefronts per block
-size_t transport_lds_bytes(int ri, const Tables& T, int waves) {
-    return ((size_t)stage_offset(ri, T, waves) + (size_t)waves * 4u * kStage) * sizeof(float4);
+// LDS bytes of a pass with `waves` wavefronts per block (`lds`: tables and
+// records staged)
+size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds) {
+    const size_t per_wave = lds ? kSliceF4 : kRingF4;
+    return ((lds ? (size_t)tables_f4(ri, T) : 0) + (size_t)waves * per_wave) * sizeof(float4);
 }
 
 // allow the staged kernels to use `bytes` of dynamic LDS
@@ -2291,21 +2324,21 @@ hipError_t transport_lds_optin(size_t bytes) {
 namespace {
 template <bool kPerm>
 void launch_transport_form(hipStream_t st, int ri, int blocks, int threads, bool lds, bool solo, size_t bytes,
-                           Ctl* ctl, const Tables& T, const RunDev& R) {
+                           const PassArgs& a) {
     if (ri == 0) {
         if (solo)
-            hipLaunchKernelGGL((k_photon<true, true, kPerm>), dim3(blocks), dim3(threads), bytes, st, ctl, T, R);
+            hipLaunchKernelGGL((k_photon<true, true, kPerm>), dim3(blocks), dim3(threads), bytes, st, a);
         else if (lds)
-            hipLaunchKernelGGL((k_photon<true, false, kPerm>), dim3(blocks), dim3(threads), bytes, st, ctl, T, R);
+            hipLaunchKernelGGL((k_photon<true, false, kPerm>), dim3(blocks), dim3(threads), bytes, st, a);
         else
-            hipLaunchKernelGGL((k_photon<false, false, kPerm>), dim3(blocks), dim3(threads), 0, st, ctl, T, R);
+            hipLaunchKernelGGL((k_photon<false, false, kPerm>), dim3(blocks), dim3(threads), bytes, st, a);
     } else {
         if (solo)
-            hipLaunchKernelGGL((k_electron<true, true, kPerm>), dim3(blocks), dim3(threads), bytes, st, ctl, T, R);
+            hipLaunchKernelGGL((k_electron<true, true, kPerm>), dim3(blocks), dim3(threads), bytes, st, a);
         else if (lds)
-            hipLaunchKernelGGL((k_electron<true, false, kPerm>), dim3(blocks), dim3(threads), bytes, st, ctl, T, R);
+            hipLaunchKernelGGL((k_electron<true, false, kPerm>), dim3(blocks), dim3(threads), bytes, st, a);
         else
-            hipLaunchKernelGGL((k_electron<false, false, kPerm>), dim3(blocks), dim3(threads), 0, st, ctl, T, R);
+            hipLaunchKernelGGL((k_electron<false, false, kPerm>), dim3(blocks), dim3(threads), bytes, st, a);
     }
 }
 }  // namespace
@@ -2315,23 +2348,25 @@ void launch_transport_form(hipStream_t st, int ri, int blocks, int threads, bool
 // through the permutation)
 hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool solo, bool permuted,
                             Ctl* ctl, const Tables& T, const RunDev& R) {
-    const size_t bytes = lds ? transport_lds_bytes(ri, T, threads / 64) : 0;
+    const size_t bytes = transport_lds_bytes(ri, T, threads / 64, lds);
     if (solo && !lds) return hipErrorInvalidValue;
+    const PassArgs a{ctl, T, R, 0};
     if (permuted)
-        launch_transport_form<true>(st, ri, blocks, threads, lds, solo, bytes, ctl, T, R);
+        launch_transport_form<true>(st, ri, blocks, threads, lds, solo, bytes, a);
     else
-        launch_transport_form<false>(st, ri, blocks, threads, lds, solo, bytes, ctl, T, R);
+        launch_transport_form<false>(st, ri, blocks, threads, lds, solo, bytes, a);
     return hipGetLastError();
 }
 // both passes in one launch (k_transport); its LDS is the electron pass's
-// layout (transport_lds_bytes(1, T, threads / 64))
+// layout (transport_lds_bytes(1, T, threads / 64, true))
 hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_waves, bool permuted, Ctl* ctl,
                         const Tables& T, const RunDev& R) {
-    const size_t bytes = transport_lds_bytes(1, T, threads / 64);
+    const size_t bytes = transport_lds_bytes(1, T, threads / 64, true);
+    const PassArgs a{ctl, T, R, photon_waves};
     if (permuted)
-        hipLaunchKernelGGL((k_transport<true>), dim3(blocks), dim3(threads), bytes, st, ctl, T, R, photon_waves);
+        hipLaunchKernelGGL((k_transport<true>), dim3(blocks), dim3(threads), bytes, st, a);
     else
-        hipLaunchKernelGGL((k_transport<false>), dim3(blocks), dim3(threads), bytes, st, ctl, T, R, photon_waves);
+        hipLaunchKernelGGL((k_transport<false>), dim3(blocks), dim3(threads), bytes, st, a);
     return hipGetLastError();
 }
 
