@@ -7,7 +7,8 @@
 namespace gdpm {
 
 constexpr int kMaxMaterials = 8;
-constexpr uint32_t kPushChunk = 256;    // ring slots a wavefront reserves at a time
+constexpr uint32_t kPushMin = 32;       // ring slots a wavefront reserves at a time: its
+constexpr uint32_t kPushMax = 256;      // first claim of the pass, within these bounds
 constexpr uint32_t kClaimMin = 32;      // smallest number of queue items a wavefront claims
                                         // with one atomic, and the largest, per particle type:
 constexpr uint32_t kClaimMaxPhoton = 2048;   // a photon record lasts a few short iterations, so
@@ -59,21 +60,31 @@ struct alignas(16) Particle {
 };
 static_assert(sizeof(Particle) == 64, "particle record is 64 bytes");
 
-// One queue (ring buffer of 2^k records, indices wrap modulo 2^32).
-struct RingCtl {
-    uint32_t head, tail;     // records in [head, tail)
+// One queue (ring buffer of 2^k records, indices wrap modulo 2^32).  Counters
+// that many wavefronts add to have a cache line of their own each: additions to
+// one line are served one after the other (85 million a second, whatever the
+// address in it), and readers of its other words wait with them.
+struct alignas(128) RingCtl {
+    uint32_t tail;                   // records in [head, tail); wavefronts reserve slots here
+    uint32_t pad0[31];
+    uint32_t head;
     uint32_t begin, count;   // input of the running pass: [begin, begin + count)
-    uint32_t claim;          // claim counter of the running pass
+    uint32_t first;          // records a wavefront takes without claiming them (0: it claims)
+    uint32_t push;           // slots a wavefront of the running pass reserves at a time
     uint32_t permuted;       // 1: the pass reads its input through the permutation
     uint32_t next_head;      // head after a permuted pass (the tail before it)
+    uint32_t pad1[25];
 };
+static_assert(sizeof(RingCtl) == 256, "two cache lines");
 
 // Device-resident control block of the transport (the host reads it back
 // after every scheduler iteration).
 struct Ctl {
     RingCtl ring[2];                  // 0 photons, 1 electrons/positrons
-    uint32_t overflow;
+    uint32_t overflow;                // (read before every claim)
+    uint32_t pad0[31];
     uint32_t n_valid;                 // records kept by the last compaction
+    uint32_t pad1;
     unsigned long long ev[8];
     unsigned long long pass_ev[2][4];  // per pass type: records loaded, records
                                        // stored, tally deposits, records handed
@@ -84,6 +95,16 @@ struct Ctl {
     unsigned long long dmax_bits;
     unsigned long long anomalies;     // particles ended by a loop bound (0 in a sound run)
 };
+
+// counters of a transport pass, per particle type
+enum PassCounters { PC_EVENTS = 0,    // flights or steps
+                    PC_REAL,          // real interactions; hard-event candidates
+                    PC_HARD,          // electrons: hard events
+                    PC_DEPOSITS, PC_PUSHES, PC_LOADED, PC_REQUEUED, PC_ANOMALIES,
+                    PC_TYPE0,         // photoelectric; Moller
+                    PC_TYPE1,         // pair
+                    kPassCounters = 16 };
+constexpr int kParts = 8;
 
 // Per-job counters and the job segments of the running pass.  The first four
 // arrays are read back by the host after every iteration: a job whose births
@@ -100,6 +121,10 @@ struct JobCtl {
     unsigned long long left[2][kMaxJobs / 64];  // jobs with unclaimed records
     uint32_t bin_count[kMaxKeys];
     uint32_t bin_cursor[kMaxKeys];
+    // what the workgroups of a running pass counted (see PassCounters), in
+    // kParts parts that lie on different cache lines; folded into the control
+    // block by the pass's completion
+    unsigned long long part[2][kParts][kPassCounters];
 };
 
 // Interpolation tables (single precision, linear in log2 E).

@@ -32,10 +32,10 @@
 #include "tables.h"
 
 namespace gdpm {
-hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone);
+hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, int waves);
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
                          const SrcHdr* hdr, int ri);
-hipError_t launch_finish(hipStream_t st, Ctl* ctl, int ri);
+hipError_t launch_finish(hipStream_t st, Ctl* ctl, JobCtl* jc, int ri);
 size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds);
 hipError_t transport_lds_optin(size_t bytes);
 hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool solo, bool permuted,
@@ -237,8 +237,8 @@ struct StepGraphKey {
     int src_blocks[2];
     int rebin[2], lds[2];
     int lone;            // the one job holding particles (queues not re-binned), or -1
-    int blocks, threads, nb, space;
-    int threads_photon;        // block size of the photon pass (separate launches)
+    int blocks, nb, space;     // one workgroup per CU (source, re-binning)
+    int pass_blocks[2], threads[2];   // grid of each pass
     int fused, photon_waves;   // both passes in one launch; its photon-first wavefronts
     float blo, binv;
     RunDev R;
@@ -358,7 +358,7 @@ struct gdpm_source_s {
 
 namespace {
 
-constexpr int kMaxBlockThreads = 768;   // launch bound of the transport kernels
+constexpr int kMaxWaves = 12;           // wavefronts of the transport kernels' workgroups (launch bound)
 constexpr int kMaxSegs = 4096;          // source segments per iteration (both types)
 constexpr int kMaxBatches = 1000;       // N_b of a job
 constexpr int kMaxGrid = 8192;          // nodes of an interpolation grid
@@ -465,9 +465,19 @@ gdpm_status context_mem(gdpm_context ctx, EngineMem* m) {
     return GDPM_OK;
 }
 
-// persistent transport grid: one workgroup of waves_per_cu wavefronts per CU
 int grid_blocks(gdpm_context ctx) { return std::max(1, ctx->cu_count); }
-int block_threads(gdpm_context ctx) { return std::min(kMaxBlockThreads, 64 * ctx->waves_per_cu); }
+
+// persistent grid of a transport pass: one workgroup of waves_per_cu (photons:
+// photon_waves_per_cu) wavefronts per CU; lds: its tables and records are staged
+struct PassShape {
+    int blocks, threads, lds;
+};
+PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri) {
+    int waves = ctx->waves_per_cu;
+    if (ri == 0 && ctx->photon_waves_per_cu) waves = std::min(waves, ctx->photon_waves_per_cu);
+    return PassShape{grid_blocks(ctx), 64 * waves,
+                     ctx->lds_tables && transport_lds_bytes(ri, T, waves, true) <= (size_t)ctx->max_lds};
+}
 
 // ---------------------------------------------------------------------------
 // one run
@@ -944,8 +954,6 @@ gdpm_status Engine::step() {
         k.src_blocks[ri] = (int)(graph ? std::min<uint64_t>(pow2_at_least(need, 1), 4u * (uint64_t)blocks) : need);
     }
     k.blocks = blocks;
-    k.threads = block_threads(ctx);
-    k.threads_photon = ctx->photon_waves_per_cu ? std::min(k.threads, 64 * ctx->photon_waves_per_cu) : k.threads;
     k.nb = nb;
     k.space = space;
     k.blo = blo;
@@ -959,8 +967,10 @@ gdpm_status Engine::step() {
         // locality), the pass then reads the queue as it is, empty slots included
         k.rebin[ri] = !M.fixed && ((ri == 0 ? ctx->rebin_photons : ctx->rebin_electrons) || holders > 1 || lone < 0);
         if (k.rebin[ri]) tm.passes_rebinned++;
-        const int tpb = ri == 0 ? k.threads_photon : k.threads;
-        k.lds[ri] = ctx->lds_tables && transport_lds_bytes(ri, T, tpb / 64, true) <= (size_t)ctx->max_lds;
+        const PassShape shape = pass_shape(ctx, T, ri);
+        k.pass_blocks[ri] = shape.blocks;
+        k.threads[ri] = shape.threads;
+        k.lds[ri] = shape.lds;
         tm.passes++;
         (ri == 0 ? tm.passes_photon : tm.passes_electron)++;
     }
@@ -969,7 +979,7 @@ gdpm_status Engine::step() {
     // tables are read through the caches); not in the one-particle form
     k.fused = ctx->fused_passes && !ctx->solo_lanes && k.lds[1];
     if (k.fused) {
-        const int waves = k.threads / 64;
+        const int waves = k.threads[1] / 64;
         k.photon_waves = ctx->photon_waves < 0 ? waves / 2 : std::min(ctx->photon_waves, waves);
         k.lds[0] = 0;
     }
@@ -1054,29 +1064,29 @@ gdpm_status Engine::issue(const StepGraphKey& k, bool recording) {
         // both queues set up, then one launch runs both passes
         for (int ri = 0; ri < 2; ++ri) {
             if (k.rebin[ri]) HIP_TRY(launch_rebin(st, 4 * k.blocks, dc, k.R, ri, k.nb, k.blo, k.binv, k.space));
-            HIP_TRY(launch_setup(st, dc, k.R, ri, k.rebin[ri], k.lone));
+            HIP_TRY(launch_setup(st, dc, k.R, ri, k.rebin[ri], k.lone, k.blocks * k.threads[1] / 64));
         }
         HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[0], st, hipEventRecordExternal)
                           : hipEventRecord(ctx->events[0], st));
-        HIP_TRY(launch_fused(st, k.blocks, k.threads, k.photon_waves, k.rebin[0] || k.rebin[1], dc, k.T, k.R));
+        HIP_TRY(launch_fused(st, k.blocks, k.threads[1], k.photon_waves, k.rebin[0] || k.rebin[1], dc, k.T, k.R));
         HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[1], st, hipEventRecordExternal)
                           : hipEventRecord(ctx->events[1], st));
-        for (int ri = 0; ri < 2; ++ri) HIP_TRY(launch_finish(st, dc, ri));
+        for (int ri = 0; ri < 2; ++ri) HIP_TRY(launch_finish(st, dc, M.jc, ri));
         HIP_TRY(hipMemcpyAsync(ctx->host_ctl, dc, sizeof(Ctl), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipMemcpyAsync(ctx->h_jc, M.jc, kJcMirrorBytes, hipMemcpyDeviceToHost, st));
         return GDPM_OK;
     }
     for (int ri = 0; ri < 2; ++ri) {
         if (k.rebin[ri]) HIP_TRY(launch_rebin(st, 4 * k.blocks, dc, k.R, ri, k.nb, k.blo, k.binv, k.space));
-        HIP_TRY(launch_setup(st, dc, k.R, ri, k.rebin[ri], k.lone));
+        HIP_TRY(launch_setup(st, dc, k.R, ri, k.rebin[ri], k.lone, k.pass_blocks[ri] * k.threads[ri] / 64));
         // a recorded event becomes a node of the graph that records it at replay
         HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[2 * ri], st, hipEventRecordExternal)
                           : hipEventRecord(ctx->events[2 * ri], st));
-        HIP_TRY(launch_transport(st, ri, k.blocks, ri == 0 ? k.threads_photon : k.threads, k.lds[ri] != 0,
+        HIP_TRY(launch_transport(st, ri, k.pass_blocks[ri], k.threads[ri], k.lds[ri] != 0,
                                  ctx->solo_lanes != 0, k.rebin[ri] != 0, dc, k.T, k.R));
         HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[2 * ri + 1], st, hipEventRecordExternal)
                           : hipEventRecord(ctx->events[2 * ri + 1], st));
-        HIP_TRY(launch_finish(st, dc, ri));
+        HIP_TRY(launch_finish(st, dc, M.jc, ri));
     }
     HIP_TRY(hipMemcpyAsync(ctx->host_ctl, dc, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipMemcpyAsync(ctx->h_jc, M.jc, kJcMirrorBytes, hipMemcpyDeviceToHost, st));
@@ -1552,8 +1562,8 @@ gdpm_status gdpm_context_create(int hip_device, const char* opts_json, gdpm_cont
     if (ring_start >= (1ull << 32)) return fail(GDPM_E_INVALID, "ring_start below 2^32");
     ctx->ring_start = (uint32_t)ring_start;
     if (ctx->ring_log2 < 12 || ctx->ring_log2 > 28) return fail(GDPM_E_INVALID, "ring_capacity_log2 in [12, 28]");
-    if (ctx->waves_per_cu < 1 || ctx->waves_per_cu > kMaxBlockThreads / 64)
-        return fail(GDPM_E_INVALID, "waves_per_cu in [1, %d]", kMaxBlockThreads / 64);
+    if (ctx->waves_per_cu < 1 || ctx->waves_per_cu > kMaxWaves)
+        return fail(GDPM_E_INVALID, "waves_per_cu in [1, %d]", kMaxWaves);
     if (ctx->rebin_bins < 0 || ctx->rebin_bins > kMaxBins) return fail(GDPM_E_INVALID, "rebin_bins in [0, 64]");
     if (ctx->rebin_space != 0 && ctx->rebin_space != 1) return fail(GDPM_E_INVALID, "rebin_space must be 0 or 1");
     if (ctx->pass_histories < 0) return fail(GDPM_E_INVALID, "pass_histories must be >= 0");
@@ -1567,8 +1577,8 @@ gdpm_status gdpm_context_create(int hip_device, const char* opts_json, gdpm_cont
     if (ctx->solo_lanes != 0 && (ctx->solo_lanes != 1 || !ctx->lds_tables || ctx->autotune))
         return fail(GDPM_E_INVALID, "solo_lanes is 0 or 1 and needs lds_tables on and autotune off");
     if (ctx->fused_passes != 0 && ctx->fused_passes != 1) return fail(GDPM_E_INVALID, "fused_passes is 0 or 1");
-    if (ctx->photon_waves_per_cu < 0 || ctx->photon_waves_per_cu > kMaxBlockThreads / 64)
-        return fail(GDPM_E_INVALID, "photon_waves_per_cu in [0, %d]", kMaxBlockThreads / 64);
+    if (ctx->photon_waves_per_cu < 0 || ctx->photon_waves_per_cu > kMaxWaves)
+        return fail(GDPM_E_INVALID, "photon_waves_per_cu in [0, %d]", kMaxWaves);
     if (ctx->photon_waves != -1 && (ctx->photon_waves < 0 || ctx->photon_waves > ctx->waves_per_cu))
         return fail(GDPM_E_INVALID, "photon_waves in [0, waves_per_cu] (or -1: half)");
     HIP_TRY(hipDeviceGetAttribute(&ctx->cu_count, hipDeviceAttributeMultiprocessorCount, hip_device));

@@ -76,6 +76,7 @@ GDPM_DEV double wave_sum(double v) {
 #define GDPM_GLOBAL __attribute__((address_space(1)))
 #define GDPM_LDS __attribute__((address_space(3)))
 #define GDPM_CONST __attribute__((address_space(4)))
+typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
@@ -260,37 +261,91 @@ GDPM_DEV float lerp1(P tab, int i, float t) {
     return fmaf(t, b - a, a);
 }
 
-// TT: Tables, in any address space
-template <class TT, class P>
-GDPM_DEV f4 elec_at(const TT& T, P etab, int m, float e) {
-    int i;
-    float t;
-    grid(hlog2(e), T.eg_lo, T.eg_inv, T.eg_n, i, t);
-    return lerp4(etab + m * T.eg_n, i, t);
-}
+// What a flight needs of the photon table, the total cross section, and what a
+// step needs of the electron table: in LDS the columns lie apart (a pass reads
+// one or two of the four, and neighbouring rows fall on different banks), in
+// global memory they are the table's float4 rows.  The columns that only an
+// interaction needs are read from global memory in either case.
+struct PhotLds {
+    const GDPM_LDS float* tot;                  // [mat][pg_n]
+    GDPM_DEV float total(int i, float t) const { return lerp1(tot, i, t); }
+};
+struct PhotGlobal {
+    const GDPM_GLOBAL f4* tab;
+    GDPM_DEV float total(int i, float t) const {
+        const float a = tab[i].w, b = tab[i + 1].w;
+        return fmaf(t, b - a, a);
+    }
+};
+struct ElecLds {
+    const GDPM_LDS f2* rh;                      // [mat][eg_n] range, mu_hard
+    const GDPM_LDS float* lam;                  // [mat][eg_n] 1/lambda_1
+    const GDPM_LDS float* rinv;                 // [mat][nr], then the scales [mat]
+    GDPM_DEV f2 range_hard(int i, float t) const {
+        const f2 a = rh[i], b = rh[i + 1];
+        return f2{fmaf(t, b.x - a.x, a.x), fmaf(t, b.y - a.y, a.y)};
+    }
+    GDPM_DEV float range(int i, float t) const {
+        const float a = rh[i].x, b = rh[i + 1].x;
+        return fmaf(t, b - a, a);
+    }
+    GDPM_DEV float inv_lambda(int i, float t) const { return lerp1(lam, i, t); }
+};
+struct ElecGlobal {
+    const GDPM_GLOBAL f4* tab;
+    const GDPM_GLOBAL float* rinv;
+    const GDPM_GLOBAL float* rscale;
+    GDPM_DEV f2 range_hard(int i, float t) const {
+        const f4 a = tab[i], b = tab[i + 1];
+        return f2{fmaf(t, b.x - a.x, a.x), fmaf(t, b.y - a.y, a.y)};
+    }
+    GDPM_DEV float range(int i, float t) const {
+        const float a = tab[i].x, b = tab[i + 1].x;
+        return fmaf(t, b - a, a);
+    }
+    GDPM_DEV float inv_lambda(int i, float t) const {
+        const float a = tab[i].w, b = tab[i + 1].w;
+        return fmaf(t, b - a, a);
+    }
+};
 
-// energy whose residual range is r (g/cm^2); rtab holds the material's nodes
-// followed (after all materials) by the per-material scales
-template <class TT, class P>
-GDPM_DEV float range_inv(const TT& T, P rtab, P rscale, int m, float r) {
-    const float f = fminf(hsqrt(fmaxf(r, 0.0f)) * rscale[m], (float)(T.nr - 1));
-    const int i = min((int)f, T.nr - 2);
-    return lerp1(rtab + m * T.nr, i, f - (float)i);
+// the electron tables' parameters, in scalar registers for a whole pass
+struct ElecGrid {
+    float lo, inv, aw_lo, aw_inv;
+    int n, nr, aw_n;
+    const GDPM_GLOBAL float* aw;
+    template <class TT>
+    GDPM_DEV explicit ElecGrid(const TT& T)
+        : lo(T.eg_lo), inv(T.eg_inv), aw_lo(T.aw_lo), aw_inv(T.aw_inv), n(T.eg_n), nr(T.nr), aw_n(T.aw_n),
+          aw(global_ptr(T.aw)) {}
+    // cell of energy e of material m
+    GDPM_DEV void cell(int m, float e, int& i, float& t) const {
+        grid(hlog2(e), lo, inv, n, i, t);
+        i += m * n;
+    }
+};
+
+// energy whose residual range is r (g/cm^2): the inverse range on sqrt(r)
+template <class P>
+GDPM_DEV float range_inv(P rtab, float scale, int nr, int m, float r) {
+    const float f = fminf(hsqrt(fmaxf(r, 0.0f)) * scale, (float)(nr - 1));
+    const int i = min((int)f, nr - 2);
+    return lerp1(rtab + m * nr, i, f - (float)i);
 }
+GDPM_DEV float rinv_scale(const ElecLds& E, const ElecGrid& g, int n_mat, int m) { return E.rinv[n_mat * g.nr + m]; }
+GDPM_DEV float rinv_scale(const ElecGlobal& E, const ElecGrid&, int, int m) { return E.rscale[m]; }
 
 // screening A of the modified-Wentzel law for t = s / lambda_1 (t < t_iso)
-template <class TT>
-GDPM_DEV float mw_screening(const TT& T, float tt) {
-    const float f = fminf((hlog2(tt) - T.aw_lo) * T.aw_inv, (float)(T.aw_n - 1));
-    const int i = min(max((int)f, 0), T.aw_n - 2);  // f < 0 extrapolates the first cell
-    return hexp2(lerp1(global_ptr(T.aw), i, f - (float)i));
+GDPM_DEV float mw_screening(const ElecGrid& g, float tt) {
+    const float f = fminf((hlog2(tt) - g.aw_lo) * g.aw_inv, (float)(g.aw_n - 1));
+    const int i = min(max((int)f, 0), g.aw_n - 2);  // f < 0 extrapolates the first cell
+    return hexp2(lerp1(g.aw, i, f - (float)i));
 }
 
 // modified-Wentzel deflection mu = (1 - cos)/2 for t = s / lambda_1
-template <class TT>
-GDPM_DEV float mw_mu(const TT& T, float tt, float u) {
+GDPM_DEV float mw_mu(const ElecGrid& g, float tt, float u) {
     if (!(tt < kMwIsoF)) return u;
-    const float a = mw_screening(T, tt);
+    const float a = mw_screening(g, tt);
     return fdiv(a * u, 1.0f + a - u);
 }
 
@@ -336,18 +391,21 @@ GDPM_DEV uint32_t pack_vox(int ix, int iy, int iz) {
     return (uint32_t)ix | ((uint32_t)iy << 11) | ((uint32_t)iz << 22);
 }
 
-// x in [0, lx) and so on.  For non-negative floats the order of the values is
+// x in [0, lx) and so on (lx: the extent's bits).  For non-negative floats the order of the values is
 // the order of their bits; a negative number's sign bit and a NaN's exponent make
 // it larger than any extent.  (A position of -0 counts as outside; a position is
 // set to a face as +0 or as a product with a non-negative index, and a sum that
 // cancels is +0.)
-template <class GG>
-GDPM_DEV bool inside(const GG& G, float x, float y, float z) {
-    const bool ix = __float_as_uint(x) < __float_as_uint(G.lx);
-    const bool iy = __float_as_uint(y) < __float_as_uint(G.ly);
-    const bool iz = __float_as_uint(z) < __float_as_uint(G.lz);
+GDPM_DEV bool inside(uint32_t lx, uint32_t ly, uint32_t lz, float x, float y, float z) {
+    const bool ix = __float_as_uint(x) < lx;
+    const bool iy = __float_as_uint(y) < ly;
+    const bool iz = __float_as_uint(z) < lz;
     return ix && iy && iz;
 }
+
+struct Spacing {
+    float dx, dy, dz;   // voxel size
+};
 
 // distance to the exit face of voxel (ix, iy, iz) along the direction; axis of that face
 template <class GG>
@@ -577,6 +635,7 @@ GDPM_DEV const GDPM_CONST RingCtl* ring_const(Args A, int ri) {
 // ---------------------------------------------------------------------------
 struct PushState {
     uint32_t next, end;  // reserved, unused ring slots [next, end)
+    uint32_t chunk;      // slots reserved at a time
 };
 
 // Reserve `n` consecutive logical positions for this wave; item j of the wave
@@ -598,11 +657,12 @@ GDPM_DEV Reservation reserve(PushState& ps, Args A, int ri, uint32_t n) {
         return r;
     }
     GDPM_GLOBAL Ctl* ctl = global_ptr(A->ctl);
+    const uint32_t chunk = max(ps.chunk, n - r.old_avail);
     const uint32_t leader = first_lane(ballot(true));
     uint32_t base = 0;
-    if (lane_id() == leader) base = atomic_add(&ctl->ring[ri].tail, kPushChunk);
+    if (lane_id() == leader) base = atomic_add(&ctl->ring[ri].tail, chunk);
     base = bcast(base, leader);
-    if (base + kPushChunk - ring_const(A, ri)->head > A->R.hard[ri]) {
+    if (base + chunk - ring_const(A, ri)->head > A->R.hard[ri]) {
         if (lane_id() == leader) atomic_or(&ctl->overflow, 1u);
         r.ok = false;
         ps.next = ps.end;
@@ -610,7 +670,7 @@ GDPM_DEV Reservation reserve(PushState& ps, Args A, int ri, uint32_t n) {
     }
     r.new_base = base;
     ps.next = base + (n - r.old_avail);
-    ps.end = base + kPushChunk;
+    ps.end = base + chunk;
     return r;
 }
 
@@ -782,37 +842,78 @@ GDPM_DEV void history_escape(JobPtr J, double e, const Rng& r) {
     }
 }
 
-// fold the per-job counters into the job's (before a switch, at the end)
-GDPM_DEV void job_flush(double& e_esc, WaveTally& c, const WJob& W, GDPM_GLOBAL JobCtl* jc) {
+// What a workgroup counts, in LDS: the jobs' particle births and deaths and
+// escaped energy, and the pass counters of the two particle types.  The
+// wavefronts add to it when they leave a job and when they end, and the
+// workgroup folds it into global memory once.  With every wavefront adding its
+// own counters to global memory, a pass with next to no work took 130 us: 3072
+// wavefronts x 14 additions to a few lines.
+struct GroupTally {
+    uint32_t born[kMaxJobs], died[kMaxJobs];
+    double esc[kMaxJobs];
+    uint32_t pc[2][kPassCounters];
+};
+constexpr uint32_t kGroupTallyF4 = (sizeof(GroupTally) + 15u) / 16u;
+typedef GDPM_LDS GroupTally* GroupPtr;
+
+template <class T>
+GDPM_DEV void lds_add(GDPM_LDS T* p, T v) {
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+GDPM_DEV void group_clear(GroupPtr g) {
+    GDPM_LDS uint32_t* w = (GDPM_LDS uint32_t*)g;
+    for (uint32_t i = threadIdx.x; i < sizeof(GroupTally) / 4u; i += blockDim.x) w[i] = 0u;
+}
+
+// fold the per-job counters of a wavefront into the workgroup's (before a
+// switch, at the end)
+GDPM_DEV void job_flush(double& e_esc, WaveTally& c, int j, GroupPtr g) {
     const double esc = wave_sum(e_esc);
     if (lane_id() == 0) {
-        if (esc != 0.0) atomic_add_f64(&jc->e_esc[W.j], esc);
-        if (c.born) atomic_add(&jc->births[W.j], (unsigned long long)c.born);
-        if (c.died) atomic_add(&jc->deaths[W.j], (unsigned long long)c.died);
+        if (esc != 0.0) lds_add(&g->esc[j], esc);
+        if (c.born) lds_add(&g->born[j], c.born);
+        if (c.died) lds_add(&g->died[j], c.died);
     }
     e_esc = 0.0;
     c.pushes += c.born;
     c.born = c.died = 0u;
 }
 
-// fold the pass counters into the run's; `ri` is the pass's particle type
-GDPM_DEV void pass_finish(const WaveTally& c, GDPM_GLOBAL Ctl* ctl, int ri) {
+// fold the pass counters of a wavefront into the workgroup's
+GDPM_DEV void pass_finish(const WaveTally& c, int ri, GroupPtr g) {
     if (lane_id() == 0) {
-        auto add = [](GDPM_GLOBAL unsigned long long* p, uint32_t v) {
-            if (v) atomic_add(p, (unsigned long long)v);
+        GDPM_LDS uint32_t* p = g->pc[ri];
+        auto add = [p](int i, uint32_t v) {
+            if (v) lds_add(p + i, v);
         };
-        add(&ctl->anomalies, c.bad);
-        add(&ctl->ev[ri == 0 ? EV_FLIGHTS : EV_ESTEPS], c.events);
-        add(&ctl->ev[EV_PUSHES], c.pushes);
-        add(&ctl->ev[EV_DEPOSITS], c.dep);
-        add(&ctl->ev[ri == 0 ? EV_REAL : EV_HARD_CAND], c.real[0]);
-        if (ri == 1) add(&ctl->ev[EV_HARD], c.real[1]);
-        add(&ctl->pass_ev[ri][0], c.ld);
-        add(&ctl->pass_ev[ri][1], c.pushes + c.rq);
-        add(&ctl->pass_ev[ri][2], c.dep);
-        add(&ctl->pass_ev[ri][3], c.rq);
-        add(&ctl->itype[ri == 0 ? 1 : 3], c.it[0]);
-        if (ri == 0) add(&ctl->itype[2], c.it[1]);
+        add(PC_EVENTS, c.events);
+        add(PC_REAL, c.real[0]);
+        add(PC_HARD, c.real[1]);
+        add(PC_DEPOSITS, c.dep);
+        add(PC_PUSHES, c.pushes);
+        add(PC_LOADED, c.ld);
+        add(PC_REQUEUED, c.rq);
+        add(PC_ANOMALIES, c.bad);
+        add(PC_TYPE0, c.it[0]);
+        add(PC_TYPE1, c.it[1]);
+    }
+}
+
+// fold the workgroup's counters into the jobs' and the pass's (every thread of
+// the workgroup takes part)
+GDPM_DEV void group_flush(Args A, GroupPtr g) {
+    __syncthreads();
+    GDPM_GLOBAL JobCtl* jc = global_ptr(A->R.jc);
+    const int n_jobs = A->R.n_jobs;
+    for (int j = (int)threadIdx.x; j < n_jobs; j += blockDim.x) {
+        if (g->esc[j] != 0.0) atomic_add_f64(&jc->e_esc[j], g->esc[j]);
+        if (g->born[j]) atomic_add(&jc->births[j], (unsigned long long)g->born[j]);
+        if (g->died[j]) atomic_add(&jc->deaths[j], (unsigned long long)g->died[j]);
+    }
+    for (int i = (int)threadIdx.x; i < 2 * kPassCounters; i += blockDim.x) {
+        const uint32_t v = g->pc[i / kPassCounters][i % kPassCounters];
+        if (v)
+            atomic_add(&jc->part[i / kPassCounters][blockIdx.x % kParts][i % kPassCounters], (unsigned long long)v);
     }
 }
 
@@ -994,7 +1095,13 @@ GDPM_DEV void push_photons(const PendPhoton& q, PushState& ps, Args A, JobPtr J,
 // particles: the whole queue, empty slots included, is that job's segment and
 // the other jobs' segments are empty (they start at its end, so that a
 // wavefront's first job is `lone`)
-__global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int rebinned, int lone) {
+// `waves`: the wavefronts of the pass.  In a pass of one job's queue, read as
+// it is, wavefront w starts with records [w first, (w + 1) first) of the
+// segment, without claiming them, and claims begin after those of the last.
+GDPM_DEV uint32_t claim_size(uint32_t left, uint32_t waves, int ri) {
+    return min(max(left / (2u * waves), kClaimMin), ri == 0 ? kClaimMaxPhoton : kClaimMaxElectron);
+}
+__global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int rebinned, int lone, uint32_t waves) {
     JobCtl* jc = R.jc;
     RingCtl& r = ctl->ring[ri];
     // a permuted pass reads positions [0, n_valid) of the permutation; its
@@ -1010,11 +1117,14 @@ __global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int r
     if (threadIdx.x == 0) {
         r.begin = perm ? 0u : r.head;
         r.count = count;
-        r.claim = 0u;
+        const uint32_t claim = claim_size(count, waves, ri);
+        r.first = rebinned ? 0u : claim;
+        r.push = min(max(claim, kPushMin), kPushMax);
         r.next_head = r.tail;
         if (!perm) r.permuted = 0u;
     }
-    for (int j = threadIdx.x; j < R.n_jobs; j += blockDim.x) jc->claim[ri][j] = 0u;
+    for (int j = threadIdx.x; j < R.n_jobs; j += blockDim.x)
+        jc->claim[ri][j] = rebinned ? 0u : waves * claim_size(count, waves, ri);
     const int nw = (R.n_jobs + 63) >> 6;
     for (int k = threadIdx.x; k < kMaxJobs / 64; k += blockDim.x) {
         unsigned long long m = 0ull;
@@ -1025,16 +1135,48 @@ __global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int r
     }
 }
 
-__global__ void k_finish(Ctl* ctl, int ri) {
-    RingCtl& r = ctl->ring[ri];
-    r.head = r.permuted ? r.next_head : r.begin + r.count;
-    r.count = 0u;
-    r.permuted = 0u;
+__global__ void __launch_bounds__(64) k_finish(Ctl* ctl, JobCtl* jc, int ri) {
+    if (threadIdx.x == 0) {
+        RingCtl& r = ctl->ring[ri];
+        r.head = r.permuted ? r.next_head : r.begin + r.count;
+        r.count = 0u;
+        r.permuted = 0u;
+    }
+    // the pass counters of the workgroups: lane i folds counter i
+    unsigned long long v = 0ull;
+    if (threadIdx.x < (unsigned)kPassCounters)
+        for (int k = 0; k < kParts; ++k) {
+            v += jc->part[ri][k][threadIdx.x];
+            jc->part[ri][k][threadIdx.x] = 0ull;
+        }
+    switch (threadIdx.x) {
+        case PC_EVENTS: ctl->ev[ri == 0 ? EV_FLIGHTS : EV_ESTEPS] += v; break;
+        case PC_REAL: ctl->ev[ri == 0 ? EV_REAL : EV_HARD_CAND] += v; break;
+        case PC_HARD: ctl->ev[EV_HARD] += v; break;
+        case PC_DEPOSITS:
+            ctl->ev[EV_DEPOSITS] += v;
+            ctl->pass_ev[ri][2] += v;
+            break;
+        case PC_LOADED: ctl->pass_ev[ri][0] += v; break;
+        case PC_ANOMALIES: ctl->anomalies += v; break;
+        case PC_TYPE0: ctl->itype[ri == 0 ? 1 : 3] += v; break;
+        case PC_TYPE1: ctl->itype[2] += v; break;
+        default: break;
+    }
+    const unsigned long long rq = __shfl(v, PC_REQUEUED), pushes = __shfl(v, PC_PUSHES);
+    if (threadIdx.x == 0) {
+        ctl->ev[EV_PUSHES] += pushes;
+        ctl->pass_ev[ri][1] += pushes + rq;
+        ctl->pass_ev[ri][3] += rq;
+    }
 }
 
 // ---------------------------------------------------------------------------
 // claiming input: positions [0, seg_count) of the job's segment
 // ---------------------------------------------------------------------------
+// (kPerm: other jobs may have records in the pass, and look for them in the
+// masks of unclaimed jobs)
+template <bool kPerm>
 GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
     if (cs.done || cs.next != cs.end) return;
     // the wave has used up its items: claim a new chunk if the job has more.
@@ -1046,7 +1188,7 @@ GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
     const uint32_t count = W.seg_count;
     const uint32_t waves = gridDim.x * (blockDim.x >> 6);
     const uint32_t left = count - min(cs.seen, count);
-    const uint32_t chunk = min(max(left / (2u * waves), kClaimMin), ri == 0 ? kClaimMaxPhoton : kClaimMaxElectron);
+    const uint32_t chunk = claim_size(left, waves, ri);
     if (load_agent(&ctl->overflow)) {   // a queue overflowed: the run is void
         cs.done = true;
         return;
@@ -1057,7 +1199,7 @@ GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
     base = bcast(base, leader);
     cs.seen = base + chunk;
     if (base >= count) {
-        if (lane_id() == leader)
+        if (kPerm && lane_id() == leader)
             (void)__hip_atomic_fetch_and(&jc->left[ri][W.j >> 6], ~(1ull << (W.j & 63)), __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
         cs.done = true;
@@ -1067,11 +1209,26 @@ GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
     cs.end = min(base + chunk, count);
 }
 
+// the claims of a wavefront that starts on a job; `first`: what it takes
+// without claiming (see k_setup).  The wavefronts of a workgroup start far apart
+// in the segment, so that a small pass spreads over the CUs.
+GDPM_DEV ClaimState claim_start(const WJob& W, uint32_t first) {
+    ClaimState cs{0u, 0u, 0u, false, 0u, 0u};
+    if (first) {
+        const uint32_t w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
+        cs.next = min(w * first, W.seg_count);
+        cs.end = min(cs.next + first, W.seg_count);
+        cs.seen = gridDim.x * (blockDim.x >> 6) * first;
+        cs.done = cs.next == cs.end;
+    }
+    return cs;
+}
+
 // Records of the wave's claimed chunk are staged in its LDS slice (kStage
 // records, 64 bytes each) by direct-to-LDS loads issued right after a refill,
 // so the next refills read them from LDS instead of waiting for memory.
-constexpr uint32_t kStage = 64;
-constexpr uint32_t kStageLow = 24;   // restage when fewer staged records are left
+constexpr uint32_t kStage = 32;
+constexpr uint32_t kStageLow = 16;   // restage when fewer staged records are left
 
 // the queue position of input position `pos` of a pass: itself, or through the
 // permutation of a pass re-binned by job (`perm` non-null); both masked, so
@@ -1080,7 +1237,7 @@ GDPM_DEV uint32_t input_slot(const GDPM_GLOBAL uint32_t* perm, uint32_t mask, ui
     return (perm ? perm[pos & mask] : pos) & mask;
 }
 
-// stage the records of positions [cs.next, cs.next + kStage) (every lane: 4
+// stage the records of positions [cs.next, cs.next + kStage) (every lane: 2
 // loads of 16 bytes; lane L of load c fetches piece L % 4 of record 16 c + L / 4,
 // which lands at float4 64 c + L of the slice).  Positions past the chunk are
 // loaded too (the ring index is masked) and never used.  The loads are written
@@ -1094,7 +1251,7 @@ GDPM_DEV void stage_records(ClaimState& cs, GDPM_LDS f4* st, Args A, int ri, uin
     const uint32_t l = lane_id();
     const uint32_t mask = A->R.mask[ri];
 #pragma unroll
-    for (uint32_t c = 0; c < 4; ++c) {
+    for (uint32_t c = 0; c < kStage / 16u; ++c) {
         const uint32_t rec = 16u * c + (l >> 2);
         const GDPM_GLOBAL f4* src = record_ptr(A, ri, input_slot(perm, mask, first + cs.next + rec)) + (l & 3u);
         const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(st + 64u * c));
@@ -1111,7 +1268,7 @@ GDPM_DEV void stage_records(ClaimState& cs, GDPM_LDS f4* st, Args A, int ri, uin
 // (kStaged: `st`, LDS) the records come from it when they are staged.  kSolo (a
 // measurement form): one particle per wavefront at a time, so the wavefront
 // executes exactly the instructions of that particle's path.
-template <bool kSolo, bool kStaged>
+template <bool kSolo, bool kPerm, bool kStaged>
 GDPM_DEV bool refill(bool active, ClaimState& cs, Args A, const WJob& W, int ri, uint32_t begin,
                      const GDPM_GLOBAL uint32_t* perm, Rec& p, WaveTally& c, GDPM_LDS f4* st) {
     if (cs.done) return false;
@@ -1122,7 +1279,7 @@ GDPM_DEV bool refill(bool active, ClaimState& cs, Args A, const WJob& W, int ri,
     } else {
         if ((uint32_t)__popcll(need) < kRefillMin && ballot(active)) return false;
     }
-    claim_refill(cs, A, W, ri);
+    claim_refill<kPerm>(cs, A, W, ri);
     const uint32_t have = cs.end - cs.next;
     const uint32_t rank = mbcnt(need);
     const uint32_t take = kSolo ? min(have, 1u) : min(have, (uint32_t)__popcll(need));
@@ -1279,28 +1436,36 @@ __global__ void k_commit(Ctl* ctl, int ri, const SrcHdr* hdr) {
 // per CU shares them.
 extern __shared__ f4 lds_tables[];
 
-// Layout (float4 units): the tables (photons: the cross sections, then the
-// majorant of the pass's job; electrons: the stopping and scattering data, the
+// Layout (float4 units): the workgroup's counters; the tables (photons: the total cross sections, then the
+// majorant of the pass's job; electrons: range and mu_hard, 1/lambda_1, the
 // inverse range and its scales), if staged; then per wavefront one slice of
 // kStage staged records (with the tables) and its lanes' generator words
 constexpr uint32_t kRingF4 = kRngWords * 64u / 4u;   // generator words of a wavefront
 template <class TT>
 GDPM_HD uint32_t tables_f4(int ri, const TT& T) {
-    const uint32_t floats = ri == 0 ? (uint32_t)T.pg_n : (uint32_t)(T.n_mat * T.nr + T.n_mat);
-    const uint32_t tab = ri == 0 ? (uint32_t)(T.n_mat * T.pg_n) : (uint32_t)(T.n_mat * T.eg_n);
-    return tab + (floats + 3u) / 4u;
+    const uint32_t floats = ri == 0 ? (uint32_t)((T.n_mat + 1) * T.pg_n)
+                                    : (uint32_t)(T.n_mat * (3 * T.eg_n + T.nr) + T.n_mat);
+    return (floats + 3u) / 4u;
 }
 constexpr uint32_t kSliceF4 = 4u * kStage + kRingF4;
+
+// a workgroup none of whose wavefronts has a record to start with: it ends
+// before it stages the tables (nothing is left to claim either)
+GDPM_DEV bool group_idle(Args A, int ri) {
+    const GDPM_CONST RingCtl* rc = ring_const(A, ri);
+    return rc->count == 0u || (rc->first && blockIdx.x * rc->first >= rc->count);
+}
 
 // ---------------------------------------------------------------------------
 // photon pass: Woodcock tracking (section 2.1), one flight per iteration
 // ---------------------------------------------------------------------------
-// One wavefront's share of a photon pass.  ptab: the cross sections (LDS or
-// global); lmaj: the job's majorant in LDS (kMajLds: a pass of one job; else it
+// One wavefront's share of a photon pass.  ptab: the total cross sections (in
+// LDS or global memory); lmaj: the job's majorant in LDS (kMajLds: a pass of one job; else it
 // is read from global memory); stage: the wavefront's LDS slice for staged
 // records (kStaged); ring: its generator words.
 template <bool kSolo, bool kPerm, bool kStaged, bool kMajLds, class PT>
-GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS f4* stage, GDPM_LDS float* ring) {
+GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS f4* stage, GDPM_LDS float* ring,
+                          GroupPtr group) {
     const GDPM_CONST RingCtl* rc = ring_const(A0, 0);
     const uint32_t begin = rc->begin, total = rc->count;
     // a re-binned pass reads its input through the permutation (only the kPerm
@@ -1310,16 +1475,30 @@ GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS
     const bool big = !kSolo && total >= kTailMinPerLane * gridDim.x * blockDim.x;
 
     int j = first_job(A0, total, 0);
-    PushState pg{0u, 0u}, pe{0u, 0u};
+    uint32_t first = rc->first;
+    PushState pg{0u, 0u, rc->push}, pe{0u, 0u, rc->push};
     double e_esc = 0.0;   // escaped energy of the current job
     WaveTally wt{};
     uint32_t iters = 0u;
     bool last_job = !kPerm;   // no other job has records left in this pass
+    const float pg_lo = A0->T.pg_lo, pg_inv = A0->T.pg_inv;
+    const int pg_n = A0->T.pg_n;
     // one job at a time: a wavefront switches jobs with all its lanes empty
     while (j >= 0) {
         WJob W;
         load_job(W, A0, j, 0);
-        ClaimState cs{0u, 0u, 0u, false, 0u, 0u};
+        // what a flight needs of the job, in scalar registers: read again in each
+        // iteration, every use waited for a scalar load of its own
+        const float idx = W.p->G.idx, idy = W.p->G.idy, idz = W.p->G.idz;
+        const uint32_t lx = __float_as_uint(W.p->G.lx), ly = __float_as_uint(W.p->G.ly),
+                       lz = __float_as_uint(W.p->G.lz);
+        const int nx = W.p->G.nx, ny = W.p->G.ny, nz = W.p->G.nz;
+        const GDPM_GLOBAL uint32_t* vox = reread(global_ptr(W.p->G.vox));
+        const uint32_t k0 = W.p->k0, k1 = W.p->k1;
+        const GDPM_GLOBAL float* gmaj = global_ptr(W.p->mumax);
+        const bool hist = W.p->hist != nullptr;
+        ClaimState cs = claim_start(W, first);
+        first = 0u;
         bool active = false;
         float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0;
         uint32_t pb = 0u;   // batch slot of the lane's history
@@ -1332,7 +1511,7 @@ GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS
             const Args A = reread(A0);
             const JobPtr J = reread(W.p);
             Rec p;
-            if (refill<kSolo, kStaged>(active, cs, A, W, 0, begin, perm_in, p, wt, stage)) {
+            if (refill<kSolo, kPerm, kStaged>(active, cs, A, W, 0, begin, perm_in, p, wt, stage)) {
                 // + 0: a position of -0 becomes +0 (see inside)
                 x = p.a.x + 0.0f; y = p.a.y + 0.0f; z = p.a.z + 0.0f; e = p.a.w;
                 u = p.b.x; v = p.b.y; w = p.b.z;
@@ -1349,40 +1528,38 @@ GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS
             } else {
                 const uint64_t act0 = ballot(active);
                 const bool fly = active && pm < 0;
-                rng_topup(rng, fly, active, 2u, J->k0, J->k1);
+                rng_topup(rng, fly, active, 2u, k0, k1);
                 wt.events += count(fly);
+                const float ul = rng.peek(0u), ua = rng.peek(1u);
                 // energy grid cell of the flight and of a waiting interaction
                 // (the energy is unchanged in between)
                 int gi;
                 float gt;
-                grid(hlog2(e), A->T.pg_lo, A->T.pg_inv, A->T.pg_n, gi, gt);
+                grid(hlog2(e), pg_lo, pg_inv, pg_n, gi, gt);
                 float mumax;
                 if constexpr (kMajLds) mumax = lerp1(lmaj, gi, gt);
-                else mumax = lerp1(global_ptr(J->mumax), gi, gt);
+                else mumax = lerp1(gmaj, gi, gt);
                 // The flight is computed on every lane, without branches: a lane
                 // that waits or is empty flies a distance of 0, which leaves it
                 // where it is, and only the loads and the tallies are masked.
-                const float ul = rng.peek(0u), ua = rng.peek(1u);
                 const float s = fly ? neg_ln(ul) * hrcp(mumax) : 0.0f;
                 rng.ctr += fly ? 2u : 0u;
                 x = fmaf(s, u, x);
                 y = fmaf(s, v, y);
                 z = fmaf(s, w, z);
-                const bool in = fly && inside(J->G, x, y, z);
+                const bool in = fly && inside(lx, ly, lz, x, y, z);
                 int ix, iy, iz;
-                const int vv = voxel_of(J->G, x, y, z, ix, iy, iz);
+                const int vv = voxel_of(idx, idy, idz, nx, ny, nz, x, y, z, ix, iy, iz);
                 uint32_t vx = 0u;
-                if (in) vx = global_ptr(J->G.vox)[vv];
+                if (in) vx = vox[vv];
                 if (fly && !in) {
                     e_esc += (double)e;
-                    history_escape(J, (double)e, rng);
+                    if (hist) history_escape(J, (double)e, rng);
                     active = false;
                 }
                 {
                     const int m = voxel_material(vx);
-                    const PT row = ptab + m * A->T.pg_n + gi;
-                    const float m0 = row[0].w, m1 = row[1].w;
-                    const float mu = fmaf(gt, m1 - m0, m0);
+                    const float mu = ptab.total(m * pg_n + gi, gt);
                     const bool real = in && ua * mumax < voxel_density(vx) * mu;
                     pm = real ? m : pm;   // the interaction waits (see below)
                     wt.real[0] += count(real);
@@ -1403,7 +1580,7 @@ GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS
                     qg.n = 0;
                     int itype = -1;    // the interaction sampled by this lane
                     double dep = 0.0;  // its deposit, in the lane's voxel
-                    rng_topup(rng, pm >= 0, active, 4u, J->k0, J->k1);
+                    rng_topup(rng, pm >= 0, active, 4u, k0, k1);
                     if (pm == kAbsorb) {
                         if (e <= kMaxEnergy) dep = (double)e;
                         else atomic_add(&global_ptr(A->ctl)->anomalies, 1ull);
@@ -1411,8 +1588,7 @@ GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS
                         pm = -1;
                     }
                     if (pm >= 0) {
-                        const uint32_t k0 = J->k0, k1 = J->k1;
-                        const f4 mu = lerp4(ptab + pm * A->T.pg_n, gi, gt);
+                        const f4 mu = lerp4(global_f4(A->T.phot) + pm * pg_n, gi, gt);
                         const float r = uniform(rng, k0, k1) * mu.w;
                         itype = r < mu.x ? 0 : (r < mu.x + mu.y ? 1 : 2);
                         if (itype == 0) {
@@ -1520,14 +1696,14 @@ GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS
                 }
             }
         }
-        job_flush(e_esc, wt, W, global_ptr(A0->R.jc));
+        job_flush(e_esc, wt, W.j, group);
         j = next;
     }
     // no staging load may still be writing the slice when the wave moves on
     if constexpr (kStaged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     release(pe, A0, 1);
     release(pg, A0, 0);
-    pass_finish(wt, global_ptr(A0->ctl), 0);
+    pass_finish(wt, 0, group);
 }
 
 // The kernel's arguments are read through pass_args(); the parameter only
@@ -1535,13 +1711,17 @@ GDPM_DEV void photon_pass(Args A0, PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS
 template <bool kLds, bool kSolo, bool kPerm>
 __global__ void __launch_bounds__(768) k_photon(PassArgs) {
     const Args A = pass_args();
-    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables;
+    if (!kPerm && group_idle(A, 0)) return;
+    const GroupPtr group = (GroupPtr)lds_tables;
+    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables + kGroupTallyF4;
+    group_clear(group);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (kLds) {
         const GDPM_CONST Tables& T = A->T;
         const int np = T.n_mat * T.pg_n;
-        for (int i = threadIdx.x; i < np; i += blockDim.x) lds[i] = global_f4(T.phot)[i];
-        GDPM_LDS float* lmaj = (GDPM_LDS float*)(lds + np);
+        GDPM_LDS float* tot = (GDPM_LDS float*)lds;
+        for (int i = threadIdx.x; i < np; i += blockDim.x) tot[i] = global_f4(T.phot)[i].w;
+        GDPM_LDS float* lmaj = tot + np;
         if constexpr (!kPerm) {
             // a pass of one job: its majorant too
             const int j = first_job(A, ring_const(A, 0)->count, 0);
@@ -1552,24 +1732,25 @@ __global__ void __launch_bounds__(768) k_photon(PassArgs) {
         }
         __syncthreads();
         GDPM_LDS f4* slice = lds + tables_f4(0, T) + wave * kSliceF4;
-        photon_pass<kSolo, kPerm, true, !kPerm>(A, (const GDPM_LDS f4*)lds, lmaj, slice,
-                                                (GDPM_LDS float*)(slice + 4u * kStage));
+        photon_pass<kSolo, kPerm, true, !kPerm>(A, PhotLds{tot}, lmaj, slice, (GDPM_LDS float*)(slice + 4u * kStage),
+                                                group);
     } else {
-        photon_pass<kSolo, kPerm, false, false>(A, global_f4(A->T.phot), nullptr, nullptr,
-                                                (GDPM_LDS float*)(lds + wave * kRingF4));
+        __syncthreads();
+        photon_pass<kSolo, kPerm, false, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, nullptr,
+                                                (GDPM_LDS float*)(lds + wave * kRingF4), group);
     }
+    group_flush(A, group);
 }
 
 // ---------------------------------------------------------------------------
 // electron pass: class-II condensed history with a random hinge, one step per
 // iteration (section 2.1)
 // ---------------------------------------------------------------------------
-// One wavefront's share of an electron pass.  etab, rtab, rscale: the
-// stopping and scattering data, the inverse range and its scales (LDS or
-// global); stage: the wavefront's LDS slice for staged records (kStaged);
+// One wavefront's share of an electron pass.  E: the stopping and scattering
+// data and the inverse range (in LDS or global memory); stage: the wavefront's LDS slice for staged records (kStaged);
 // ring: its generator words.
-template <bool kSolo, bool kPerm, bool kStaged, class PE, class PR>
-GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* stage, GDPM_LDS float* ring) {
+template <bool kSolo, bool kPerm, bool kStaged, class EL>
+GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS float* ring, GroupPtr group) {
     const GDPM_CONST RingCtl* rc = ring_const(A0, 1);
     const uint32_t begin = rc->begin, total = rc->count;
     const GDPM_GLOBAL uint32_t* perm_in =
@@ -1577,16 +1758,27 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
     const bool big = !kSolo && total >= kTailMinPerLane * gridDim.x * blockDim.x;
 
     int j = first_job(A0, total, 1);
-    PushState pg{0u, 0u}, pe{0u, 0u};
+    uint32_t first = rc->first;
+    PushState pg{0u, 0u, rc->push}, pe{0u, 0u, rc->push};
     double e_esc = 0.0;   // escaped energy of the current job
     WaveTally wt{};
     uint32_t iters = 0u;
     bool last_job = !kPerm;   // no other job has records left in this pass
+    const ElecGrid eg(A0->T);
+    const int n_mat = A0->T.n_mat;
+    const float ecut = A0->R.ecut_e;
     // one job at a time: a wavefront switches jobs with all its lanes empty
     while (j >= 0) {
         WJob W;
         load_job(W, A0, j, 1);
-        ClaimState cs{0u, 0u, 0u, false, 0u, 0u};
+        // what a step needs of the job, in scalar registers (see the photon pass)
+        const Spacing G{W.p->G.dx, W.p->G.dy, W.p->G.dz};
+        const int nx = W.p->G.nx, ny = W.p->G.ny, nz = W.p->G.nz;
+        const GDPM_GLOBAL uint32_t* vox = reread(global_ptr(W.p->G.vox));
+        const uint32_t k0 = W.p->k0, k1 = W.p->k1;
+        const bool no_ms = (W.p->flags & 8u) != 0u;
+        ClaimState cs = claim_start(W, first);
+        first = 0u;
         bool active = false;
         float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0, nh = -1.0f;
         float aa = 0.0f;    // > 0: a positron, and its annihilation energy
@@ -1602,9 +1794,8 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
         for (;;) {
             const Args A = reread(A0);
             const JobPtr J = reread(W.p);
-            const float ecut = A->R.ecut_e;
             Rec p;
-            if (refill<kSolo, kStaged>(active, cs, A, W, 1, begin, perm_in, p, wt, stage)) {
+            if (refill<kSolo, kPerm, kStaged>(active, cs, A, W, 1, begin, perm_in, p, wt, stage)) {
                 x = p.a.x; y = p.a.y; z = p.a.z; e = p.a.w;
                 u = p.b.x; v = p.b.y; w = p.b.z; nh = p.b.w;
                 ix = (int)(p.d.x & 2047u);
@@ -1613,7 +1804,7 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
                 aa = (p.d.z & 1u) ? __uint_as_float(p.d.y) : 0.0f;
                 pb = p.d.w >> 16;
                 rng_start(rng, p.c.x, p.c.y, p.c.z, p.c.w);
-                vx = global_ptr(J->G.vox)[ix + J->G.nx * (iy + J->G.ny * iz)];
+                vx = vox[ix + nx * (iy + ny * iz)];
                 active = true;
             }
             if (!ballot(active)) {
@@ -1632,40 +1823,45 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
                 const bool step = active && hq < 0.0f && e > ecut;
                 wt.events += count(step);
                 // a step draws at most 4 numbers, the first for a fresh hard-event distance
-                rng_topup(rng, step, active, 4u, J->k0, J->k1);
-                const int vv = ix + J->G.nx * (iy + J->G.ny * iz);   // voxel of the step
+                rng_topup(rng, step, active, 4u, k0, k1);
+                const int vv = ix + nx * (iy + ny * iz);   // voxel of the step
                 bool crossed = false;
                 if (step) {
-                    const bool no_ms = (J->flags & 8u) != 0u;
                     const float rho = voxel_density(vx);
                     const int m = voxel_material(vx);
                     const float irho = hrcp(rho);
                     if (nh < 0.0f) nh = neg_ln(rng.draw());
                     const float xi = rng.draw();
                     const float t0 = e;
-                    const f4 q0 = elec_at(A->T, etab, m, t0);
+                    int ci;
+                    float ct;
+                    eg.cell(m, t0, ci, ct);
+                    const f2 q0 = E.range_hard(ci, ct);
+                    const float rsc = rinv_scale(E, eg, n_mat, m);
                     const float mus = rho * q0.y;
                     const float sh = mus > 0.0f ? nh * hrcp(mus) : 3.0e38f;
                     const float tfl = fmaxf(0.75f * t0, ecut);
-                    const float rfl = tfl > ecut ? elec_at(A->T, etab, m, tfl).x : 0.0f;
+                    eg.cell(m, tfl, ci, ct);
+                    const float rtf = E.range(ci, ct);
+                    const float rfl = tfl > ecut ? rtf : 0.0f;
                     const float se = (q0.x - rfl) * irho;
                     const bool hard = sh < se;
                     const float s = hard ? sh : se;
                     const float s1 = xi * s, s2 = s - s1;
                     float tend = tfl;
-                    if (hard) tend = fminf(fmaxf(range_inv(A->T, rtab, rscale, m, q0.x - rho * s), tfl), t0);
+                    if (hard) tend = fminf(fmaxf(range_inv(E.rinv, rsc, eg.nr, m, q0.x - rho * s), tfl), t0);
                     // first half: to the hinge, or to the voxel face if that comes
                     // first.  Lanes that cross and lanes that reach the hinge share
                     // one move, one range lookup and one deposit.
                     int ax;
-                    float db = face_dist(J->G, x, y, z, u, v, w, ix, iy, iz, ax);
+                    float db = face_dist(G, x, y, z, u, v, w, ix, iy, iz, ax);
                     crossed = db < s1;
                     float travelled = db;
                     {
                         const float d1 = crossed ? db : s1;
                         x = fmaf(d1, u, x); y = fmaf(d1, v, y); z = fmaf(d1, w, z);
                         const float t1 =
-                            fminf(fmaxf(range_inv(A->T, rtab, rscale, m, q0.x - rho * d1), tend), e);
+                            fminf(fmaxf(range_inv(E.rinv, rsc, eg.nr, m, q0.x - rho * d1), tend), e);
                         de += (double)(e - t1);
                         e = t1;
                     }
@@ -1673,21 +1869,22 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
                         // hinge: modified-Wentzel deflection for the whole step
                         if (!no_ms) {
                             const float tmid = 0.5f * (t0 + tend);
-                            const float tt = s * rho * elec_at(A->T, etab, m, tmid).w;
-                            const float mu = mw_mu(A->T, tt, rng.draw());
+                            eg.cell(m, tmid, ci, ct);
+                            const float tt = s * rho * E.inv_lambda(ci, ct);
+                            const float mu = mw_mu(eg, tt, rng.draw());
                             const float turns = rng.draw();
                             rotate(u, v, w, 1.0f - 2.0f * mu, 2.0f * hsqrt(mu * (1.0f - mu)), turns);
                         }
                         // second half: to the step end or the face; a lane that
                         // reaches the end loses exactly the energy left above tend
-                        db = face_dist(J->G, x, y, z, u, v, w, ix, iy, iz, ax);
+                        db = face_dist(G, x, y, z, u, v, w, ix, iy, iz, ax);
                         crossed = db < s2;
                         travelled = s1 + db;
                         const float d2 = crossed ? db : s2;
                         x = fmaf(d2, u, x); y = fmaf(d2, v, y); z = fmaf(d2, w, z);
                         float t2 = tend;
                         if (crossed)
-                            t2 = fminf(fmaxf(range_inv(A->T, rtab, rscale, m, q0.x - rho * travelled), tend), e);
+                            t2 = fminf(fmaxf(range_inv(E.rinv, rsc, eg.nr, m, q0.x - rho * travelled), tend), e);
                         de += (double)(e - t2);
                         e = t2;
                     }
@@ -1697,8 +1894,8 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
                         const bool a0 = ax == 0, a1 = ax == 1;
                         const float da = a0 ? u : (a1 ? v : w);
                         const int ia = a0 ? ix : (a1 ? iy : iz);
-                        const int na = a0 ? J->G.nx : (a1 ? J->G.ny : J->G.nz);
-                        const float ha = a0 ? J->G.dx : (a1 ? J->G.dy : J->G.dz);
+                        const int na = a0 ? nx : (a1 ? ny : nz);
+                        const float ha = a0 ? G.dx : (a1 ? G.dy : G.dz);
                         const int in = da > 0.0f ? ia + 1 : ia - 1;
                         const float pa = (float)(da > 0.0f ? in : ia) * ha;
                         x = a0 ? pa : x;
@@ -1715,7 +1912,7 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
                             active = false;
                         } else {
                             // the next voxel's density and material, needed by the next step
-                            vx = global_ptr(J->G.vox)[ix + J->G.nx * (iy + J->G.ny * iz)];
+                            vx = vox[ix + nx * (iy + ny * iz)];
                         }
                     } else if (hard) {
                         hq = q0.y;   // the hard event waits (see below)
@@ -1737,12 +1934,14 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
                 if (bh && (cs.done || (uint32_t)__popcll(bh) >= kHardBatch || bh == ballot(active))) {
                     int htype = -1;   // the hard event sampled by this lane
                     wt.real[0] += (uint32_t)__popcll(bh);
-                    rng_topup(rng, hq >= 0.0f, active, 4u, J->k0, J->k1);
+                    rng_topup(rng, hq >= 0.0f, active, 4u, k0, k1);
                     if (hq >= 0.0f) {
-                        const uint32_t k0 = J->k0, k1 = J->k1;
                         // delta scattering against the step-start majorant
                         // (mu_h grows with T; the step ended at e)
-                        const f4 q1 = elec_at(A->T, etab, voxel_material(vx), e);
+                        int ci;
+                        float ct;
+                        eg.cell(voxel_material(vx), e, ci, ct);
+                        const f4 q1 = lerp4(global_f4(A->T.elec), ci, ct);
                         if (uniform(rng, k0, k1) * hq < q1.y) {
                             htype = uniform(rng, k0, k1) * q1.y < q1.z ? 0 : 1;
                             if (htype == 0) {
@@ -1796,8 +1995,8 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
                     de += (double)e;
                     if (aa > 0.0f) {
                         float du, dv, dw;
-                        rng.ensure(2u, J->k0, J->k1);
-                        sample_iso(rng, J->k0, J->k1, du, dv, dw);
+                        rng.ensure(2u, k0, k1);
+                        sample_iso(rng, k0, k1, du, dv, dw);
                         qg.n = 2; qg.e = 0.5f * aa; qg.u = du; qg.v = dv; qg.w = dw; qg.wb = 0u;
                     }
                     active = false;
@@ -1846,45 +2045,54 @@ GDPM_DEV void electron_pass(Args A0, PE etab, PR rtab, PR rscale, GDPM_LDS f4* s
             }
         }
         // deposits of the particles handed on (or ended by the bound), in their voxels
-        if (de != 0.0) add_dose(W.p, pb, ix + W.p->G.nx * (iy + W.p->G.ny * iz), de, rng);
+        if (de != 0.0) add_dose(W.p, pb, ix + nx * (iy + ny * iz), de, rng);
         wt.dep += count(de != 0.0);
-        job_flush(e_esc, wt, W, global_ptr(A0->R.jc));
+        job_flush(e_esc, wt, W.j, group);
         j = next;
     }
     // no staging load may still be writing the slice when the wave moves on
     if constexpr (kStaged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     release(pe, A0, 1);
     release(pg, A0, 0);
-    pass_finish(wt, global_ptr(A0->ctl), 1);
+    pass_finish(wt, 1, group);
 }
 
 // stage the electron tables; every thread of the workgroup takes part
-GDPM_DEV void stage_electron_tables(const GDPM_CONST Tables& T, GDPM_LDS f4* lds) {
+GDPM_DEV ElecLds stage_electron_tables(const GDPM_CONST Tables& T, GDPM_LDS f4* lds) {
     const int ne = T.n_mat * T.eg_n, nr = T.n_mat * T.nr;
-    for (int i = threadIdx.x; i < ne; i += blockDim.x) lds[i] = global_f4(T.elec)[i];
-    GDPM_LDS float* lr = (GDPM_LDS float*)(lds + ne);
+    GDPM_LDS f2* rh = (GDPM_LDS f2*)lds;
+    GDPM_LDS float* lam = (GDPM_LDS float*)(rh + ne);
+    GDPM_LDS float* lr = lam + ne;
+    for (int i = threadIdx.x; i < ne; i += blockDim.x) {
+        const f4 q = global_f4(T.elec)[i];
+        rh[i] = f2{q.x, q.y};
+        lam[i] = q.w;
+    }
     for (int i = threadIdx.x; i < nr; i += blockDim.x) lr[i] = global_ptr(T.rinv)[i];
     for (int i = threadIdx.x; i < T.n_mat; i += blockDim.x) lr[nr + i] = global_ptr(T.rinv_scale)[i];
     __syncthreads();
+    return ElecLds{rh, lam, lr};
 }
 
 template <bool kLds, bool kSolo, bool kPerm>
 __global__ void __launch_bounds__(768) k_electron(PassArgs) {
     const Args A = pass_args();
-    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables;
+    if (!kPerm && group_idle(A, 1)) return;
+    const GroupPtr group = (GroupPtr)lds_tables;
+    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables + kGroupTallyF4;
+    group_clear(group);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (kLds) {
-        const GDPM_CONST Tables& T = A->T;
-        stage_electron_tables(T, lds);
-        const GDPM_LDS float* lr = (const GDPM_LDS float*)(lds + T.n_mat * T.eg_n);
-        GDPM_LDS f4* slice = lds + tables_f4(1, T) + wave * kSliceF4;
-        electron_pass<kSolo, kPerm, true>(A, (const GDPM_LDS f4*)lds, lr, lr + T.n_mat * T.nr, slice,
-                                          (GDPM_LDS float*)(slice + 4u * kStage));
+        const ElecLds E = stage_electron_tables(A->T, lds);
+        GDPM_LDS f4* slice = lds + tables_f4(1, A->T) + wave * kSliceF4;
+        electron_pass<kSolo, kPerm, true>(A, E, slice, (GDPM_LDS float*)(slice + 4u * kStage), group);
     } else {
-        electron_pass<kSolo, kPerm, false>(A, global_f4(A->T.elec), (const GDPM_GLOBAL float*)global_ptr(A->T.rinv),
-                                           (const GDPM_GLOBAL float*)global_ptr(A->T.rinv_scale), nullptr,
-                                           (GDPM_LDS float*)(lds + wave * kRingF4));
+        __syncthreads();
+        electron_pass<kSolo, kPerm, false>(
+            A, ElecGlobal{global_f4(A->T.elec), global_ptr(A->T.rinv), global_ptr(A->T.rinv_scale)}, nullptr,
+            (GDPM_LDS float*)(lds + wave * kRingF4), group);
     }
+    group_flush(A, group);
 }
 
 // ---------------------------------------------------------------------------
@@ -1901,20 +2109,21 @@ __global__ void __launch_bounds__(768) k_electron(PassArgs) {
 template <bool kPerm>
 __global__ void __launch_bounds__(768) k_transport(PassArgs) {
     const Args A = pass_args();
-    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables;
+    const GroupPtr group = (GroupPtr)lds_tables;
+    GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables + kGroupTallyF4;
+    group_clear(group);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const GDPM_CONST Tables& T = A->T;
-    stage_electron_tables(T, lds);
-    const GDPM_LDS float* lr = (const GDPM_LDS float*)(lds + T.n_mat * T.eg_n);
-    GDPM_LDS f4* slice = lds + tables_f4(1, T) + wave * kSliceF4;
+    const ElecLds E = stage_electron_tables(A->T, lds);
+    GDPM_LDS f4* slice = lds + tables_f4(1, A->T) + wave * kSliceF4;
     GDPM_LDS float* ring = (GDPM_LDS float*)(slice + 4u * kStage);
     for (int k = 0; k < 2; ++k) {
         const bool photons = ((int)wave < A->photon_waves) == (k == 0);
         if (photons)
-            photon_pass<false, kPerm, true, false>(A, global_f4(A->T.phot), nullptr, slice, ring);
+            photon_pass<false, kPerm, true, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, slice, ring, group);
         else
-            electron_pass<false, kPerm, true>(A, (const GDPM_LDS f4*)lds, lr, lr + T.n_mat * T.nr, slice, ring);
+            electron_pass<false, kPerm, true>(A, E, slice, ring, group);
     }
+    group_flush(A, group);
 }
 
 // ---------------------------------------------------------------------------
@@ -2191,12 +2400,12 @@ __global__ void k_test_sample(Tables T, int which, float e, float p1, float p2, 
     } else if (which == 2) {
         a = sample_brems(r, k0, k1, e, p1);
     } else if (which == 3) {
-        a = mw_mu(T, e, uniform(r, k0, k1));
+        a = mw_mu(ElecGrid(T), e, uniform(r, k0, k1));
     } else if (which == 4) {
         float u = 0.0f, v = 0.0f, w = 1.0f;
         const int nh = (int)p2;
         for (int k = 0; k < nh; ++k) {
-            const float mu = mw_mu(T, e, uniform(r, k0, k1));
+            const float mu = mw_mu(ElecGrid(T), e, uniform(r, k0, k1));
             const float turns = uniform(r, k0, k1);
             rotate(u, v, w, 1.0f - 2.0f * mu, 2.0f * hsqrt(mu * (1.0f - mu)), turns);
         }
@@ -2273,12 +2482,15 @@ __global__ void k_test_lookup(Tables T, int which, int m, const float* in, float
         grid(hlog2(x), T.pg_lo, T.pg_inv, T.pg_n, gi, gt);
         r = lerp4(global_f4(T.phot) + m * T.pg_n, gi, gt).w;
     } else if (which >= 1 && which <= 4) {
-        const f4 q = elec_at(T, global_f4(T.elec), m, x);
+        int i;
+        float t;
+        ElecGrid(T).cell(m, x, i, t);
+        const f4 q = lerp4(global_f4(T.elec), i, t);
         r = which == 1 ? q.x : (which == 2 ? q.y : (which == 3 ? q.z : q.w));
     } else if (which == 5) {
-        r = range_inv(T, global_ptr(T.rinv), global_ptr(T.rinv_scale), m, x);
+        r = range_inv(global_ptr(T.rinv), T.rinv_scale[m], T.nr, m, x);
     } else if (which == 6) {
-        r = mw_screening(T, x);
+        r = mw_screening(ElecGrid(T), x);
     }
     out[i] = r;
 }
@@ -2286,8 +2498,8 @@ __global__ void k_test_lookup(Tables T, int which, int m, const float* in, float
 // ---------------------------------------------------------------------------
 // host launchers (the host runtime calls these; kernels stay in this unit)
 // ---------------------------------------------------------------------------
-hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone) {
-    hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, st, ctl, R, ri, rebinned, lone);
+hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, int waves) {
+    hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, st, ctl, R, ri, rebinned, lone, (uint32_t)waves);
     return hipGetLastError();
 }
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
@@ -2296,15 +2508,15 @@ hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, 
     hipLaunchKernelGGL(k_commit, dim3(1), dim3(1), 0, st, ctl, ri, hdr);
     return hipGetLastError();
 }
-hipError_t launch_finish(hipStream_t st, Ctl* ctl, int ri) {
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1), 0, st, ctl, ri);
+hipError_t launch_finish(hipStream_t st, Ctl* ctl, JobCtl* jc, int ri) {
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, st, ctl, jc, ri);
     return hipGetLastError();
 }
 // LDS bytes of a pass with `waves` wavefronts per block (`lds`: tables and
 // records staged)
 size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds) {
     const size_t per_wave = lds ? kSliceF4 : kRingF4;
-    return ((lds ? (size_t)tables_f4(ri, T) : 0) + (size_t)waves * per_wave) * sizeof(float4);
+    return (kGroupTallyF4 + (lds ? (size_t)tables_f4(ri, T) : 0) + (size_t)waves * per_wave) * sizeof(float4);
 }
 
 // allow the staged kernels to use `bytes` of dynamic LDS
