@@ -91,9 +91,17 @@ struct Ctl {
                                        // to the next pass of the same type
     unsigned long long itype[5];      // real interactions: Compton, photoelectric,
                                        // pair, Moller, bremsstrahlung
-    double red[4];                    // statistics reductions
-    unsigned long long dmax_bits;
     unsigned long long anomalies;     // particles ended by a loop bound (0 in a sound run)
+};
+
+// a job's statistics: the batches' normalisation going in, the reductions coming
+// out (copied as one piece each way)
+constexpr int kMaxBatches = 1000;       // N_b of a job
+struct StatsDev {
+    double e_dep, sigma_sum, count;     // energy in the tallies; sum of sigma and number of
+                                        // voxels above half the maximum dose
+    unsigned long long dmax_bits;       // the maximum dose
+    double inv_n[kMaxBatches];          // 1 / histories of each batch
 };
 
 // counters of a transport pass, per particle type

@@ -46,9 +46,8 @@ hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_wave
                         const Tables& T, const RunDev& R);
 hipError_t launch_count_records(hipStream_t st, int blocks, const Ctl* ctl, const RunDev& R,
                                 unsigned long long* counts);
-hipError_t launch_stats(hipStream_t st, int blocks, Ctl* ctl, const double* slots, size_t nvox,
-                        int nb, const double* inv_n, const uint32_t* vox, double vvox, float min_rho,
-                        double* dose, double* sigma);
+hipError_t launch_stats(hipStream_t st, int cus, StatsDev* red, const double* slots, size_t nvox, int nb,
+                        const uint32_t* vox, double vvox, float min_rho, double* dose, double* sigma);
 hipError_t launch_test_philox(hipStream_t st, uint32_t k0, uint32_t k1, const uint4* ctr, uint4* out,
                               int n);
 hipError_t launch_test_sample(hipStream_t st, const Tables& T, int which, float e, float p1, float p2,
@@ -285,13 +284,13 @@ struct gdpm_context_s {
     DevBuf bins[2];    // their re-binning buffers
     DevBuf ctl;
     Ctl* host_ctl = nullptr;   // pinned mirror
-    DevBuf jobs_dev, jc, segs, inv_n, counts;
+    DevBuf jobs_dev, jc, segs, stats_dev, counts;
     JobDev* h_jobs = nullptr;  // pinned: job table, source segments, the read-back
     SrcSeg* h_segs = nullptr;  // part of the job counters, statistics reductions
     DevBuf src_hdr;            // per particle type: segments and histories of the
     SrcHdr* h_hdr = nullptr;   // iteration's source pass (device, pinned host)
     void* h_jc = nullptr;
-    double* h_red = nullptr;
+    StatsDev* h_stats = nullptr;
     double resident_bytes = 0.0;   // phantoms and sources alive in the context
     unsigned char* scratch = nullptr;  // this device's scratch array (gdpm_run_noalloc)
     // the autotuner's latest record: candidates, mean scores, the one kept (-1: undecided)
@@ -360,7 +359,6 @@ namespace {
 
 constexpr int kMaxWaves = 12;           // wavefronts of the transport kernels' workgroups (launch bound)
 constexpr int kMaxSegs = 4096;          // source segments per iteration (both types)
-constexpr int kMaxBatches = 1000;       // N_b of a job
 constexpr int kMaxGrid = 8192;          // nodes of an interpolation grid
 constexpr size_t kMaxStepGraphs = 32;   // launch settings an engine remembers
 uint64_t pow2_at_least(uint64_t n, uint64_t lo) {
@@ -440,7 +438,7 @@ struct EngineMem {
     JobCtl* jc;
     SrcSeg* segs;
     SrcHdr* hdr;
-    double* inv_n;                 // kMaxBatches doubles
+    StatsDev* stats;
     unsigned long long* counts;    // kMaxJobs counters
     bool fixed;                    // given memory: no allocation, no graph, no re-binning
 };
@@ -459,7 +457,7 @@ gdpm_status context_mem(gdpm_context ctx, EngineMem* m) {
     m->jc = ctx->jc.as<JobCtl>();
     m->segs = ctx->segs.as<SrcSeg>();
     m->hdr = ctx->src_hdr.as<SrcHdr>();
-    m->inv_n = ctx->inv_n.as<double>();
+    m->stats = ctx->stats_dev.as<StatsDev>();
     m->counts = ctx->counts.as<unsigned long long>();
     m->fixed = false;
     return GDPM_OK;
@@ -1136,28 +1134,22 @@ gdpm_status Engine::replay(const StepGraphKey& k) {
 
 gdpm_status compute_stats(gdpm_context ctx, const EngineMem& M, EJob* j, hipStream_t st) {
     const int nb = j->plan.nb;
-    const size_t nv = j->nv;
-    std::vector<double> inv(nb);
+    StatsDev* hs = ctx->h_stats;   // pinned
+    hs->e_dep = hs->sigma_sum = hs->count = 0.0;
+    hs->dmax_bits = 0ull;
     // a split job's tallies hold 2^split copies at weight 1 each
-    for (int b = 0; b < nb; ++b) inv[b] = j->nhist[b] > 0 ? std::ldexp(1.0 / j->nhist[b], -j->plan.split) : 0.0;
-    HIP_TRY(hipMemcpyAsync(M.inv_n, inv.data(), nb * sizeof(double), hipMemcpyHostToDevice, st));
-    Ctl* dc = M.ctl;
-    double* red = ctx->h_red;
-    memset(red, 0, 4 * sizeof(double) + sizeof(unsigned long long));
-    HIP_TRY(hipMemcpyAsync(&dc->red[0], red, 4 * sizeof(double) + sizeof(unsigned long long),
-                           hipMemcpyHostToDevice, st));
-    const int blocks = (int)std::min<size_t>((nv + 255) / 256, 8192);
-    HIP_TRY(launch_stats(st, blocks, dc, j->tally_p, nv, nb, M.inv_n,
-                         j->ph->vox.as<const uint32_t>(), j->ph->dx * j->ph->dy * j->ph->dz,
-                         (float)j->prm.stat_min_density, j->d_dose, j->d_sigma));
-    HIP_TRY(hipMemcpyAsync(red, &dc->red[0], 4 * sizeof(double) + sizeof(unsigned long long),
-                           hipMemcpyDeviceToHost, st));
+    for (int b = 0; b < nb; ++b)
+        hs->inv_n[b] = j->nhist[b] > 0 ? std::ldexp(1.0 / j->nhist[b], -j->plan.split) : 0.0;
+    HIP_TRY(hipMemcpyAsync(M.stats, hs, offsetof(StatsDev, inv_n) + nb * sizeof(double), hipMemcpyHostToDevice, st));
+    HIP_TRY(launch_stats(st, grid_blocks(ctx), M.stats, j->tally_p, j->nv, nb, j->ph->vox.as<const uint32_t>(),
+                         j->ph->dx * j->ph->dy * j->ph->dz, (float)j->prm.stat_min_density, j->d_dose, j->d_sigma));
+    HIP_TRY(hipMemcpyAsync(hs, M.stats, offsetof(StatsDev, inv_n), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     double dm;
-    memcpy(&dm, red + 4, sizeof dm);
+    memcpy(&dm, &hs->dmax_bits, sizeof dm);
     j->dmax = dm;
-    j->edep = std::ldexp(red[0], -j->plan.split);
-    j->unc = (red[2] > 0 && dm > 0) ? red[1] / red[2] / dm : 0.0;
+    j->edep = std::ldexp(hs->e_dep, -j->plan.split);
+    j->unc = (hs->count > 0 && dm > 0) ? hs->sigma_sum / hs->count / dm : 0.0;
     return GDPM_OK;
 }
 
@@ -1310,7 +1302,7 @@ bool scratch_layout(unsigned char* base, EJob* j, EngineMem* M) {
     M->jc = reinterpret_cast<JobCtl*>(take(sizeof(JobCtl)));
     M->segs = reinterpret_cast<SrcSeg*>(take(kMaxSegs * sizeof(SrcSeg)));
     M->hdr = reinterpret_cast<SrcHdr*>(take(2 * sizeof(SrcHdr)));
-    M->inv_n = reinterpret_cast<double*>(take(kMaxBatches * sizeof(double)));
+    M->stats = reinterpret_cast<StatsDev*>(take(sizeof(StatsDev)));
     M->counts = reinterpret_cast<unsigned long long*>(take(kMaxJobs * sizeof(unsigned long long)));
     j->mumax_p = reinterpret_cast<float*>(take(kMaxGrid * sizeof(float)));
     j->chains_p = reinterpret_cast<uint32_t*>(take(kMetroChains * sizeof(uint32_t)));
@@ -1602,8 +1594,8 @@ gdpm_status gdpm_context_create(int hip_device, const char* opts_json, gdpm_cont
     HIP_TRY(hipHostMalloc((void**)&ctx->h_hdr, 2 * sizeof(SrcHdr), hipHostMallocDefault));
     memset(ctx->h_hdr, 0, 2 * sizeof(SrcHdr));
     HIP_TRY(hipHostMalloc(&ctx->h_jc, kJcMirrorBytes, hipHostMallocDefault));
-    HIP_TRY(hipHostMalloc((void**)&ctx->h_red, 8 * sizeof(double), hipHostMallocDefault));
-    HIP_TRY(ctx->inv_n.alloc(kMaxBatches * sizeof(double)));
+    HIP_TRY(hipHostMalloc((void**)&ctx->h_stats, sizeof(StatsDev), hipHostMallocDefault));
+    HIP_TRY(ctx->stats_dev.alloc(sizeof(StatsDev)));
     HIP_TRY(ctx->counts.alloc(kMaxJobs * sizeof(unsigned long long)));
     for (int i = 0; i < 4; ++i) {   // timing events of the two transport passes
         hipEvent_t ev;
@@ -1624,7 +1616,7 @@ gdpm_status gdpm_context_destroy(gdpm_context ctx) {
     if (ctx->h_jobs) (void)hipHostFree(ctx->h_jobs);
     if (ctx->h_segs) (void)hipHostFree(ctx->h_segs);
     if (ctx->h_jc) (void)hipHostFree(ctx->h_jc);
-    if (ctx->h_red) (void)hipHostFree(ctx->h_red);
+    if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
     if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
     return GDPM_OK;

@@ -2296,55 +2296,94 @@ __global__ void k_bin_swap(Ctl* ctl, int ri) {
 // batch statistics (section 2.2.1, section 3.1): per voxel the mean over the
 // batches of D_b = E_b / (rho V n_b) and its standard error
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_dose_stats(Ctl* ctl, const double* slots, size_t nvox,
-                                                    int nb, const double* inv_mass_n,
-                                                    const uint32_t* vox, double vvox, float min_rho,
-                                                    double* dose, double* sigma) {
-    double emax = 0.0, edep = 0.0;
+// Both kernels are bound by HBM once their grid is small: two workgroups per CU.
+// With a workgroup per 256 voxels the reductions at the end, one addition of
+// every workgroup to the same address (85 million a second), were all of their
+// time: 70 and 96 us on a million voxels, where the data take 20 and 5 us.
+constexpr int kStatThreads = 512;
+
+// sums of a and b and maximum of c over the workgroup, in thread 0
+GDPM_DEV void block_reduce(double& a, double& b, double& c) {
+    __shared__ double sh[3][kStatThreads / 64];
+    a = wave_sum(a);
+    b = wave_sum(b);
+    for (int o = 32; o > 0; o >>= 1) c = fmax(c, __shfl_xor(c, o));
+    const int w = threadIdx.x >> 6;
+    if (lane_id() == 0) {
+        sh[0][w] = a;
+        sh[1][w] = b;
+        sh[2][w] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int i = 1; i < kStatThreads / 64; ++i) {
+            a += sh[0][i];
+            b += sh[1][i];
+            c = fmax(c, sh[2][i]);
+        }
+}
+
+// mean and sum of squared deviations of a voxel's batch doses d(0) .. d(nb - 1)
+template <class F>
+GDPM_DEV void voxel_stats(int nb, F d, double& mean, double& s2) {
+    double s = 0.0;
+    for (int b = 0; b < nb; ++b) s += d(b);
+    mean = s / nb;
+    s2 = 0.0;
+    for (int b = 0; b < nb; ++b) {
+        const double x = d(b) - mean;
+        s2 += x * x;
+    }
+}
+
+// red: {energy deposited, sum of sigma, voxels counted, -, bits of D_max}, zero at the start
+__global__ void __launch_bounds__(kStatThreads) k_dose_stats(StatsDev* red, const double* slots, size_t nvox, int nb,
+                                                             const uint32_t* vox, double vvox, float min_rho,
+                                                             double* dose, double* sigma) {
+    constexpr int kHeld = 10;   // batches whose energies stay in registers between the two sums
+    double emax = 0.0, edep = 0.0, none = 0.0;
+    const double* inv_n = red->inv_n;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox;
          i += (size_t)gridDim.x * blockDim.x) {
         const double rho = (double)voxel_density(vox[i]);
         const double im = 1.0 / (rho * vvox);
-        double s = 0.0, s2 = 0.0;
-        for (int b = 0; b < nb; ++b) {
-            const double eb = slots[(size_t)b * nvox + i];
-            edep += eb;
-            const double d = eb * im * inv_mass_n[b];
-            s += d;
-        }
-        const double mean = s / nb;
-        for (int b = 0; b < nb; ++b) {
-            const double d = slots[(size_t)b * nvox + i] * im * inv_mass_n[b] - mean;
-            s2 += d * d;
+        double mean, s2;
+        if (nb == kHeld) {
+            double eb[kHeld];
+#pragma unroll
+            for (int b = 0; b < kHeld; ++b) eb[b] = slots[(size_t)b * nvox + i];
+#pragma unroll
+            for (int b = 0; b < kHeld; ++b) edep += eb[b];
+            double s = 0.0;
+#pragma unroll
+            for (int b = 0; b < kHeld; ++b) s += eb[b] * im * inv_n[b];
+            mean = s / kHeld;
+            s2 = 0.0;
+#pragma unroll
+            for (int b = 0; b < kHeld; ++b) {
+                const double x = eb[b] * im * inv_n[b] - mean;
+                s2 += x * x;
+            }
+        } else {
+            for (int b = 0; b < nb; ++b) edep += slots[(size_t)b * nvox + i];
+            voxel_stats(nb, [&](int b) { return slots[(size_t)b * nvox + i] * im * inv_n[b]; }, mean, s2);
         }
         if (dose) dose[i] = mean;
         if (sigma) sigma[i] = nb > 1 ? sqrt(s2 / ((double)nb * (nb - 1))) : 0.0;
         if (rho >= (double)min_rho) emax = fmax(emax, mean);
     }
-    // block reductions
-    __shared__ double sh[256];
-    sh[threadIdx.x] = emax;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + o]);
-        __syncthreads();
+    block_reduce(edep, none, emax);
+    if (threadIdx.x == 0) {
+        unsafeAtomicAdd(&red->e_dep, edep);
+        atomicMax(&red->dmax_bits, (unsigned long long)__double_as_longlong(emax));
     }
-    if (threadIdx.x == 0) atomicMax(&ctl->dmax_bits, (unsigned long long)__double_as_longlong(sh[0]));
-    __syncthreads();
-    sh[threadIdx.x] = edep;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) unsafeAtomicAdd(&ctl->red[0], sh[0]);
 }
 
 // mean of sigma / D_max over voxels with D > D_max / 2
-__global__ void __launch_bounds__(256) k_unc(Ctl* ctl, const double* dose, const double* sigma,
-                                             const uint32_t* vox, float min_rho, size_t nvox) {
-    const double dmax = __longlong_as_double((long long)ctl->dmax_bits);
-    double s = 0.0, c = 0.0;
+__global__ void __launch_bounds__(kStatThreads) k_unc(StatsDev* red, const double* dose, const double* sigma,
+                                                      const uint32_t* vox, float min_rho, size_t nvox) {
+    const double dmax = __longlong_as_double((long long)red->dmax_bits);
+    double s = 0.0, c = 0.0, none = 0.0;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox;
          i += (size_t)gridDim.x * blockDim.x) {
         if (dose[i] > 0.5 * dmax && voxel_density(vox[i]) >= min_rho) {
@@ -2352,20 +2391,10 @@ __global__ void __launch_bounds__(256) k_unc(Ctl* ctl, const double* dose, const
             c += 1.0;
         }
     }
-    __shared__ double sh[2][256];
-    sh[0][threadIdx.x] = s;
-    sh[1][threadIdx.x] = c;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            sh[0][threadIdx.x] += sh[0][threadIdx.x + o];
-            sh[1][threadIdx.x] += sh[1][threadIdx.x + o];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        unsafeAtomicAdd(&ctl->red[1], sh[0][0]);
-        unsafeAtomicAdd(&ctl->red[2], sh[1][0]);
+    block_reduce(s, c, none);
+    if (threadIdx.x == 0 && c != 0.0) {
+        unsafeAtomicAdd(&red->sigma_sum, s);
+        unsafeAtomicAdd(&red->count, c);
     }
 }
 
@@ -2600,13 +2629,15 @@ hipError_t launch_count_records(hipStream_t st, int blocks, const Ctl* ctl, cons
     hipLaunchKernelGGL(k_count_records, dim3(blocks), dim3(256), 0, st, ctl, R, counts);
     return hipGetLastError();
 }
-hipError_t launch_stats(hipStream_t st, int blocks, Ctl* ctl, const double* slots, size_t nvox,
-                        int nb, const double* inv_n, const uint32_t* vox, double vvox, float min_rho,
-                        double* dose, double* sigma) {
-    hipLaunchKernelGGL(k_dose_stats, dim3(blocks), dim3(256), 0, st, ctl, slots, nvox, nb, inv_n,
-                       vox, vvox, min_rho, dose, sigma);
-    hipLaunchKernelGGL(k_unc, dim3(blocks), dim3(256), 0, st, ctl, (const double*)dose,
-                       (const double*)sigma, vox, min_rho, nvox);
+// red: inv_n set, the reductions zero
+hipError_t launch_stats(hipStream_t st, int cus, StatsDev* red, const double* slots, size_t nvox, int nb,
+                        const uint32_t* vox, double vvox, float min_rho, double* dose, double* sigma) {
+    const size_t need = (nvox + kStatThreads - 1) / kStatThreads;
+    const int blocks = (int)(need < (size_t)(2 * cus) ? need : (size_t)(2 * cus));
+    hipLaunchKernelGGL(k_dose_stats, dim3(blocks), dim3(kStatThreads), 0, st, red, slots, nvox, nb, vox, vvox, min_rho,
+                       dose, sigma);
+    hipLaunchKernelGGL(k_unc, dim3(blocks), dim3(kStatThreads), 0, st, red, (const double*)dose, (const double*)sigma,
+                       vox, min_rho, nvox);
     return hipGetLastError();
 }
 hipError_t launch_test_philox(hipStream_t st, uint32_t k0, uint32_t k1, const uint4* ctr, uint4* out,
