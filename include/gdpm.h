@@ -184,7 +184,7 @@ typedef struct {
                                     stat_min_density) */
     double dmax;                 /* MeV/g per history, same voxels */
     double t_total_s;            /* wall time of the call */
-    double t_kernel_s;           /* device time of the transport kernels (HIP events) */
+    double t_kernel_s;           /* device time of the transport passes (device clock) */
     double t_photon_s, t_electron_s;  /* device time per pass type, when the passes are
                                          launched apart (0 with fused_passes) */
     uint64_t events[8];          /* GDPM_EV_* counters of the run (for a job of a batch or a

@@ -85,6 +85,8 @@ struct Ctl {
     uint32_t pad0[31];
     uint32_t n_valid;                 // records kept by the last compaction
     uint32_t pad1;
+    unsigned long long t_start;       // device clock when the running pass started
+    unsigned long long ticks[3];      // clock ticks in photon, electron and fused passes
     unsigned long long ev[8];
     unsigned long long pass_ev[2][4];  // per pass type: records loaded, records
                                        // stored, tally deposits, records handed
@@ -94,14 +96,29 @@ struct Ctl {
     unsigned long long anomalies;     // particles ended by a loop bound (0 in a sound run)
 };
 
-// a job's statistics: the batches' normalisation going in, the reductions coming
-// out (copied as one piece each way)
+// a job's statistics: the reductions, and the batches' normalisation if there
+// are more than kArgBatches (else it goes with the kernel's arguments)
 constexpr int kMaxBatches = 1000;       // N_b of a job
+constexpr int kArgBatches = 32;
 struct StatsDev {
     double e_dep, sigma_sum, count;     // energy in the tallies; sum of sigma and number of
                                         // voxels above half the maximum dose
     unsigned long long dmax_bits;       // the maximum dose
+    uint32_t seq, pad[7];               // (in the host's copy: number of the calculation)
     double inv_n[kMaxBatches];          // 1 / histories of each batch
+};
+
+struct StatsArgs {
+    StatsDev* red;           // zero at the start
+    const double* slots;     // [nb][nvox] energy tallies
+    size_t nvox;
+    const uint32_t* vox;
+    double vvox;
+    double* dose;
+    double* sigma;
+    int nb;
+    float min_rho;
+    double inv_n[kArgBatches];
 };
 
 // counters of a transport pass, per particle type
@@ -248,12 +265,31 @@ struct SrcSeg {
     uint32_t rpos, rsize;      // position of h0 in its round, and the round's size
 };
 
-// the source pass of one particle type in one scheduler iteration: segments
-// and histories; read by the kernels from device memory, so that a recorded
-// launch sequence stays valid while these change
+// The source passes of one scheduler iteration, per particle type: the host
+// writes the numbers of segments and records (pinned memory), the iteration's
+// first kernel copies the segments to the device and notes where the records go.
+// The kernels read all of it from memory, so that a recorded launch sequence
+// stays valid while it changes.
 struct SrcHdr {
-    uint32_t nseg, total;
-    uint32_t pad0, pad1;
+    uint32_t nseg, total;    // segments, records
+    uint32_t base;           // queue position of the first record
+    uint32_t pad;
+};
+constexpr int kMaxSegs = 4096;          // source segments per iteration (both types)
+struct StepHost {
+    SrcHdr hdr[2];
+    uint32_t seq;            // number of the iteration, echoed when it has ended
+    uint32_t pad[7];
+    SrcSeg segs[kMaxSegs];   // photon sources' segments, then from kMaxSegs / 2 electron sources'
+};
+
+// what the host reads after an iteration (pinned memory, written by the
+// iteration's last kernel, `seq` last)
+struct StepMirror {
+    Ctl ctl;
+    unsigned long long births[kMaxJobs], deaths[kMaxJobs];
+    double e_in[kMaxJobs], e_esc[kMaxJobs];
+    uint32_t seq, pad[31];
 };
 
 // The re-binning leaves the records where they are.  Each queue has a

@@ -35,7 +35,13 @@ namespace gdpm {
 hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, int waves);
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
                          const SrcHdr* hdr, int ri);
-hipError_t launch_finish(hipStream_t st, Ctl* ctl, JobCtl* jc, int ri);
+hipError_t launch_begin(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, SrcHdr* hdr, SrcSeg* segs,
+                        int setup, int lone, int waves0, int waves1);
+hipError_t launch_mid(hipStream_t st, Ctl* ctl, const RunDev& R, int setup, int lone, int waves);
+hipError_t launch_end(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, StepMirror* out, int fused);
+hipError_t launch_init(hipStream_t st, Ctl* ctl, JobCtl* jc, StatsDev* stats, uint32_t start);
+hipError_t launch_admit(hipStream_t st, int cus, const JobDev& job, JobDev* jobs, JobCtl* jc, const float* majorant,
+                        float* mumax, size_t n_tally, size_t n_hist, int slot, int n_grid);
 size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds);
 hipError_t transport_lds_optin(size_t bytes);
 hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool solo, bool permuted,
@@ -46,8 +52,7 @@ hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_wave
                         const Tables& T, const RunDev& R);
 hipError_t launch_count_records(hipStream_t st, int blocks, const Ctl* ctl, const RunDev& R,
                                 unsigned long long* counts);
-hipError_t launch_stats(hipStream_t st, int cus, StatsDev* red, const double* slots, size_t nvox, int nb,
-                        const uint32_t* vox, double vvox, float min_rho, double* dose, double* sigma);
+hipError_t launch_stats(hipStream_t st, int cus, const StatsArgs& a, StatsDev* out, uint32_t seq);
 hipError_t launch_test_philox(hipStream_t st, uint32_t k0, uint32_t k1, const uint4* ctr, uint4* out,
                               int n);
 hipError_t launch_test_sample(hipStream_t st, const Tables& T, int which, float e, float p1, float p2,
@@ -232,8 +237,7 @@ double now_s() {
 // Compared bytewise: built on a zeroed object.
 struct StepGraphKey {
     hipStream_t st;
-    int seg_copy[2];     // source segments copied per particle type (0: no source pass)
-    int src_blocks[2];
+    int src_blocks[2];   // grid of the source pass per particle type (0: none)
     int rebin[2], lds[2];
     int lone;            // the one job holding particles (queues not re-binned), or -1
     int blocks, nb, space;     // one workgroup per CU (source, re-binning)
@@ -283,21 +287,21 @@ struct gdpm_context_s {
     DevBuf rings[2];   // the queues' records
     DevBuf bins[2];    // their re-binning buffers
     DevBuf ctl;
-    Ctl* host_ctl = nullptr;   // pinned mirror
+    StepMirror* mirror = nullptr;   // pinned: what an iteration reports
+    StepHost* h_step = nullptr;     // pinned: the iteration's source segments
     DevBuf jobs_dev, jc, segs, stats_dev, counts;
-    JobDev* h_jobs = nullptr;  // pinned: job table, source segments, the read-back
-    SrcSeg* h_segs = nullptr;  // part of the job counters, statistics reductions
-    DevBuf src_hdr;            // per particle type: segments and histories of the
-    SrcHdr* h_hdr = nullptr;   // iteration's source pass (device, pinned host)
-    void* h_jc = nullptr;
-    StatsDev* h_stats = nullptr;
+    DevBuf src_hdr;
+    StatsDev* h_stats = nullptr;    // pinned: a job's statistics
+    float* h_maj = nullptr;         // pinned: majorant of each job slot, n_grid values
+    size_t maj_bytes = 0;
+    uint32_t seq = 0;               // iterations and statistics, numbered
+    double tick_s = 1e-8;           // period of the device clock
     double resident_bytes = 0.0;   // phantoms and sources alive in the context
     unsigned char* scratch = nullptr;  // this device's scratch array (gdpm_run_noalloc)
     // the autotuner's latest record: candidates, mean scores, the one kept (-1: undecided)
     std::vector<std::pair<int, int>> tune_cand;
     std::vector<double> tune_score;
     int tune_kept = -1;
-    std::vector<hipEvent_t> events;
     bool busy = false;
 };
 
@@ -358,7 +362,6 @@ struct gdpm_source_s {
 namespace {
 
 constexpr int kMaxWaves = 12;           // wavefronts of the transport kernels' workgroups (launch bound)
-constexpr int kMaxSegs = 4096;          // source segments per iteration (both types)
 constexpr int kMaxGrid = 8192;          // nodes of an interpolation grid
 constexpr size_t kMaxStepGraphs = 32;   // launch settings an engine remembers
 uint64_t pow2_at_least(uint64_t n, uint64_t lo) {
@@ -366,14 +369,6 @@ uint64_t pow2_at_least(uint64_t n, uint64_t lo) {
     while (p < n) p <<= 1;
     return p;
 }
-// the host reads back the first four arrays of JobCtl after every iteration
-struct JobCtlMirror {
-    unsigned long long births[kMaxJobs], deaths[kMaxJobs];
-    double e_in[kMaxJobs], e_esc[kMaxJobs];
-};
-constexpr size_t kJcMirrorBytes = sizeof(JobCtlMirror);
-static_assert(offsetof(JobCtl, seg_begin) == kJcMirrorBytes, "JobCtl starts with the read-back arrays");
-
 Geom geom_of(const gdpm_phantom_s* ph) {
     Geom g;
     g.vox = ph->vox.as<const uint32_t>();
@@ -619,14 +614,16 @@ struct Engine {
         unsigned long long last_events = 0;
         double last_time = 0.0;
     } tune;
+    gdpm_status wait(const uint32_t* number, uint32_t seq);
     void tune_begin();
     void tune_account();
 
     gdpm_status init(gdpm_context c, hipStream_t s, const RunPlan& plan, const EngineMem* mem = nullptr);
     gdpm_status admit(EJob* j);
     gdpm_status step();
-    gdpm_status issue(const StepGraphKey& k, bool recording);
+    gdpm_status issue(const StepGraphKey& k);
     gdpm_status replay(const StepGraphKey& k);
+    gdpm_status compute_stats(EJob* j);
     gdpm_status settle();       // super-round ends, statistics, finished jobs
     void release(EJob* j);
     bool any_active() const {
@@ -654,7 +651,7 @@ void Engine::tune_begin() {
 // after an iteration: score the candidate it ran with, move to the next
 void Engine::tune_account() {
     if (!tune.on || tune.fixed) return;
-    const Ctl* hc = ctx->host_ctl;
+    const Ctl* hc = &ctx->mirror->ctl;
     const unsigned long long ev = hc->ev[GDPM_EV_FLIGHTS] + hc->ev[GDPM_EV_ESTEPS];
     const double t = tm.photon + tm.electron + tm.fused;
     const unsigned long long dev = ev - tune.last_events;
@@ -704,12 +701,12 @@ gdpm_status Engine::init(gdpm_context c, hipStream_t s, const RunPlan& plan, con
         if (e) return e;
     }
     T = tab->view(nullptr);
-    Ctl* hc = ctx->host_ctl;
-    memset(hc, 0, sizeof(Ctl));
-    for (int r = 0; r < 2; ++r) hc->ring[r].head = hc->ring[r].tail = hc->ring[r].begin = ctx->ring_start;
-    HIP_TRY(hipMemcpyAsync(M.ctl, hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemsetAsync(M.jc, 0, sizeof(JobCtl), st));
-    memset(ctx->h_jc, 0, kJcMirrorBytes);
+    memset(ctx->mirror, 0, sizeof(StepMirror));
+    for (int r = 0; r < 2; ++r) {
+        RingCtl& q = ctx->mirror->ctl.ring[r];
+        q.head = q.tail = q.begin = ctx->ring_start;
+    }
+    HIP_TRY(launch_init(st, M.ctl, M.jc, M.stats, ctx->ring_start));
     memset(&R, 0, sizeof R);
     R.ecut_g = (float)plan.ecut_g;
     R.ecut_e = (float)plan.ecut_e;
@@ -759,12 +756,12 @@ gdpm_status Engine::admit(EJob* j) {
         HIP_TRY(j->mumax.alloc(mm.size() * sizeof(float)));
         j->mumax_p = j->mumax.as<float>();
     }
-    HIP_TRY(hipMemcpyAsync(j->mumax_p, mm.data(), mm.size() * sizeof(float), hipMemcpyHostToDevice, st));
+    float* hm = ctx->h_maj + (size_t)slot * mm.size();
+    std::copy(mm.begin(), mm.end(), hm);
     if (!j->tally_p) {
         HIP_TRY(j->tally.alloc((size_t)plan.nb * nv * sizeof(double)));
         j->tally_p = j->tally.as<double>();
     }
-    HIP_TRY(hipMemsetAsync(j->tally_p, 0, (size_t)plan.nb * nv * sizeof(double), st));
     if (!j->d_dose) {
         HIP_TRY(j->dose_buf.alloc(nv * sizeof(double)));
         j->d_dose = j->dose_buf.as<double>();
@@ -774,11 +771,8 @@ gdpm_status Engine::admit(EJob* j) {
         j->d_sigma = j->sigma_buf.as<double>();
     }
     double* hist = nullptr;
-    if (j->hist.bytes) {
-        HIP_TRY(hipMemsetAsync(j->hist.p, 0, j->hist.bytes, st));
-        hist = j->hist.as<double>();
-    }
-    JobDev& d = ctx->h_jobs[slot];
+    if (j->hist.bytes) hist = j->hist.as<double>();
+    JobDev d;
     memset(&d, 0, sizeof d);
     d.G = geom_of(j->ph);
     d.S = j->src->view();
@@ -805,13 +799,10 @@ gdpm_status Engine::admit(EJob* j) {
         HIP_TRY(launch_metro_init(st, d.S, d.k0, d.k1, j->chains_p));
         d.chains = j->chains_p;
     }
-    HIP_TRY(hipMemcpyAsync(M.jobs + slot, &d, sizeof d, hipMemcpyHostToDevice, st));
-    // the job's counters start from zero
-    JobCtl* dj = M.jc;
-    HIP_TRY(hipMemsetAsync(&dj->births[slot], 0, sizeof(unsigned long long), st));
-    HIP_TRY(hipMemsetAsync(&dj->deaths[slot], 0, sizeof(unsigned long long), st));
-    HIP_TRY(hipMemsetAsync(&dj->e_in[slot], 0, sizeof(double), st));
-    HIP_TRY(hipMemsetAsync(&dj->e_esc[slot], 0, sizeof(double), st));
+    HIP_TRY(launch_admit(st, grid_blocks(ctx), d, M.jobs, M.jc, hm, j->mumax_p, (size_t)plan.nb * nv,
+                         hist ? j->hist.bytes / sizeof(double) : 0, slot, (int)mm.size()));
+    ctx->mirror->births[slot] = ctx->mirror->deaths[slot] = 0;   // (the host's copy, until the next iteration)
+    ctx->mirror->e_in[slot] = ctx->mirror->e_esc[slot] = 0.0;
     j->births = j->deaths = 0;
     // schedule: fixed mode is one super-round; target mode starts from n_histories
     j->hbase = plan.target ? 0 : j->prm.hist0;
@@ -840,7 +831,7 @@ void Engine::release(EJob* j) {
 
 // one scheduler iteration: new histories, a photon pass, an electron pass
 gdpm_status Engine::step() {
-    Ctl* hc = ctx->host_ctl;
+    const Ctl* hc = &ctx->mirror->ctl;
     const int blocks = grid_blocks(ctx);
     const uint32_t cap = 1u << M.ring_log2;
     // new histories: at most half a queue (or pass_histories) less what the
@@ -865,7 +856,7 @@ gdpm_status Engine::step() {
         });
     int nseg[2] = {0, 0};
     uint32_t total[2] = {0u, 0u};
-    SrcSeg* hs = ctx->h_segs;
+    SrcSeg* hs = ctx->h_step->segs;
     const int seg_cap = kMaxSegs / 2;   // per source type
     for (size_t k = 0; k < want.size() && room > 0; ++k) {
         EJob* j = want[k];
@@ -904,7 +895,9 @@ gdpm_status Engine::step() {
         }
     }
     R.n_jobs = std::max(n_slots, 1);
-    for (int ri = 0; ri < 2; ++ri) ctx->h_hdr[ri] = SrcHdr{(uint32_t)nseg[ri], total[ri], 0u, 0u};
+    for (int ri = 0; ri < 2; ++ri) ctx->h_step->hdr[ri] = SrcHdr{(uint32_t)nseg[ri], total[ri], 0u, 0u};
+    const uint32_t seq = ++ctx->seq;
+    ctx->h_step->seq = seq;
     // bins per job so that jobs x bins fits the re-binning keys; boxes of the
     // phantom come as space^3 (the largest cube within the bins)
     int nb = std::max(1, std::min(std::min(ctx->rebin_bins, kMaxBins), kMaxKeys / R.n_jobs));
@@ -920,7 +913,7 @@ gdpm_status Engine::step() {
     // the queues need no re-binning: they are all its segment.
     int holders = 0, lone = -1, first_slot = -1;
     {
-        const JobCtlMirror* m = reinterpret_cast<const JobCtlMirror*>(ctx->h_jc);
+        const StepMirror* m = ctx->mirror;
         std::vector<char> fresh(n_slots, 0);
         for (int ri = 0; ri < 2; ++ri)
             for (int q = 0; q < nseg[ri]; ++q) fresh[hs[ri * seg_cap + q].job] = 1;
@@ -937,8 +930,8 @@ gdpm_status Engine::step() {
         if (holders == 0) lone = first_slot;   // queues hold no particle at all
     }
     // A graph needs a launch sequence that does not change between iterations:
-    // copy sizes and source grids are rounded up to powers of two (the kernels
-    // read the true counts from the header), so a few recordings serve a run.
+    // source grids are rounded up to powers of two (the kernels read the true
+    // counts from the header), so a few recordings serve a run.
     // (A null stream cannot record; it never reaches here, a run without a
     // stream of its own uses the context's.)
     const bool graph = ctx->graphs != 0 && st != nullptr && !M.fixed;
@@ -948,7 +941,6 @@ gdpm_status Engine::step() {
     for (int ri = 0; ri < 2; ++ri) {
         if (!nseg[ri]) continue;
         const uint64_t need = std::min<uint64_t>((total[ri] + 255) / 256, 4u * (uint64_t)blocks);
-        k.seg_copy[ri] = graph ? (int)std::min<uint64_t>(pow2_at_least(nseg[ri], 8), seg_cap) : nseg[ri];
         k.src_blocks[ri] = (int)(graph ? std::min<uint64_t>(pow2_at_least(need, 1), 4u * (uint64_t)blocks) : need);
     }
     k.blocks = blocks;
@@ -984,21 +976,16 @@ gdpm_status Engine::step() {
     k.R = R;
     k.T = T;
     {
-        const gdpm_status s = graph ? replay(k) : issue(k, false);
+        const gdpm_status s = graph ? replay(k) : issue(k);
         if (s != GDPM_OK) return s;
     }
-    HIP_TRY(hipStreamSynchronize(st));
-    if (k.fused) {
-        float ms = 0.0f;
-        HIP_TRY(hipEventElapsedTime(&ms, ctx->events[0], ctx->events[1]));
-        tm.fused += ms * 1e-3;
-    } else {
-        for (int ri = 0; ri < 2; ++ri) {
-            float ms = 0.0f;
-            HIP_TRY(hipEventElapsedTime(&ms, ctx->events[2 * ri], ctx->events[2 * ri + 1]));
-            (ri == 0 ? tm.photon : tm.electron) += ms * 1e-3;
-        }
+    {
+        const gdpm_status s = wait(&ctx->mirror->seq, seq);
+        if (s != GDPM_OK) return s;
     }
+    tm.photon = (double)hc->ticks[0] * ctx->tick_s;
+    tm.electron = (double)hc->ticks[1] * ctx->tick_s;
+    tm.fused = (double)hc->ticks[2] * ctx->tick_s;
     ++iter;
     last = k;
     tune_account();
@@ -1009,6 +996,23 @@ gdpm_status Engine::step() {
     if (hc->overflow)
         return fail(GDPM_E_OVERFLOW, "a particle queue filled up (capacity 2^%d); raise ring_capacity_log2",
                     M.ring_log2);
+    return GDPM_OK;
+}
+
+// Wait until the device has written `seq` to a number in pinned memory (the last
+// thing an iteration or a job's statistics do).  The number is polled for a short
+// while, which saves the 20 us that a wait for the stream takes to wake up; long
+// iterations wait for the stream.
+gdpm_status Engine::wait(const uint32_t* number, uint32_t seq) {
+    const double t0 = now_s();
+    for (uint32_t spins = 0; __atomic_load_n(number, __ATOMIC_ACQUIRE) != seq; ++spins) {
+        if ((spins & 63u) == 63u && now_s() - t0 > 300e-6) {
+            HIP_TRY(hipStreamSynchronize(st));
+            if (__atomic_load_n(number, __ATOMIC_ACQUIRE) != seq)
+                return fail(GDPM_E_DEVICE, "an iteration ended without its report");
+            break;
+        }
+    }
     return GDPM_OK;
 }
 
@@ -1023,8 +1027,8 @@ gdpm_status Engine::check_accounting() {
     HIP_TRY(hipMemcpyAsync(live.data(), M.counts, kMaxJobs * sizeof(unsigned long long),
                            hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    const JobCtlMirror* m = reinterpret_cast<const JobCtlMirror*>(ctx->h_jc);
-    const Ctl* hc = ctx->host_ctl;
+    const StepMirror* m = ctx->mirror;
+    const Ctl* hc = &m->ctl;
     for (int i = 0; i < n_slots; ++i) {
         const EJob* j = slots[i];
         if (!j || j->done) continue;
@@ -1036,58 +1040,49 @@ gdpm_status Engine::check_accounting() {
                 "(offset %lld) but %llu live records; slots %d, source segments %d/%d, re-binned %d/%d, "
                 "queues [%u, %u) [%u, %u), graph %d\n",
                 iter, i, j->prm.job_id, (unsigned long long)m->births[i], (unsigned long long)m->deaths[i],
-                (long long)j->death_offset, live[i], n_slots, last.seg_copy[0], last.seg_copy[1],
+                (long long)j->death_offset, live[i], n_slots, ctx->h_step->hdr[0].nseg, ctx->h_step->hdr[1].nseg,
                 last.rebin[0], last.rebin[1], hc->ring[0].head, hc->ring[0].tail, hc->ring[1].head,
                 hc->ring[1].tail, ctx->graphs);
     }
     return GDPM_OK;
 }
 
-// the launch sequence of one iteration: source passes, then for photons and
-// electrons re-binning, set-up, transport (between two timing events) and
-// completion, then the read-back of the counters
-gdpm_status Engine::issue(const StepGraphKey& k, bool recording) {
+// the launch sequence of one iteration: the new histories' segments and the
+// set-up, the source passes, then photons and electrons (each re-binned first if
+// several jobs hold particles), and the report to the host
+gdpm_status Engine::issue(const StepGraphKey& k) {
     Ctl* dc = M.ctl;
-    SrcHdr* dh = M.hdr;
-    const int seg_cap = kMaxSegs / 2;
-    HIP_TRY(hipMemcpyAsync(dh, ctx->h_hdr, 2 * sizeof(SrcHdr), hipMemcpyHostToDevice, st));
-    for (int ri = 0; ri < 2; ++ri) {
-        if (!k.seg_copy[ri]) continue;
-        SrcSeg* dseg = M.segs + ri * seg_cap;
-        HIP_TRY(hipMemcpyAsync(dseg, ctx->h_segs + ri * seg_cap, k.seg_copy[ri] * sizeof(SrcSeg),
-                               hipMemcpyHostToDevice, st));
-        HIP_TRY(launch_source(st, k.src_blocks[ri], dc, k.R, dseg, dh + ri, ri));
-    }
+    int waves[2];
+    for (int ri = 0; ri < 2; ++ri) waves[ri] = (k.fused ? k.blocks * k.threads[1] : k.pass_blocks[ri] * k.threads[ri]) / 64;
+    auto rebin = [&](int ri) -> gdpm_status {
+        if (!k.rebin[ri]) return GDPM_OK;
+        HIP_TRY(launch_rebin(st, 4 * k.blocks, dc, k.R, ri, k.nb, k.blo, k.binv, k.space));
+        HIP_TRY(launch_setup(st, dc, k.R, ri, 1, k.lone, waves[ri]));
+        return GDPM_OK;
+    };
+    auto pass = [&](int ri) -> gdpm_status {
+        HIP_TRY(launch_transport(st, ri, k.pass_blocks[ri], k.threads[ri], k.lds[ri] != 0, ctx->solo_lanes != 0,
+                                 k.rebin[ri] != 0, dc, k.T, k.R));
+        return GDPM_OK;
+    };
+    gdpm_status s;
+    const int setup = (k.rebin[0] ? 0 : 1) | (k.fused && !k.rebin[1] ? 2 : 0);
+    HIP_TRY(launch_begin(st, dc, k.R, ctx->h_step, M.hdr, M.segs, setup, k.lone, waves[0], waves[1]));
+    for (int ri = 0; ri < 2; ++ri)
+        if (k.src_blocks[ri])
+            HIP_TRY(launch_source(st, k.src_blocks[ri], dc, k.R, M.segs + ri * (kMaxSegs / 2), M.hdr + ri, ri));
+    if ((s = rebin(0))) return s;
     if (k.fused) {
         // both queues set up, then one launch runs both passes
-        for (int ri = 0; ri < 2; ++ri) {
-            if (k.rebin[ri]) HIP_TRY(launch_rebin(st, 4 * k.blocks, dc, k.R, ri, k.nb, k.blo, k.binv, k.space));
-            HIP_TRY(launch_setup(st, dc, k.R, ri, k.rebin[ri], k.lone, k.blocks * k.threads[1] / 64));
-        }
-        HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[0], st, hipEventRecordExternal)
-                          : hipEventRecord(ctx->events[0], st));
+        if ((s = rebin(1))) return s;
         HIP_TRY(launch_fused(st, k.blocks, k.threads[1], k.photon_waves, k.rebin[0] || k.rebin[1], dc, k.T, k.R));
-        HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[1], st, hipEventRecordExternal)
-                          : hipEventRecord(ctx->events[1], st));
-        for (int ri = 0; ri < 2; ++ri) HIP_TRY(launch_finish(st, dc, M.jc, ri));
-        HIP_TRY(hipMemcpyAsync(ctx->host_ctl, dc, sizeof(Ctl), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(ctx->h_jc, M.jc, kJcMirrorBytes, hipMemcpyDeviceToHost, st));
-        return GDPM_OK;
+    } else {
+        if ((s = pass(0))) return s;
+        HIP_TRY(launch_mid(st, dc, k.R, !k.rebin[1], k.lone, waves[1]));
+        if ((s = rebin(1))) return s;
+        if ((s = pass(1))) return s;
     }
-    for (int ri = 0; ri < 2; ++ri) {
-        if (k.rebin[ri]) HIP_TRY(launch_rebin(st, 4 * k.blocks, dc, k.R, ri, k.nb, k.blo, k.binv, k.space));
-        HIP_TRY(launch_setup(st, dc, k.R, ri, k.rebin[ri], k.lone, k.pass_blocks[ri] * k.threads[ri] / 64));
-        // a recorded event becomes a node of the graph that records it at replay
-        HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[2 * ri], st, hipEventRecordExternal)
-                          : hipEventRecord(ctx->events[2 * ri], st));
-        HIP_TRY(launch_transport(st, ri, k.pass_blocks[ri], k.threads[ri], k.lds[ri] != 0,
-                                 ctx->solo_lanes != 0, k.rebin[ri] != 0, dc, k.T, k.R));
-        HIP_TRY(recording ? hipEventRecordWithFlags(ctx->events[2 * ri + 1], st, hipEventRecordExternal)
-                          : hipEventRecord(ctx->events[2 * ri + 1], st));
-        HIP_TRY(launch_finish(st, dc, M.jc, ri));
-    }
-    HIP_TRY(hipMemcpyAsync(ctx->host_ctl, dc, sizeof(Ctl), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(ctx->h_jc, M.jc, kJcMirrorBytes, hipMemcpyDeviceToHost, st));
+    HIP_TRY(launch_end(st, dc, k.R, ctx->h_step, ctx->mirror, k.fused));
     return GDPM_OK;
 }
 
@@ -1107,11 +1102,11 @@ gdpm_status Engine::replay(const StepGraphKey& k) {
             graphs.erase(old);
         }
         graphs.push_back(StepGraph{k, nullptr, ++graph_clock});
-        return issue(k, false);
+        return issue(k);
     }
     if (!hit->exec) {
         HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        const gdpm_status s = issue(k, true);
+        const gdpm_status s = issue(k);
         hipGraph_t graph = nullptr;
         const hipError_t e = hipStreamEndCapture(st, &graph);
         if (s != GDPM_OK) {
@@ -1132,19 +1127,28 @@ gdpm_status Engine::replay(const StepGraphKey& k) {
     return GDPM_OK;
 }
 
-gdpm_status compute_stats(gdpm_context ctx, const EngineMem& M, EJob* j, hipStream_t st) {
+gdpm_status Engine::compute_stats(EJob* j) {
     const int nb = j->plan.nb;
     StatsDev* hs = ctx->h_stats;   // pinned
-    hs->e_dep = hs->sigma_sum = hs->count = 0.0;
-    hs->dmax_bits = 0ull;
+    StatsArgs a{};
     // a split job's tallies hold 2^split copies at weight 1 each
-    for (int b = 0; b < nb; ++b)
-        hs->inv_n[b] = j->nhist[b] > 0 ? std::ldexp(1.0 / j->nhist[b], -j->plan.split) : 0.0;
-    HIP_TRY(hipMemcpyAsync(M.stats, hs, offsetof(StatsDev, inv_n) + nb * sizeof(double), hipMemcpyHostToDevice, st));
-    HIP_TRY(launch_stats(st, grid_blocks(ctx), M.stats, j->tally_p, j->nv, nb, j->ph->vox.as<const uint32_t>(),
-                         j->ph->dx * j->ph->dy * j->ph->dz, (float)j->prm.stat_min_density, j->d_dose, j->d_sigma));
-    HIP_TRY(hipMemcpyAsync(hs, M.stats, offsetof(StatsDev, inv_n), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    double* inv = nb <= kArgBatches ? a.inv_n : hs->inv_n;
+    for (int b = 0; b < nb; ++b) inv[b] = j->nhist[b] > 0 ? std::ldexp(1.0 / j->nhist[b], -j->plan.split) : 0.0;
+    if (nb > kArgBatches)
+        HIP_TRY(hipMemcpyAsync(M.stats->inv_n, hs->inv_n, nb * sizeof(double), hipMemcpyHostToDevice, st));
+    a.red = M.stats;
+    a.slots = j->tally_p;
+    a.nvox = j->nv;
+    a.vox = j->ph->vox.as<const uint32_t>();
+    a.vvox = j->ph->dx * j->ph->dy * j->ph->dz;
+    a.dose = j->d_dose;
+    a.sigma = j->d_sigma;
+    a.nb = nb;
+    a.min_rho = (float)j->prm.stat_min_density;
+    const uint32_t seq = ++ctx->seq;
+    HIP_TRY(launch_stats(st, grid_blocks(ctx), a, hs, seq));
+    const gdpm_status s = wait(&hs->seq, seq);
+    if (s) return s;
     double dm;
     memcpy(&dm, &hs->dmax_bits, sizeof dm);
     j->dmax = dm;
@@ -1157,7 +1161,7 @@ gdpm_status compute_stats(gdpm_context ctx, const EngineMem& M, EJob* j, hipStre
 // and either finish or start the next super-round
 gdpm_status Engine::settle() {
     bool progress = false;
-    const JobCtlMirror* m = reinterpret_cast<const JobCtlMirror*>(ctx->h_jc);
+    const StepMirror* m = ctx->mirror;
     for (int i = 0; i < n_slots; ++i) {
         EJob* j = slots[i];
         if (!j || j->done) continue;
@@ -1167,7 +1171,7 @@ gdpm_status Engine::settle() {
         j->e_esc = std::ldexp(m->e_esc[i], -j->plan.split);
         if (j->issued < j->sr_end || j->births != j->deaths) continue;
         progress = true;
-        gdpm_status s = compute_stats(ctx, M, j, st);
+        gdpm_status s = compute_stats(j);
         if (s) return s;
         j->rounds += (uint32_t)j->plan.nb;
         const gdpm_run_params& p = j->prm;
@@ -1196,7 +1200,7 @@ gdpm_status Engine::settle() {
         j->sr_final = true;   // sized to reach the target (or the history cap)
     }
     // nothing left anywhere but a job still waits: the bookkeeping is broken
-    const Ctl* hc = ctx->host_ctl;
+    const Ctl* hc = &ctx->mirror->ctl;
     const bool empty = hc->ring[0].tail == hc->ring[0].head && hc->ring[1].tail == hc->ring[1].head;
     bool issuing = false;
     for (int i = 0; i < n_slots; ++i)
@@ -1234,7 +1238,7 @@ gdpm_status Engine::settle() {
 
 void fill_stats(const Engine& E, const EJob* j, double t_start, gdpm_run_stats* out) {
     memset(out, 0, sizeof *out);
-    const Ctl* hc = E.ctx->host_ctl;
+    const Ctl* hc = &E.ctx->mirror->ctl;
     out->histories = j->issued;
     out->e_in = j->e_in;
     out->e_esc = j->e_esc;
@@ -1582,26 +1586,21 @@ gdpm_status gdpm_context_create(int hip_device, const char* opts_json, gdpm_cont
     }
     HIP_TRY(hipStreamCreateWithFlags(&ctx->stream, hipStreamNonBlocking));
     HIP_TRY(ctx->ctl.alloc(sizeof(Ctl)));
-    HIP_TRY(hipHostMalloc((void**)&ctx->host_ctl, sizeof(Ctl), hipHostMallocDefault));
-    memset(ctx->host_ctl, 0, sizeof(Ctl));
+    HIP_TRY(hipHostMalloc((void**)&ctx->mirror, sizeof(StepMirror), hipHostMallocDefault));
+    memset(ctx->mirror, 0, sizeof(StepMirror));
     HIP_TRY(ctx->jobs_dev.alloc(kMaxJobs * sizeof(JobDev)));
     HIP_TRY(ctx->jc.alloc(sizeof(JobCtl)));
     HIP_TRY(ctx->segs.alloc(kMaxSegs * sizeof(SrcSeg)));
-    HIP_TRY(hipHostMalloc((void**)&ctx->h_jobs, kMaxJobs * sizeof(JobDev), hipHostMallocDefault));
-    HIP_TRY(hipHostMalloc((void**)&ctx->h_segs, kMaxSegs * sizeof(SrcSeg), hipHostMallocDefault));
-    memset(ctx->h_segs, 0, kMaxSegs * sizeof(SrcSeg));
+    HIP_TRY(hipHostMalloc((void**)&ctx->h_step, sizeof(StepHost), hipHostMallocDefault));
+    memset(ctx->h_step, 0, sizeof(StepHost));
     HIP_TRY(ctx->src_hdr.alloc(2 * sizeof(SrcHdr)));
-    HIP_TRY(hipHostMalloc((void**)&ctx->h_hdr, 2 * sizeof(SrcHdr), hipHostMallocDefault));
-    memset(ctx->h_hdr, 0, 2 * sizeof(SrcHdr));
-    HIP_TRY(hipHostMalloc(&ctx->h_jc, kJcMirrorBytes, hipHostMallocDefault));
     HIP_TRY(hipHostMalloc((void**)&ctx->h_stats, sizeof(StatsDev), hipHostMallocDefault));
+    memset(ctx->h_stats, 0, sizeof(StatsDev));   // (its number is waited for)
     HIP_TRY(ctx->stats_dev.alloc(sizeof(StatsDev)));
     HIP_TRY(ctx->counts.alloc(kMaxJobs * sizeof(unsigned long long)));
-    for (int i = 0; i < 4; ++i) {   // timing events of the two transport passes
-        hipEvent_t ev;
-        HIP_TRY(hipEventCreate(&ev));
-        ctx->events.push_back(ev);
-    }
+    int khz = 0;   // the device clock that times the passes
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, hip_device) == hipSuccess && khz > 0)
+        ctx->tick_s = 1e-3 / khz;
     *out = ctx.release();
     return GDPM_OK;
 }
@@ -1610,12 +1609,9 @@ gdpm_status gdpm_context_destroy(gdpm_context ctx) {
     if (!ctx) return fail(GDPM_E_INVALID, "NULL context");
     (void)hipSetDevice(ctx->device);
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
-    for (auto e : ctx->events) (void)hipEventDestroy(e);
-    if (ctx->h_hdr) (void)hipHostFree(ctx->h_hdr);
-    if (ctx->host_ctl) (void)hipHostFree(ctx->host_ctl);
-    if (ctx->h_jobs) (void)hipHostFree(ctx->h_jobs);
-    if (ctx->h_segs) (void)hipHostFree(ctx->h_segs);
-    if (ctx->h_jc) (void)hipHostFree(ctx->h_jc);
+    if (ctx->mirror) (void)hipHostFree(ctx->mirror);
+    if (ctx->h_step) (void)hipHostFree(ctx->h_step);
+    if (ctx->h_maj) (void)hipHostFree(ctx->h_maj);
     if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
     if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1639,6 +1635,14 @@ gdpm_status gdpm_set_materials(gdpm_context ctx, const gdpm_material* m, int n, 
     ctx->tables.clear();
     // the table set of the default absorption energies, resident from now on
     HIP_TRY(hipSetDevice(ctx->device));
+    const size_t maj = (size_t)kMaxJobs * n_grid * sizeof(float);
+    if (ctx->maj_bytes < maj) {
+        if (ctx->h_maj) (void)hipHostFree(ctx->h_maj);
+        ctx->h_maj = nullptr;
+        ctx->maj_bytes = 0;
+        HIP_TRY(hipHostMalloc((void**)&ctx->h_maj, maj, hipHostMallocDefault));
+        ctx->maj_bytes = maj;
+    }
     DevTables* t = nullptr;
     return get_tables(ctx, 0.05, 0.2, 0u, &t);
 }

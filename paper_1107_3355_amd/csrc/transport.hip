@@ -1101,7 +1101,7 @@ GDPM_DEV void push_photons(const PendPhoton& q, PushState& ps, Args A, JobPtr J,
 GDPM_DEV uint32_t claim_size(uint32_t left, uint32_t waves, int ri) {
     return min(max(left / (2u * waves), kClaimMin), ri == 0 ? kClaimMaxPhoton : kClaimMaxElectron);
 }
-__global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int rebinned, int lone, uint32_t waves) {
+GDPM_DEV void setup_pass(Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, uint32_t waves) {
     JobCtl* jc = R.jc;
     RingCtl& r = ctl->ring[ri];
     // a permuted pass reads positions [0, n_valid) of the permutation; its
@@ -1114,15 +1114,6 @@ __global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int r
             jc->seg_count[ri][j] = j == lone ? count : 0u;
         }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        r.begin = perm ? 0u : r.head;
-        r.count = count;
-        const uint32_t claim = claim_size(count, waves, ri);
-        r.first = rebinned ? 0u : claim;
-        r.push = min(max(claim, kPushMin), kPushMax);
-        r.next_head = r.tail;
-        if (!perm) r.permuted = 0u;
-    }
     for (int j = threadIdx.x; j < R.n_jobs; j += blockDim.x)
         jc->claim[ri][j] = rebinned ? 0u : waves * claim_size(count, waves, ri);
     const int nw = (R.n_jobs + 63) >> 6;
@@ -1133,14 +1124,31 @@ __global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int r
                 if (jc->seg_count[ri][k * 64 + b] > 0u) m |= 1ull << b;
         jc->left[ri][k] = m;
     }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        r.begin = perm ? 0u : r.head;
+        r.count = count;
+        const uint32_t claim = claim_size(count, waves, ri);
+        r.first = rebinned ? 0u : claim;
+        r.push = min(max(claim, kPushMin), kPushMax);
+        r.next_head = r.tail;
+        if (!perm) r.permuted = 0u;
+    }
+}
+__global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int rebinned, int lone, uint32_t waves) {
+    setup_pass(ctl, R, ri, rebinned, lone, waves);
 }
 
-__global__ void __launch_bounds__(64) k_finish(Ctl* ctl, JobCtl* jc, int ri) {
+// completion of a pass, by the first wavefront of a workgroup; clock: the slot of
+// Ctl::ticks that its time goes to (-1: none)
+GDPM_DEV void finish_pass(Ctl* ctl, JobCtl* jc, int ri, int clock) {
+    if (threadIdx.x >= 64) return;
     if (threadIdx.x == 0) {
         RingCtl& r = ctl->ring[ri];
         r.head = r.permuted ? r.next_head : r.begin + r.count;
         r.count = 0u;
         r.permuted = 0u;
+        if (clock >= 0) ctl->ticks[clock] += wall_clock64() - ctl->t_start;
     }
     // the pass counters of the workgroups: lane i folds counter i
     unsigned long long v = 0ull;
@@ -1168,6 +1176,122 @@ __global__ void __launch_bounds__(64) k_finish(Ctl* ctl, JobCtl* jc, int ri) {
         ctl->ev[EV_PUSHES] += pushes;
         ctl->pass_ev[ri][1] += pushes + rq;
         ctl->pass_ev[ri][3] += rq;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The ends of a scheduler iteration.  An iteration is a chain of small kernels
+// around the passes, and most of a small job's time went into the gaps between
+// them: copies to and from the host, timing events (6 us on either side of a
+// pass), set-up and completion apart.  The first kernel reads the iteration's
+// source segments from pinned host memory, the last writes the counters there
+// and then the iteration's number, which the host waits for.
+// ---------------------------------------------------------------------------
+// what is written here is read by the passes' kernels, or by the host
+GDPM_DEV void host_store(unsigned long long* p, unsigned long long v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// a value this kernel may have just changed
+GDPM_DEV unsigned long long fresh(const unsigned long long* p) {
+    return __hip_atomic_load(const_cast<unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// setup: bit ri set: also set up pass ri (a pass that is not re-binned first)
+__global__ void __launch_bounds__(256) k_begin(Ctl* ctl, RunDev R, const StepHost* h, SrcHdr* hdr, SrcSeg* segs,
+                                               int setup, int lone, uint32_t waves0, uint32_t waves1) {
+    __shared__ uint32_t n[2];
+    if (threadIdx.x < 2) {
+        const int ri = threadIdx.x;
+        SrcHdr d = h->hdr[ri];
+        n[ri] = d.nseg;
+        RingCtl& r = ctl->ring[ri];
+        // the records are part of the queue from here on; the source kernels
+        // write them at [base, base + total)
+        d.base = r.tail;
+        if (d.total) {
+            if (r.tail + d.total - r.head > R.hard[ri]) atomicOr(&ctl->overflow, 1u);
+            else r.tail += d.total;
+        }
+        hdr[ri] = d;
+    }
+    __syncthreads();
+    constexpr int kCap = kMaxSegs / 2, kWords = sizeof(SrcSeg) / 8;
+    static_assert(sizeof(SrcSeg) % 8 == 0, "copied in 8-byte words");
+    for (int ri = 0; ri < 2; ++ri) {
+        const unsigned long long* q = reinterpret_cast<const unsigned long long*>(h->segs + ri * kCap);
+        unsigned long long* d = reinterpret_cast<unsigned long long*>(segs + ri * kCap);
+        for (uint32_t i = threadIdx.x; i < n[ri] * kWords; i += blockDim.x) d[i] = q[i];
+    }
+    if (setup & 1) setup_pass(ctl, R, 0, 0, lone, waves0);
+    if (setup & 2) setup_pass(ctl, R, 1, 0, lone, waves1);
+}
+
+// between the passes: completion of the photon pass, set-up of the electron pass
+__global__ void __launch_bounds__(256) k_mid(Ctl* ctl, RunDev R, int setup, int lone, uint32_t waves) {
+    finish_pass(ctl, R.jc, 0, 0);
+    if (setup) setup_pass(ctl, R, 1, 0, lone, waves);
+}
+
+// the end of an iteration; fused: one launch ran both passes
+__global__ void __launch_bounds__(256) k_end(Ctl* ctl, RunDev R, const StepHost* h, StepMirror* out, int fused) {
+    if (fused) finish_pass(ctl, R.jc, 0, 2);
+    finish_pass(ctl, R.jc, 1, fused ? -1 : 1);
+    __threadfence();
+    __syncthreads();
+    static_assert(sizeof(Ctl) % 8 == 0, "copied in 8-byte words");
+    const unsigned long long* c = reinterpret_cast<const unsigned long long*>(ctl);
+    unsigned long long* o = reinterpret_cast<unsigned long long*>(&out->ctl);
+    for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 8; i += blockDim.x) host_store(o + i, fresh(c + i));
+    const JobCtl* jc = R.jc;
+    for (int j = threadIdx.x; j < R.n_jobs; j += blockDim.x) {
+        host_store(&out->births[j], jc->births[j]);
+        host_store(&out->deaths[j], jc->deaths[j]);
+        host_store(reinterpret_cast<unsigned long long*>(&out->e_in[j]), __double_as_longlong(jc->e_in[j]));
+        host_store(reinterpret_cast<unsigned long long*>(&out->e_esc[j]), __double_as_longlong(jc->e_esc[j]));
+    }
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&out->seq, h->seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// the control blocks at the start of a run (queues empty, at position `start`)
+__global__ void __launch_bounds__(1024) k_init(Ctl* ctl, JobCtl* jc, StatsDev* stats, uint32_t start) {
+    uint32_t* c = reinterpret_cast<uint32_t*>(ctl);
+    for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += blockDim.x) c[i] = 0u;
+    uint32_t* q = reinterpret_cast<uint32_t*>(jc);
+    for (uint32_t i = threadIdx.x; i < sizeof(JobCtl) / 4; i += blockDim.x) q[i] = 0u;
+    uint32_t* t = reinterpret_cast<uint32_t*>(stats);
+    for (uint32_t i = threadIdx.x; i < offsetof(StatsDev, inv_n) / 4; i += blockDim.x) t[i] = 0u;
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        RingCtl& r = ctl->ring[threadIdx.x];
+        r.head = r.tail = r.begin = start;
+    }
+}
+
+// a job enters slot `slot`: its description, its majorant (from pinned host
+// memory), zero counters and tallies
+struct AdmitArgs {
+    JobDev job;
+    JobDev* jobs;
+    JobCtl* jc;
+    const float* majorant;   // pinned host memory, n_grid values
+    float* mumax;
+    size_t n_tally, n_hist;  // doubles
+    int slot, n_grid;
+};
+__global__ void __launch_bounds__(256) k_admit(AdmitArgs a) {
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x, n = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = t; i < (size_t)a.n_grid; i += n) a.mumax[i] = a.majorant[i];
+    double2* q = reinterpret_cast<double2*>(a.job.tally);   // (at least 256-byte aligned)
+    for (size_t i = t; i < a.n_tally / 2; i += n) q[i] = make_double2(0.0, 0.0);
+    if (t == 0 && (a.n_tally & 1)) a.job.tally[a.n_tally - 1] = 0.0;
+    for (size_t i = t; i < a.n_hist; i += n) a.job.hist[i] = 0.0;
+    if (t == 0) {
+        a.jobs[a.slot] = a.job;
+        a.jc->births[a.slot] = a.jc->deaths[a.slot] = 0ull;
+        a.jc->e_in[a.slot] = a.jc->e_esc[a.slot] = 0.0;
     }
 }
 
@@ -1342,13 +1466,7 @@ __global__ void __launch_bounds__(256) k_source(Ctl* ctl, RunDev R, const SrcSeg
     __shared__ double sh[4];
     if (ctl->overflow) return;
     const int nseg = (int)__builtin_amdgcn_readfirstlane(hdr->nseg);
-    const uint32_t total = __builtin_amdgcn_readfirstlane(hdr->total);
-    const RingCtl& r = ctl->ring[ri];
-    const uint32_t tail = r.tail;
-    if (tail + total - r.head > R.hard[ri]) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&ctl->overflow, 1u);
-        return;
-    }
+    const uint32_t tail = __builtin_amdgcn_readfirstlane(hdr->base);
     Particle* buf = R.buf[ri];
     const uint32_t nthreads = gridDim.x * blockDim.x;
     const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1423,12 +1541,6 @@ __global__ void __launch_bounds__(256) k_source(Ctl* ctl, RunDev R, const SrcSeg
     }
 }
 
-// make the records written by the source pass part of the queue
-__global__ void k_commit(Ctl* ctl, int ri, const SrcHdr* hdr) {
-    if (ctl->overflow) return;
-    ctl->ring[ri].tail += hdr->total;
-}
-
 // ---------------------------------------------------------------------------
 // LDS of a transport workgroup
 // ---------------------------------------------------------------------------
@@ -1448,6 +1560,11 @@ GDPM_HD uint32_t tables_f4(int ri, const TT& T) {
     return (floats + 3u) / 4u;
 }
 constexpr uint32_t kSliceF4 = 4u * kStage + kRingF4;
+
+// the device clock at the start of a pass (its completion takes the difference)
+GDPM_DEV void start_clock(Args A) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) global_ptr(A->ctl)->t_start = wall_clock64();
+}
 
 // a workgroup none of whose wavefronts has a record to start with: it ends
 // before it stages the tables (nothing is left to claim either)
@@ -1711,6 +1828,7 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
 template <bool kLds, bool kSolo, bool kPerm>
 __global__ void __launch_bounds__(768) k_photon(PassArgs) {
     const Args A = pass_args();
+    start_clock(A);
     if (!kPerm && group_idle(A, 0)) return;
     const GroupPtr group = (GroupPtr)lds_tables;
     GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables + kGroupTallyF4;
@@ -2077,6 +2195,7 @@ GDPM_DEV ElecLds stage_electron_tables(const GDPM_CONST Tables& T, GDPM_LDS f4* 
 template <bool kLds, bool kSolo, bool kPerm>
 __global__ void __launch_bounds__(768) k_electron(PassArgs) {
     const Args A = pass_args();
+    start_clock(A);
     if (!kPerm && group_idle(A, 1)) return;
     const GroupPtr group = (GroupPtr)lds_tables;
     GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables + kGroupTallyF4;
@@ -2109,6 +2228,7 @@ __global__ void __launch_bounds__(768) k_electron(PassArgs) {
 template <bool kPerm>
 __global__ void __launch_bounds__(768) k_transport(PassArgs) {
     const Args A = pass_args();
+    start_clock(A);
     const GroupPtr group = (GroupPtr)lds_tables;
     GDPM_LDS f4* lds = (GDPM_LDS f4*)lds_tables + kGroupTallyF4;
     group_clear(group);
@@ -2336,17 +2456,25 @@ GDPM_DEV void voxel_stats(int nb, F d, double& mean, double& s2) {
     }
 }
 
-// red: {energy deposited, sum of sigma, voxels counted, -, bits of D_max}, zero at the start
-__global__ void __launch_bounds__(kStatThreads) k_dose_stats(StatsDev* red, const double* slots, size_t nvox, int nb,
-                                                             const uint32_t* vox, double vvox, float min_rho,
-                                                             double* dose, double* sigma) {
+typedef const GDPM_CONST StatsArgs* StatsPtr;
+
+// The arguments are read through the kernel-argument segment (the batches'
+// normalisation is indexed there).
+__global__ void __launch_bounds__(kStatThreads) k_dose_stats(StatsArgs) {
+    const StatsPtr A = (StatsPtr)__builtin_amdgcn_kernarg_segment_ptr();
     constexpr int kHeld = 10;   // batches whose energies stay in registers between the two sums
+    const GDPM_GLOBAL double* slots = global_ptr(A->slots);
+    const GDPM_GLOBAL uint32_t* vox = global_ptr(A->vox);
+    GDPM_GLOBAL double* dose = global_ptr(A->dose);
+    GDPM_GLOBAL double* sigma = global_ptr(A->sigma);
+    const size_t nvox = A->nvox;
+    const int nb = A->nb;
+    const double min_rho = (double)A->min_rho;
     double emax = 0.0, edep = 0.0, none = 0.0;
-    const double* inv_n = red->inv_n;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox;
          i += (size_t)gridDim.x * blockDim.x) {
         const double rho = (double)voxel_density(vox[i]);
-        const double im = 1.0 / (rho * vvox);
+        const double im = 1.0 / (rho * A->vvox);
         double mean, s2;
         if (nb == kHeld) {
             double eb[kHeld];
@@ -2356,24 +2484,30 @@ __global__ void __launch_bounds__(kStatThreads) k_dose_stats(StatsDev* red, cons
             for (int b = 0; b < kHeld; ++b) edep += eb[b];
             double s = 0.0;
 #pragma unroll
-            for (int b = 0; b < kHeld; ++b) s += eb[b] * im * inv_n[b];
+            for (int b = 0; b < kHeld; ++b) s += eb[b] * im * A->inv_n[b];
             mean = s / kHeld;
             s2 = 0.0;
 #pragma unroll
             for (int b = 0; b < kHeld; ++b) {
-                const double x = eb[b] * im * inv_n[b] - mean;
+                const double x = eb[b] * im * A->inv_n[b] - mean;
                 s2 += x * x;
             }
         } else {
             for (int b = 0; b < nb; ++b) edep += slots[(size_t)b * nvox + i];
-            voxel_stats(nb, [&](int b) { return slots[(size_t)b * nvox + i] * im * inv_n[b]; }, mean, s2);
+            if (nb <= kArgBatches) {
+                voxel_stats(nb, [&](int b) { return slots[(size_t)b * nvox + i] * im * A->inv_n[b]; }, mean, s2);
+            } else {
+                const GDPM_GLOBAL double* inv = (const GDPM_GLOBAL double*)A->red->inv_n;
+                voxel_stats(nb, [&](int b) { return slots[(size_t)b * nvox + i] * im * inv[b]; }, mean, s2);
+            }
         }
         if (dose) dose[i] = mean;
         if (sigma) sigma[i] = nb > 1 ? sqrt(s2 / ((double)nb * (nb - 1))) : 0.0;
-        if (rho >= (double)min_rho) emax = fmax(emax, mean);
+        if (rho >= min_rho) emax = fmax(emax, mean);
     }
     block_reduce(edep, none, emax);
     if (threadIdx.x == 0) {
+        StatsDev* red = A->red;
         unsafeAtomicAdd(&red->e_dep, edep);
         atomicMax(&red->dmax_bits, (unsigned long long)__double_as_longlong(emax));
     }
@@ -2396,6 +2530,18 @@ __global__ void __launch_bounds__(kStatThreads) k_unc(StatsDev* red, const doubl
         unsafeAtomicAdd(&red->sigma_sum, s);
         unsafeAtomicAdd(&red->count, c);
     }
+}
+
+// the reductions to the host (pinned memory, `seq` last), and zero again
+__global__ void k_stats_end(StatsDev* red, StatsDev* out, uint32_t seq) {
+    static_assert(offsetof(StatsDev, seq) == 32, "four 8-byte reductions");
+    unsigned long long* r = reinterpret_cast<unsigned long long*>(red);
+    unsigned long long* o = reinterpret_cast<unsigned long long*>(out);
+    for (int i = 0; i < 4; ++i) {
+        host_store(o + i, r[i]);
+        r[i] = 0ull;
+    }
+    __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------------------
@@ -2534,11 +2680,31 @@ hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int r
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
                          const SrcHdr* hdr, int ri) {
     hipLaunchKernelGGL(k_source, dim3(blocks), dim3(256), 0, st, ctl, R, segs, hdr, ri);
-    hipLaunchKernelGGL(k_commit, dim3(1), dim3(1), 0, st, ctl, ri, hdr);
     return hipGetLastError();
 }
-hipError_t launch_finish(hipStream_t st, Ctl* ctl, JobCtl* jc, int ri) {
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, st, ctl, jc, ri);
+hipError_t launch_begin(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, SrcHdr* hdr, SrcSeg* segs,
+                        int setup, int lone, int waves0, int waves1) {
+    hipLaunchKernelGGL(k_begin, dim3(1), dim3(256), 0, st, ctl, R, h, hdr, segs, setup, lone, (uint32_t)waves0,
+                       (uint32_t)waves1);
+    return hipGetLastError();
+}
+hipError_t launch_mid(hipStream_t st, Ctl* ctl, const RunDev& R, int setup, int lone, int waves) {
+    hipLaunchKernelGGL(k_mid, dim3(1), dim3(256), 0, st, ctl, R, setup, lone, (uint32_t)waves);
+    return hipGetLastError();
+}
+hipError_t launch_end(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, StepMirror* out, int fused) {
+    hipLaunchKernelGGL(k_end, dim3(1), dim3(256), 0, st, ctl, R, h, out, fused);
+    return hipGetLastError();
+}
+hipError_t launch_init(hipStream_t st, Ctl* ctl, JobCtl* jc, StatsDev* stats, uint32_t start) {
+    hipLaunchKernelGGL(k_init, dim3(1), dim3(1024), 0, st, ctl, jc, stats, start);
+    return hipGetLastError();
+}
+hipError_t launch_admit(hipStream_t st, int cus, const JobDev& job, JobDev* jobs, JobCtl* jc, const float* majorant,
+                        float* mumax, size_t n_tally, size_t n_hist, int slot, int n_grid) {
+    const AdmitArgs a{job, jobs, jc, majorant, mumax, n_tally, n_hist, slot, n_grid};
+    const size_t need = (n_tally + n_hist + 2047) / 2048 + 1;
+    hipLaunchKernelGGL(k_admit, dim3((unsigned)(need < (size_t)(8 * cus) ? need : (size_t)(8 * cus))), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 // LDS bytes of a pass with `waves` wavefronts per block (`lds`: tables and
@@ -2629,15 +2795,13 @@ hipError_t launch_count_records(hipStream_t st, int blocks, const Ctl* ctl, cons
     hipLaunchKernelGGL(k_count_records, dim3(blocks), dim3(256), 0, st, ctl, R, counts);
     return hipGetLastError();
 }
-// red: inv_n set, the reductions zero
-hipError_t launch_stats(hipStream_t st, int cus, StatsDev* red, const double* slots, size_t nvox, int nb,
-                        const uint32_t* vox, double vvox, float min_rho, double* dose, double* sigma) {
-    const size_t need = (nvox + kStatThreads - 1) / kStatThreads;
+hipError_t launch_stats(hipStream_t st, int cus, const StatsArgs& a, StatsDev* out, uint32_t seq) {
+    const size_t need = (a.nvox + kStatThreads - 1) / kStatThreads;
     const int blocks = (int)(need < (size_t)(2 * cus) ? need : (size_t)(2 * cus));
-    hipLaunchKernelGGL(k_dose_stats, dim3(blocks), dim3(kStatThreads), 0, st, red, slots, nvox, nb, vox, vvox, min_rho,
-                       dose, sigma);
-    hipLaunchKernelGGL(k_unc, dim3(blocks), dim3(kStatThreads), 0, st, red, (const double*)dose, (const double*)sigma,
-                       vox, min_rho, nvox);
+    hipLaunchKernelGGL(k_dose_stats, dim3(blocks), dim3(kStatThreads), 0, st, a);
+    hipLaunchKernelGGL(k_unc, dim3(blocks), dim3(kStatThreads), 0, st, a.red, (const double*)a.dose,
+                       (const double*)a.sigma, a.vox, a.min_rho, a.nvox);
+    hipLaunchKernelGGL(k_stats_end, dim3(1), dim3(1), 0, st, a.red, out, seq);
     return hipGetLastError();
 }
 hipError_t launch_test_philox(hipStream_t st, uint32_t k0, uint32_t k1, const uint4* ctr, uint4* out,
