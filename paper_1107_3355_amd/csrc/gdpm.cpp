@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -19,6 +20,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <list>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -154,6 +156,109 @@ struct DevBuf {
     hipError_t ensure(size_t n) { return n <= bytes ? hipSuccess : alloc(n); }
     template <class T>
     T* as() const { return static_cast<T*>(p); }
+};
+
+// Device memory of jobs (tallies, outputs, majorants, chains) kept between jobs:
+// a job's hipMalloc and hipFree calls took 150 us of a small job and 10 ms of a
+// batch of 24.  A block comes back when the job's buffers go, after the job's
+// stream has been waited for; at most kMaxHeld bytes are kept, the oldest blocks
+// go first, and all go when the context or a server ends or memory runs out.
+// Jobs of a server end on the server's thread and are released on the caller's,
+// hence the lock.
+struct DevPool {
+    static constexpr size_t kMaxHeld = (size_t)2 << 30;
+    struct Block {
+        void* p;
+        size_t bytes;
+    };
+    std::mutex m;
+    std::list<Block> blocks;   // oldest first
+    size_t held = 0;
+    bool closed = false;
+    ~DevPool() { trim(); }
+    void trim() {
+        std::lock_guard<std::mutex> lk(m);
+        for (auto& b : blocks) (void)hipFree(b.p);
+        blocks.clear();
+        held = 0;
+    }
+    void close() {
+        trim();
+        std::lock_guard<std::mutex> lk(m);
+        closed = true;
+    }
+    // the smallest kept block of n to 2 n bytes (a megabyte more for small
+    // ones), or a new one
+    hipError_t take(size_t n, Block* out) {
+        const size_t grain = n > ((size_t)1 << 20) ? (size_t)1 << 16 : 4096;
+        n = (std::max<size_t>(n, 1) + grain - 1) / grain * grain;
+        {
+            std::lock_guard<std::mutex> lk(m);
+            auto best = blocks.end();
+            for (auto it = blocks.begin(); it != blocks.end(); ++it)
+                if (it->bytes >= n && it->bytes <= 2 * n + ((size_t)1 << 20) &&
+                    (best == blocks.end() || it->bytes < best->bytes))
+                    best = it;
+            if (best != blocks.end()) {
+                *out = *best;
+                held -= best->bytes;
+                blocks.erase(best);
+                return hipSuccess;
+            }
+        }
+        out->bytes = n;
+        hipError_t e = hipMalloc(&out->p, n);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            trim();
+            e = hipMalloc(&out->p, n);
+        }
+        if (e != hipSuccess) *out = Block{nullptr, 0};
+        return e;
+    }
+    void give(Block b) {
+        std::lock_guard<std::mutex> lk(m);
+        if (closed || b.bytes > kMaxHeld) {
+            (void)hipFree(b.p);
+            return;
+        }
+        while (held + b.bytes > kMaxHeld) {
+            held -= blocks.front().bytes;
+            (void)hipFree(blocks.front().p);
+            blocks.pop_front();
+        }
+        held += b.bytes;
+        blocks.push_back(b);
+    }
+    size_t held_bytes() {
+        std::lock_guard<std::mutex> lk(m);
+        return held;
+    }
+};
+
+// a job's buffer out of the pool
+struct PoolBuf {
+    std::shared_ptr<DevPool> pool;
+    DevPool::Block b{nullptr, 0};
+    size_t bytes = 0;   // as asked for
+    PoolBuf() = default;
+    PoolBuf(const PoolBuf&) = delete;
+    PoolBuf& operator=(const PoolBuf&) = delete;
+    ~PoolBuf() { reset(); }
+    void reset() {
+        if (b.p) pool->give(b);
+        b = DevPool::Block{nullptr, 0};
+        bytes = 0;
+    }
+    hipError_t alloc(const std::shared_ptr<DevPool>& from, size_t n) {
+        reset();
+        pool = from;
+        const hipError_t e = pool->take(n, &b);
+        if (e == hipSuccess) bytes = n;
+        return e;
+    }
+    template <class T>
+    T* as() const { return static_cast<T*>(b.p); }
 };
 
 template <class T>
@@ -296,6 +401,10 @@ struct gdpm_context_s {
     size_t maj_bytes = 0;
     uint32_t seq = 0;               // iterations and statistics, numbered
     double tick_s = 1e-8;           // period of the device clock
+    std::shared_ptr<DevPool> pool = std::make_shared<DevPool>();   // jobs' device memory
+    void* out_ring = nullptr;       // pinned: outputs on their way to host arrays
+    size_t out_chunks = 0;          // (chunks it holds)
+    std::vector<hipEvent_t> out_events;
     double resident_bytes = 0.0;   // phantoms and sources alive in the context
     unsigned char* scratch = nullptr;  // this device's scratch array (gdpm_run_noalloc)
     // the autotuner's latest record: candidates, mean scores, the one kept (-1: undecided)
@@ -537,8 +646,8 @@ struct EJob {
     RunPlan plan{};
     int slot = -1;
     size_t nv = 0;
-    DevBuf tally, mumax, hist, dose_buf, sigma_buf;
-    DevBuf chains;               // Metropolis chain states of the job's source
+    PoolBuf tally, mumax, hist, dose_buf, sigma_buf;
+    PoolBuf chains;              // Metropolis chain states of the job's source
     // the job's device arrays: set by admit() from the buffers above, or given
     // beforehand (an engine on fixed memory)
     double* tally_p = nullptr;
@@ -753,21 +862,21 @@ gdpm_status Engine::admit(EJob* j) {
     if (M.fixed && (!j->mumax_p || !j->tally_p || !j->d_dose || !j->d_sigma))
         return fail(GDPM_E_INVALID, "a job of an engine on fixed memory needs its arrays given");
     if (!j->mumax_p) {
-        HIP_TRY(j->mumax.alloc(mm.size() * sizeof(float)));
+        HIP_TRY(j->mumax.alloc(ctx->pool, mm.size() * sizeof(float)));
         j->mumax_p = j->mumax.as<float>();
     }
     float* hm = ctx->h_maj + (size_t)slot * mm.size();
     std::copy(mm.begin(), mm.end(), hm);
     if (!j->tally_p) {
-        HIP_TRY(j->tally.alloc((size_t)plan.nb * nv * sizeof(double)));
+        HIP_TRY(j->tally.alloc(ctx->pool, (size_t)plan.nb * nv * sizeof(double)));
         j->tally_p = j->tally.as<double>();
     }
     if (!j->d_dose) {
-        HIP_TRY(j->dose_buf.alloc(nv * sizeof(double)));
+        HIP_TRY(j->dose_buf.alloc(ctx->pool, nv * sizeof(double)));
         j->d_dose = j->dose_buf.as<double>();
     }
     if (!j->d_sigma) {
-        HIP_TRY(j->sigma_buf.alloc(nv * sizeof(double)));
+        HIP_TRY(j->sigma_buf.alloc(ctx->pool, nv * sizeof(double)));
         j->d_sigma = j->sigma_buf.as<double>();
     }
     double* hist = nullptr;
@@ -793,7 +902,7 @@ gdpm_status Engine::admit(EJob* j) {
         // the job's Metropolis chains start afresh at its first history
         if (!j->chains_p) {
             if (M.fixed) return fail(GDPM_E_INVALID, "a job of an engine on fixed memory needs its chain states given");
-            HIP_TRY(j->chains.alloc(kMetroChains * sizeof(uint32_t)));
+            HIP_TRY(j->chains.alloc(ctx->pool, kMetroChains * sizeof(uint32_t)));
             j->chains_p = j->chains.as<uint32_t>();
         }
         HIP_TRY(launch_metro_init(st, d.S, d.k0, d.k1, j->chains_p));
@@ -821,6 +930,108 @@ gdpm_status Engine::admit(EJob* j) {
     slots[slot] = j;
     n_slots = std::max(n_slots, slot + 1);
     return GDPM_OK;
+}
+
+// One host array to fill from device memory.
+struct OutCopy {
+    double* dst;
+    const double* src;
+    size_t bytes;
+};
+constexpr size_t kOutChunk = (size_t)1 << 20;
+constexpr size_t kOutChunks = 32;   // chunks in flight, at most
+
+// Copy outputs to the caller's host arrays; complete on return.  The device
+// writes chunks to pinned memory and a few host threads copy them on: a copy
+// straight to pageable memory is one thread's work, and mostly the page faults of
+// arrays that were never written (13 GB/s at best, 10 ms of a batch of 24 jobs).
+gdpm_status copy_out(gdpm_context ctx, hipStream_t st, const std::vector<OutCopy>& list) {
+    struct Chunk {
+        char* dst;
+        const char* src;
+        size_t n;
+    };
+    std::vector<Chunk> chunks;
+    for (const OutCopy& c : list)
+        for (size_t o = 0; o < c.bytes; o += kOutChunk)
+            chunks.push_back(Chunk{(char*)c.dst + o, (const char*)c.src + o, std::min(kOutChunk, c.bytes - o)});
+    if (chunks.empty()) return GDPM_OK;
+    if (ctx->out_chunks < std::min(chunks.size(), kOutChunks)) {
+        const size_t cap = std::min(chunks.size(), kOutChunks);
+        if (ctx->out_ring) (void)hipHostFree(ctx->out_ring);
+        ctx->out_ring = nullptr;
+        ctx->out_chunks = 0;
+        HIP_TRY(hipHostMalloc(&ctx->out_ring, kOutChunk * cap, hipHostMallocDefault));
+        ctx->out_chunks = cap;
+        while (ctx->out_events.size() < cap) {
+            hipEvent_t e;
+            HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            ctx->out_events.push_back(e);
+        }
+    }
+    const size_t cap = ctx->out_chunks;
+    const size_t n = chunks.size();
+    std::atomic<size_t> issued{0}, next{0};
+    std::vector<std::atomic<bool>> copied(n);
+    for (auto& c : copied) c = false;
+    std::atomic<int> error{0};
+    auto slot = [&](size_t i) { return (char*)ctx->out_ring + (i % cap) * kOutChunk; };
+    // takes the chunks in order, each once it has been issued and has arrived
+    auto work = [&] {
+        (void)hipSetDevice(ctx->device);
+        for (size_t i; (i = next.fetch_add(1)) < n;) {
+            while (issued.load(std::memory_order_acquire) <= i && !error.load()) std::this_thread::yield();
+            if (error.load()) return;
+            const hipError_t e = hipEventSynchronize(ctx->out_events[i % cap]);
+            if (e != hipSuccess) {
+                error = (int)e;
+                return;
+            }
+            memcpy(chunks[i].dst, slot(i), chunks[i].n);
+            copied[i].store(true, std::memory_order_release);
+        }
+    };
+    // a thread for every four chunks, up to six beside this one
+    std::vector<std::thread> threads;
+    const size_t want = std::min<size_t>({6, n / 4, std::thread::hardware_concurrency() / 2});
+    try {
+        threads.reserve(want);
+        while (threads.size() < want) threads.emplace_back(work);
+    } catch (...) {   // with fewer threads, then
+    }
+    for (size_t i = 0; i < n && !error.load(); ++i) {
+        if (i >= cap) {
+            // the slot's last chunk must have been copied on
+            if (threads.empty()) {
+                issued.store(i, std::memory_order_release);
+                while (next.load() < i) {   // this thread does it
+                    const size_t c = next.fetch_add(1);
+                    const hipError_t e = hipEventSynchronize(ctx->out_events[c % cap]);
+                    if (e != hipSuccess) error = (int)e;
+                    if (error.load()) break;
+                    memcpy(chunks[c].dst, slot(c), chunks[c].n);
+                    copied[c] = true;
+                }
+            }
+            while (!copied[i - cap].load(std::memory_order_acquire) && !error.load()) std::this_thread::yield();
+            if (error.load()) break;
+        }
+        hipError_t e = hipMemcpyAsync(slot(i), chunks[i].src, chunks[i].n, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipEventRecord(ctx->out_events[i % cap], st);
+        if (e != hipSuccess) error = (int)e;
+        issued.store(i + 1, std::memory_order_release);
+    }
+    work();
+    for (auto& t : threads) t.join();
+    if (error.load())
+        return fail(GDPM_E_DEVICE, "copying the outputs: %s", hipGetErrorString((hipError_t)error.load()));
+    return GDPM_OK;
+}
+
+// a finished job's outputs into host arrays (either may be null)
+void add_outputs(std::vector<OutCopy>& list, const EJob* j, double* dose, double* sigma) {
+    if (dose) list.push_back(OutCopy{dose, j->d_dose, j->nv * sizeof(double)});
+    if (sigma) list.push_back(OutCopy{sigma, j->d_sigma, j->nv * sizeof(double)});
 }
 
 void Engine::release(EJob* j) {
@@ -1289,7 +1500,6 @@ gdpm_status make_job(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const g
     return GDPM_OK;
 }
 
-// one job through the engine, blocking; outputs stay in device memory
 // the scratch array carved into the engine's memory and one job's arrays
 // (see kScratchBytes); false if the job's batch tallies do not fit
 bool scratch_layout(unsigned char* base, EJob* j, EngineMem* M) {
@@ -1324,13 +1534,10 @@ bool scratch_layout(unsigned char* base, EJob* j, EngineMem* M) {
 // one job through the engine, blocking; outputs stay in device memory.  With
 // `scr` (this device's scratch array) the engine's queues, control blocks and
 // the job's arrays live there and nothing is allocated.
-gdpm_status do_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdpm_run_params* prm,
-                   double* d_dose, double* d_sigma, double* h_batch, double* h_hist,
-                   hipStream_t st, gdpm_run_stats* out, EJob* keep, unsigned char* scr = nullptr) {
+gdpm_status run_job(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdpm_run_params* prm,
+                    double* d_dose, double* d_sigma, double* h_batch, double* h_hist,
+                    hipStream_t st, gdpm_run_stats* out, EJob* j, unsigned char* scr) {
     const double t_start = now_s();
-    if (!ctx) return fail(GDPM_E_INVALID, "NULL context");
-    EJob local;
-    EJob* j = keep ? keep : &local;
     gdpm_status s = make_job(ctx, ph, src, prm, j);
     if (s) return s;
     if (h_hist && (j->plan.target || j->plan.n_hist > ((uint64_t)1 << 24)))
@@ -1347,7 +1554,7 @@ gdpm_status do_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdp
                         "of the scratch memory", (size_t)j->plan.nb * j->nv * sizeof(double), j->plan.nb,
                         j->nv, kScratchTallyBytes);
     }
-    if (h_hist) HIP_TRY(j->hist.alloc(j->plan.n_hist * 2 * sizeof(double)));
+    if (h_hist) HIP_TRY(j->hist.alloc(ctx->pool, j->plan.n_hist * 2 * sizeof(double)));
     Engine E;
     s = E.init(ctx, st, j->plan, scr ? &sm : nullptr);
     if (s) return s;
@@ -1364,7 +1571,7 @@ gdpm_status do_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdp
         HIP_TRY(hipMemcpyAsync(h_batch, j->tally_p, (size_t)j->plan.nb * nv * sizeof(double),
                                hipMemcpyDeviceToHost, st));
     if (h_hist)
-        HIP_TRY(hipMemcpyAsync(h_hist, j->hist.p, j->plan.n_hist * 2 * sizeof(double),
+        HIP_TRY(hipMemcpyAsync(h_hist, j->hist.as<void>(), j->plan.n_hist * 2 * sizeof(double),
                                hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (j->plan.split) {
@@ -1378,6 +1585,31 @@ gdpm_status do_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdp
     E.release(j);
     if (j->status == GDPM_E_NOT_CONVERGED) fail(GDPM_E_NOT_CONVERGED, "%s", j->err.c_str());
     return j->status;
+}
+
+// the same with the job's memory back in the pool; the device has finished with
+// it then, whatever the outcome.  h_dose, h_sigma: host outputs (either may be
+// null)
+gdpm_status do_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdpm_run_params* prm,
+                   double* d_dose, double* d_sigma, double* h_dose, double* h_sigma, double* h_batch,
+                   double* h_hist, hipStream_t st, gdpm_run_stats* out, unsigned char* scr = nullptr) {
+    if (!ctx) return fail(GDPM_E_INVALID, "NULL context");
+    EJob job;
+    gdpm_status s = run_job(ctx, ph, src, prm, d_dose, d_sigma, h_batch, h_hist, st, out, &job, scr);
+    const std::string msg = g_err;
+    if (s == GDPM_OK || s == GDPM_E_NOT_CONVERGED) {
+        std::vector<OutCopy> list;
+        add_outputs(list, &job, h_dose, h_sigma);
+        const gdpm_status c = copy_out(ctx, st, list);
+        if (c) {
+            (void)hipStreamSynchronize(st);
+            return c;
+        }
+    } else {
+        (void)hipStreamSynchronize(st);
+    }
+    g_err = msg;
+    return s;
 }
 
 }  // namespace
@@ -1468,7 +1700,10 @@ void gdpm_server_s::loop() {
             running.push_back(job);
         }
         if (running.empty()) {
-            if (stop && pending.empty()) break;
+            if (stop && pending.empty()) {
+                ctx->pool->trim();
+                break;
+            }
             cv_work.wait(lk, [&] { return stop || !pending.empty(); });
             continue;
         }
@@ -1479,6 +1714,7 @@ void gdpm_server_s::loop() {
         if (s) {
             // a device error or an overflow ends every running job
             const std::string msg = g_err;
+            (void)hipStreamSynchronize(st);
             for (gdpm_job_s* job : running) {
                 E.release(job->ej.get());
                 finish_server_job(this, job, s, msg);
@@ -1488,6 +1724,10 @@ void gdpm_server_s::loop() {
             ready = false;
             continue;
         }
+        std::vector<OutCopy> list;
+        for (gdpm_job_s* job : running)
+            if (job->ej->done) add_outputs(list, job->ej.get(), job->dose, job->sigma);
+        const gdpm_status cs = copy_out(ctx, st, list);
         for (size_t i = 0; i < running.size();) {
             gdpm_job_s* job = running[i];
             EJob* j = job->ej.get();
@@ -1495,14 +1735,6 @@ void gdpm_server_s::loop() {
                 ++i;
                 continue;
             }
-            gdpm_status cs = GDPM_OK;
-            if (job->dose && hipMemcpyAsync(job->dose, j->d_dose, j->nv * sizeof(double),
-                                            hipMemcpyDeviceToHost, st) != hipSuccess)
-                cs = GDPM_E_DEVICE;
-            if (job->sigma && hipMemcpyAsync(job->sigma, j->d_sigma, j->nv * sizeof(double),
-                                             hipMemcpyDeviceToHost, st) != hipSuccess)
-                cs = GDPM_E_DEVICE;
-            if (hipStreamSynchronize(st) != hipSuccess) cs = GDPM_E_DEVICE;
             fill_stats(E, j, j->t_submit, &job->stats);
             E.release(j);
             j->tally.reset();
@@ -1612,6 +1844,9 @@ gdpm_status gdpm_context_destroy(gdpm_context ctx) {
     if (ctx->mirror) (void)hipHostFree(ctx->mirror);
     if (ctx->h_step) (void)hipHostFree(ctx->h_step);
     if (ctx->h_maj) (void)hipHostFree(ctx->h_maj);
+    if (ctx->out_ring) (void)hipHostFree(ctx->out_ring);
+    for (auto e : ctx->out_events) (void)hipEventDestroy(e);
+    ctx->pool->close();
     if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
     if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1911,15 +2146,9 @@ gdpm_status gdpm_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const g
     if (ctx->busy) return fail(GDPM_E_BUSY, "context busy");
     HIP_TRY(hipSetDevice(ctx->device));
     ctx->busy = true;
-    EJob job;
-    gdpm_status s = do_run(ctx, ph, src, prm, nullptr, nullptr, batch_edep, hist_out, ctx->stream,
-                           stats, &job);
+    const gdpm_status s = do_run(ctx, ph, src, prm, nullptr, nullptr, dose, sigma, batch_edep, hist_out, ctx->stream,
+                                 stats);
     ctx->busy = false;
-    if (s != GDPM_OK && s != GDPM_E_NOT_CONVERGED) return s;
-    const std::string msg = g_err;
-    if (dose) HIP_TRY(hipMemcpy(dose, job.d_dose, job.nv * sizeof(double), hipMemcpyDeviceToHost));
-    if (sigma) HIP_TRY(hipMemcpy(sigma, job.d_sigma, job.nv * sizeof(double), hipMemcpyDeviceToHost));
-    g_err = msg;
     return s;
 }
 
@@ -1935,7 +2164,7 @@ gdpm_status gdpm_run_async(gdpm_context ctx, gdpm_phantom ph, gdpm_source src,
     memset(&job->stats, 0, sizeof job->stats);
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     ctx->busy = true;
-    job->status = do_run(ctx, ph, src, prm, d_dose, d_sigma, nullptr, nullptr, st, &job->stats, nullptr);
+    job->status = do_run(ctx, ph, src, prm, d_dose, d_sigma, nullptr, nullptr, nullptr, nullptr, st, &job->stats);
     ctx->busy = false;
     if (job->status != GDPM_OK && job->status != GDPM_E_NOT_CONVERGED) return job->status;
     *out = job.release();
@@ -1951,8 +2180,8 @@ gdpm_status gdpm_run_noalloc(gdpm_context ctx, gdpm_phantom ph, gdpm_source src,
     HIP_TRY(hipSetDevice(ctx->device));
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     ctx->busy = true;
-    const gdpm_status s = do_run(ctx, ph, src, prm, d_dose, d_sigma, nullptr, nullptr, st, stats,
-                                 nullptr, ctx->scratch);
+    const gdpm_status s = do_run(ctx, ph, src, prm, d_dose, d_sigma, nullptr, nullptr, nullptr, nullptr, st, stats,
+                                 ctx->scratch);
     ctx->busy = false;
     return s;
 }
@@ -2008,15 +2237,18 @@ gdpm_status gdpm_run_batch(gdpm_context ctx, int n, const gdpm_job_desc* jobs,
             first_err = s;
             break;
         }
+        // outputs of the finished jobs, then their device memory goes back
+        std::vector<OutCopy> list;
+        for (int i = 0; i < next; ++i)
+            if (ej[i]->done && ej[i]->slot >= 0) add_outputs(list, ej[i].get(), jobs[i].dose, jobs[i].sigma);
+        s = copy_out(ctx, st, list);
+        if (s) {
+            first_err = s;
+            break;
+        }
         for (int i = 0; i < next; ++i) {
             EJob* j = ej[i].get();
             if (!j->done || j->slot < 0) continue;
-            // outputs of a finished job, then its device memory goes back
-            if (jobs[i].dose)
-                HIP_TRY(hipMemcpyAsync(jobs[i].dose, j->d_dose, j->nv * sizeof(double), hipMemcpyDeviceToHost, st));
-            if (jobs[i].sigma)
-                HIP_TRY(hipMemcpyAsync(jobs[i].sigma, j->d_sigma, j->nv * sizeof(double), hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipStreamSynchronize(st));
             if (stats) fill_stats(E, j, t0, &stats[i]);
             if (status) status[i] = j->status;
             E.release(j);
@@ -2157,6 +2389,7 @@ gdpm_status gdpm_server_info_get(gdpm_server srv, gdpm_server_info* info) {
         res += (double)(t.second->phot.bytes + t.second->elec.bytes + t.second->rinv.bytes +
                         t.second->rinv_scale.bytes + t.second->aw.bytes + t.second->kn.bytes);
     res += ctx->resident_bytes;
+    res += (double)ctx->pool->held_bytes();
     info->resident_bytes = res;
     return GDPM_OK;
 }
