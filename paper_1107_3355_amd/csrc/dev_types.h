@@ -236,8 +236,6 @@ struct SourceDev {
     unsigned long long n_phsp;
 };
 
-constexpr uint32_t kMetroChains = 16384;   // Metropolis chains of a job
-
 // One dose job: its phantom, source, random key and tallies.
 struct JobDev {
     Geom G;
@@ -263,7 +261,25 @@ struct SrcSeg {
     uint32_t n, off;
     uint32_t job, batch;
     uint32_t rpos, rsize;      // position of h0 in its round, and the round's size
+    uint32_t unit0;            // its first unit of work in the source pass (see source_units)
+    uint32_t lanes, group;     // Metropolis sources: lanes per chain, and the number of
+    uint32_t pad;              // segments, this one first, that the job's chains run through
 };
+
+// Units of the source pass, one wavefront's work at a time: 64 histories of a
+// segment; or 64 / lanes of a Metropolis source's chains through all segments of
+// the job (the units are the first segment's).  A chain of n / kMetroChains
+// steps per segment gets as many lanes as it has steps, a power of two up to 64.
+constexpr uint32_t kMetroChains = 16384;   // Metropolis chains of a job
+inline uint32_t metro_lanes(uint64_t n) {
+    uint32_t g = 1;
+    while (g < 64u && 2u * g <= n / kMetroChains) g *= 2u;
+    return g;
+}
+inline uint32_t source_units(uint64_t n, bool metro, uint32_t lanes) {
+    return metro ? kMetroChains / (64u / lanes) : (uint32_t)((n + 63) / 64);
+}
+
 
 // The source passes of one scheduler iteration, per particle type: the host
 // writes the numbers of segments and records (pinned memory), the iteration's
@@ -273,7 +289,7 @@ struct SrcSeg {
 struct SrcHdr {
     uint32_t nseg, total;    // segments, records
     uint32_t base;           // queue position of the first record
-    uint32_t pad;
+    uint32_t units;          // units of work
 };
 constexpr int kMaxSegs = 4096;          // source segments per iteration (both types)
 struct StepHost {

@@ -1066,7 +1066,7 @@ gdpm_status Engine::step() {
             return a->sr_end - a->issued < b->sr_end - b->issued;
         });
     int nseg[2] = {0, 0};
-    uint32_t total[2] = {0u, 0u};
+    uint32_t total[2] = {0u, 0u}, units[2] = {0u, 0u};
     SrcSeg* hs = ctx->h_step->segs;
     const int seg_cap = kMaxSegs / 2;   // per source type
     for (size_t k = 0; k < want.size() && room > 0; ++k) {
@@ -1084,6 +1084,8 @@ gdpm_status Engine::step() {
         const uint32_t copies = 1u << j->plan.split;
         n = std::min<uint64_t>(n, room / copies);
         const int ri = j->src->particle == 0 ? 0 : 1;
+        const int seg0 = nseg[ri];
+        uint32_t longest = 0;
         while (n > 0 && nseg[ri] < seg_cap) {
             const uint64_t rel = j->issued - j->sr_start;
             const uint32_t b = (uint32_t)std::min<uint64_t>(rel / j->round_size, j->plan.nb - 1);
@@ -1098,15 +1100,27 @@ gdpm_status Engine::step() {
             sg.off = total[ri];   // in records: history i's copy c at off + i 2^split + c
             sg.job = (uint32_t)j->slot;
             sg.batch = b;
+            sg.unit0 = units[ri];
+            sg.lanes = sg.group = sg.pad = 0u;
+            if (!j->src->metro) units[ri] += source_units(m, false, 0);
+            longest = std::max(longest, (uint32_t)m);
             total[ri] += (uint32_t)(m * copies);
             j->issued += m;
             j->nhist[b] += (double)m;
             room -= m * copies;
             n -= m;
         }
+        if (j->src->metro && nseg[ri] > seg0) {
+            // the job's chains run through its segments in order
+            SrcSeg& sg = hs[ri * seg_cap + seg0];
+            sg.lanes = metro_lanes(longest);
+            sg.group = (uint32_t)(nseg[ri] - seg0);
+            units[ri] += source_units(0, true, sg.lanes);
+            for (int q = seg0 + 1; q < nseg[ri]; ++q) hs[ri * seg_cap + q].unit0 = units[ri];
+        }
     }
     R.n_jobs = std::max(n_slots, 1);
-    for (int ri = 0; ri < 2; ++ri) ctx->h_step->hdr[ri] = SrcHdr{(uint32_t)nseg[ri], total[ri], 0u, 0u};
+    for (int ri = 0; ri < 2; ++ri) ctx->h_step->hdr[ri] = SrcHdr{(uint32_t)nseg[ri], total[ri], 0u, units[ri]};
     const uint32_t seq = ++ctx->seq;
     ctx->h_step->seq = seq;
     // bins per job so that jobs x bins fits the re-binning keys; boxes of the
@@ -1151,7 +1165,7 @@ gdpm_status Engine::step() {
     k.st = st;
     for (int ri = 0; ri < 2; ++ri) {
         if (!nseg[ri]) continue;
-        const uint64_t need = std::min<uint64_t>((total[ri] + 255) / 256, 4u * (uint64_t)blocks);
+        const uint64_t need = std::min<uint64_t>((units[ri] + 3) / 4, 4u * (uint64_t)blocks);
         k.src_blocks[ri] = (int)(graph ? std::min<uint64_t>(pow2_at_least(need, 1), 4u * (uint64_t)blocks) : need);
     }
     k.blocks = blocks;

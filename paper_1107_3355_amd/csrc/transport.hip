@@ -428,28 +428,35 @@ GDPM_DEV float face_dist(const GG& G, float x, float y, float z, float u, float 
 // ---------------------------------------------------------------------------
 // source: history h -> primary particle (section 2.3)
 // ---------------------------------------------------------------------------
-GDPM_DEV float spectrum_energy(const SourceDev& S, float u) {
+// SS, GG: SourceDev and Geom in any address space
+template <class SS>
+GDPM_DEV float spectrum_energy(const SS& S, float u) {
     if (S.spec_kind == 0) return S.e_mono;
+    const GDPM_GLOBAL float* sc = global_ptr(S.spec_c);
+    const GDPM_GLOBAL float* se = global_ptr(S.spec_e);
+    const GDPM_GLOBAL float* sp = global_ptr(S.spec_p);
     const int n = S.spec_n;
-    const float r = u * S.spec_c[n - 1];
+    const float r = u * sc[n - 1];
     int j = 0;
-    while (j < n - 2 && S.spec_c[j + 1] <= r) ++j;
-    const float e0 = S.spec_e[j], e1 = S.spec_e[j + 1];
-    const float p0 = S.spec_p[j], sl = (S.spec_p[j + 1] - p0) / (e1 - e0);
-    const float d = r - S.spec_c[j];
+    while (j < n - 2 && sc[j + 1] <= r) ++j;
+    const float e0 = se[j], e1 = se[j + 1];
+    const float p0 = sp[j], sl = (sp[j + 1] - p0) / (e1 - e0);
+    const float d = r - sc[j];
     const float den = p0 + hsqrt(fmaxf(0.0f, p0 * p0 + 2.0f * sl * d));
     const float x = den > 0.0f ? 2.0f * d / den : 0.0f;
     return fminf(fmaxf(e0 + x, e0), e1);
 }
 
 // beamlet I with P(I) <= r < P(I+1); start from the guide table, walk both ways
-GDPM_DEV int beamlet_of(const SourceDev& S, float u) {
+template <class SS>
+GDPM_DEV int beamlet_of(const SS& S, float u) {
+    const GDPM_GLOBAL double* cdf = global_ptr(S.cdf);
     const double r = (double)u;
     int k = (int)(r * (double)S.n_guide);
     k = min(k, S.n_guide - 1);
-    int i = (int)S.guide[k];
-    while (i > 0 && S.cdf[i] > r) --i;
-    while (i < S.nf - 1 && S.cdf[i + 1] <= r) ++i;
+    int i = (int)global_ptr(S.guide)[k];
+    while (i > 0 && cdf[i] > r) --i;
+    while (i < S.nf - 1 && cdf[i + 1] <= r) ++i;
     return i;
 }
 
@@ -460,42 +467,50 @@ struct Primary {
     bool in;
 };
 
-// one step of a Metropolis chain (Algorithm A1, section 2.3.1): trial beamlet J
-// with equal probability among those of nonzero intensity, then r; the chain
-// moves to J when r < f_J / f_prev, tested as r f_prev < f_J in double
+// Metropolis chains (Algorithm A1, section 2.3.1): at each step a trial beamlet J
+// is drawn with equal probability among those of nonzero intensity, then r; the
+// chain moves to J when r < f_J / f_prev, tested as r f_prev < f_J in double
 // precision (exact for single-precision r and f)
-GDPM_DEV int metropolis_step(const SourceDev& S, float uj, float r, uint32_t& prev) {
-    const uint32_t J = S.nz[min((int)((double)uj * (double)S.n_nz), S.n_nz - 1)];
-    if ((double)r * (double)S.f[prev] < (double)S.f[J]) prev = J;
-    return (int)prev;
+template <class SS>
+GDPM_DEV uint32_t metropolis_trial(const SS& S, float uj) {
+    return global_ptr(S.nz)[min((int)((double)uj * (double)S.n_nz), S.n_nz - 1)];
 }
+GDPM_DEV bool metropolis_moves(float r, float f_prev, float f_j) { return (double)r * (double)f_prev < (double)f_j; }
 
 // chain start: a beamlet drawn with equal probability among those of nonzero
 // intensity, from the chain's own stream (history id (2^32-1) 2^32 + chain)
-GDPM_DEV uint32_t metropolis_start(const SourceDev& S, uint32_t chain, uint32_t k0, uint32_t k1) {
+template <class SS>
+GDPM_DEV uint32_t metropolis_start(const SS& S, uint32_t chain, uint32_t k0, uint32_t k1) {
     uint32_t x0 = chain, x1 = 0xFFFFFFFFu, x2 = 0u, x3 = 0u;
     philox(k0, k1, x0, x1, x2, x3);
-    const float u = unit_float(x0);
-    return S.nz[min((int)((double)u * (double)S.n_nz), S.n_nz - 1)];
+    return metropolis_trial(S, unit_float(x0));
 }
 
 // section 2.3.2: energy of the history at position i of a round of `size`:
 // interval k with C_k <= i < C_{k+1}, C_k = floor(size F_k + 1/2); inside it
 // the energy is uniform (strata_shape 0) or the spectrum's inverse CDF at
 // F_k + u (F_{k+1} - F_k) (strata_shape 1)
-GDPM_DEV float stratified_energy(const SourceDev& S, uint32_t i, uint32_t size, float u) {
-    int k = 0;
-    while (k < S.strata - 1 && floor((double)size * S.strata_F[k + 1] + 0.5) <= (double)i) ++k;
+template <class SS>
+GDPM_DEV float stratified_energy(const SS& S, uint32_t i, uint32_t size, float u) {
+    const GDPM_GLOBAL double* F = global_ptr(S.strata_F);
+    // the first k that is the last interval or has C_{k+1} > i (C never falls)
+    int k = 0, hi = S.strata - 1;
+    while (k < hi) {
+        const int mid = (k + hi) >> 1;
+        if (floor((double)size * F[mid + 1] + 0.5) <= (double)i) k = mid + 1;
+        else hi = mid;
+    }
     if (S.strata_shape == 0) return fmaf(u, S.strata_w, fmaf((float)k, S.strata_w, S.strata_lo));
-    const double f0 = S.strata_F[k], f1 = S.strata_F[k + 1];
+    const double f0 = F[k], f1 = F[k + 1];
     return spectrum_energy(S, (float)(f0 + (double)u * (f1 - f0)));
 }
 
 // section 2.3.3: history h starts as phase-space record h mod n: inside the phantom where it is, outside where its forward ray
 // enters (else it escapes); the record number stands in for the beamlet
-GDPM_DEV Primary phase_space_primary(const SourceDev& S, const Geom& G, unsigned long long h) {
+template <class SS, class GG>
+GDPM_DEV Primary phase_space_primary(const SS& S, const GG& G, unsigned long long h) {
     const unsigned long long k = h % S.n_phsp;
-    const float* rec = S.phsp + 7 * k;
+    const GDPM_GLOBAL float* rec = global_ptr(S.phsp) + 7 * k;
     Primary p;
     p.draws = 0u;
     p.beamlet = (int)k;
@@ -536,33 +551,36 @@ GDPM_DEV Primary phase_space_primary(const SourceDev& S, const Geom& G, unsigned
     return p;
 }
 
-// the primary of history h; `chain` (Metropolis sources only) holds the state
-// of the history's chain and is advanced; rpos and rsize (stratified spectra
-// only) place the history in its round
-GDPM_DEV Primary make_primary(const SourceDev& S, const Geom& G, unsigned long long h, uint32_t k0, uint32_t k1,
-                              uint32_t* chain = nullptr, uint32_t rpos = 0u, uint32_t rsize = 1u) {
-    if (S.n_phsp) return phase_space_primary(S, G, h);
-    Primary p;
-    // draws 0-3 of the history's stream, path 0; a Metropolis source takes a fifth
+// draws 0-3 of history h's stream, path 0
+GDPM_DEV f4 source_draws(unsigned long long h, uint32_t k0, uint32_t k1) {
     uint32_t x0 = (uint32_t)h, x1 = (uint32_t)(h >> 32), x2 = 0u, x3 = 0u;
     philox(k0, k1, x0, x1, x2, x3);
-    const float ue = unit_float(x0), u1 = unit_float(x1), u2 = unit_float(x2), u3 = unit_float(x3);
-    p.e = S.strata ? stratified_energy(S, rpos, rsize, ue) : spectrum_energy(S, ue);
-    int gi;
-    float ux = u2, uy = u3;
+    return f4{unit_float(x0), unit_float(x1), unit_float(x2), unit_float(x3)};
+}
+
+// The primary of history h, whose first draws are d.  chain_beamlet >= 0: the
+// beamlet of its Metropolis chain (draws 1 and 2 are then the chain's, and a
+// fifth draw is taken), else the beamlet is searched for.  rpos and rsize
+// (stratified spectra only) place the history in its round.
+template <class SS, class GG>
+GDPM_DEV Primary make_primary(const SS& S, const GG& G, unsigned long long h, f4 d, uint32_t k0, uint32_t k1,
+                              int chain_beamlet, uint32_t rpos, uint32_t rsize) {
+    Primary p;
+    p.e = S.strata ? stratified_energy(S, rpos, rsize, d.x) : spectrum_energy(S, d.x);
+    int gi = chain_beamlet;
+    float ux = d.z, uy = d.w;
     p.draws = 4u;
-    if (chain) {
+    if (S.metro) {
         uint32_t w0 = (uint32_t)h, w1 = (uint32_t)(h >> 32), w2 = 0u, w3 = 1u;
         philox(k0, k1, w0, w1, w2, w3);
-        gi = metropolis_step(S, u1, u2, *chain);
-        ux = u3;
+        ux = d.w;
         uy = unit_float(w0);
         p.draws = 5u;
     } else {
-        gi = beamlet_of(S, u1);
+        gi = beamlet_of(S, d.y);
     }
     p.beamlet = gi;
-    const BeamDev& b = S.beams[S.beam_of[gi]];
+    const GDPM_GLOBAL BeamDev& b = global_ptr(S.beams)[global_ptr(S.beam_of)[gi]];
     const int j = gi - b.off;
     const int jx = j % b.nbx, jy = j / b.nbx;
     const float px = ((float)jx + ux) * b.bw - b.hx;
@@ -594,11 +612,11 @@ GDPM_DEV Primary make_primary(const SourceDev& S, const Geom& G, unsigned long l
     float tmin = tlo, tmax = 3.0e38f;
     int ax = -1;
     bool miss = false;
-    const float o[3] = {ox, oy, oz}, d[3] = {p.u, p.v, p.w}, L[3] = {G.lx, G.ly, G.lz};
+    const float o[3] = {ox, oy, oz}, dir[3] = {p.u, p.v, p.w}, L[3] = {G.lx, G.ly, G.lz};
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        if (d[i] != 0.0f) {
-            const float ta = (0.0f - o[i]) / d[i], tb = (L[i] - o[i]) / d[i];
+        if (dir[i] != 0.0f) {
+            const float ta = (0.0f - o[i]) / dir[i], tb = (L[i] - o[i]) / dir[i];
             const float tn = fminf(ta, tb), tf = fmaxf(ta, tb);
             if (tn > tmin) {
                 tmin = tn;
@@ -1446,98 +1464,218 @@ GDPM_DEV bool refill(bool active, ClaimState& cs, Args A, const WJob& W, int ri,
 
 // ---------------------------------------------------------------------------
 // source pass: segments of new histories (job, first id, count, batch slot) ->
-// primaries appended to the queue of the source particle type (section 2.3);
-// a primary whose ray misses the phantom leaves an empty slot and counts as
-// escaped
+// primaries in the queue of the source particle type (section 2.3); a primary
+// whose ray misses the phantom leaves an empty slot and counts as escaped
 // ---------------------------------------------------------------------------
-GDPM_DEV double block_sum(double v, double* sh) {
-    v = wave_sum(v);
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    __syncthreads();
-    if (lane_id() == 0) sh[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int i = 0; i < nw; ++i) s += sh[i];
-    return s;
+// The segments are cut into units, and each wavefront takes a run of consecutive
+// units: 64 histories of a segment, or, for a Metropolis source, a group of chains
+// through all of the job's segments.  With all workgroups on one segment after the
+// other, each added its sums to the job's counters after every segment: 24 us a
+// segment, and a round of ten batches has ten.  What bounds it now is the
+// writing of the records (64 B each), so these go through LDS to be
+// written as whole lines.
+struct SourceArgs {
+    Ctl* ctl;
+    RunDev R;
+    const SrcSeg* segs;
+    const SrcHdr* hdr;
+    int ri;
+};
+struct SourceTally {   // of a workgroup, per job
+    double e_in[kMaxJobs], e_esc[kMaxJobs];
+    uint32_t born[kMaxJobs];
+};
+
+// the records of a history: its 2^split copies, copy c on stream path c (copy 0
+// is the unsplit primary)
+GDPM_DEV Rec primary_record(const Primary& p, unsigned long long h, uint32_t copy, uint32_t vox, uint32_t jb) {
+    Rec r;
+    // the stream continues at the draw after the source's draws
+    r.a = f4{p.x, p.y, p.z, p.in ? p.e : kEmptyEnergy};
+    r.b = f4{p.u, p.v, p.w, -1.0f};
+    r.c = u4{(uint32_t)h, (uint32_t)(h >> 32), copy, p.draws};
+    r.d = u4{vox, 0u, 0u, jb};
+    return r;
 }
 
-__global__ void __launch_bounds__(256) k_source(Ctl* ctl, RunDev R, const SrcSeg* segs,
-                                                const SrcHdr* hdr, int ri) {
-    __shared__ double sh[4];
-    if (ctl->overflow) return;
-    const int nseg = (int)__builtin_amdgcn_readfirstlane(hdr->nseg);
-    const uint32_t tail = __builtin_amdgcn_readfirstlane(hdr->base);
-    Particle* buf = R.buf[ri];
-    const uint32_t nthreads = gridDim.x * blockDim.x;
-    const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
-    for (int s = 0; s < nseg; ++s) {
-        const SrcSeg sg = uniform_copy(segs[s]);
-        const JobDev& d = R.jobs[sg.job];
-        const Geom G = uniform_copy(d.G);
-        const SourceDev S = uniform_copy(d.S);
-        const uint32_t k0 = __builtin_amdgcn_readfirstlane(d.k0);
-        const uint32_t k1 = __builtin_amdgcn_readfirstlane(d.k1);
-        double* hist = uniform_copy(d.hist);
-        const unsigned long long hist0 = uniform_copy(d.hist0);
-        const uint32_t jb = sg.job | ((__builtin_amdgcn_readfirstlane(d.gen) & 0xFFu) << 8) | (sg.batch << 16);
-        const uint32_t copies = 1u << __builtin_amdgcn_readfirstlane(d.split);
-        double e_in = 0.0, e_esc = 0.0, born = 0.0;
-        // history sg.h0 + i; `chain` holds its Metropolis chain (or is null).
-        // A split history writes its 2^split copies to consecutive records,
-        // copy c on stream path c (copy 0 is the unsplit primary).
-        auto one = [&](uint32_t i, uint32_t* chain) {
-            const unsigned long long h = sg.h0 + i;
-            const Primary pr = make_primary(S, G, h, k0, k1, chain, sg.rpos + i, sg.rsize);
-            e_in += (double)pr.e;
-            uint32_t vox = 0u;
-            if (pr.in && ri == 1) {
-                int ix, iy, iz;
-                voxel_of(G, pr.x, pr.y, pr.z, ix, iy, iz);
-                vox = pack_vox(ix, iy, iz);
-            }
-            for (uint32_t c = 0; c < copies; ++c) {
-                float4* q = reinterpret_cast<float4*>(buf + ((tail + sg.off + i * copies + c) & R.mask[ri]));
-                if (pr.in) {
-                    // the stream continues at the draw after the source's draws
-                    q[0] = make_float4(pr.x, pr.y, pr.z, pr.e);
-                    q[1] = make_float4(pr.u, pr.v, pr.w, -1.0f);
-                    q[2] = make_float4(__uint_as_float((uint32_t)h), __uint_as_float((uint32_t)(h >> 32)),
-                                       __uint_as_float(c), __uint_as_float(pr.draws));
-                    q[3] = make_float4(__uint_as_float(vox), 0.0f, 0.0f, __uint_as_float(jb));
-                } else {
-                    reinterpret_cast<float*>(q)[3] = kEmptyEnergy;
-                }
-            }
-            if (pr.in) {
-                born += (double)copies;
-            } else {
+__global__ void __launch_bounds__(256) k_source(SourceArgs) {
+    const GDPM_CONST SourceArgs* A = (const GDPM_CONST SourceArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ SourceTally tally;
+    __shared__ f4 line[4][4 * 64];
+    if (((const GDPM_CONST Ctl*)A->ctl)->overflow) return;
+    const GDPM_CONST SrcHdr* hdr = (const GDPM_CONST SrcHdr*)A->hdr;
+    const GDPM_CONST SrcSeg* segs = (const GDPM_CONST SrcSeg*)A->segs;
+    const int nseg = (int)hdr->nseg, ri = A->ri;
+    const uint32_t base = hdr->base, units = hdr->units;
+    for (uint32_t i = threadIdx.x; i < sizeof(SourceTally) / 4u; i += blockDim.x)
+        reinterpret_cast<uint32_t*>(&tally)[i] = 0u;
+    __syncthreads();
+    GDPM_LDS f4* lds = (GDPM_LDS f4*)line[threadIdx.x >> 6];
+    const uint32_t lane = lane_id();
+    const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    const uint32_t per = (units + waves - 1u) / waves;
+    const uint32_t c1 = min((w + 1u) * per, units);
+    uint32_t c = min(w * per, units);
+    int s = 0;   // the last segment that starts at or before unit c
+    for (int hi = nseg - 1; s < hi;) {
+        const int mid = (s + hi + 1) >> 1;
+        if (segs[mid].unit0 <= c) s = mid;
+        else hi = mid - 1;
+    }
+    double e_in = 0.0, e_esc = 0.0;
+    uint32_t born = 0u;
+    int job = -1;
+    // a wavefront's sums of one job
+    auto flush = [&]() {
+        if (job < 0) return;
+        const double in = wave_sum(e_in), out = wave_sum(e_esc);
+        if (lane == 0) {
+            lds_add((GDPM_LDS double*)&tally.e_in[job], in);
+            if (out != 0.0) lds_add((GDPM_LDS double*)&tally.e_esc[job], out);
+            lds_add((GDPM_LDS uint32_t*)&tally.born[job], born);
+        }
+        e_in = e_esc = 0.0;
+        born = 0u;
+    };
+    for (; c < c1; ++c) {
+        while (s + 1 < nseg && segs[s + 1].unit0 <= c) ++s;
+        const GDPM_CONST SrcSeg* sg = segs + s;
+        if ((int)sg->job != job) {
+            flush();
+            job = (int)sg->job;
+        }
+        const JobPtr J = (JobPtr)A->R.jobs + job;
+        const uint32_t k0 = J->k0, k1 = J->k1;
+        const uint32_t copies = 1u << J->split;
+        const uint32_t tag = (uint32_t)job | ((J->gen & 0xFFu) << 8);
+        // counts and, if its records are not written together, writes a primary
+        auto account = [&](const Primary& p, unsigned long long h, bool live) {
+            if (!live) return;
+            e_in += (double)p.e;
+            if (!p.in) {
                 // all copies escape: weight 1 each, like the tallies
-                const double out = (double)pr.e * (double)copies;
+                const double out = (double)p.e * (double)copies;
                 e_esc += out;
-                if (hist) unsafeAtomicAdd(&hist[2 * (h - hist0) + 1], out);
+                if (J->hist) atomic_add_f64(global_ptr(J->hist) + 2 * (h - J->hist0) + 1, out);
             }
         };
-        if (S.metro) {
-            // a chain's histories in increasing order, by one thread (a chain
-            // runs across segments and iterations through its stored state)
-            uint32_t* chains = uniform_copy(d.chains);
-            for (uint32_t c = tid; c < kMetroChains; c += nthreads) {
-                uint32_t state = chains[c];
-                const uint32_t first = (uint32_t)((c + kMetroChains - sg.h0 % kMetroChains) % kMetroChains);
-                for (uint32_t i = first; i < sg.n; i += kMetroChains) one(i, &state);
-                chains[c] = state;
+        auto voxel = [&](const Primary& p) {
+            if (ri == 0 || !p.in) return 0u;
+            int ix, iy, iz;
+            voxel_of(J->G, p.x, p.y, p.z, ix, iy, iz);
+            return pack_vox(ix, iy, iz);
+        };
+        auto write = [&](const Primary& p, unsigned long long h, uint32_t first, uint32_t jb) {
+            const uint32_t vox = voxel(p);
+            for (uint32_t k = 0; k < copies; ++k)
+                write_record((GDPM_GLOBAL f4*)(global_ptr(A->R.buf[ri]) + ((base + first + k) & A->R.mask[ri])),
+                             primary_record(p, h, k, vox, jb));
+        };
+        if (!J->S.metro) {
+            const uint32_t i0 = (c - sg->unit0) * 64u, i = i0 + lane;
+            const uint32_t n = min(64u, sg->n - i0);   // histories of this unit
+            const bool live = lane < n;
+            const unsigned long long h = sg->h0 + (live ? i : i0);
+            Primary p;
+            if (J->S.n_phsp) p = phase_space_primary(J->S, J->G, h);
+            else p = make_primary(J->S, J->G, h, source_draws(h, k0, k1), k0, k1, -1, sg->rpos + i, sg->rsize);
+            account(p, h, live);
+            born += copies * count(live && p.in);
+            const uint32_t jb = tag | (sg->batch << 16);
+            if (copies > 1u) {
+                if (live) write(p, h, sg->off + i * copies, jb);
+                continue;
             }
-        } else {
-            for (uint32_t i = tid; i < sg.n; i += nthreads) one(i, nullptr);
+            // 64 records of 64 B are consecutive in the queue: lane L writes piece
+            // L % 4 of record 16 k + L / 4.  In LDS the pieces of a record are
+            // rotated by its number, so that neither side has a bank conflict.
+            const Rec r = primary_record(p, h, 0u, voxel(p), jb);
+            const uint32_t rot = (lane >> 2) & 3u;
+            lds[4u * lane + (0u ^ rot)] = r.a;
+            lds[4u * lane + (1u ^ rot)] = r.b;
+            ((GDPM_LDS u4*)lds)[4u * lane + (2u ^ rot)] = r.c;
+            ((GDPM_LDS u4*)lds)[4u * lane + (3u ^ rot)] = r.d;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const uint32_t slot0 = base + sg->off + i0;
+#pragma unroll
+            for (uint32_t k = 0; k < 4u; ++k) {
+                const uint32_t rec = 16u * k + (lane >> 2), piece = lane & 3u;
+                const f4 v = lds[4u * rec + (piece ^ ((rec >> 2) & 3u))];
+                if (rec < n)
+                    ((GDPM_GLOBAL f4*)(global_ptr(A->R.buf[ri]) + ((slot0 + rec) & A->R.mask[ri])))[piece] = v;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            continue;
         }
-        e_in = block_sum(e_in, sh);
-        e_esc = block_sum(e_esc, sh);
-        born = block_sum(born, sh);
-        if (threadIdx.x == 0) {
-            if (e_in != 0.0) unsafeAtomicAdd(&R.jc->e_in[sg.job], e_in);
-            if (e_esc != 0.0) unsafeAtomicAdd(&R.jc->e_esc[sg.job], e_esc);
-            if (born != 0.0) atomicAdd(&R.jc->births[sg.job], (unsigned long long)born);
+        // Metropolis: 64 / g chains, g lanes each, through the job's segments in
+        // order.  A chain's g next steps are resolved together: which of them move
+        // depends on the state before each, the last move or the state the
+        // chain came with, so the moves are found from the states that the moves
+        // of the last turn imply, until they no longer change (after turn t the
+        // first t steps are right; a few turns do).
+        const uint32_t g = sg->lanes;
+        const uint32_t sub = lane & (g - 1u), lead = lane - sub;
+        const uint32_t chain = (c - sg->unit0) * (64u / g) + lead / g;
+        GDPM_GLOBAL uint32_t* chains = global_ptr(J->chains);
+        const GDPM_GLOBAL float* f = global_ptr(J->S.f);
+        uint32_t state = chains[chain];
+        float f_state = f[state];
+        const uint64_t mine = (g == 64u ? ~0ull : ((1ull << g) - 1ull)) << lead;
+        for (uint32_t q = 0; q < sg->group; ++q) {
+            const GDPM_CONST SrcSeg* t = sg + q;
+            const uint32_t first = (uint32_t)((chain + kMetroChains - t->h0 % kMetroChains) % kMetroChains);
+            const uint32_t jb = tag | (t->batch << 16);
+            for (uint32_t b = first; ballot(b < t->n); b += g * kMetroChains) {
+                const uint32_t i = b + sub * kMetroChains;
+                const bool live = b < t->n && i < t->n && i >= b;
+                const unsigned long long h = t->h0 + (live ? i : 0u);
+                const f4 d = source_draws(h, k0, k1);
+                const uint32_t trial = metropolis_trial(J->S, d.y);
+                const float f_j = f[trial];
+                uint64_t moves = 0ull;
+                uint32_t from = 64u;   // the lane whose trial the step starts from (64: the chain's state)
+                for (uint32_t turn = 0; turn <= g; ++turn) {
+                    const uint64_t before = moves & mine & ((1ull << lane) - 1ull);
+                    from = before ? 63u - (uint32_t)__clzll(before) : 64u;
+                    const float f_from = __shfl(f_j, (int)(from & 63u));
+                    const uint64_t now =
+                        ballot(live && metropolis_moves(d.z, from == 64u ? f_state : f_from, f_j));
+                    const bool same = now == moves;
+                    moves = now;
+                    if (same) break;
+                }
+                // the beamlet of this step: its trial if it moved, else the state before it
+                const uint32_t held = __shfl(trial, (int)(from & 63u));
+                const uint32_t beamlet = (moves >> lane) & 1ull ? trial : (from == 64u ? state : held);
+                // the chain's state after its last move here
+                const uint64_t all = moves & mine;
+                const uint32_t last = all ? 63u - (uint32_t)__clzll(all) : 0u;
+                const uint32_t end_state = __shfl(trial, (int)last);
+                const float end_f = __shfl(f_j, (int)last);
+                state = all ? end_state : state;
+                f_state = all ? end_f : f_state;
+                const Primary p =
+                    make_primary(J->S, J->G, h, d, k0, k1, (int)beamlet, t->rpos + i, t->rsize);
+                account(p, h, live);
+                born += copies * count(live && p.in);
+                if (live) write(p, h, t->off + i * copies, jb);
+            }
         }
+        if (sub == 0u) chains[chain] = state;
+    }
+    flush();
+    __syncthreads();
+    GDPM_GLOBAL JobCtl* jc = global_ptr(A->R.jc);
+    const int n_jobs = A->R.n_jobs;
+    for (int j = (int)threadIdx.x; j < n_jobs; j += blockDim.x) {
+        if (tally.e_in[j] != 0.0) atomic_add_f64(&jc->e_in[j], tally.e_in[j]);
+        if (tally.e_esc[j] != 0.0) atomic_add_f64(&jc->e_esc[j], tally.e_esc[j]);
+        if (tally.born[j]) atomic_add(&jc->births[j], (unsigned long long)tally.born[j]);
     }
 }
 
@@ -2615,7 +2753,17 @@ __global__ void k_test_sample(Tables T, int which, float e, float p1, float p2, 
 GDPM_DEV void test_source_one(const SourceDev& S, const Geom& G, uint32_t k0, uint32_t k1,
                               unsigned long long hist0, int i, int n, float* out, uint32_t* chain) {
     const unsigned long long h = hist0 + i;
-    const Primary p = make_primary(S, G, h, k0, k1, chain, (uint32_t)i, (uint32_t)n);
+    Primary p;
+    if (S.n_phsp) {
+        p = phase_space_primary(S, G, h);
+    } else {
+        const f4 d = source_draws(h, k0, k1);
+        if (chain) {
+            const uint32_t trial = metropolis_trial(S, d.y);
+            if (metropolis_moves(d.z, S.f[*chain], S.f[trial])) *chain = trial;
+        }
+        p = make_primary(S, G, h, d, k0, k1, chain ? (int)*chain : -1, (uint32_t)i, (uint32_t)n);
+    }
     float* o = out + 8 * (size_t)i;
     o[0] = p.e;
     o[1] = p.in ? (float)p.beamlet : -1.0f;
@@ -2679,7 +2827,8 @@ hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int r
 }
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
                          const SrcHdr* hdr, int ri) {
-    hipLaunchKernelGGL(k_source, dim3(blocks), dim3(256), 0, st, ctl, R, segs, hdr, ri);
+    const SourceArgs a{ctl, R, segs, hdr, ri};
+    hipLaunchKernelGGL(k_source, dim3(blocks), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 hipError_t launch_begin(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, SrcHdr* hdr, SrcSeg* segs,
