@@ -14,6 +14,8 @@ constexpr uint32_t kClaimMin = 32;      // smallest number of queue items a wave
 constexpr uint32_t kClaimMaxPhoton = 2048;   // a photon record lasts a few short iterations, so
 constexpr uint32_t kClaimMaxElectron = 256;  // photon wavefronts claim often: larger chunks keep
                                              // them off the shared claim counter
+constexpr uint32_t kWideMin = 16;       // a pass with this many records per lane uses all
+                                        // wavefronts of its workgroups (see PassGrid)
 constexpr int kMaxBins = 64;            // energy bins of the queue re-binning
 constexpr int kMaxJobs = 256;           // dose jobs transported together
 constexpr int kMaxKeys = 4096;          // re-binning keys (job x energy bin)
@@ -64,6 +66,18 @@ static_assert(sizeof(Particle) == 64, "particle record is 64 bytes");
 // that many wavefronts add to have a cache line of their own each: additions to
 // one line are served one after the other (85 million a second, whatever the
 // address in it), and readers of its other words wait with them.
+// The wavefronts of a pass: `wide` per workgroup are launched, and if the pass has
+// fewer than kWideMin records for each of their lanes only the first `narrow` of them
+// work.  Electrons run 16 wavefronts per CU instead of 12, since the pass waits on its
+// dependent table lookups: 19.9 instead of 22.0 ms on passes of 5e6 photons' electrons
+// (CT, 0.4 cm).  With few records they only share them: 24 jobs of 1.2e5 histories took
+// 8.9 ms with 16 and 8.4 with 12, one of 1e5 372 and 343 us.  The line: with 4, 8, 16
+// and 32 records 3e6 split histories took 1.97, 1.87, 1.87 and 1.99 ms, 1e7 histories
+// on slabs 2.33, 2.28, 2.22 and 2.22.
+struct PassGrid {
+    uint32_t blocks, wide, narrow;
+};
+
 struct alignas(128) RingCtl {
     uint32_t tail;                   // records in [head, tail); wavefronts reserve slots here
     uint32_t pad0[31];
@@ -73,7 +87,8 @@ struct alignas(128) RingCtl {
     uint32_t push;           // slots a wavefront of the running pass reserves at a time
     uint32_t permuted;       // 1: the pass reads its input through the permutation
     uint32_t next_head;      // head after a permuted pass (the tail before it)
-    uint32_t pad1[25];
+    uint32_t group_waves;    // the wavefronts of a workgroup that work in the running pass
+    uint32_t pad1[24];
 };
 static_assert(sizeof(RingCtl) == 256, "two cache lines");
 
@@ -108,10 +123,36 @@ struct StatsDev {
     double inv_n[kMaxBatches];          // 1 / histories of each batch
 };
 
+// The order of a job's energy tally: bricks of up to kBrickVoxels voxels, x fastest,
+// with the voxels of a brick together (x fastest too).  The electron pass sums a
+// particle's deposits in a brick and adds them to the tally together: the tally is
+// bound by the number of 64-byte lines that the additions touch (23.5 G a second on the
+// whole device, wherever they lie), not by their bytes.  A brick is two voxels wide
+// along the two axes with the smallest spacing, whose faces particles cross most
+// often (z, then y if equal: the fixed beams run along z), of those with an even
+// number of voxels, so that bricks need no padding.
+struct Brick {
+    int mx, my, mz;   // 1: bricks are two voxels wide along the axis, else 0
+};
+constexpr int kBrickVoxels = 4;
+inline Brick brick_of(const int n[3], const double d[3], bool plain) {
+    Brick b{0, 0, 0};
+    int* m[3] = {&b.mx, &b.my, &b.mz};
+    for (int k = 1; k < kBrickVoxels && !plain; k *= 2) {
+        int best = -1;
+        for (int a = 2; a >= 0; --a)
+            if (!*m[a] && n[a] % 2 == 0 && (best < 0 || d[a] < d[best])) best = a;
+        if (best >= 0) *m[best] = 1;
+    }
+    return b;
+}
+
 struct StatsArgs {
     StatsDev* red;           // zero at the start
-    const double* slots;     // [nb][nvox] energy tallies
+    const double* slots;     // [nb][nvox] energy tallies, in `brick` order
     size_t nvox;
+    Brick brick;
+    int nx, ny;              // voxels along x and y
     const uint32_t* vox;
     double vvox;
     double* dose;
@@ -241,8 +282,9 @@ struct JobDev {
     Geom G;
     SourceDev S;
     const float* mumax;        // [pg_n] Woodcock majorant of the job's phantom, 1/cm
-    double* tally;             // [n_batches][nv] energy tallies (MeV per voxel)
+    double* tally;             // [n_batches][nv] energy tallies (MeV per voxel), in `brick` order
     unsigned long long nv;     // voxels of the phantom
+    Brick brick;
     double* hist;              // per-history (deposited, escaped) or null
     unsigned long long hist0;  // history id of hist[0]
     uint32_t k0, k1;           // Philox key
@@ -336,6 +378,7 @@ struct PassArgs {
     Tables T;
     RunDev R;
     int photon_waves;   // fused form: wavefronts of a workgroup that start with photons
+    int bricks;         // the workgroup's LDS holds the brick sums of the electrons
 };
 
 }  // namespace gdpm

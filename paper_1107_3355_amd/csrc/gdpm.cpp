@@ -34,24 +34,24 @@
 #include "tables.h"
 
 namespace gdpm {
-hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, int waves);
+hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, const PassGrid& grid);
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
                          const SrcHdr* hdr, int ri);
 hipError_t launch_begin(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, SrcHdr* hdr, SrcSeg* segs,
-                        int setup, int lone, int waves0, int waves1);
-hipError_t launch_mid(hipStream_t st, Ctl* ctl, const RunDev& R, int setup, int lone, int waves);
+                        int setup, int lone, const PassGrid& grid0, const PassGrid& grid1);
+hipError_t launch_mid(hipStream_t st, Ctl* ctl, const RunDev& R, int setup, int lone, const PassGrid& grid);
 hipError_t launch_end(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, StepMirror* out, int fused);
 hipError_t launch_init(hipStream_t st, Ctl* ctl, JobCtl* jc, StatsDev* stats, uint32_t start);
 hipError_t launch_admit(hipStream_t st, int cus, const JobDev& job, JobDev* jobs, JobCtl* jc, const float* majorant,
                         float* mumax, size_t n_tally, size_t n_hist, int slot, int n_grid);
-size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds);
+size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds, bool bricks);
 hipError_t transport_lds_optin(size_t bytes);
-hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool solo, bool permuted,
-                            Ctl* ctl, const Tables& T, const RunDev& R);
+hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool bricks, bool solo,
+                            bool permuted, Ctl* ctl, const Tables& T, const RunDev& R);
 hipError_t launch_rebin(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, int ri, int nb,
                         float lo, float inv, int space);
-hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_waves, bool permuted, Ctl* ctl,
-                        const Tables& T, const RunDev& R);
+hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_waves, bool bricks, bool permuted,
+                        Ctl* ctl, const Tables& T, const RunDev& R);
 hipError_t launch_count_records(hipStream_t st, int blocks, const Ctl* ctl, const RunDev& R,
                                 unsigned long long* counts);
 hipError_t launch_stats(hipStream_t st, int cus, const StatsArgs& a, StatsDev* out, uint32_t seq);
@@ -343,10 +343,10 @@ double now_s() {
 struct StepGraphKey {
     hipStream_t st;
     int src_blocks[2];   // grid of the source pass per particle type (0: none)
-    int rebin[2], lds[2];
+    int rebin[2], lds[2], bricks;
     int lone;            // the one job holding particles (queues not re-binned), or -1
     int blocks, nb, space;     // one workgroup per CU (source, re-binning)
-    int pass_blocks[2], threads[2];   // grid of each pass
+    PassGrid pass[2];    // grid of each pass (fused: the same one)
     int fused, photon_waves;   // both passes in one launch; its photon-first wavefronts
     float blo, binv;
     RunDev R;
@@ -569,16 +569,21 @@ gdpm_status context_mem(gdpm_context ctx, EngineMem* m) {
 
 int grid_blocks(gdpm_context ctx) { return std::max(1, ctx->cu_count); }
 
-// persistent grid of a transport pass: one workgroup of waves_per_cu (photons:
-// photon_waves_per_cu) wavefronts per CU; lds: its tables and records are staged
+// persistent grid of a transport pass (ri = 2: of both in one launch): one workgroup per
+// CU of waves_per_cu wavefronts (photons: photon_waves_per_cu; electrons: a third more
+// in passes of many records, see PassGrid); lds: its tables (and the photons' records)
+// are staged; bricks: the electrons' brick sums have room
 struct PassShape {
-    int blocks, threads, lds;
+    PassGrid grid;
+    int lds, bricks;
 };
 PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri) {
-    int waves = ctx->waves_per_cu;
-    if (ri == 0 && ctx->photon_waves_per_cu) waves = std::min(waves, ctx->photon_waves_per_cu);
-    return PassShape{grid_blocks(ctx), 64 * waves,
-                     ctx->lds_tables && transport_lds_bytes(ri, T, waves, true) <= (size_t)ctx->max_lds};
+    int narrow = ctx->waves_per_cu;
+    if (ri == 0 && ctx->photon_waves_per_cu) narrow = std::min(narrow, ctx->photon_waves_per_cu);
+    const int waves = ri == 1 ? narrow + narrow / 3 : narrow;
+    const bool lds = ctx->lds_tables && transport_lds_bytes(ri, T, waves, true, false) <= (size_t)ctx->max_lds;
+    const bool bricks = ri != 0 && transport_lds_bytes(ri, T, waves, lds, true) <= (size_t)ctx->max_lds;
+    return PassShape{{(uint32_t)grid_blocks(ctx), (uint32_t)waves, (uint32_t)narrow}, lds, bricks};
 }
 
 // ---------------------------------------------------------------------------
@@ -655,6 +660,12 @@ struct EJob {
     uint32_t* chains_p = nullptr;
     double* d_dose = nullptr;   // outputs in device memory
     double* d_sigma = nullptr;
+    bool plain_tally = false;   // the batches' tallies are an output
+    Brick brick() const {
+        const int n[3] = {ph->nx, ph->ny, ph->nz};
+        const double d[3] = {ph->dx, ph->dy, ph->dz};
+        return brick_of(n, d, plain_tally);
+    }
     uint64_t hbase = 0;         // id of the job's first history
     uint64_t issued = 0;        // histories started (relative ids [0, issued))
     uint64_t sr_start = 0, sr_end = 0;  // the running super-round
@@ -888,6 +899,7 @@ gdpm_status Engine::admit(EJob* j) {
     d.mumax = j->mumax_p;
     d.tally = j->tally_p;
     d.nv = nv;
+    d.brick = j->brick();
     d.hist = hist;
     d.hist0 = j->prm.hist0;
     d.k0 = (uint32_t)j->prm.seed;
@@ -1183,18 +1195,21 @@ gdpm_status Engine::step() {
         k.rebin[ri] = !M.fixed && ((ri == 0 ? ctx->rebin_photons : ctx->rebin_electrons) || holders > 1 || lone < 0);
         if (k.rebin[ri]) tm.passes_rebinned++;
         const PassShape shape = pass_shape(ctx, T, ri);
-        k.pass_blocks[ri] = shape.blocks;
-        k.threads[ri] = shape.threads;
+        k.pass[ri] = shape.grid;
         k.lds[ri] = shape.lds;
+        if (ri == 1) k.bricks = shape.bricks;
         tm.passes++;
         (ri == 0 ? tm.passes_photon : tm.passes_electron)++;
     }
     k.lone = (k.rebin[0] && k.rebin[1]) ? -1 : lone;
     // both passes in one launch: needs the electron tables staged (the photon
     // tables are read through the caches); not in the one-particle form
-    k.fused = ctx->fused_passes && !ctx->solo_lanes && k.lds[1];
+    const PassShape both = pass_shape(ctx, T, 2);
+    k.fused = ctx->fused_passes && !ctx->solo_lanes && both.lds;
     if (k.fused) {
-        const int waves = k.threads[1] / 64;
+        const int waves = (int)both.grid.wide;
+        k.pass[0] = k.pass[1] = both.grid;
+        k.bricks = both.bricks;
         k.photon_waves = ctx->photon_waves < 0 ? waves / 2 : std::min(ctx->photon_waves, waves);
         k.lds[0] = 0;
     }
@@ -1277,22 +1292,20 @@ gdpm_status Engine::check_accounting() {
 // several jobs hold particles), and the report to the host
 gdpm_status Engine::issue(const StepGraphKey& k) {
     Ctl* dc = M.ctl;
-    int waves[2];
-    for (int ri = 0; ri < 2; ++ri) waves[ri] = (k.fused ? k.blocks * k.threads[1] : k.pass_blocks[ri] * k.threads[ri]) / 64;
     auto rebin = [&](int ri) -> gdpm_status {
         if (!k.rebin[ri]) return GDPM_OK;
         HIP_TRY(launch_rebin(st, 4 * k.blocks, dc, k.R, ri, k.nb, k.blo, k.binv, k.space));
-        HIP_TRY(launch_setup(st, dc, k.R, ri, 1, k.lone, waves[ri]));
+        HIP_TRY(launch_setup(st, dc, k.R, ri, 1, k.lone, k.pass[ri]));
         return GDPM_OK;
     };
     auto pass = [&](int ri) -> gdpm_status {
-        HIP_TRY(launch_transport(st, ri, k.pass_blocks[ri], k.threads[ri], k.lds[ri] != 0, ctx->solo_lanes != 0,
-                                 k.rebin[ri] != 0, dc, k.T, k.R));
+        HIP_TRY(launch_transport(st, ri, (int)k.pass[ri].blocks, 64 * (int)k.pass[ri].wide, k.lds[ri] != 0,
+                                 ri == 1 && k.bricks, ctx->solo_lanes != 0, k.rebin[ri] != 0, dc, k.T, k.R));
         return GDPM_OK;
     };
     gdpm_status s;
     const int setup = (k.rebin[0] ? 0 : 1) | (k.fused && !k.rebin[1] ? 2 : 0);
-    HIP_TRY(launch_begin(st, dc, k.R, ctx->h_step, M.hdr, M.segs, setup, k.lone, waves[0], waves[1]));
+    HIP_TRY(launch_begin(st, dc, k.R, ctx->h_step, M.hdr, M.segs, setup, k.lone, k.pass[0], k.pass[1]));
     for (int ri = 0; ri < 2; ++ri)
         if (k.src_blocks[ri])
             HIP_TRY(launch_source(st, k.src_blocks[ri], dc, k.R, M.segs + ri * (kMaxSegs / 2), M.hdr + ri, ri));
@@ -1300,10 +1313,11 @@ gdpm_status Engine::issue(const StepGraphKey& k) {
     if (k.fused) {
         // both queues set up, then one launch runs both passes
         if ((s = rebin(1))) return s;
-        HIP_TRY(launch_fused(st, k.blocks, k.threads[1], k.photon_waves, k.rebin[0] || k.rebin[1], dc, k.T, k.R));
+        HIP_TRY(launch_fused(st, (int)k.pass[1].blocks, 64 * (int)k.pass[1].wide, k.photon_waves, k.bricks != 0,
+                             k.rebin[0] || k.rebin[1], dc, k.T, k.R));
     } else {
         if ((s = pass(0))) return s;
-        HIP_TRY(launch_mid(st, dc, k.R, !k.rebin[1], k.lone, waves[1]));
+        HIP_TRY(launch_mid(st, dc, k.R, !k.rebin[1], k.lone, k.pass[1]));
         if ((s = rebin(1))) return s;
         if ((s = pass(1))) return s;
     }
@@ -1364,6 +1378,9 @@ gdpm_status Engine::compute_stats(EJob* j) {
     a.red = M.stats;
     a.slots = j->tally_p;
     a.nvox = j->nv;
+    a.brick = j->brick();
+    a.nx = j->ph->nx;
+    a.ny = j->ph->ny;
     a.vox = j->ph->vox.as<const uint32_t>();
     a.vvox = j->ph->dx * j->ph->dy * j->ph->dz;
     a.dose = j->d_dose;
@@ -1568,6 +1585,7 @@ gdpm_status run_job(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gd
                         "of the scratch memory", (size_t)j->plan.nb * j->nv * sizeof(double), j->plan.nb,
                         j->nv, kScratchTallyBytes);
     }
+    j->plain_tally = h_batch != nullptr;
     if (h_hist) HIP_TRY(j->hist.alloc(ctx->pool, j->plan.n_hist * 2 * sizeof(double)));
     Engine E;
     s = E.init(ctx, st, j->plan, scr ? &sm : nullptr);

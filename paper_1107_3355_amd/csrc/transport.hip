@@ -181,6 +181,13 @@ GDPM_DEV void rng_start(Rng& r, uint32_t hlo, uint32_t hhi, uint32_t path, uint3
     r.nb = ctr >> 2;
 }
 
+// The wavefront's lanes exchange data in LDS here: no LDS access moves across (they
+// complete in order).
+GDPM_DEV void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // with the wavefront converged: n <= 4 draws in the lanes of `want`; every lane
 // of `live` that holds fewer than two blocks gets one in each turn (a fresh
 // stream may need two)
@@ -281,6 +288,8 @@ struct ElecLds {
     const GDPM_LDS f2* rh;                      // [mat][eg_n] range, mu_hard
     const GDPM_LDS float* lam;                  // [mat][eg_n] 1/lambda_1
     const GDPM_LDS float* rinv;                 // [mat][nr], then the scales [mat]
+    const GDPM_LDS float* aw;                   // [aw_n] (a global load in a step would wait for
+                                                // the wavefront's tally additions before it)
     GDPM_DEV f2 range_hard(int i, float t) const {
         const f2 a = rh[i], b = rh[i + 1];
         return f2{fmaf(t, b.x - a.x, a.x), fmaf(t, b.y - a.y, a.y)};
@@ -295,6 +304,7 @@ struct ElecGlobal {
     const GDPM_GLOBAL f4* tab;
     const GDPM_GLOBAL float* rinv;
     const GDPM_GLOBAL float* rscale;
+    const GDPM_GLOBAL float* aw;
     GDPM_DEV f2 range_hard(int i, float t) const {
         const f4 a = tab[i], b = tab[i + 1];
         return f2{fmaf(t, b.x - a.x, a.x), fmaf(t, b.y - a.y, a.y)};
@@ -313,11 +323,9 @@ struct ElecGlobal {
 struct ElecGrid {
     float lo, inv, aw_lo, aw_inv;
     int n, nr, aw_n;
-    const GDPM_GLOBAL float* aw;
     template <class TT>
     GDPM_DEV explicit ElecGrid(const TT& T)
-        : lo(T.eg_lo), inv(T.eg_inv), aw_lo(T.aw_lo), aw_inv(T.aw_inv), n(T.eg_n), nr(T.nr), aw_n(T.aw_n),
-          aw(global_ptr(T.aw)) {}
+        : lo(T.eg_lo), inv(T.eg_inv), aw_lo(T.aw_lo), aw_inv(T.aw_inv), n(T.eg_n), nr(T.nr), aw_n(T.aw_n) {}
     // cell of energy e of material m
     GDPM_DEV void cell(int m, float e, int& i, float& t) const {
         grid(hlog2(e), lo, inv, n, i, t);
@@ -336,16 +344,18 @@ GDPM_DEV float rinv_scale(const ElecLds& E, const ElecGrid& g, int n_mat, int m)
 GDPM_DEV float rinv_scale(const ElecGlobal& E, const ElecGrid&, int, int m) { return E.rscale[m]; }
 
 // screening A of the modified-Wentzel law for t = s / lambda_1 (t < t_iso)
-GDPM_DEV float mw_screening(const ElecGrid& g, float tt) {
+template <class P>
+GDPM_DEV float mw_screening(const ElecGrid& g, P aw, float tt) {
     const float f = fminf((hlog2(tt) - g.aw_lo) * g.aw_inv, (float)(g.aw_n - 1));
     const int i = min(max((int)f, 0), g.aw_n - 2);  // f < 0 extrapolates the first cell
-    return hexp2(lerp1(g.aw, i, f - (float)i));
+    return hexp2(lerp1(aw, i, f - (float)i));
 }
 
 // modified-Wentzel deflection mu = (1 - cos)/2 for t = s / lambda_1
-GDPM_DEV float mw_mu(const ElecGrid& g, float tt, float u) {
+template <class P>
+GDPM_DEV float mw_mu(const ElecGrid& g, P aw, float tt, float u) {
     if (!(tt < kMwIsoF)) return u;
-    const float a = mw_screening(g, tt);
+    const float a = mw_screening(g, aw, tt);
     return fdiv(a * u, 1.0f + a - u);
 }
 
@@ -648,6 +658,9 @@ GDPM_DEV const GDPM_CONST RingCtl* ring_const(Args A, int ri) {
     return &((const GDPM_CONST Ctl*)A->ctl)->ring[ri];
 }
 
+// the wavefronts that work in the pass (the first group_waves of each workgroup)
+GDPM_DEV uint32_t pass_waves(Args A, int ri) { return gridDim.x * ring_const(A, ri)->group_waves; }
+
 // ---------------------------------------------------------------------------
 // queue reservation and claiming (wave-uniform state)
 // ---------------------------------------------------------------------------
@@ -790,8 +803,9 @@ GDPM_DEV void load_job(WJob& w, Args A, int j, int ri) {
 GDPM_DEV int first_job(Args A, uint32_t total, int ri) {
     if (total == 0) return -1;
     const GDPM_CONST JobCtl* jc = (const GDPM_CONST JobCtl*)A->R.jc;
-    const uint32_t waves = gridDim.x * (blockDim.x >> 6);
-    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    const uint32_t waves = pass_waves(A, ri);
+    const uint32_t w =
+        __builtin_amdgcn_readfirstlane(blockIdx.x * ring_const(A, ri)->group_waves + (threadIdx.x >> 6));
     const uint32_t pos = (uint32_t)(((unsigned long long)w * total + total / 2) / waves);
     int lo = 0, hi = A->R.n_jobs - 1;   // last job whose segment starts at or before pos
     while (lo < hi) {
@@ -844,12 +858,34 @@ struct ClaimState {
 // deposits go to the batch slot `pb` of the particle's history; a split job's
 // particles are tallied at weight 1 and the host scales the sums by 2^-split
 // (exact: a power of two commutes with every rounding of the sum)
-GDPM_DEV void add_dose(JobPtr J, uint32_t pb, int v, double de, const Rng& r) {
-    atomic_add_f64(global_ptr(J->tally) + ((unsigned long long)pb * J->nv + (unsigned)v), de);
+GDPM_DEV void add_history(JobPtr J, double de, const Rng& r) {
     if (J->hist) {
         const unsigned long long h = ((unsigned long long)r.hhi << 32 | r.hlo) - J->hist0;
         atomic_add_f64(global_ptr(J->hist) + 2 * h, de);
     }
+}
+GDPM_DEV void add_dose(JobPtr J, uint32_t pb, uint32_t pos, double de, const Rng& r) {
+    atomic_add_f64(global_ptr(J->tally) + ((unsigned long long)pb * J->nv + pos), de);
+    add_history(J, de, r);
+}
+
+// positions in a tally (see Brick)
+struct TallyOrder {
+    int mx, my, mz, sy, sz, s;   // widths less one; the voxel's bit positions; log2 of the brick's size
+    int nbx, nby;                // bricks along x and y
+    GDPM_DEV TallyOrder(int x, int y, int z, int nx, int ny)
+        : mx(x), my(y), mz(z), sy(x), sz(x + y), s(x + y + z), nbx(nx >> x), nby(ny >> y) {}
+    GDPM_DEV uint32_t brick(int ix, int iy, int iz) const {
+        return (uint32_t)((ix >> mx) + nbx * ((iy >> my) + nby * (iz >> mz)));
+    }
+    GDPM_DEV uint32_t voxel(int ix, int iy, int iz) const {   // in its brick
+        return (uint32_t)((ix & mx) | (iy & my) << sy | (iz & mz) << sz);
+    }
+    GDPM_DEV uint32_t pos(int ix, int iy, int iz) const { return brick(ix, iy, iz) << s | voxel(ix, iy, iz); }
+};
+template <class J>
+GDPM_DEV TallyOrder tally_order(const J& job, int nx, int ny) {
+    return TallyOrder(job.brick.mx, job.brick.my, job.brick.mz, nx, ny);
 }
 
 // energy leaving the phantom: per-history output (test mode)
@@ -1113,19 +1149,21 @@ GDPM_DEV void push_photons(const PendPhoton& q, PushState& ps, Args A, JobPtr J,
 // particles: the whole queue, empty slots included, is that job's segment and
 // the other jobs' segments are empty (they start at its end, so that a
 // wavefront's first job is `lone`)
-// `waves`: the wavefronts of the pass.  In a pass of one job's queue, read as
+// In a pass of one job's queue, read as
 // it is, wavefront w starts with records [w first, (w + 1) first) of the
 // segment, without claiming them, and claims begin after those of the last.
 GDPM_DEV uint32_t claim_size(uint32_t left, uint32_t waves, int ri) {
     return min(max(left / (2u * waves), kClaimMin), ri == 0 ? kClaimMaxPhoton : kClaimMaxElectron);
 }
-GDPM_DEV void setup_pass(Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, uint32_t waves) {
+GDPM_DEV void setup_pass(Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, PassGrid grid) {
     JobCtl* jc = R.jc;
     RingCtl& r = ctl->ring[ri];
     // a permuted pass reads positions [0, n_valid) of the permutation; its
     // records stay in [head, tail), which it consumes whole
     const bool perm = rebinned && r.permuted;
     const uint32_t count = ctl->overflow ? 0u : (perm ? ctl->n_valid : r.tail - r.head);
+    const uint32_t group_waves = count >= kWideMin * 64u * grid.blocks * grid.wide ? grid.wide : grid.narrow;
+    const uint32_t waves = grid.blocks * group_waves;
     if (!rebinned)
         for (int j = threadIdx.x; j < R.n_jobs; j += blockDim.x) {
             jc->seg_begin[ri][j] = j <= lone ? 0u : count;
@@ -1146,6 +1184,7 @@ GDPM_DEV void setup_pass(Ctl* ctl, const RunDev& R, int ri, int rebinned, int lo
     if (threadIdx.x == 0) {
         r.begin = perm ? 0u : r.head;
         r.count = count;
+        r.group_waves = group_waves;
         const uint32_t claim = claim_size(count, waves, ri);
         r.first = rebinned ? 0u : claim;
         r.push = min(max(claim, kPushMin), kPushMax);
@@ -1153,8 +1192,8 @@ GDPM_DEV void setup_pass(Ctl* ctl, const RunDev& R, int ri, int rebinned, int lo
         if (!perm) r.permuted = 0u;
     }
 }
-__global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int rebinned, int lone, uint32_t waves) {
-    setup_pass(ctl, R, ri, rebinned, lone, waves);
+__global__ void __launch_bounds__(256) k_setup(Ctl* ctl, RunDev R, int ri, int rebinned, int lone, PassGrid grid) {
+    setup_pass(ctl, R, ri, rebinned, lone, grid);
 }
 
 // completion of a pass, by the first wavefront of a workgroup; clock: the slot of
@@ -1216,7 +1255,7 @@ GDPM_DEV unsigned long long fresh(const unsigned long long* p) {
 
 // setup: bit ri set: also set up pass ri (a pass that is not re-binned first)
 __global__ void __launch_bounds__(256) k_begin(Ctl* ctl, RunDev R, const StepHost* h, SrcHdr* hdr, SrcSeg* segs,
-                                               int setup, int lone, uint32_t waves0, uint32_t waves1) {
+                                               int setup, int lone, PassGrid grid0, PassGrid grid1) {
     __shared__ uint32_t n[2];
     if (threadIdx.x < 2) {
         const int ri = threadIdx.x;
@@ -1240,14 +1279,14 @@ __global__ void __launch_bounds__(256) k_begin(Ctl* ctl, RunDev R, const StepHos
         unsigned long long* d = reinterpret_cast<unsigned long long*>(segs + ri * kCap);
         for (uint32_t i = threadIdx.x; i < n[ri] * kWords; i += blockDim.x) d[i] = q[i];
     }
-    if (setup & 1) setup_pass(ctl, R, 0, 0, lone, waves0);
-    if (setup & 2) setup_pass(ctl, R, 1, 0, lone, waves1);
+    if (setup & 1) setup_pass(ctl, R, 0, 0, lone, grid0);
+    if (setup & 2) setup_pass(ctl, R, 1, 0, lone, grid1);
 }
 
 // between the passes: completion of the photon pass, set-up of the electron pass
-__global__ void __launch_bounds__(256) k_mid(Ctl* ctl, RunDev R, int setup, int lone, uint32_t waves) {
+__global__ void __launch_bounds__(256) k_mid(Ctl* ctl, RunDev R, int setup, int lone, PassGrid grid) {
     finish_pass(ctl, R.jc, 0, 0);
-    if (setup) setup_pass(ctl, R, 1, 0, lone, waves);
+    if (setup) setup_pass(ctl, R, 1, 0, lone, grid);
 }
 
 // the end of an iteration; fused: one launch ran both passes
@@ -1328,7 +1367,7 @@ GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
     GDPM_GLOBAL Ctl* ctl = global_ptr(A->ctl);
     GDPM_GLOBAL JobCtl* jc = global_ptr(A->R.jc);
     const uint32_t count = W.seg_count;
-    const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+    const uint32_t waves = pass_waves(A, ri);
     const uint32_t left = count - min(cs.seen, count);
     const uint32_t chunk = claim_size(left, waves, ri);
     if (load_agent(&ctl->overflow)) {   // a queue overflowed: the run is void
@@ -1354,21 +1393,23 @@ GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
 // the claims of a wavefront that starts on a job; `first`: what it takes
 // without claiming (see k_setup).  The wavefronts of a workgroup start far apart
 // in the segment, so that a small pass spreads over the CUs.
-GDPM_DEV ClaimState claim_start(const WJob& W, uint32_t first) {
+GDPM_DEV ClaimState claim_start(const WJob& W, uint32_t first, uint32_t waves) {
     ClaimState cs{0u, 0u, 0u, false, 0u, 0u};
     if (first) {
         const uint32_t w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
         cs.next = min(w * first, W.seg_count);
         cs.end = min(cs.next + first, W.seg_count);
-        cs.seen = gridDim.x * (blockDim.x >> 6) * first;
+        cs.seen = waves * first;
         cs.done = cs.next == cs.end;
     }
     return cs;
 }
 
-// Records of the wave's claimed chunk are staged in its LDS slice (kStage
-// records, 64 bytes each) by direct-to-LDS loads issued right after a refill,
-// so the next refills read them from LDS instead of waiting for memory.
+// Records of a photon wavefront's claimed chunk are staged in its LDS slice
+// (kStage records, 64 bytes each) by direct-to-LDS loads issued right after a
+// refill, so the next refills read them from LDS instead of waiting for memory.
+// (The electron pass waits for them: staged, its 12 wavefronts took as long, and
+// 16 records a wavefront were worth 0.3% to 16 wavefronts.)
 constexpr uint32_t kStage = 32;
 constexpr uint32_t kStageLow = 16;   // restage when fewer staged records are left
 
@@ -1686,18 +1727,25 @@ __global__ void __launch_bounds__(256) k_source(SourceArgs) {
 // per CU shares them.
 extern __shared__ f4 lds_tables[];
 
-// Layout (float4 units): the workgroup's counters; the tables (photons: the total cross sections, then the
-// majorant of the pass's job; electrons: range and mu_hard, 1/lambda_1, the
-// inverse range and its scales), if staged; then per wavefront one slice of
-// kStage staged records (with the tables) and its lanes' generator words
+// Layout (float4 units): the workgroup's counters; the tables, if staged (photons:
+// the total cross sections, then the majorant of the pass's job; electrons: range and
+// mu_hard, 1/lambda_1, the inverse range and its scales, the screening); then per
+// wavefront one slice: kStage staged records (photons, with the tables), its lanes'
+// generator words and the brick sums (electrons, if there is room)
 constexpr uint32_t kRingF4 = kRngWords * 64u / 4u;   // generator words of a wavefront
 template <class TT>
 GDPM_HD uint32_t tables_f4(int ri, const TT& T) {
     const uint32_t floats = ri == 0 ? (uint32_t)((T.n_mat + 1) * T.pg_n)
-                                    : (uint32_t)(T.n_mat * (3 * T.eg_n + T.nr) + T.n_mat);
+                                    : (uint32_t)(T.n_mat * (3 * T.eg_n + T.nr) + T.n_mat + T.aw_n);
     return (floats + 3u) / 4u;
 }
-constexpr uint32_t kSliceF4 = 4u * kStage + kRingF4;
+// an electron wavefront's brick sums, [voxel of the brick][lane] (FP64), and its list
+// of lanes that leave their bricks
+constexpr uint32_t kBrickF4 = kBrickVoxels * 64u / 2u + 64u * 2u / 16u;
+// ri: 0 photons, 1 electrons, 2 both (k_transport: the electron pass's tables)
+GDPM_HD uint32_t slice_f4(int ri, bool staged, bool bricks) {
+    return (ri != 1 && staged ? 4u * kStage : 0u) + kRingF4 + (bricks ? kBrickF4 : 0u);
+}
 
 // the device clock at the start of a pass (its completion takes the difference)
 GDPM_DEV void start_clock(Args A) {
@@ -1727,7 +1775,8 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
     // form has that code: the passes of a lone job keep the plain reads)
     const GDPM_GLOBAL uint32_t* perm_in =
         kPerm && rc->permuted ? global_ptr(bin_perm(A0->R.bin[0], A0->R.mask[0])) : nullptr;
-    const bool big = !kSolo && total >= kTailMinPerLane * gridDim.x * blockDim.x;
+    const uint32_t waves = pass_waves(A0, 0);
+    const bool big = !kSolo && total >= kTailMinPerLane * 64u * waves;
 
     int j = first_job(A0, total, 0);
     uint32_t first = rc->first;
@@ -1752,7 +1801,7 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
         const uint32_t k0 = W.p->k0, k1 = W.p->k1;
         const GDPM_GLOBAL float* gmaj = global_ptr(W.p->mumax);
         const bool hist = W.p->hist != nullptr;
-        ClaimState cs = claim_start(W, first);
+        ClaimState cs = claim_start(W, first, waves);
         first = 0u;
         bool active = false;
         float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0;
@@ -1910,7 +1959,7 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                         }
                         pm = -1;
                     }
-                    if (dep != 0.0) add_dose(J, pb, vv, dep, rng);
+                    if (dep != 0.0) add_dose(J, pb, tally_order(*J, J->G.nx, J->G.ny).pos(ix, iy, iz), dep, rng);
                     wt.dep += count(dep != 0.0);
                     wt.it[0] += count(itype == 1);
                     wt.it[1] += count(itype == 2);
@@ -1987,13 +2036,13 @@ __global__ void __launch_bounds__(768) k_photon(PassArgs) {
             }
         }
         __syncthreads();
-        GDPM_LDS f4* slice = lds + tables_f4(0, T) + wave * kSliceF4;
+        GDPM_LDS f4* slice = lds + tables_f4(0, T) + wave * slice_f4(0, true, false);
         photon_pass<kSolo, kPerm, true, !kPerm>(A, PhotLds{tot}, lmaj, slice, (GDPM_LDS float*)(slice + 4u * kStage),
                                                 group);
     } else {
         __syncthreads();
         photon_pass<kSolo, kPerm, false, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, nullptr,
-                                                (GDPM_LDS float*)(lds + wave * kRingF4), group);
+                                                (GDPM_LDS float*)(lds + wave * slice_f4(0, false, false)), group);
     }
     group_flush(A, group);
 }
@@ -2003,15 +2052,34 @@ __global__ void __launch_bounds__(768) k_photon(PassArgs) {
 // iteration (section 2.1)
 // ---------------------------------------------------------------------------
 // One wavefront's share of an electron pass.  E: the stopping and scattering
-// data and the inverse range (in LDS or global memory); stage: the wavefront's LDS slice for staged records (kStaged);
-// ring: its generator words.
-template <bool kSolo, bool kPerm, bool kStaged, class EL>
-GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS float* ring, GroupPtr group) {
+// data and the inverse range (in LDS or global memory); ring: the wavefront's
+// generator words, and behind them its brick sums (if A0->bricks).
+//
+// A deposit added to the tally as the particle left its voxel made the pass wait
+// for the additions: 307 M of them took 13.1 of 15.9 ms on a CT of 0.2 cm voxels,
+// where the rest of the pass takes 10.8.  Now a particle's deposits are summed per
+// voxel in LDS while it stays in a brick of the tally (see Brick), and when it
+// leaves, as many lanes as the brick has voxels add the sums in one instruction, one
+// line of memory.  A particle that leaves with one deposit adds it itself.  Bricks of
+// 2x2x2 voxels leave room for 14 wavefronts and not for the screening table (a
+// lookup of it in global memory waits for the additions before it), those of 4 voxels
+// for 16 with it: what took 15.9, 10.2, 4.6 and 18.4 ms (5e7 photons on CTs of 0.2 and
+// 0.4 cm, 2e7 photons and 5e6 electrons on 0.3 cm slabs) took 13.1, 9.9, 4.4 and 12.5
+// with the former and takes 12.5, 8.9, 4.0 and 13.8 with the latter.  What bounds it now is
+// vector instructions (71% of the cycles) with half of their lanes at work, and
+// the latencies between them.
+template <bool kSolo, bool kPerm, class EL>
+GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr group) {
+    GDPM_LDS double* const sums = (GDPM_LDS double*)(ring + 4u * kRingF4);
+    GDPM_LDS uint16_t* const leavers = (GDPM_LDS uint16_t*)(sums + kBrickVoxels * 64u);
+    if (A0->bricks)
+        for (int i = 0; i < kBrickVoxels; ++i) sums[64u * i + lane_id()] = 0.0;
     const GDPM_CONST RingCtl* rc = ring_const(A0, 1);
     const uint32_t begin = rc->begin, total = rc->count;
     const GDPM_GLOBAL uint32_t* perm_in =
         kPerm && rc->permuted ? global_ptr(bin_perm(A0->R.bin[1], A0->R.mask[1])) : nullptr;
-    const bool big = !kSolo && total >= kTailMinPerLane * gridDim.x * blockDim.x;
+    const uint32_t waves = pass_waves(A0, 1);
+    const bool big = !kSolo && total >= kTailMinPerLane * 64u * waves;
 
     int j = first_job(A0, total, 1);
     uint32_t first = rc->first;
@@ -2033,7 +2101,9 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS fl
         const GDPM_GLOBAL uint32_t* vox = reread(global_ptr(W.p->G.vox));
         const uint32_t k0 = W.p->k0, k1 = W.p->k1;
         const bool no_ms = (W.p->flags & 8u) != 0u;
-        ClaimState cs = claim_start(W, first);
+        const TallyOrder O = tally_order(*W.p, nx, ny);
+        const bool sum_bricks = A0->bricks && O.s > 0;
+        ClaimState cs = claim_start(W, first, waves);
         first = 0u;
         bool active = false;
         float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0, nh = -1.0f;
@@ -2047,11 +2117,34 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS fl
         rng.buf = ring + lane_id();
         rng_start(rng, 0u, 0u, 0u, 0u);
         int next = -1;
+        bool summed = false;    // the lane's brick has sums in LDS
+        // Add the sums of the lanes of `leave` (their brick: b) to the tally, one lane
+        // per voxel, and clear them; the wavefront is converged.
+        auto flush_bricks = [&](JobPtr J, bool leave, uint32_t b) {
+            const uint64_t m = ballot(leave);
+            const uint32_t n = (uint32_t)__popcll(m);
+            if (leave) leavers[mbcnt(m)] = (uint16_t)(lane_id() | pb << 6);
+            wave_fence();
+            GDPM_GLOBAL double* const tally = global_ptr(J->tally);
+            const uint32_t nv = (uint32_t)J->nv;   // (positions fit 31 bits)
+            for (uint32_t k = 0; k < n; k += 64 / kBrickVoxels) {
+                const uint32_t g = k + lane_id() / kBrickVoxels, v = lane_id() % kBrickVoxels;
+                const uint32_t l = leavers[min(g, n - 1u)];
+                const uint32_t lb = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(l << 2), (int)b);
+                GDPM_LDS double* q = sums + 64u * v + (l & 63u);
+                const double d = *q;
+                if (g < n && d != 0.0) {
+                    *q = 0.0;
+                    atomic_add_f64(tally + ((unsigned long long)(l >> 6) * nv + (lb << O.s | v)), d);
+                }
+            }
+            wave_fence();
+        };
         for (;;) {
             const Args A = reread(A0);
             const JobPtr J = reread(W.p);
             Rec p;
-            if (refill<kSolo, kPerm, kStaged>(active, cs, A, W, 1, begin, perm_in, p, wt, stage)) {
+            if (refill<kSolo, kPerm, false>(active, cs, A, W, 1, begin, perm_in, p, wt, nullptr)) {
                 x = p.a.x; y = p.a.y; z = p.a.z; e = p.a.w;
                 u = p.b.x; v = p.b.y; w = p.b.z; nh = p.b.w;
                 ix = (int)(p.d.x & 2047u);
@@ -2080,8 +2173,9 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS fl
                 wt.events += count(step);
                 // a step draws at most 4 numbers, the first for a fresh hard-event distance
                 rng_topup(rng, step, active, 4u, k0, k1);
-                const int vv = ix + nx * (iy + ny * iz);   // voxel of the step
+                const uint32_t brick = O.brick(ix, iy, iz), vin = O.voxel(ix, iy, iz);   // voxel of the step
                 bool crossed = false;
+                bool left = false;   // the brick
                 if (step) {
                     const float rho = voxel_density(vx);
                     const int m = voxel_material(vx);
@@ -2127,7 +2221,7 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS fl
                             const float tmid = 0.5f * (t0 + tend);
                             eg.cell(m, tmid, ci, ct);
                             const float tt = s * rho * E.inv_lambda(ci, ct);
-                            const float mu = mw_mu(eg, tt, rng.draw());
+                            const float mu = mw_mu(eg, E.aw, tt, rng.draw());
                             const float turns = rng.draw();
                             rotate(u, v, w, 1.0f - 2.0f * mu, 2.0f * hsqrt(mu * (1.0f - mu)), turns);
                         }
@@ -2154,6 +2248,7 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS fl
                         const float ha = a0 ? G.dx : (a1 ? G.dy : G.dz);
                         const int in = da > 0.0f ? ia + 1 : ia - 1;
                         const float pa = (float)(da > 0.0f ? in : ia) * ha;
+                        left = ((in ^ ia) & ~(a0 ? O.mx : (a1 ? O.my : O.mz))) != 0;
                         x = a0 ? pa : x;
                         y = a1 ? pa : y;
                         z = a0 || a1 ? z : pa;
@@ -2260,9 +2355,21 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS fl
                 // the deposit of a voxel goes to the tally when the particle leaves
                 // the voxel or ends
                 const bool flush = (crossed || absorb) && de != 0.0;
+                const bool leave = left || !active;
                 if (flush) {
-                    add_dose(J, pb, vv, de, rng);
+                    if (!sum_bricks || (leave && !summed)) {
+                        add_dose(J, pb, brick << O.s | vin, de, rng);
+                    } else {
+                        lds_add(sums + 64u * vin + lane_id(), de);
+                        add_history(J, de, rng);
+                        summed = true;
+                    }
                     de = 0.0;
+                }
+                if (ballot(leave && summed)) {
+                    wave_fence();
+                    flush_bricks(J, leave && summed, brick);
+                    summed = summed && !leave;
                 }
                 wt.dep += count(flush);
                 wt.died += (uint32_t)__popcll(act0 & ~ballot(active));
@@ -2301,13 +2408,12 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS f4* stage, GDPM_LDS fl
             }
         }
         // deposits of the particles handed on (or ended by the bound), in their voxels
-        if (de != 0.0) add_dose(W.p, pb, ix + nx * (iy + ny * iz), de, rng);
+        if (de != 0.0) add_dose(W.p, pb, O.pos(ix, iy, iz), de, rng);
         wt.dep += count(de != 0.0);
+        if (ballot(summed)) flush_bricks(W.p, summed, O.brick(ix, iy, iz));
         job_flush(e_esc, wt, W.j, group);
         j = next;
     }
-    // no staging load may still be writing the slice when the wave moves on
-    if constexpr (kStaged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     release(pe, A0, 1);
     release(pg, A0, 0);
     pass_finish(wt, 1, group);
@@ -2326,12 +2432,14 @@ GDPM_DEV ElecLds stage_electron_tables(const GDPM_CONST Tables& T, GDPM_LDS f4* 
     }
     for (int i = threadIdx.x; i < nr; i += blockDim.x) lr[i] = global_ptr(T.rinv)[i];
     for (int i = threadIdx.x; i < T.n_mat; i += blockDim.x) lr[nr + i] = global_ptr(T.rinv_scale)[i];
+    GDPM_LDS float* aw = lr + nr + T.n_mat;
+    for (int i = threadIdx.x; i < T.aw_n; i += blockDim.x) aw[i] = global_ptr(T.aw)[i];
     __syncthreads();
-    return ElecLds{rh, lam, lr};
+    return ElecLds{rh, lam, lr, aw};
 }
 
 template <bool kLds, bool kSolo, bool kPerm>
-__global__ void __launch_bounds__(768) k_electron(PassArgs) {
+__global__ void __launch_bounds__(1024) k_electron(PassArgs) {
     const Args A = pass_args();
     start_clock(A);
     if (!kPerm && group_idle(A, 1)) return;
@@ -2341,13 +2449,15 @@ __global__ void __launch_bounds__(768) k_electron(PassArgs) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (kLds) {
         const ElecLds E = stage_electron_tables(A->T, lds);
-        GDPM_LDS f4* slice = lds + tables_f4(1, A->T) + wave * kSliceF4;
-        electron_pass<kSolo, kPerm, true>(A, E, slice, (GDPM_LDS float*)(slice + 4u * kStage), group);
+        if (wave < ring_const(A, 1)->group_waves)
+            electron_pass<kSolo, kPerm>(
+                A, E, (GDPM_LDS float*)(lds + tables_f4(1, A->T) + wave * slice_f4(1, true, A->bricks)), group);
     } else {
         __syncthreads();
-        electron_pass<kSolo, kPerm, false>(
-            A, ElecGlobal{global_f4(A->T.elec), global_ptr(A->T.rinv), global_ptr(A->T.rinv_scale)}, nullptr,
-            (GDPM_LDS float*)(lds + wave * kRingF4), group);
+        const ElecGlobal E{global_f4(A->T.elec), global_ptr(A->T.rinv), global_ptr(A->T.rinv_scale),
+                           global_ptr(A->T.aw)};
+        if (wave < ring_const(A, 1)->group_waves)
+            electron_pass<kSolo, kPerm>(A, E, (GDPM_LDS float*)(lds + wave * slice_f4(1, false, A->bricks)), group);
     }
     group_flush(A, group);
 }
@@ -2372,14 +2482,14 @@ __global__ void __launch_bounds__(768) k_transport(PassArgs) {
     group_clear(group);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ElecLds E = stage_electron_tables(A->T, lds);
-    GDPM_LDS f4* slice = lds + tables_f4(1, A->T) + wave * kSliceF4;
+    GDPM_LDS f4* slice = lds + tables_f4(1, A->T) + wave * slice_f4(2, true, A->bricks);
     GDPM_LDS float* ring = (GDPM_LDS float*)(slice + 4u * kStage);
     for (int k = 0; k < 2; ++k) {
         const bool photons = ((int)wave < A->photon_waves) == (k == 0);
         if (photons)
             photon_pass<false, kPerm, true, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, slice, ring, group);
         else
-            electron_pass<false, kPerm, true>(A, E, slice, ring, group);
+            electron_pass<false, kPerm>(A, E, ring, group);
     }
     group_flush(A, group);
 }
@@ -2606,12 +2716,23 @@ __global__ void __launch_bounds__(kStatThreads) k_dose_stats(StatsArgs) {
     GDPM_GLOBAL double* dose = global_ptr(A->dose);
     GDPM_GLOBAL double* sigma = global_ptr(A->sigma);
     const size_t nvox = A->nvox;
+    const TallyOrder O = tally_order(*A, A->nx, A->ny);
     const int nb = A->nb;
     const double min_rho = (double)A->min_rho;
     double emax = 0.0, edep = 0.0, none = 0.0;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox;
          i += (size_t)gridDim.x * blockDim.x) {
-        const double rho = (double)voxel_density(vox[i]);
+        // the voxel whose energies are at position i of the tallies
+        size_t o = i;
+        if (O.s > 0) {
+            const uint32_t b = (uint32_t)(i >> O.s), v = (uint32_t)i;
+            const uint32_t row = b / (uint32_t)O.nbx, bz = row / (uint32_t)O.nby;
+            const uint32_t bx = b - row * (uint32_t)O.nbx, by = row - bz * (uint32_t)O.nby;
+            const uint32_t x = bx << O.mx | (v & O.mx), y = by << O.my | (v >> O.sy & O.my),
+                           z = bz << O.mz | (v >> O.sz & O.mz);
+            o = x + (size_t)A->nx * (y + (size_t)A->ny * z);
+        }
+        const double rho = (double)voxel_density(vox[o]);
         const double im = 1.0 / (rho * A->vvox);
         double mean, s2;
         if (nb == kHeld) {
@@ -2639,8 +2760,8 @@ __global__ void __launch_bounds__(kStatThreads) k_dose_stats(StatsArgs) {
                 voxel_stats(nb, [&](int b) { return slots[(size_t)b * nvox + i] * im * inv[b]; }, mean, s2);
             }
         }
-        if (dose) dose[i] = mean;
-        if (sigma) sigma[i] = nb > 1 ? sqrt(s2 / ((double)nb * (nb - 1))) : 0.0;
+        if (dose) dose[o] = mean;
+        if (sigma) sigma[o] = nb > 1 ? sqrt(s2 / ((double)nb * (nb - 1))) : 0.0;
         if (rho >= min_rho) emax = fmax(emax, mean);
     }
     block_reduce(edep, none, emax);
@@ -2713,12 +2834,12 @@ __global__ void k_test_sample(Tables T, int which, float e, float p1, float p2, 
     } else if (which == 2) {
         a = sample_brems(r, k0, k1, e, p1);
     } else if (which == 3) {
-        a = mw_mu(ElecGrid(T), e, uniform(r, k0, k1));
+        a = mw_mu(ElecGrid(T), global_ptr(T.aw), e, uniform(r, k0, k1));
     } else if (which == 4) {
         float u = 0.0f, v = 0.0f, w = 1.0f;
         const int nh = (int)p2;
         for (int k = 0; k < nh; ++k) {
-            const float mu = mw_mu(ElecGrid(T), e, uniform(r, k0, k1));
+            const float mu = mw_mu(ElecGrid(T), global_ptr(T.aw), e, uniform(r, k0, k1));
             const float turns = uniform(r, k0, k1);
             rotate(u, v, w, 1.0f - 2.0f * mu, 2.0f * hsqrt(mu * (1.0f - mu)), turns);
         }
@@ -2813,7 +2934,7 @@ __global__ void k_test_lookup(Tables T, int which, int m, const float* in, float
     } else if (which == 5) {
         r = range_inv(global_ptr(T.rinv), T.rinv_scale[m], T.nr, m, x);
     } else if (which == 6) {
-        r = mw_screening(ElecGrid(T), x);
+        r = mw_screening(ElecGrid(T), global_ptr(T.aw), x);
     }
     out[i] = r;
 }
@@ -2821,8 +2942,8 @@ __global__ void k_test_lookup(Tables T, int which, int m, const float* in, float
 // ---------------------------------------------------------------------------
 // host launchers (the host runtime calls these; kernels stay in this unit)
 // ---------------------------------------------------------------------------
-hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, int waves) {
-    hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, st, ctl, R, ri, rebinned, lone, (uint32_t)waves);
+hipError_t launch_setup(hipStream_t st, Ctl* ctl, const RunDev& R, int ri, int rebinned, int lone, const PassGrid& grid) {
+    hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, st, ctl, R, ri, rebinned, lone, grid);
     return hipGetLastError();
 }
 hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, const SrcSeg* segs,
@@ -2832,13 +2953,13 @@ hipError_t launch_source(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, 
     return hipGetLastError();
 }
 hipError_t launch_begin(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, SrcHdr* hdr, SrcSeg* segs,
-                        int setup, int lone, int waves0, int waves1) {
-    hipLaunchKernelGGL(k_begin, dim3(1), dim3(256), 0, st, ctl, R, h, hdr, segs, setup, lone, (uint32_t)waves0,
-                       (uint32_t)waves1);
+                        int setup, int lone, const PassGrid& grid0, const PassGrid& grid1) {
+    hipLaunchKernelGGL(k_begin, dim3(1), dim3(256), 0, st, ctl, R, h, hdr, segs, setup, lone, grid0,
+                       grid1);
     return hipGetLastError();
 }
-hipError_t launch_mid(hipStream_t st, Ctl* ctl, const RunDev& R, int setup, int lone, int waves) {
-    hipLaunchKernelGGL(k_mid, dim3(1), dim3(256), 0, st, ctl, R, setup, lone, (uint32_t)waves);
+hipError_t launch_mid(hipStream_t st, Ctl* ctl, const RunDev& R, int setup, int lone, const PassGrid& grid) {
+    hipLaunchKernelGGL(k_mid, dim3(1), dim3(256), 0, st, ctl, R, setup, lone, grid);
     return hipGetLastError();
 }
 hipError_t launch_end(hipStream_t st, Ctl* ctl, const RunDev& R, const StepHost* h, StepMirror* out, int fused) {
@@ -2856,10 +2977,10 @@ hipError_t launch_admit(hipStream_t st, int cus, const JobDev& job, JobDev* jobs
     hipLaunchKernelGGL(k_admit, dim3((unsigned)(need < (size_t)(8 * cus) ? need : (size_t)(8 * cus))), dim3(256), 0, st, a);
     return hipGetLastError();
 }
-// LDS bytes of a pass with `waves` wavefronts per block (`lds`: tables and
-// records staged)
-size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds) {
-    const size_t per_wave = lds ? kSliceF4 : kRingF4;
+// LDS bytes of a pass (ri = 2: both in one launch) with `waves` wavefronts per block
+// (lds: its tables and the photons' records staged; bricks: the electrons' brick sums)
+size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds, bool bricks) {
+    const size_t per_wave = slice_f4(ri, lds, bricks);
     return (kGroupTallyF4 + (lds ? (size_t)tables_f4(ri, T) : 0) + (size_t)waves * per_wave) * sizeof(float4);
 }
 
@@ -2902,23 +3023,22 @@ void launch_transport_form(hipStream_t st, int ri, int blocks, int threads, bool
 // `solo`: the one-particle-per-wavefront measurement form (staged tables only);
 // `permuted`: the pass follows a re-binning by job alone (its input is read
 // through the permutation)
-hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool solo, bool permuted,
-                            Ctl* ctl, const Tables& T, const RunDev& R) {
-    const size_t bytes = transport_lds_bytes(ri, T, threads / 64, lds);
+hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, bool lds, bool bricks, bool solo,
+                            bool permuted, Ctl* ctl, const Tables& T, const RunDev& R) {
+    const size_t bytes = transport_lds_bytes(ri, T, threads / 64, lds, bricks);
     if (solo && !lds) return hipErrorInvalidValue;
-    const PassArgs a{ctl, T, R, 0};
+    const PassArgs a{ctl, T, R, 0, bricks};
     if (permuted)
         launch_transport_form<true>(st, ri, blocks, threads, lds, solo, bytes, a);
     else
         launch_transport_form<false>(st, ri, blocks, threads, lds, solo, bytes, a);
     return hipGetLastError();
 }
-// both passes in one launch (k_transport); its LDS is the electron pass's
-// layout (transport_lds_bytes(1, T, threads / 64, true))
-hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_waves, bool permuted, Ctl* ctl,
-                        const Tables& T, const RunDev& R) {
-    const size_t bytes = transport_lds_bytes(1, T, threads / 64, true);
-    const PassArgs a{ctl, T, R, photon_waves};
+// both passes in one launch (k_transport)
+hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_waves, bool bricks, bool permuted,
+                        Ctl* ctl, const Tables& T, const RunDev& R) {
+    const size_t bytes = transport_lds_bytes(2, T, threads / 64, true, bricks);
+    const PassArgs a{ctl, T, R, photon_waves, bricks};
     if (permuted)
         hipLaunchKernelGGL((k_transport<true>), dim3(blocks), dim3(threads), bytes, st, a);
     else

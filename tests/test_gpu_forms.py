@@ -74,3 +74,64 @@ def test_host_outputs(gctx, side):
     src = I.Source(I.PHOTON, I.mono(2.0), [I.parallel_beam_z(ph, 5.0)])
     g = gpu_run(gctx, ph, src, n_hist=3_000, seed=2, n_batches=2, want_batches=True)
     check_statistics(g, ph, 3_000, nb=2)
+
+
+# the electron pass sums a particle's deposits per brick of the tally, two voxels wide
+# along up to two axes with an even number of voxels; with the batches as an output the
+# tally stays in plain order and every deposit is added by itself
+@pytest.mark.parametrize("opts", ['{}', '{"lds_tables": 0}', '{"fused_passes": 1}',
+                                  '{"rebin_photons": 1, "rebin_electrons": 1}'])
+@pytest.mark.parametrize("n", [(8, 10, 12), (9, 10, 12), (8, 11, 12), (8, 10, 13), (9, 11, 12), (8, 11, 13),
+                               (9, 11, 13), (1, 1, 2), (2, 1, 1), (1, 30, 1)])
+def test_tally_bricks(n, opts):
+    rng = np.random.default_rng(sum(n))
+    d = (0.3, 0.2, 0.25) if n[0] % 2 else (0.2, 0.3, 0.25)
+    ph = I.Phantom(*n, *d, rng.integers(1, 4, n[::-1]).astype(np.uint8), rng.uniform(0.3, 1.6, n[::-1]).astype(np.float32))
+    src = I.Source(I.ELECTRON, I.mono(6.0), [I.parallel_beam_z(ph, min(n[0] * d[0], n[1] * d[1]))])
+    kw = dict(n_hist=20_000, seed=11, n_batches=3)
+    c = G.Context(0, opts=opts, materials=MATS)
+    try:
+        a = gpu_run(c, ph, src, **kw)
+        b = gpu_run(c, ph, src, want_batches=True, **kw)
+    finally:
+        c.close()
+    _same(a, b)
+    np.testing.assert_allclose(a["sigma"], b["sigma"], rtol=1e-9, atol=1e-12 * b["dose"].max())
+    assert balance(a) < 1e-12
+    check_statistics(b, ph, 20_000, nb=3)
+
+
+# tables that leave no room for the brick sums beside them (6 materials), or that
+# are not staged (8)
+@pytest.mark.parametrize("n_mat", [5, 6, 7, 8])
+def test_more_materials(n_mat):
+    mats = (list(MATS) + list(MATS))[:n_mat]
+    n, d = (16, 16, 20), (0.5, 0.5, 0.5)
+    mat = (np.arange(16 * 16 * 20).reshape(n[::-1]) % n_mat).astype(np.uint8)
+    ph = I.Phantom(*n, *d, mat, np.ones(n[::-1], np.float32))
+    src = I.Source(I.PHOTON, I.mono(6.0), [I.parallel_beam_z(ph, 4.0)])
+    res = []
+    for opts in ('{}', '{"lds_tables": 0, "waves_per_cu": 4}'):
+        c = G.Context(0, opts=opts, materials=mats)
+        try:
+            res.append(gpu_run(c, ph, src, n_hist=20_000, seed=4, n_batches=2))
+        finally:
+            c.close()
+    _same(*res)
+
+
+# a pass with 16 records or more per lane of its 16 wavefronts per CU runs them all,
+# one with fewer runs 12 (3 and 4 here): below, at and above the line in one run
+def test_wide_passes():
+    w = I.water_cube_2mev(2_600_000)
+    res = []
+    for opts in ('{"waves_per_cu": 3}', '{"waves_per_cu": 12, "pass_histories": 100000}'):
+        c = G.Context(0, opts=opts, materials=MATS)
+        try:
+            res.append(gpu_run(c, w.phantom, w.source, n_hist=2_600_000, seed=4, n_batches=2))
+        finally:
+            c.close()
+    a, b = res
+    assert physics_events(a) == physics_events(b)
+    rtol = 2 * max(sum(r["deposits"]) for r in res) * np.finfo(float).eps   # any order of all deposits
+    np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
