@@ -15,7 +15,8 @@ constexpr uint32_t kClaimMaxPhoton = 2048;   // a photon record lasts a few shor
 constexpr uint32_t kClaimMaxElectron = 256;  // photon wavefronts claim often: larger chunks keep
                                              // them off the shared claim counter
 constexpr uint32_t kWideMin = 16;       // a pass with this many records per lane uses all
-                                        // wavefronts of its workgroups (see PassGrid)
+                                        // wavefronts of its workgroups (see PassGrid),
+constexpr uint32_t kWideMinJob = 8;     // if each job has this many on average
 constexpr int kMaxBins = 64;            // energy bins of the queue re-binning
 constexpr int kMaxJobs = 256;           // dose jobs transported together
 constexpr int kMaxKeys = 4096;          // re-binning keys (job x energy bin)
@@ -67,13 +68,16 @@ static_assert(sizeof(Particle) == 64, "particle record is 64 bytes");
 // one line are served one after the other (85 million a second, whatever the
 // address in it), and readers of its other words wait with them.
 // The wavefronts of a pass: `wide` per workgroup are launched, and if the pass has
-// fewer than kWideMin records for each of their lanes only the first `narrow` of them
-// work.  Electrons run 16 wavefronts per CU instead of 12, since the pass waits on its
-// dependent table lookups: 19.9 instead of 22.0 ms on passes of 5e6 photons' electrons
-// (CT, 0.4 cm).  With few records they only share them: 24 jobs of 1.2e5 histories took
-// 8.9 ms with 16 and 8.4 with 12, one of 1e5 372 and 343 us.  The line: with 4, 8, 16
-// and 32 records 3e6 split histories took 1.97, 1.87, 1.87 and 1.99 ms, 1e7 histories
-// on slabs 2.33, 2.28, 2.22 and 2.22.
+// fewer than kWideMin records for each of their lanes, or kWideMinJob in each job,
+// only the first `narrow` of them work.  16 wavefronts per CU instead of 12 hide more of
+// the latencies, of the electrons' dependent table lookups and the photons' random
+// voxel reads: on passes of 5e6 histories (CT, 0.4 cm) the electrons took 19.9
+// instead of 22.0 ms and the photons 19.1 instead of 20.7.  With few records the
+// wavefronts only share them: the electrons of 1e5 histories took 372 and 343 us.  The
+// line: with 4, 8, 16 and 32 records the electrons of 3e6 split histories took 1.97, 1.87,
+// 1.87 and 1.99 ms, those of 1e7 histories on slabs 2.33, 2.28, 2.22 and 2.22.  Of
+// several jobs: 24 of 1e5 to 3e6 histories took 6.0 ms (photons) and 8.8 (electrons)
+// with 16 and 5.3 and 7.9 with 12; four of 5e6 237 ms with 16 and 245 with 12.
 struct PassGrid {
     uint32_t blocks, wide, narrow;
 };

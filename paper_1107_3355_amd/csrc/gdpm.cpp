@@ -570,8 +570,8 @@ gdpm_status context_mem(gdpm_context ctx, EngineMem* m) {
 int grid_blocks(gdpm_context ctx) { return std::max(1, ctx->cu_count); }
 
 // persistent grid of a transport pass (ri = 2: of both in one launch): one workgroup per
-// CU of waves_per_cu wavefronts (photons: photon_waves_per_cu; electrons: a third more
-// in passes of many records, see PassGrid); lds: its tables (and the photons' records)
+// CU of waves_per_cu wavefronts (photons: photon_waves_per_cu), a third more in passes
+// of many records (see PassGrid; not of both in one launch); lds: its tables (and the photons' records)
 // are staged; bricks: the electrons' brick sums have room
 struct PassShape {
     PassGrid grid;
@@ -580,7 +580,7 @@ struct PassShape {
 PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri) {
     int narrow = ctx->waves_per_cu;
     if (ri == 0 && ctx->photon_waves_per_cu) narrow = std::min(narrow, ctx->photon_waves_per_cu);
-    const int waves = ri == 1 ? narrow + narrow / 3 : narrow;
+    const int waves = ri < 2 ? narrow + narrow / 3 : narrow;
     const bool lds = ctx->lds_tables && transport_lds_bytes(ri, T, waves, true, false) <= (size_t)ctx->max_lds;
     const bool bricks = ri != 0 && transport_lds_bytes(ri, T, waves, lds, true) <= (size_t)ctx->max_lds;
     return PassShape{{(uint32_t)grid_blocks(ctx), (uint32_t)waves, (uint32_t)narrow}, lds, bricks};

@@ -1162,7 +1162,12 @@ GDPM_DEV void setup_pass(Ctl* ctl, const RunDev& R, int ri, int rebinned, int lo
     // records stay in [head, tail), which it consumes whole
     const bool perm = rebinned && r.permuted;
     const uint32_t count = ctl->overflow ? 0u : (perm ? ctl->n_valid : r.tail - r.head);
-    const uint32_t group_waves = count >= kWideMin * 64u * grid.blocks * grid.wide ? grid.wide : grid.narrow;
+    // of several jobs a wavefront takes one after the other, so it counts what each has
+    const uint32_t lanes = 64u * grid.blocks * grid.wide;
+    static_assert(kMaxJobs <= 256, "one thread per job");
+    const uint32_t jobs =
+        rebinned ? (uint32_t)__syncthreads_count((int)threadIdx.x < R.n_jobs && jc->seg_count[ri][threadIdx.x] > 0u) : 1u;
+    const uint32_t group_waves = count >= kWideMin * lanes && count >= kWideMinJob * jobs * lanes ? grid.wide : grid.narrow;
     const uint32_t waves = grid.blocks * group_waves;
     if (!rebinned)
         for (int j = threadIdx.x; j < R.n_jobs; j += blockDim.x) {
@@ -2013,7 +2018,7 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
 // The kernel's arguments are read through pass_args(); the parameter only
 // declares their layout.
 template <bool kLds, bool kSolo, bool kPerm>
-__global__ void __launch_bounds__(768) k_photon(PassArgs) {
+__global__ void __launch_bounds__(1024) k_photon(PassArgs) {
     const Args A = pass_args();
     start_clock(A);
     if (!kPerm && group_idle(A, 0)) return;
@@ -2037,12 +2042,14 @@ __global__ void __launch_bounds__(768) k_photon(PassArgs) {
         }
         __syncthreads();
         GDPM_LDS f4* slice = lds + tables_f4(0, T) + wave * slice_f4(0, true, false);
-        photon_pass<kSolo, kPerm, true, !kPerm>(A, PhotLds{tot}, lmaj, slice, (GDPM_LDS float*)(slice + 4u * kStage),
-                                                group);
+        if (wave < ring_const(A, 0)->group_waves)
+            photon_pass<kSolo, kPerm, true, !kPerm>(A, PhotLds{tot}, lmaj, slice,
+                                                    (GDPM_LDS float*)(slice + 4u * kStage), group);
     } else {
         __syncthreads();
-        photon_pass<kSolo, kPerm, false, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, nullptr,
-                                                (GDPM_LDS float*)(lds + wave * slice_f4(0, false, false)), group);
+        if (wave < ring_const(A, 0)->group_waves)
+            photon_pass<kSolo, kPerm, false, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, nullptr,
+                                                    (GDPM_LDS float*)(lds + wave * slice_f4(0, false, false)), group);
     }
     group_flush(A, group);
 }

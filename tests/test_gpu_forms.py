@@ -135,3 +135,20 @@ def test_wide_passes():
     assert physics_events(a) == physics_events(b)
     rtol = 2 * max(sum(r["deposits"]) for r in res) * np.finfo(float).eps   # any order of all deposits
     np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
+
+
+# several jobs: 8 records per lane in each of them on average
+@pytest.mark.parametrize("n", [400_000, 1_500_000])
+def test_wide_passes_of_jobs(n):
+    w = I.water_cube_2mev(n)
+    kw = dict(n_hist=n, seed=4, n_batches=2)
+    c = G.Context(0, opts='{"waves_per_cu": 3}', materials=MATS)
+    try:
+        ph, src = c.phantom(w.phantom), c.source(w.source)
+        a = c.run_batch([(ph, src, dict(kw, job_id=k)) for k in range(2)])
+        b = [c.run(ph, src, **dict(kw, job_id=k)) for k in range(2)]
+    finally:
+        c.close()
+    for x, y in zip(a, b):
+        rtol = 2 * max(sum(r["deposits"]) for r in b) * np.finfo(float).eps   # any order of all deposits
+        np.testing.assert_allclose(x["dose"], y["dose"], rtol=rtol, atol=rtol * y["dose"].max())
