@@ -96,6 +96,15 @@ GDPM_DEV T* reread(T* p) {
     return p;
 }
 
+// A wave-uniform value (32 bits, or a pointer) that stays in scalar registers: without
+// it the compiler reads a kernel argument or a field of the job again inside the loop,
+// and each of those scalar loads is waited for.
+template <class T>
+GDPM_DEV T pin(T v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 // ---------------------------------------------------------------------------
 // Philox4x32-10
 // ---------------------------------------------------------------------------
@@ -325,7 +334,8 @@ struct ElecGrid {
     int n, nr, aw_n;
     template <class TT>
     GDPM_DEV explicit ElecGrid(const TT& T)
-        : lo(T.eg_lo), inv(T.eg_inv), aw_lo(T.aw_lo), aw_inv(T.aw_inv), n(T.eg_n), nr(T.nr), aw_n(T.aw_n) {}
+        : lo(pin(T.eg_lo)), inv(pin(T.eg_inv)), aw_lo(pin(T.aw_lo)), aw_inv(pin(T.aw_inv)), n(pin(T.eg_n)),
+          nr(pin(T.nr)), aw_n(pin(T.aw_n)) {}
     // cell of energy e of material m
     GDPM_DEV void cell(int m, float e, int& i, float& t) const {
         grid(hlog2(e), lo, inv, n, i, t);
@@ -1790,21 +1800,21 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
     WaveTally wt{};
     uint32_t iters = 0u;
     bool last_job = !kPerm;   // no other job has records left in this pass
-    const float pg_lo = A0->T.pg_lo, pg_inv = A0->T.pg_inv;
-    const int pg_n = A0->T.pg_n;
+    const float pg_lo = pin(A0->T.pg_lo), pg_inv = pin(A0->T.pg_inv);
+    const int pg_n = pin(A0->T.pg_n);
     // one job at a time: a wavefront switches jobs with all its lanes empty
     while (j >= 0) {
         WJob W;
         load_job(W, A0, j, 0);
         // what a flight needs of the job, in scalar registers: read again in each
         // iteration, every use waited for a scalar load of its own
-        const float idx = W.p->G.idx, idy = W.p->G.idy, idz = W.p->G.idz;
-        const uint32_t lx = __float_as_uint(W.p->G.lx), ly = __float_as_uint(W.p->G.ly),
-                       lz = __float_as_uint(W.p->G.lz);
-        const int nx = W.p->G.nx, ny = W.p->G.ny, nz = W.p->G.nz;
-        const GDPM_GLOBAL uint32_t* vox = reread(global_ptr(W.p->G.vox));
-        const uint32_t k0 = W.p->k0, k1 = W.p->k1;
-        const GDPM_GLOBAL float* gmaj = global_ptr(W.p->mumax);
+        const float idx = pin(W.p->G.idx), idy = pin(W.p->G.idy), idz = pin(W.p->G.idz);
+        const uint32_t lx = pin(__float_as_uint(W.p->G.lx)), ly = pin(__float_as_uint(W.p->G.ly)),
+                       lz = pin(__float_as_uint(W.p->G.lz));
+        const int nx = pin(W.p->G.nx), ny = pin(W.p->G.ny), nz = pin(W.p->G.nz);
+        const GDPM_GLOBAL uint32_t* vox = pin(global_ptr(W.p->G.vox));
+        const uint32_t k0 = pin(W.p->k0), k1 = pin(W.p->k1);
+        const GDPM_GLOBAL float* gmaj = pin(global_ptr(W.p->mumax));
         const bool hist = W.p->hist != nullptr;
         ClaimState cs = claim_start(W, first, waves);
         first = 0u;
@@ -2096,19 +2106,22 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr 
     uint32_t iters = 0u;
     bool last_job = !kPerm;   // no other job has records left in this pass
     const ElecGrid eg(A0->T);
-    const int n_mat = A0->T.n_mat;
-    const float ecut = A0->R.ecut_e;
+    const int n_mat = pin(A0->T.n_mat);
+    const float ecut = pin(A0->R.ecut_e);
     // one job at a time: a wavefront switches jobs with all its lanes empty
     while (j >= 0) {
         WJob W;
         load_job(W, A0, j, 1);
         // what a step needs of the job, in scalar registers (see the photon pass)
-        const Spacing G{W.p->G.dx, W.p->G.dy, W.p->G.dz};
-        const int nx = W.p->G.nx, ny = W.p->G.ny, nz = W.p->G.nz;
-        const GDPM_GLOBAL uint32_t* vox = reread(global_ptr(W.p->G.vox));
-        const uint32_t k0 = W.p->k0, k1 = W.p->k1;
+        const Spacing G{pin(W.p->G.dx), pin(W.p->G.dy), pin(W.p->G.dz)};
+        const int nx = pin(W.p->G.nx), ny = pin(W.p->G.ny), nz = pin(W.p->G.nz);
+        const GDPM_GLOBAL uint32_t* vox = pin(global_ptr(W.p->G.vox));
+        const uint32_t k0 = pin(W.p->k0), k1 = pin(W.p->k1);
         const bool no_ms = (W.p->flags & 8u) != 0u;
         const TallyOrder O = tally_order(*W.p, nx, ny);
+        GDPM_GLOBAL double* const tally = pin(global_ptr(W.p->tally));
+        const uint32_t nv = pin((uint32_t)W.p->nv);   // (positions fit 31 bits)
+        const bool hist = W.p->hist != nullptr;
         const bool sum_bricks = A0->bricks && O.s > 0;
         ClaimState cs = claim_start(W, first, waves);
         first = 0u;
@@ -2127,13 +2140,11 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr 
         bool summed = false;    // the lane's brick has sums in LDS
         // Add the sums of the lanes of `leave` (their brick: b) to the tally, one lane
         // per voxel, and clear them; the wavefront is converged.
-        auto flush_bricks = [&](JobPtr J, bool leave, uint32_t b) {
+        auto flush_bricks = [&](bool leave, uint32_t b) {
             const uint64_t m = ballot(leave);
             const uint32_t n = (uint32_t)__popcll(m);
             if (leave) leavers[mbcnt(m)] = (uint16_t)(lane_id() | pb << 6);
             wave_fence();
-            GDPM_GLOBAL double* const tally = global_ptr(J->tally);
-            const uint32_t nv = (uint32_t)J->nv;   // (positions fit 31 bits)
             for (uint32_t k = 0; k < n; k += 64 / kBrickVoxels) {
                 const uint32_t g = k + lane_id() / kBrickVoxels, v = lane_id() % kBrickVoxels;
                 const uint32_t l = leavers[min(g, n - 1u)];
@@ -2365,17 +2376,17 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr 
                 const bool leave = left || !active;
                 if (flush) {
                     if (!sum_bricks || (leave && !summed)) {
-                        add_dose(J, pb, brick << O.s | vin, de, rng);
+                        atomic_add_f64(tally + ((unsigned long long)pb * nv + (brick << O.s | vin)), de);
                     } else {
                         lds_add(sums + 64u * vin + lane_id(), de);
-                        add_history(J, de, rng);
                         summed = true;
                     }
+                    if (hist) add_history(J, de, rng);
                     de = 0.0;
                 }
                 if (ballot(leave && summed)) {
                     wave_fence();
-                    flush_bricks(J, leave && summed, brick);
+                    flush_bricks(leave && summed, brick);
                     summed = summed && !leave;
                 }
                 wt.dep += count(flush);
@@ -2417,7 +2428,7 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr 
         // deposits of the particles handed on (or ended by the bound), in their voxels
         if (de != 0.0) add_dose(W.p, pb, O.pos(ix, iy, iz), de, rng);
         wt.dep += count(de != 0.0);
-        if (ballot(summed)) flush_bricks(W.p, summed, O.brick(ix, iy, iz));
+        if (ballot(summed)) flush_bricks(summed, O.brick(ix, iy, iz));
         job_flush(e_esc, wt, W.j, group);
         j = next;
     }
