@@ -571,8 +571,8 @@ int grid_blocks(gdpm_context ctx) { return std::max(1, ctx->cu_count); }
 
 // persistent grid of a transport pass (ri = 2: of both in one launch): one workgroup per
 // CU of waves_per_cu wavefronts (photons: photon_waves_per_cu), a third more in passes
-// of many records (see PassGrid; not of both in one launch); lds: its tables (and the photons' records)
-// are staged; bricks: the electrons' brick sums have room
+// of many records (see PassGrid; not of both in one launch) if the LDS has room; lds: its
+// tables are staged; bricks: the electrons' brick sums have room
 struct PassShape {
     PassGrid grid;
     int lds, bricks;
@@ -580,8 +580,10 @@ struct PassShape {
 PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri) {
     int narrow = ctx->waves_per_cu;
     if (ri == 0 && ctx->photon_waves_per_cu) narrow = std::min(narrow, ctx->photon_waves_per_cu);
-    const int waves = ri < 2 ? narrow + narrow / 3 : narrow;
-    const bool lds = ctx->lds_tables && transport_lds_bytes(ri, T, waves, true, false) <= (size_t)ctx->max_lds;
+    int waves = ri < 2 ? narrow + narrow / 3 : narrow;
+    auto fits = [&](int w, bool lds) { return transport_lds_bytes(ri, T, w, lds, false) <= (size_t)ctx->max_lds; };
+    if (ctx->lds_tables && !fits(waves, true) && fits(narrow, true)) waves = narrow;
+    const bool lds = ctx->lds_tables && fits(waves, true);
     const bool bricks = ri != 0 && transport_lds_bytes(ri, T, waves, lds, true) <= (size_t)ctx->max_lds;
     return PassShape{{(uint32_t)grid_blocks(ctx), (uint32_t)waves, (uint32_t)narrow}, lds, bricks};
 }
@@ -1844,7 +1846,7 @@ gdpm_status gdpm_context_create(int hip_device, const char* opts_json, gdpm_cont
     HIP_TRY(hipDeviceGetAttribute(&ctx->cu_count, hipDeviceAttributeMultiprocessorCount, hip_device));
     HIP_TRY(hipDeviceGetAttribute(&ctx->max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, hip_device));
     if (ctx->lds_tables) {
-        // the staged kernels may use all of it (above 64 KB an opt-in is needed)
+        // the kernels may use all of it (above 64 KB an opt-in is needed)
         if (transport_lds_optin((size_t)ctx->max_lds) != hipSuccess) ctx->lds_tables = 0;
         (void)hipGetLastError();
     }

@@ -146,6 +146,7 @@ GDPM_DEV float unit_float(uint32_t x) { return fmaf((float)(x >> 9), 0x1p-23f, 0
 // the wavefront take part, where generating each lane's block as it came due ran
 // the generator in every iteration for about half of them.
 constexpr uint32_t kRngWords = 8;    // draws buffered per lane
+template <uint32_t kCols>
 struct Rng {
     uint32_t hlo, hhi, path;
     uint32_t ctr;                    // next draw
@@ -153,7 +154,7 @@ struct Rng {
     GDPM_LDS float* buf;             // the lane's column of the wavefront's LDS slice
     // draws buffered (negative in a fresh stream that starts inside a block)
     GDPM_DEV int left() const { return (int)(4u * nb - ctr); }
-    GDPM_DEV float peek(uint32_t ahead) const { return buf[((ctr + ahead) & (kRngWords - 1u)) * 64u]; }
+    GDPM_DEV float peek(uint32_t ahead) const { return buf[((ctr + ahead) & (kRngWords - 1u)) * kCols]; }
     // the next draw; the caller has made sure that it is buffered
     GDPM_DEV float draw() {
         const float u = peek(0u);
@@ -165,11 +166,11 @@ struct Rng {
         // the round keys are formed here, not kept in 18 scalar registers
         asm volatile("" : "+s"(k0), "+s"(k1));
         philox(k0, k1, x0, x1, x2, x3);
-        GDPM_LDS float* b = buf + (nb & 1u) * 256u;
+        GDPM_LDS float* b = buf + (nb & 1u) * (4u * kCols);
         b[0] = unit_float(x0);
-        b[64] = unit_float(x1);
-        b[128] = unit_float(x2);
-        b[192] = unit_float(x3);
+        b[kCols] = unit_float(x1);
+        b[2u * kCols] = unit_float(x2);
+        b[3u * kCols] = unit_float(x3);
         nb += 1u;
     }
     // at least n <= 4 draws buffered (in the lanes that call it: a divergent branch)
@@ -179,10 +180,12 @@ struct Rng {
 };
 
 // counter of the next draw
-GDPM_DEV uint32_t rng_ctr(const Rng& r) { return r.ctr; }
+template <uint32_t kCols>
+GDPM_DEV uint32_t rng_ctr(const Rng<kCols>& r) { return r.ctr; }
 
 // position the stream at draw `ctr` (no block generated yet)
-GDPM_DEV void rng_start(Rng& r, uint32_t hlo, uint32_t hhi, uint32_t path, uint32_t ctr) {
+template <uint32_t kCols>
+GDPM_DEV void rng_start(Rng<kCols>& r, uint32_t hlo, uint32_t hhi, uint32_t path, uint32_t ctr) {
     r.hlo = hlo;
     r.hhi = hhi;
     r.path = path;
@@ -200,7 +203,8 @@ GDPM_DEV void wave_fence() {
 // with the wavefront converged: n <= 4 draws in the lanes of `want`; every lane
 // of `live` that holds fewer than two blocks gets one in each turn (a fresh
 // stream may need two)
-GDPM_DEV void rng_topup(Rng& r, bool want, bool live, uint32_t n, uint32_t k0, uint32_t k1) {
+template <uint32_t kCols>
+GDPM_DEV void rng_topup(Rng<kCols>& r, bool want, bool live, uint32_t n, uint32_t k0, uint32_t k1) {
     while (ballot(want && r.left() < (int)n)) {
         if (live && r.nb - (r.ctr >> 2) < 2u) r.fill(k0, k1);
     }
@@ -234,7 +238,8 @@ struct RegRng {
     }
 };
 // the samplers draw from either
-GDPM_DEV float uniform(Rng& r, uint32_t, uint32_t) { return r.draw(); }
+template <uint32_t kCols>
+GDPM_DEV float uniform(Rng<kCols>& r, uint32_t, uint32_t) { return r.draw(); }
 GDPM_DEV float uniform(RegRng& r, uint32_t k0, uint32_t k1) { return r.draw(k0, k1); }
 
 // device-coherent load of a counter, made wave-uniform
@@ -859,7 +864,6 @@ struct ClaimState {
     uint32_t next, end;  // claimed positions of the job's segment not yet handed out
     uint32_t seen;       // the job's claim counter as this wave last saw it
     bool done;           // the job's segment has nothing left to claim
-    uint32_t st_lo, st_hi;  // positions whose records are staged in the wave's LDS slice
 };
 
 // ---------------------------------------------------------------------------
@@ -868,13 +872,15 @@ struct ClaimState {
 // deposits go to the batch slot `pb` of the particle's history; a split job's
 // particles are tallied at weight 1 and the host scales the sums by 2^-split
 // (exact: a power of two commutes with every rounding of the sum)
-GDPM_DEV void add_history(JobPtr J, double de, const Rng& r) {
+template <class R>
+GDPM_DEV void add_history(JobPtr J, double de, const R& r) {
     if (J->hist) {
         const unsigned long long h = ((unsigned long long)r.hhi << 32 | r.hlo) - J->hist0;
         atomic_add_f64(global_ptr(J->hist) + 2 * h, de);
     }
 }
-GDPM_DEV void add_dose(JobPtr J, uint32_t pb, uint32_t pos, double de, const Rng& r) {
+template <class R>
+GDPM_DEV void add_dose(JobPtr J, uint32_t pb, uint32_t pos, double de, const R& r) {
     atomic_add_f64(global_ptr(J->tally) + ((unsigned long long)pb * J->nv + pos), de);
     add_history(J, de, r);
 }
@@ -899,7 +905,8 @@ GDPM_DEV TallyOrder tally_order(const J& job, int nx, int ny) {
 }
 
 // energy leaving the phantom: per-history output (test mode)
-GDPM_DEV void history_escape(JobPtr J, double e, const Rng& r) {
+template <class R>
+GDPM_DEV void history_escape(JobPtr J, double e, const R& r) {
     if (J->hist) {
         const unsigned long long h = ((unsigned long long)r.hhi << 32 | r.hlo) - J->hist0;
         atomic_add_f64(global_ptr(J->hist) + 2 * h + 1, e);
@@ -1110,8 +1117,9 @@ struct PendPhoton {
 };
 
 // a new particle of annihilation energy a (0: an electron or a photon)
+template <class R>
 GDPM_DEV void write_particle(GDPM_GLOBAL f4* q, float x, float y, float z, float e, float u, float v, float w,
-                             const Rng& r, uint32_t path, uint32_t vox, float a, uint32_t job) {
+                             const R& r, uint32_t path, uint32_t vox, float a, uint32_t job) {
     q[0] = f4{x, y, z, e};
     q[1] = f4{u, v, w, -1.0f};
     ((GDPM_GLOBAL u4*)q)[2] = u4{r.hlo, r.hhi, path, 0u};
@@ -1119,8 +1127,9 @@ GDPM_DEV void write_particle(GDPM_GLOBAL f4* q, float x, float y, float z, float
 }
 
 // secondaries inherit the job and the batch slot (`jb`) of their history
+template <class R>
 GDPM_DEV void push_charged(const PendCharged& q, PushState& ps, Args A, JobPtr J, uint32_t jb, float x, float y,
-                           float z, uint32_t vox, const Rng& rng, WaveTally& c) {
+                           float z, uint32_t vox, const R& rng, WaveTally& c) {
     const uint64_t b0 = ballot(q.n >= 1), b1 = ballot(q.n >= 2);
     const uint32_t n0 = (uint32_t)__popcll(b0), n = n0 + (uint32_t)__popcll(b1);
     if (n == 0) return;
@@ -1135,8 +1144,9 @@ GDPM_DEV void push_charged(const PendCharged& q, PushState& ps, Args A, JobPtr J
     c.born += n;
 }
 
+template <class R>
 GDPM_DEV void push_photons(const PendPhoton& q, PushState& ps, Args A, JobPtr J, uint32_t jb, float x, float y,
-                           float z, const Rng& rng, WaveTally& c) {
+                           float z, const R& rng, WaveTally& c) {
     const uint64_t b0 = ballot(q.n >= 1), b1 = ballot(q.n >= 2);
     const uint32_t n0 = (uint32_t)__popcll(b0), n = n0 + (uint32_t)__popcll(b1);
     if (n == 0) return;
@@ -1409,7 +1419,7 @@ GDPM_DEV void claim_refill(ClaimState& cs, Args A, const WJob& W, int ri) {
 // without claiming (see k_setup).  The wavefronts of a workgroup start far apart
 // in the segment, so that a small pass spreads over the CUs.
 GDPM_DEV ClaimState claim_start(const WJob& W, uint32_t first, uint32_t waves) {
-    ClaimState cs{0u, 0u, 0u, false, 0u, 0u};
+    ClaimState cs{0u, 0u, 0u, false};
     if (first) {
         const uint32_t w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
         cs.next = min(w * first, W.seg_count);
@@ -1420,14 +1430,6 @@ GDPM_DEV ClaimState claim_start(const WJob& W, uint32_t first, uint32_t waves) {
     return cs;
 }
 
-// Records of a photon wavefront's claimed chunk are staged in its LDS slice
-// (kStage records, 64 bytes each) by direct-to-LDS loads issued right after a
-// refill, so the next refills read them from LDS instead of waiting for memory.
-// (The electron pass waits for them: staged, its 12 wavefronts took as long, and
-// 16 records a wavefront were worth 0.3% to 16 wavefronts.)
-constexpr uint32_t kStage = 32;
-constexpr uint32_t kStageLow = 16;   // restage when fewer staged records are left
-
 // the queue position of input position `pos` of a pass: itself, or through the
 // permutation of a pass re-binned by job (`perm` non-null); both masked, so
 // that any value reads inside the queue
@@ -1435,40 +1437,15 @@ GDPM_DEV uint32_t input_slot(const GDPM_GLOBAL uint32_t* perm, uint32_t mask, ui
     return (perm ? perm[pos & mask] : pos) & mask;
 }
 
-// stage the records of positions [cs.next, cs.next + kStage) (every lane: 2
-// loads of 16 bytes; lane L of load c fetches piece L % 4 of record 16 c + L / 4,
-// which lands at float4 64 c + L of the slice).  Positions past the chunk are
-// loaded too (the ring index is masked) and never used.  The loads are written
-// out because the compiler orders every later LDS access of the wavefront (table
-// lookups, draws) behind a direct-to-LDS load it knows of; nothing but
-// load_staged reads the slice, after a wait of its own.
-GDPM_DEV void stage_records(ClaimState& cs, GDPM_LDS f4* st, Args A, int ri, uint32_t first,
-                            const GDPM_GLOBAL uint32_t* perm) {
-    // the refill's reads of the slice are complete before it is overwritten
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-    const uint32_t l = lane_id();
-    const uint32_t mask = A->R.mask[ri];
-#pragma unroll
-    for (uint32_t c = 0; c < kStage / 16u; ++c) {
-        const uint32_t rec = 16u * c + (l >> 2);
-        const GDPM_GLOBAL f4* src = record_ptr(A, ri, input_slot(perm, mask, first + cs.next + rec)) + (l & 3u);
-        const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(st + 64u * c));
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");
-    }
-    cs.st_lo = cs.next;
-    cs.st_hi = cs.next + kStage;
-}
-
 // refill the lanes without a particle from the wave's claimed items; returns
 // true in the lanes that loaded a record.  Lanes wait until kRefillMin of them
 // are empty (or no lane is busy): a refill stalls the wavefront on record
-// loads, so it pays to do it for several lanes at once.  With a staging slice
-// (kStaged: `st`, LDS) the records come from it when they are staged.  kSolo (a
+// loads, so it pays to do it for several lanes at once.  kSolo (a
 // measurement form): one particle per wavefront at a time, so the wavefront
 // executes exactly the instructions of that particle's path.
-template <bool kSolo, bool kPerm, bool kStaged>
+template <bool kSolo, bool kPerm>
 GDPM_DEV bool refill(bool active, ClaimState& cs, Args A, const WJob& W, int ri, uint32_t begin,
-                     const GDPM_GLOBAL uint32_t* perm, Rec& p, WaveTally& c, GDPM_LDS f4* st) {
+                     const GDPM_GLOBAL uint32_t* perm, Rec& p, WaveTally& c) {
     if (cs.done) return false;
     const uint64_t need = ballot(!active);
     if (!need) return false;
@@ -1482,23 +1459,13 @@ GDPM_DEV bool refill(bool active, ClaimState& cs, Args A, const WJob& W, int ri,
     const uint32_t rank = mbcnt(need);
     const uint32_t take = kSolo ? min(have, 1u) : min(have, (uint32_t)__popcll(need));
     const uint32_t first = begin + W.seg_begin;
-    const bool staged = kStaged && take > 0u && cs.next >= cs.st_lo && cs.next + take <= cs.st_hi;
-    if (staged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the staging loads have landed
     bool got = false;
     if (!active && rank < take) {
-        if (staged) {
-            const GDPM_LDS f4* q = st + 4u * (cs.next + rank - cs.st_lo);
-            p.a = q[0];
-            p.b = q[1];
-            p.c = ((const GDPM_LDS u4*)q)[2];
-            p.d = ((const GDPM_LDS u4*)q)[3];
-        } else {
-            const GDPM_GLOBAL f4* q = record_ptr(A, ri, input_slot(perm, A->R.mask[ri], first + cs.next + rank));
-            p.a = q[0];
-            p.b = q[1];
-            p.c = ((const GDPM_GLOBAL u4*)q)[2];
-            p.d = ((const GDPM_GLOBAL u4*)q)[3];
-        }
+        const GDPM_GLOBAL f4* q = record_ptr(A, ri, input_slot(perm, A->R.mask[ri], first + cs.next + rank));
+        p.a = q[0];
+        p.b = q[1];
+        p.c = ((const GDPM_GLOBAL u4*)q)[2];
+        p.d = ((const GDPM_GLOBAL u4*)q)[3];
         got = !record_empty(p.a.w);
         if (got && (p.d.w & 0xFFFFu) != W.tag) {
             // a record of another job (or of an earlier job in this slot) in
@@ -1510,11 +1477,6 @@ GDPM_DEV bool refill(bool active, ClaimState& cs, Args A, const WJob& W, int ri,
     }
     cs.next += take;
     c.ld += take;
-    if (kStaged && cs.next < cs.end) {
-        // positions of a pass's segment do not wrap: plain comparisons
-        const uint32_t left = cs.next >= cs.st_lo && cs.next < cs.st_hi ? cs.st_hi - cs.next : 0u;
-        if (left <= kStageLow) stage_records(cs, st, A, ri, first, perm);
-    }
     return got;
 }
 
@@ -1745,8 +1707,8 @@ extern __shared__ f4 lds_tables[];
 // Layout (float4 units): the workgroup's counters; the tables, if staged (photons:
 // the total cross sections, then the majorant of the pass's job; electrons: range and
 // mu_hard, 1/lambda_1, the inverse range and its scales, the screening); then per
-// wavefront one slice: kStage staged records (photons, with the tables), its lanes'
-// generator words and the brick sums (electrons, if there is room)
+// wavefront one slice: its lanes' generator words, then the photons' pool or the
+// electrons' brick sums (if there is room)
 constexpr uint32_t kRingF4 = kRngWords * 64u / 4u;   // generator words of a wavefront
 template <class TT>
 GDPM_HD uint32_t tables_f4(int ri, const TT& T) {
@@ -1757,9 +1719,14 @@ GDPM_HD uint32_t tables_f4(int ri, const TT& T) {
 // an electron wavefront's brick sums, [voxel of the brick][lane] (FP64), and its list
 // of lanes that leave their bricks
 constexpr uint32_t kBrickF4 = kBrickVoxels * 64u / 2u + 64u * 2u / 16u;
-// ri: 0 photons, 1 electrons, 2 both (k_transport: the electron pass's tables)
-GDPM_HD uint32_t slice_f4(int ri, bool staged, bool bricks) {
-    return (ri != 1 && staged ? 4u * kStage : 0u) + kRingF4 + (bricks ? kBrickF4 : 0u);
+// a photon wavefront's pool of photons, [piece][slot], 48 bytes each, the slots'
+// columns, and generator words of as many columns more (see photon_pass)
+constexpr uint32_t kPool = 64u, kPhotonCols = 64u + kPool;
+constexpr uint32_t kPoolF4 = 3u * kPool + kPool / 4u;
+// ri: 0 photons, 1 electrons, 2 both (k_transport)
+GDPM_HD uint32_t slice_f4(int ri, bool bricks) {
+    const uint32_t photons = kRngWords * kPhotonCols / 4u + kPoolF4, electrons = kRingF4 + (bricks ? kBrickF4 : 0u);
+    return ri == 0 || (ri == 2 && photons > electrons) ? photons : electrons;
 }
 
 // the device clock at the start of a pass (its completion takes the difference)
@@ -1779,11 +1746,23 @@ GDPM_DEV bool group_idle(Args A, int ri) {
 // ---------------------------------------------------------------------------
 // One wavefront's share of a photon pass.  ptab: the total cross sections (in
 // LDS or global memory); lmaj: the job's majorant in LDS (kMajLds: a pass of one job; else it
-// is read from global memory); stage: the wavefront's LDS slice for staged
-// records (kStaged); ring: its generator words.
-template <bool kSolo, bool kPerm, bool kStaged, bool kMajLds, class PT>
-GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS f4* stage, GDPM_LDS float* ring,
-                          GroupPtr group) {
+// is read from global memory); ring: the wavefront's generator words and its pool.
+//
+// Vector instructions bound the pass (two thirds of the cycles), and half of them sample
+// interactions, which come in one of four flights.  Sampled as soon as 22 lanes had one,
+// they ran on 26 of 64 lanes and the flights on 50, since the lanes of those waited.
+// In a pass with several photons per lane they are parked instead, in a pool of 64
+// photons in LDS, and the lane goes on with another photon, until there is one for each
+// lane; then the wavefront exchanges the photons in its lanes for parked ones, samples
+// them and flies on, and the exchanged ones are the first that empty lanes take.
+// Interactions run on 60 lanes and flights too: 8.10 instead of 8.49 ms for 5e7
+// photons on a CT of 0.4 cm voxels, 9.25 instead of 9.54 on 0.2 cm, 4.09 instead of 4.21 for
+// 2e7 on slabs.  A photon keeps its buffered draws when it changes places (the column
+// of the generator words goes with it): generated again, they took what the fuller
+// lanes gave.  In a pass with few photons a lane waits: they end before the pool fills,
+// and the exchange cost 8% of it (1e5 photons).
+template <bool kSolo, bool kPerm, bool kMajLds, class PT>
+GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS float* ring, GroupPtr group) {
     const GDPM_CONST RingCtl* rc = ring_const(A0, 0);
     const uint32_t begin = rc->begin, total = rc->count;
     // a re-binned pass reads its input through the permutation (only the kPerm
@@ -1793,6 +1772,8 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
     const uint32_t waves = pass_waves(A0, 0);
     const bool big = !kSolo && total >= kTailMinPerLane * 64u * waves;
 
+    GDPM_LDS f4* const pool = (GDPM_LDS f4*)(ring + kRngWords * kPhotonCols);
+    GDPM_LDS uint32_t* const cols = (GDPM_LDS uint32_t*)(pool + 3u * kPool);
     int j = first_job(A0, total, 0);
     uint32_t first = rc->first;
     PushState pg{0u, 0u, rc->push}, pe{0u, 0u, rc->push};
@@ -1822,15 +1803,19 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
         float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0;
         uint32_t pb = 0u;   // batch slot of the lane's history
         int pm = -1;        // >= 0: a real interaction waits, in a voxel of this material
-        Rng rng;
+        Rng<kPhotonCols> rng;
         rng.buf = ring + lane_id();
+        cols[lane_id()] = kPool + lane_id();
         rng_start(rng, 0u, 0u, 0u, 0u);
         int next = -1;
+        // the pool: photons with an interaction in slots [0, parked), then `ready` ones
+        // without
+        uint32_t parked = 0u, ready = 0u;
         for (;;) {
             const Args A = reread(A0);
             const JobPtr J = reread(W.p);
             Rec p;
-            if (refill<kSolo, kPerm, kStaged>(active, cs, A, W, 0, begin, perm_in, p, wt, stage)) {
+            if (ready == 0u && refill<kSolo, kPerm>(active, cs, A, W, 0, begin, perm_in, p, wt)) {
                 // + 0: a position of -0 becomes +0 (see inside)
                 x = p.a.x + 0.0f; y = p.a.y + 0.0f; z = p.a.z + 0.0f; e = p.a.w;
                 u = p.b.x; v = p.b.y; w = p.b.z;
@@ -1841,17 +1826,14 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                 // absorption energy, or non-finite (only from a damaged record)
                 pm = e < A->R.ecut_g || !(e <= kMaxEnergy) ? kAbsorb : -1;
             }
-            if (!ballot(active)) {
+            if (!ballot(active) && parked + ready == 0u) {
                 if (cs.done && last_job) break;
                 if (!cs.done) continue;
             } else {
-                const uint64_t act0 = ballot(active);
                 const bool fly = active && pm < 0;
                 rng_topup(rng, fly, active, 2u, k0, k1);
                 wt.events += count(fly);
                 const float ul = rng.peek(0u), ua = rng.peek(1u);
-                // energy grid cell of the flight and of a waiting interaction
-                // (the energy is unchanged in between)
                 int gi;
                 float gt;
                 grid(hlog2(e), pg_lo, pg_inv, pg_n, gi, gt);
@@ -1876,6 +1858,7 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                     if (hist) history_escape(J, (double)e, rng);
                     active = false;
                 }
+                wt.died += count(fly && !in);
                 {
                     const int m = voxel_material(vx);
                     const float mu = ptab.total(m * pg_n + gi, gt);
@@ -1883,14 +1866,75 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                     pm = real ? m : pm;   // the interaction waits (see below)
                     wt.real[0] += count(real);
                 }
-                // Real interactions are sampled together once kRealBatch lanes have
-                // one (or the wavefront has no other live lane, or the pass has
-                // nothing left to claim): the lanes of a wavefront share their
-                // sampling code instead of a few running it each iteration.  A lane
-                // waits where it is without drawing, so each particle's draws keep
-                // their order; the cross sections are recomputed from the same inputs.
-                const uint64_t br = ballot(pm >= 0);
-                if (br && (cs.done || (uint32_t)__popcll(br) >= kRealBatch || br == ballot(active))) {
+                const uint64_t br = ballot(active && pm >= 0), bf = ballot(active && pm < 0), be = ballot(!active);
+                const uint32_t nr = (uint32_t)__popcll(br), nf = (uint32_t)__popcll(bf), ne = (uint32_t)__popcll(be);
+                const bool sample =
+                    parked + nr > 0u && (cs.done || nf == 0u || (big ? parked + nr > kPool : nr >= kRealBatch));
+                // Exchange photons with the pool: a lane gives its own to the slot,
+                // gets the slot's, or both.  A lane waits where it is without drawing,
+                // and in the pool, so each particle's draws keep their order; the cross
+                // sections are recomputed from the same inputs.
+                bool give = false, get = false;
+                uint32_t slot = 0u;
+                if (!big) {
+                    // (photons wait for their interactions in their lanes)
+                } else if (sample) {
+                    // the lanes without an interaction get parked photons, and their
+                    // own become ready; empty lanes get the last ready ones, or
+                    // without any the last parked ones
+                    const uint32_t kr = min(ready, ne), ke = ready ? 0u : min(parked, ne);
+                    const uint32_t ks = min(parked - ke, nf);
+                    const uint32_t r = active ? mbcnt(bf) : mbcnt(be);
+                    give = active && pm < 0 && r < ks;
+                    get = active ? give : r < kr + ke;
+                    slot = active ? parked - ke - ks + r : parked + ready - 1u - r;
+                    parked -= ke + ks;
+                    ready += ks - kr;
+                } else {
+                    // lanes with an interaction park their photon, in the place of a
+                    // ready one if there is one; empty lanes get the last ready ones
+                    const uint32_t ks = min(ready, nr), ke = min(ready - ks, ne);
+                    const uint32_t r = active ? mbcnt(br) : mbcnt(be);
+                    give = active && pm >= 0;
+                    get = active ? give && r < ks : r < ke;
+                    slot = active ? parked + r : parked + ready - 1u - r;
+                    parked += nr;
+                    ready -= ks + ke;
+                }
+                if (big) {
+                    wave_fence();
+                    if (give || get) {
+                        const f4 a = pool[slot], b = pool[kPool + slot];
+                        const u4 c = ((const GDPM_LDS u4*)pool)[2u * kPool + slot];
+                        const uint32_t col = cols[slot];
+                        if (give) {
+                            const uint32_t blocks = rng.nb - (rng.ctr >> 2);   // buffered, 0..2
+                            pool[slot] = f4{x, y, z, e};
+                            pool[kPool + slot] = f4{u, v, w, __uint_as_float(pb << 16 | blocks << 14 | (uint32_t)(pm + 1))};
+                            ((GDPM_LDS u4*)pool)[2u * kPool + slot] = u4{rng.hlo, rng.hhi, rng.path, rng.ctr};
+                        }
+                        cols[slot] = (uint32_t)(rng.buf - ring);   // a photon keeps the column of its draws
+                        rng.buf = ring + col;
+                        if (get) {
+                            const uint32_t bits = __float_as_uint(b.w);
+                            x = a.x; y = a.y; z = a.z; e = a.w;
+                            u = b.x; v = b.y; w = b.z;
+                            pb = bits >> 16;
+                            pm = (int)(bits & 0x3FFFu) - 1;
+                            rng.hlo = c.x; rng.hhi = c.y; rng.path = c.z; rng.ctr = c.w;
+                            rng.nb = (c.w >> 2) + (bits >> 14 & 3u);
+                        } else {
+                            pm = -1;
+                        }
+                        active = get;
+                    }
+                }
+                if (sample) {
+                    const uint64_t act0 = ballot(active);
+                    if (ballot(get)) {   // other photons
+                        voxel_of(idx, idy, idz, nx, ny, nz, x, y, z, ix, iy, iz);
+                        grid(hlog2(e), pg_lo, pg_inv, pg_n, gi, gt);
+                    }
                     const bool kerma = (J->flags & 64u) != 0u;
                     const float ecut_e = A->R.ecut_e;
                     PendCharged qe;
@@ -1982,13 +2026,13 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                     const uint32_t jb = W.tag | (pb << 16);
                     push_charged(qe, pe, A, J, jb, x, y, z, pack_vox(ix, iy, iz), rng, wt);
                     push_photons(qg, pg, A, J, jb, x, y, z, rng, wt);
+                    wt.died += (uint32_t)__popcll(act0 & ~ballot(active));
                 }
-                wt.died += (uint32_t)__popcll(act0 & ~ballot(active));
             }
             if (++iters > kMaxWaveIterations) {
                 // safety net, never reached in a sound run: end the particles
                 // still held (counted as anomalies) so the grid always drains
-                const uint32_t n = count(active);
+                const uint32_t n = count(active) + parked + ready;
                 wt.died += n;
                 wt.bad += n;
                 active = false;
@@ -2003,13 +2047,18 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                     nj = next_job(global_ptr(A->R.jc), W.j, A->R.n_jobs, 0);
                     last_job = nj < 0;
                 }
-                if (nj >= 0 || (big && count(active) < kTailLanes)) {
+                // (the interactions of the parked ones come first)
+                if (parked == 0u && (nj >= 0 || (big && count(active) + ready < kTailLanes))) {
                     Rec q;
                     q.a = f4{x, y, z, e};
                     q.b = f4{u, v, w, -1.0f};
                     q.c = u4{rng.hlo, rng.hhi, rng.path, rng_ctr(rng)};
                     q.d = u4{0u, 0u, 0u, W.tag | (pb << 16)};
                     requeue(active, pg, A, 0, q, wt);
+                    if (ready) {   // their turn is the next iteration
+                        active = false;
+                        continue;
+                    }
                     next = nj;
                     break;
                 }
@@ -2018,8 +2067,6 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
         job_flush(e_esc, wt, W.j, group);
         j = next;
     }
-    // no staging load may still be writing the slice when the wave moves on
-    if constexpr (kStaged) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     release(pe, A0, 1);
     release(pg, A0, 0);
     pass_finish(wt, 0, group);
@@ -2051,15 +2098,14 @@ __global__ void __launch_bounds__(1024) k_photon(PassArgs) {
             }
         }
         __syncthreads();
-        GDPM_LDS f4* slice = lds + tables_f4(0, T) + wave * slice_f4(0, true, false);
         if (wave < ring_const(A, 0)->group_waves)
-            photon_pass<kSolo, kPerm, true, !kPerm>(A, PhotLds{tot}, lmaj, slice,
-                                                    (GDPM_LDS float*)(slice + 4u * kStage), group);
+            photon_pass<kSolo, kPerm, !kPerm>(
+                A, PhotLds{tot}, lmaj, (GDPM_LDS float*)(lds + tables_f4(0, T) + wave * slice_f4(0, false)), group);
     } else {
         __syncthreads();
         if (wave < ring_const(A, 0)->group_waves)
-            photon_pass<kSolo, kPerm, false, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, nullptr,
-                                                    (GDPM_LDS float*)(lds + wave * slice_f4(0, false, false)), group);
+            photon_pass<kSolo, kPerm, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr,
+                                             (GDPM_LDS float*)(lds + wave * slice_f4(0, false)), group);
     }
     group_flush(A, group);
 }
@@ -2133,7 +2179,7 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr 
         double de = 0.0;    // deposit in it, not yet tallied
         float hq = -1.0f;   // >= 0: a hard event waits; the step-start mu_h per g/cm^2
         uint32_t pb = 0u;   // batch slot of the lane's history
-        Rng rng;
+        Rng<64u> rng;
         rng.buf = ring + lane_id();
         rng_start(rng, 0u, 0u, 0u, 0u);
         int next = -1;
@@ -2162,7 +2208,7 @@ GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr 
             const Args A = reread(A0);
             const JobPtr J = reread(W.p);
             Rec p;
-            if (refill<kSolo, kPerm, false>(active, cs, A, W, 1, begin, perm_in, p, wt, nullptr)) {
+            if (refill<kSolo, kPerm>(active, cs, A, W, 1, begin, perm_in, p, wt)) {
                 x = p.a.x; y = p.a.y; z = p.a.z; e = p.a.w;
                 u = p.b.x; v = p.b.y; w = p.b.z; nh = p.b.w;
                 ix = (int)(p.d.x & 2047u);
@@ -2469,13 +2515,13 @@ __global__ void __launch_bounds__(1024) k_electron(PassArgs) {
         const ElecLds E = stage_electron_tables(A->T, lds);
         if (wave < ring_const(A, 1)->group_waves)
             electron_pass<kSolo, kPerm>(
-                A, E, (GDPM_LDS float*)(lds + tables_f4(1, A->T) + wave * slice_f4(1, true, A->bricks)), group);
+                A, E, (GDPM_LDS float*)(lds + tables_f4(1, A->T) + wave * slice_f4(1, A->bricks)), group);
     } else {
         __syncthreads();
         const ElecGlobal E{global_f4(A->T.elec), global_ptr(A->T.rinv), global_ptr(A->T.rinv_scale),
                            global_ptr(A->T.aw)};
         if (wave < ring_const(A, 1)->group_waves)
-            electron_pass<kSolo, kPerm>(A, E, (GDPM_LDS float*)(lds + wave * slice_f4(1, false, A->bricks)), group);
+            electron_pass<kSolo, kPerm>(A, E, (GDPM_LDS float*)(lds + wave * slice_f4(1, A->bricks)), group);
     }
     group_flush(A, group);
 }
@@ -2486,7 +2532,7 @@ __global__ void __launch_bounds__(1024) k_electron(PassArgs) {
 // electron pass, and a wavefront that has finished its first pass helps with
 // the other.  The photon pass mostly waits on its random voxel reads and the
 // electron pass mostly issues vector instructions, so a CU runs one while the
-// other waits.  The electron tables and the wavefronts' staging slices are in
+// other waits.  The electron tables are in
 // LDS; the photon cross sections and majorants are read through the caches.
 // Each pass reads what its queue held at the set-up: what either pass pushes
 // is transported in the next iteration.
@@ -2500,12 +2546,11 @@ __global__ void __launch_bounds__(768) k_transport(PassArgs) {
     group_clear(group);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ElecLds E = stage_electron_tables(A->T, lds);
-    GDPM_LDS f4* slice = lds + tables_f4(1, A->T) + wave * slice_f4(2, true, A->bricks);
-    GDPM_LDS float* ring = (GDPM_LDS float*)(slice + 4u * kStage);
+    GDPM_LDS float* ring = (GDPM_LDS float*)(lds + tables_f4(1, A->T) + wave * slice_f4(2, A->bricks));
     for (int k = 0; k < 2; ++k) {
         const bool photons = ((int)wave < A->photon_waves) == (k == 0);
         if (photons)
-            photon_pass<false, kPerm, true, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, slice, ring, group);
+            photon_pass<false, kPerm, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, ring, group);
         else
             electron_pass<false, kPerm>(A, E, ring, group);
     }
@@ -2996,15 +3041,17 @@ hipError_t launch_admit(hipStream_t st, int cus, const JobDev& job, JobDev* jobs
     return hipGetLastError();
 }
 // LDS bytes of a pass (ri = 2: both in one launch) with `waves` wavefronts per block
-// (lds: its tables and the photons' records staged; bricks: the electrons' brick sums)
+// (lds: its tables staged; bricks: the electrons' brick sums)
 size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds, bool bricks) {
-    const size_t per_wave = slice_f4(ri, lds, bricks);
+    const size_t per_wave = slice_f4(ri, bricks);
     return (kGroupTallyF4 + (lds ? (size_t)tables_f4(ri, T) : 0) + (size_t)waves * per_wave) * sizeof(float4);
 }
 
-// allow the staged kernels to use `bytes` of dynamic LDS
+// allow the kernels to use `bytes` of dynamic LDS
 hipError_t transport_lds_optin(size_t bytes) {
-    const void* kernels[] = {(const void*)k_photon<true, false, false>, (const void*)k_electron<true, false, false>,
+    const void* kernels[] = {(const void*)k_photon<false, false, false>, (const void*)k_electron<false, false, false>,
+                             (const void*)k_photon<false, false, true>, (const void*)k_electron<false, false, true>,
+                             (const void*)k_photon<true, false, false>, (const void*)k_electron<true, false, false>,
                              (const void*)k_photon<true, false, true>,  (const void*)k_electron<true, false, true>,
                              (const void*)k_photon<true, true, false>,  (const void*)k_electron<true, true, false>,
                              (const void*)k_photon<true, true, true>,   (const void*)k_electron<true, true, true>,

@@ -152,3 +152,44 @@ def test_wide_passes_of_jobs(n):
     for x, y in zip(a, b):
         rtol = 2 * max(sum(r["deposits"]) for r in b) * np.finfo(float).eps   # any order of all deposits
         np.testing.assert_allclose(x["dose"], y["dose"], rtol=rtol, atol=rtol * y["dose"].max())
+
+
+# photon passes with 4 records or more per lane park the photons that interact (here
+# with one wavefront per CU: from 65,536), shorter ones let them wait in their lanes:
+# absorption alone, scattering, pairs; one particle per wavefront; several jobs
+@pytest.mark.parametrize("opts", ['{"waves_per_cu": 1}', '{"waves_per_cu": 1, "lds_tables": 0}',
+                                  '{"waves_per_cu": 1, "fused_passes": 1}', '{"waves_per_cu": 2, "solo_lanes": 1}',
+                                  '{"waves_per_cu": 1, "rebin_photons": 1}'])
+@pytest.mark.parametrize("e", [0.06, 1.0, 15.0])
+def test_photon_pool(e, opts):
+    ph = I.homogeneous((20, 20, 20), (1.0,) * 3, I.ID_BONE, 1.85)
+    src = I.Source(I.PHOTON, I.mono(e), [I.parallel_beam_z(ph, 10.0)])
+    n = 20_000 if "solo" in opts else 150_000
+    res = []
+    for o in (opts, '{"pass_histories": 3000}'):
+        c = G.Context(0, opts=o, materials=MATS)
+        try:
+            res.append(gpu_run(c, ph, src, n_hist=n, seed=6, n_batches=2))
+        finally:
+            c.close()
+    a, b = res
+    assert physics_events(a) == physics_events(b) and a["interactions"] == b["interactions"]
+    rtol = 2 * max(sum(r["deposits"]) for r in res) * np.finfo(float).eps   # any order of all deposits
+    np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
+    assert balance(a) < 1e-12
+
+
+def test_photon_pool_jobs():
+    ph = I.homogeneous((20, 20, 20), (1.0,) * 3, I.ID_WATER, 1.0)
+    src = I.Source(I.PHOTON, I.mono(6.0), [I.parallel_beam_z(ph, 10.0)])
+    kws = [dict(n_hist=n, seed=6, n_batches=2, job_id=k) for k, n in enumerate((90_000, 3_000, 120_000, 64, 70_001))]
+    c = G.Context(0, opts='{"waves_per_cu": 1}', materials=MATS)
+    try:
+        p, s = c.phantom(ph), c.source(src)
+        many = c.run_batch([(p, s, kw) for kw in kws])
+        one = [c.run(p, s, **kw) for kw in kws]
+    finally:
+        c.close()
+    for a, b in zip(many, one):
+        rtol = 2 * sum(b["deposits"]) * np.finfo(float).eps
+        np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
