@@ -10,7 +10,7 @@ different seed; `value` is histories per second over the timed jobs, with the
 phantom, source and tables already resident in device memory.
 
 Also reported: the job latency (p50/p99 over the timed jobs), the roofline
-position of the dominant transport kernel (HIP-event times of every launch on
+position of the dominant transport kernel (device-clock times of every launch on
 the library's stream; algorithmic bytes from the kernels' own counters of voxel
 lookups, queue records and tally deposits; measured HBM traffic from the
 committed hardware-counter summary), and the oracle (plain CPU transport) timed
@@ -277,7 +277,7 @@ def run_stream(G, ctx, hs, times, slots, budget, label):
     kinds = [kw.get("kind", "") for _, _, kw in hs]
     log(f"{label}: p50 {pct(lat, 50):.2f} s, p99 {pct(lat, 99):.2f} s, span {wall - times[0]:.2f} s")
     # the engine's totals when the last job finished: device time of the
-    # transport kernels (HIP events) and launches, over the whole stream
+    # transport kernels (device clock) and launches, over the whole stream
     engine = {k: max(r[k] for r in res) for k in ("t_kernel_s", "t_photon_s", "t_electron_s", "passes",
                                                    "graph_launches", "graphs_recorded", "passes_rebinned")}
     return {"seconds": wall, "histories_per_s": hist / max(wall - times[0], 1e-9), "engine_totals": engine,
@@ -695,7 +695,7 @@ def summarize_trace(stats_csv, bench_json):
                    f"{float(r['Percentage']):.2f}% |")
     trace_avg = {short_kernel(r["Name"]): float(r["AverageNs"]) / 1e6 for r in rows}
     k = roof["kernel"]
-    out += ["", f"The bench line of the same run (HIP events on the library stream) gives "
+    out += ["", f"The bench line of the same run (device clock) gives "
                 f"{roof['avg_launch_ms']:.3f} ms per {k} launch over {roof['launches']} launches; the "
                 f"trace average is {trace_avg.get(k, float('nan')):.3f} ms.",
             f"Job: {b['config']['histories_per_job']} histories, {b['ms_per_step'] / 1e3:.3f} s, "
@@ -894,7 +894,7 @@ def main():
     rates = [r["histories"] / r["t_total_s"] for r in runs]
 
     # roofline of the dominant transport kernel: algorithmic bytes per launch
-    # over the launch's average HIP-event duration
+    # over the launch's average duration
     te = sum(r["t_electron_s"] for r in runs)
     tp = sum(r["t_photon_s"] for r in runs)
     ne = sum(r["passes_electron"] for r in runs)

@@ -234,7 +234,8 @@ typedef struct {
 /* Create a context on HIP device `hip_device`.  opts_json may be NULL or a
  * flat JSON object with any of: "ring_capacity_log2" (queue records per type,
  * 2^k, default 25), "waves_per_cu" (wavefronts of the persistent workgroup
- * each CU runs, 1..12, default 12), "photon_waves_per_cu" (the same for the
+ * each CU runs, 1..12, default 12; passes of many records run a third more),
+ * "photon_waves_per_cu" (the same for the
  * photon pass alone, at most waves_per_cu, 0..12, default 0: waves_per_cu),
  * "rebin_bins" (bins per job of the queue re-binning, 0..64, default 1:
  * records are grouped by job only, which measured faster than energy order),
@@ -243,15 +244,14 @@ typedef struct {
  * "rebin_photons", "rebin_electrons" (1: re-bin the queue of that particle type
  * also when a single job holds all the particles; default 0: then the queues
  * are read unsorted, which measured faster), "lds_tables" (1: stage
- * interpolation tables in LDS when they fit, together with each wavefront's
- * next claimed queue records, default; 0: read the tables through the caches
- * and load records directly), "pass_histories" (new histories started per
+ * interpolation tables in LDS when they fit, default; 0: read the tables
+ * through the caches), "pass_histories" (new histories started per
  * scheduler iteration, default 0 = half the queue capacity less what the
  * fuller queue holds; a larger
  * value can overflow the queues, which gdpm_run reports as GDPM_E_OVERFLOW).
- * Each wavefront reserves queue slots 256 at a time, so a queue needs well
- * over 256 slots per wavefront of the grid (2^21 and up on a 256-CU device
- * with 12 wavefronts per CU); smaller queues overflow.
+ * Each wavefront reserves queue slots 32 to 256 at a time, the more the longer
+ * the pass, so a queue needs well over that many slots per wavefront of the
+ * grid (2^21 and up on a 256-CU device); much smaller queues can overflow.
  * "share" (how the jobs run together share the new histories of an iteration:
  * 1, the only value accepted, evenly; 0, oldest job first, is rejected with
  * GDPM_E_INVALID: a job taking the whole history budget of an iteration can
@@ -268,7 +268,7 @@ typedef struct {
  * "autotune" (see gdpm_context_settings), "autotune_min_events" (transport
  * events, photon flights plus electron steps, an iteration must have for the
  * autotuner to score it; default 4000000), "graphs" (1, default: a
- * scheduler iteration's launches, copies included, are recorded as a HIP
+ * scheduler iteration's launches are recorded as a HIP
  * graph the second time their launch configuration occurs in a run, and
  * replayed from then on, on the stream of the run; each run, batch or server
  * keeps its own recordings; 0: launched one by one),

@@ -13,10 +13,11 @@
 //     history), so lanes stay busy instead of idling until the slowest particle
 //     of the wave finishes;
 //   - queue traffic is per wavefront: a ballot + mbcnt prefix gives each lane
-//     its slot and one atomic per 256 records reserves ring space, one atomic
-//     per 64 items claims input;
-//   - dose goes into double-precision tallies with hardware FP64 atomics, one
-//     per voxel visit of a charged particle (deposits merged in registers).
+//     its slot, one atomic per 32 to 256 records reserves ring space and one
+//     per 32 to 2048 claims input;
+//   - dose goes into double-precision tallies with hardware FP64 atomics; a
+//     charged particle's deposits are merged per voxel, and added for several
+//     voxels of one line of memory at a time (see Brick).
 // Random numbers: Philox4x32-10 (Salmon et al., SC'11); a particle owns the
 // stream (history id, path id) and the draw order of each event is fixed, so
 // results do not depend on scheduling.
