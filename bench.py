@@ -940,13 +940,15 @@ def main():
                     algorithmic_lane_instructions_per_launch=work / max(launches, 1),
                     straight_line_instructions_per_history=per_history,
                     instructions_per_event=per_event_type)
-    # the kernel's FP64 tally additions per second against the measured rate of
-    # scattered FP64 atomics into an array of one CT tally slot (and a small one)
+    # the kernel's deposits per second against the measured rate of scattered FP64
+    # atomics into an array of one CT tally slot (and a small one); the electron pass
+    # merges the deposits of a 2 x 2 brick of voxels, so fewer additions reach memory
     peak = ctx.atomic_rate(8 * w.phantom.nvox)
     deposits = sum(r["deposits"][k] for r in runs)
     roof["atomics"] = {"tally_atomics_per_s": deposits / max(t_k, 1e-30), "measured_peak_per_s": peak,
                        "frac": deposits / max(t_k, 1e-30) / peak,
                        "measured_peak_per_s_256KiB": ctx.atomic_rate(256 << 10),
+                       "note": "deposits per second; k_electron merges those of a 2x2 brick before it adds them",
                        "probe": f"random FP64 atomicAdd into {8 * w.phantom.nvox} B (one tally slot)"}
 
     out = {
