@@ -160,8 +160,9 @@ struct DevBuf {
 
 // Device memory of jobs (tallies, outputs, majorants, chains) kept between jobs:
 // a job's hipMalloc and hipFree calls took 150 us of a small job and 10 ms of a
-// batch of 24.  A block comes back when the job's buffers go, after the job's
-// stream has been waited for; at most kMaxHeld bytes are kept, the oldest blocks
+// batch of 24.  A block comes back when the job's buffers go, once the device has
+// finished with it: the job's statistics have been reported, or its engine has ended
+// (see ~Engine); at most kMaxHeld bytes are kept, the oldest blocks
 // go first, and all go when the context or a server ends or memory runs out.
 // Jobs of a server end on the server's thread and are released on the caller's,
 // hence the lock.
@@ -715,7 +716,14 @@ struct Engine {
     Engine() = default;
     Engine(const Engine&) = delete;
     Engine& operator=(const Engine&) = delete;
-    ~Engine() { drop_graphs(); }
+    // Launches use the jobs' memory and the context's control blocks: whatever ends the
+    // engine (a refused job or an error between launches among them), the device has
+    // finished with them before their owners give them back.
+    bool in_flight = false;     // something was launched on the stream and not waited for
+    ~Engine() {
+        if (in_flight) (void)hipStreamSynchronize(st);
+        drop_graphs();
+    }
     void drop_graphs() {
         for (auto& g : graphs)
             if (g.exec) (void)hipGraphExecDestroy(g.exec);
@@ -828,6 +836,7 @@ gdpm_status Engine::init(gdpm_context c, hipStream_t s, const RunPlan& plan, con
         RingCtl& q = ctx->mirror->ctl.ring[r];
         q.head = q.tail = q.begin = ctx->ring_start;
     }
+    in_flight = true;
     HIP_TRY(launch_init(st, M.ctl, M.jc, M.stats, ctx->ring_start));
     memset(&R, 0, sizeof R);
     R.ecut_g = (float)plan.ecut_g;
@@ -1608,6 +1617,7 @@ gdpm_status run_job(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gd
         HIP_TRY(hipMemcpyAsync(h_hist, j->hist.as<void>(), j->plan.n_hist * 2 * sizeof(double),
                                hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    E.in_flight = false;
     if (j->plan.split) {
         // the device sums hold each copy at weight 1 (see compute_stats)
         if (h_batch)

@@ -1,0 +1,63 @@
+"""Memory that calls share or hand over: a job's device memory is kept for the next
+job, and host outputs are written by several threads."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_1107_3355_amd import gdpm as G
+from paper_1107_3355_amd import inputs as I
+from tests.gpu_common import balance, physics_events
+
+pytestmark = pytest.mark.gpu
+MATS = I.MATERIALS
+
+
+def _water(side, d, e=2.0):
+    ph = I.homogeneous((side,) * 3, (d,) * 3, I.ID_WATER, 1.0)
+    return ph, I.Source(I.PHOTON, I.mono(e), [I.parallel_beam_z(ph, 5.0)])
+
+
+def _hip():
+    return C.CDLL("libamdhip64.so")   # the runtime the library uses
+
+
+def _on_stream(ctx, p, s, **kw):
+    """The job on a stream of its own; dose, sigma and run statistics."""
+    hip, n = _hip(), p.desc.nvox
+    st, bufs = C.c_void_p(), [C.c_void_p(), C.c_void_p()]
+    assert hip.hipStreamCreate(C.byref(st)) == 0
+    for b in bufs:
+        assert hip.hipMalloc(C.byref(b), C.c_size_t(8 * n)) == 0
+    try:
+        r = ctx.run_async(p, s, bufs[0].value, bufs[1].value, stream=st.value, **kw)
+        for k, b in zip(("dose", "sigma"), bufs):
+            r[k] = np.empty(n)
+            assert hip.hipMemcpy(r[k].ctypes.data_as(C.c_void_p), b, C.c_size_t(8 * n), 2) == 0
+    finally:
+        for b in bufs:
+            hip.hipFree(b)
+        hip.hipStreamDestroy(st)
+    return r
+
+
+def test_memory_of_a_refused_batch():
+    """A batch is refused at its last job, with the large tallies of the jobs before it
+    still being cleared on the context's stream.  The next job, on another stream, takes
+    their memory: nothing may write to it any more (same dose as in a fresh context, to
+    the order of the FP64 additions)."""
+    ph, src = _water(200, 0.2)
+    kw = dict(seed=5, n_hist=20_000, n_batches=10)
+    c = G.Context(0, materials=MATS)
+    try:
+        p, s = c.phantom(ph), c.source(src)
+        first = _on_stream(c, p, s, **kw)
+        for _ in range(3):
+            with pytest.raises(G.GdpmError) as e:
+                c.run_batch([(p, s, kw)] * 3 + [(p, s, dict(kw, ecut_e=0.3))], want_dose=False)
+            assert e.value.status == 1 and "job 3" in str(e.value)
+            r = _on_stream(c, p, s, **kw)
+            assert physics_events(r) == physics_events(first) and balance(r) < 1e-12
+            np.testing.assert_allclose(r["dose"], first["dose"], rtol=1e-12, atol=1e-12 * first["dose"].max())
+    finally:
+        c.close()
