@@ -1046,6 +1046,7 @@ gdpm_status copy_out(gdpm_context ctx, hipStream_t st, const std::vector<OutCopy
     }
     work();
     for (auto& t : threads) t.join();
+    if (error.load()) (void)hipStreamSynchronize(st);   // copies still on their way
     if (error.load())
         return fail(GDPM_E_DEVICE, "copying the outputs: %s", hipGetErrorString((hipError_t)error.load()));
     return GDPM_OK;
@@ -1631,9 +1632,9 @@ gdpm_status run_job(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gd
     return j->status;
 }
 
-// the same with the job's memory back in the pool; the device has finished with
-// it then, whatever the outcome.  h_dose, h_sigma: host outputs (either may be
-// null)
+// the same with the job's memory back in the pool (the engine has waited for the
+// device; a call refused before its first launch waits for nothing: the stream may hold
+// other work of the caller's).  h_dose, h_sigma: host outputs (either may be null)
 gdpm_status do_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdpm_run_params* prm,
                    double* d_dose, double* d_sigma, double* h_dose, double* h_sigma, double* h_batch,
                    double* h_hist, hipStream_t st, gdpm_run_stats* out, unsigned char* scr = nullptr) {
@@ -1645,12 +1646,7 @@ gdpm_status do_run(gdpm_context ctx, gdpm_phantom ph, gdpm_source src, const gdp
         std::vector<OutCopy> list;
         add_outputs(list, &job, h_dose, h_sigma);
         const gdpm_status c = copy_out(ctx, st, list);
-        if (c) {
-            (void)hipStreamSynchronize(st);
-            return c;
-        }
-    } else {
-        (void)hipStreamSynchronize(st);
+        if (c) return c;
     }
     g_err = msg;
     return s;

@@ -61,3 +61,31 @@ def test_memory_of_a_refused_batch():
             np.testing.assert_allclose(r["dose"], first["dose"], rtol=1e-12, atol=1e-12 * first["dose"].max())
     finally:
         c.close()
+
+
+def test_refused_call_does_not_wait():
+    """A call that is refused before it launches anything leaves the caller's stream
+    alone: work that the stream holds is still running when the call returns."""
+    hip, n = _hip(), 1 << 30
+    c = G.Context(0, materials=MATS)
+    st, buf = C.c_void_p(), C.c_void_p()
+    try:
+        ph, src = _water(16, 0.5)
+        p, s = c.phantom(ph), c.source(src)
+        assert hip.hipStreamCreate(C.byref(st)) == 0 and hip.hipMalloc(C.byref(buf), C.c_size_t(n)) == 0
+        kw = dict(stream=st.value, n_hist=100, n_batches=2)
+        c.run_async(p, s, buf.value, buf.value + n // 2, **kw)
+        for call, bad in ((c.run_async, dict(n_hist=0)), (c.run_noalloc, dict(n_batches=1))):
+            for _ in range(1000):   # well over 0.1 s
+                assert hip.hipMemsetAsync(buf, 0, C.c_size_t(n), st) == 0
+            with pytest.raises(G.GdpmError) as e:
+                call(p, s, buf.value, buf.value + n // 2, **dict(kw, **bad))
+            busy = hip.hipStreamQuery(st)
+            assert hip.hipStreamSynchronize(st) == 0
+            assert e.value.status == 1 and busy == 600   # hipErrorNotReady
+    finally:
+        if st:
+            hip.hipStreamSynchronize(st)
+            hip.hipStreamDestroy(st)
+        hip.hipFree(buf)
+        c.close()
