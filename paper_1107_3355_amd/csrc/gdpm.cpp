@@ -964,11 +964,11 @@ struct OutCopy {
 constexpr size_t kOutChunk = (size_t)1 << 20;
 constexpr size_t kOutChunks = 32;   // chunks in flight, at most
 
-// Copy outputs to the caller's host arrays; complete on return.  The device
+// Copy outputs to the caller's host arrays, no two of which overlap; complete on return.  The device
 // writes chunks to pinned memory and a few host threads copy them on: a copy
 // straight to pageable memory is one thread's work, and mostly the page faults of
 // arrays that were never written (13 GB/s at best, 10 ms of a batch of 24 jobs).
-gdpm_status copy_out(gdpm_context ctx, hipStream_t st, const std::vector<OutCopy>& list) {
+gdpm_status copy_disjoint(gdpm_context ctx, hipStream_t st, const std::vector<OutCopy>& list) {
     struct Chunk {
         char* dst;
         const char* src;
@@ -1049,6 +1049,23 @@ gdpm_status copy_out(gdpm_context ctx, hipStream_t st, const std::vector<OutCopy
     if (error.load()) (void)hipStreamSynchronize(st);   // copies still on their way
     if (error.load())
         return fail(GDPM_E_DEVICE, "copying the outputs: %s", hipGetErrorString((hipError_t)error.load()));
+    return GDPM_OK;
+}
+
+// The same for any arrays.  Outputs that share memory (one array given for the dose and
+// the standard error, or for several jobs) are copied one after the other, in order, so
+// that the last one stands whole.
+gdpm_status copy_out(gdpm_context ctx, hipStream_t st, const std::vector<OutCopy>& list) {
+    std::vector<std::pair<uintptr_t, uintptr_t>> range;
+    for (const OutCopy& c : list) range.emplace_back((uintptr_t)c.dst, (uintptr_t)c.dst + c.bytes);
+    std::sort(range.begin(), range.end());
+    bool overlap = false;
+    for (size_t i = 1; i < range.size(); ++i) overlap = overlap || range[i].first < range[i - 1].second;
+    if (!overlap) return copy_disjoint(ctx, st, list);
+    for (const OutCopy& c : list) {
+        const gdpm_status s = copy_disjoint(ctx, st, {c});
+        if (s) return s;
+    }
     return GDPM_OK;
 }
 

@@ -1,6 +1,7 @@
 """Memory that calls share or hand over: a job's device memory is kept for the next
 job, and host outputs are written by several threads."""
 import ctypes as C
+import mmap
 
 import numpy as np
 import pytest
@@ -88,4 +89,27 @@ def test_refused_call_does_not_wait():
             hip.hipStreamSynchronize(st)
             hip.hipStreamDestroy(st)
         hip.hipFree(buf)
+        c.close()
+
+
+@pytest.mark.parametrize("n", [1, 12])
+def test_outputs_that_share_an_array(n):
+    """One array for the dose and the standard error, of all jobs of a batch (a caller that
+    has no use for them): the last values stand in it, whole.  An output is one long and
+    one short chunk, and the pages are new, so that a copy is slow and the next one has it
+    easy."""
+    ph = I.homogeneous((52, 51, 50), (0.2,) * 3, I.ID_WATER, 1.0)
+    src = I.Source(I.PHOTON, I.mono(6.0), [I.parallel_beam_z(ph, 5.0)])
+    kw = dict(n_hist=300, n_batches=2, flags=G.KERMA)   # all jobs end after one photon pass
+    c = G.Context(0, materials=MATS)
+    try:
+        p, s = c.phantom(ph), c.source(src)
+        ref = c.run(p, s, seed=n, **kw)["sigma"]
+        for _ in range(20):
+            shared = np.frombuffer(mmap.mmap(-1, 8 * ph.nvox), dtype=np.float64)
+            jobs = (G.JobDesc * n)(*[G.JobDesc(p.handle, s.handle, G._params(dict(kw, seed=k + 1)), G._dp(shared),
+                                               G._dp(shared)) for k in range(n)])
+            G._check(G.lib().gdpm_run_batch(c.handle, n, jobs, None, None))
+            np.testing.assert_allclose(shared, ref, rtol=1e-9, atol=1e-12 * ref.max())
+    finally:
         c.close()
