@@ -984,13 +984,13 @@ gdpm_status copy_disjoint(gdpm_context ctx, hipStream_t st, const std::vector<Ou
         if (ctx->out_ring) (void)hipHostFree(ctx->out_ring);
         ctx->out_ring = nullptr;
         ctx->out_chunks = 0;
-        HIP_TRY(hipHostMalloc(&ctx->out_ring, kOutChunk * cap, hipHostMallocDefault));
-        ctx->out_chunks = cap;
         while (ctx->out_events.size() < cap) {
             hipEvent_t e;
             HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
             ctx->out_events.push_back(e);
         }
+        HIP_TRY(hipHostMalloc(&ctx->out_ring, kOutChunk * cap, hipHostMallocDefault));
+        ctx->out_chunks = cap;
     }
     const size_t cap = ctx->out_chunks;
     const size_t n = chunks.size();
