@@ -1922,19 +1922,19 @@ gdpm_status gdpm_set_materials(gdpm_context ctx, const gdpm_material* m, int n, 
             return fail(GDPM_E_INVALID, "material %d: parameters must be positive and finite", i);
         mats[i] = {m[i].z, m[i].z_over_a, m[i].i_ev};
     }
+    HIP_TRY(hipSetDevice(ctx->device));
+    const size_t maj = (size_t)kMaxJobs * n_grid * sizeof(float);
+    if (ctx->maj_bytes < maj) {
+        float* p = nullptr;
+        HIP_TRY(hipHostMalloc((void**)&p, maj, hipHostMallocDefault));
+        if (ctx->h_maj) (void)hipHostFree(ctx->h_maj);
+        ctx->h_maj = p;
+        ctx->maj_bytes = maj;
+    }
     ctx->mats = mats;
     ctx->n_grid = n_grid;
     ctx->tables.clear();
     // the table set of the default absorption energies, resident from now on
-    HIP_TRY(hipSetDevice(ctx->device));
-    const size_t maj = (size_t)kMaxJobs * n_grid * sizeof(float);
-    if (ctx->maj_bytes < maj) {
-        if (ctx->h_maj) (void)hipHostFree(ctx->h_maj);
-        ctx->h_maj = nullptr;
-        ctx->maj_bytes = 0;
-        HIP_TRY(hipHostMalloc((void**)&ctx->h_maj, maj, hipHostMallocDefault));
-        ctx->maj_bytes = maj;
-    }
     DevTables* t = nullptr;
     return get_tables(ctx, 0.05, 0.2, 0u, &t);
 }
