@@ -1724,10 +1724,11 @@ constexpr uint32_t kBrickF4 = kBrickVoxels * 64u / 2u + 64u * 2u / 16u;
 // columns, and generator words of as many columns more (see photon_pass)
 constexpr uint32_t kPool = 64u, kPhotonCols = 64u + kPool;
 constexpr uint32_t kPoolF4 = 3u * kPool + kPool / 4u;
-// ri: 0 photons, 1 electrons, 2 both (k_transport)
+// ri: 0 photons, 1 electrons, 2 both (k_transport; its photons have no pool: with one for
+// each wavefront, 12 of them and the electron tables of 4 materials would take 175,248 of
+// the CU's 163,840 bytes)
 GDPM_HD uint32_t slice_f4(int ri, bool bricks) {
-    const uint32_t photons = kRngWords * kPhotonCols / 4u + kPoolF4, electrons = kRingF4 + (bricks ? kBrickF4 : 0u);
-    return ri == 0 || (ri == 2 && photons > electrons) ? photons : electrons;
+    return ri == 0 ? kRngWords * kPhotonCols / 4u + kPoolF4 : kRingF4 + (bricks ? kBrickF4 : 0u);
 }
 
 // the device clock at the start of a pass (its completion takes the difference)
@@ -1747,7 +1748,8 @@ GDPM_DEV bool group_idle(Args A, int ri) {
 // ---------------------------------------------------------------------------
 // One wavefront's share of a photon pass.  ptab: the total cross sections (in
 // LDS or global memory); lmaj: the job's majorant in LDS (kMajLds: a pass of one job; else it
-// is read from global memory); ring: the wavefront's generator words and its pool.
+// is read from global memory); ring: the wavefront's generator words and its pool (kPark; without it a
+// lane waits in passes of any length).
 //
 // Vector instructions bound the pass (two thirds of the cycles), and half of them sample
 // interactions, which come in one of four flights.  Sampled as soon as 22 lanes had one,
@@ -1762,7 +1764,7 @@ GDPM_DEV bool group_idle(Args A, int ri) {
 // of the generator words goes with it): generated again, they took what the fuller
 // lanes gave.  In a pass with few photons a lane waits: they end before the pool fills,
 // and the exchange cost 8% of it (1e5 photons).
-template <bool kSolo, bool kPerm, bool kMajLds, class PT>
+template <bool kSolo, bool kPerm, bool kMajLds, bool kPark, class PT>
 GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS float* ring, GroupPtr group) {
     const GDPM_CONST RingCtl* rc = ring_const(A0, 0);
     const uint32_t begin = rc->begin, total = rc->count;
@@ -1772,8 +1774,10 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
         kPerm && rc->permuted ? global_ptr(bin_perm(A0->R.bin[0], A0->R.mask[0])) : nullptr;
     const uint32_t waves = pass_waves(A0, 0);
     const bool big = !kSolo && total >= kTailMinPerLane * 64u * waves;
+    const bool park = kPark && big;
 
-    GDPM_LDS f4* const pool = (GDPM_LDS f4*)(ring + kRngWords * kPhotonCols);
+    constexpr uint32_t kCols = kPark ? kPhotonCols : 64u;
+    GDPM_LDS f4* const pool = (GDPM_LDS f4*)(ring + kRngWords * kCols);
     GDPM_LDS uint32_t* const cols = (GDPM_LDS uint32_t*)(pool + 3u * kPool);
     int j = first_job(A0, total, 0);
     uint32_t first = rc->first;
@@ -1804,9 +1808,9 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
         float x = 0, y = 0, z = 0, u = 0, v = 0, w = 0, e = 0;
         uint32_t pb = 0u;   // batch slot of the lane's history
         int pm = -1;        // >= 0: a real interaction waits, in a voxel of this material
-        Rng<kPhotonCols> rng;
+        Rng<kCols> rng;
         rng.buf = ring + lane_id();
-        cols[lane_id()] = kPool + lane_id();
+        if (kPark) cols[lane_id()] = kPool + lane_id();
         rng_start(rng, 0u, 0u, 0u, 0u);
         int next = -1;
         // the pool: photons with an interaction in slots [0, parked), then `ready` ones
@@ -1870,14 +1874,14 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                 const uint64_t br = ballot(active && pm >= 0), bf = ballot(active && pm < 0), be = ballot(!active);
                 const uint32_t nr = (uint32_t)__popcll(br), nf = (uint32_t)__popcll(bf), ne = (uint32_t)__popcll(be);
                 const bool sample =
-                    parked + nr > 0u && (cs.done || nf == 0u || (big ? parked + nr > kPool : nr >= kRealBatch));
+                    parked + nr > 0u && (cs.done || nf == 0u || (park ? parked + nr > kPool : nr >= kRealBatch));
                 // Exchange photons with the pool: a lane gives its own to the slot,
                 // gets the slot's, or both.  A lane waits where it is without drawing,
                 // and in the pool, so each particle's draws keep their order; the cross
                 // sections are recomputed from the same inputs.
                 bool give = false, get = false;
                 uint32_t slot = 0u;
-                if (!big) {
+                if (!park) {
                     // (photons wait for their interactions in their lanes)
                 } else if (sample) {
                     // the lanes without an interaction get parked photons, and their
@@ -1902,7 +1906,7 @@ GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GD
                     parked += nr;
                     ready -= ks + ke;
                 }
-                if (big) {
+                if (park) {
                     wave_fence();
                     if (give || get) {
                         const f4 a = pool[slot], b = pool[kPool + slot];
@@ -2100,12 +2104,12 @@ __global__ void __launch_bounds__(1024) k_photon(PassArgs) {
         }
         __syncthreads();
         if (wave < ring_const(A, 0)->group_waves)
-            photon_pass<kSolo, kPerm, !kPerm>(
+            photon_pass<kSolo, kPerm, !kPerm, true>(
                 A, PhotLds{tot}, lmaj, (GDPM_LDS float*)(lds + tables_f4(0, T) + wave * slice_f4(0, false)), group);
     } else {
         __syncthreads();
         if (wave < ring_const(A, 0)->group_waves)
-            photon_pass<kSolo, kPerm, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr,
+            photon_pass<kSolo, kPerm, false, true>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr,
                                              (GDPM_LDS float*)(lds + wave * slice_f4(0, false)), group);
     }
     group_flush(A, group);
@@ -2551,7 +2555,7 @@ __global__ void __launch_bounds__(768) k_transport(PassArgs) {
     for (int k = 0; k < 2; ++k) {
         const bool photons = ((int)wave < A->photon_waves) == (k == 0);
         if (photons)
-            photon_pass<false, kPerm, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, ring, group);
+            photon_pass<false, kPerm, false, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, ring, group);
         else
             electron_pass<false, kPerm>(A, E, ring, group);
     }

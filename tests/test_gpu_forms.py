@@ -193,3 +193,33 @@ def test_photon_pool_jobs():
     for a, b in zip(many, one):
         rtol = 2 * sum(b["deposits"]) * np.finfo(float).eps
         np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
+
+
+# both passes in one launch, with the wavefronts it has by default: few and many records
+# per lane (the hand-off at the tail of a long pass), queues read as they are and
+# through the permutation, all kinds of shares, and tables with less room beside them
+@pytest.mark.parametrize("n_mat,opts", [(4, ''), (4, ', "photon_waves": 0'), (4, ', "photon_waves": 12'), (5, ''), (6, ''),
+                                        (4, ', "rebin_photons": 1, "rebin_electrons": 1'),
+                                        (4, ', "rebin_photons": 1'), (4, ', "waves_per_cu": 5')])
+@pytest.mark.parametrize("n", [3_000, 1_000_000])
+def test_fused_passes(n, n_mat, opts):
+    mats = (list(MATS) + list(MATS))[:n_mat]
+    rng = np.random.default_rng(n_mat)
+    shape = (20, 18, 15)
+    ph = I.Phantom(*shape, 0.6, 0.5, 0.8, rng.integers(0, n_mat, shape[::-1]).astype(np.uint8),
+                   rng.uniform(0.3, 1.6, shape[::-1]).astype(np.float32))
+    src = I.Source(I.PHOTON, I.mono(6.0), [I.parallel_beam_z(ph, 6.0)])
+    res = []
+    for o in ('{"fused_passes": 1' + opts + '}', '{}'):
+        c = G.Context(0, opts=o, materials=mats)
+        try:
+            res.append(gpu_run(c, ph, src, n_hist=n, seed=4, n_batches=2))
+        finally:
+            c.close()
+    a, b = res
+    assert a["t_photon_s"] == 0 and a["t_electron_s"] == 0 and a["t_kernel_s"] > 0   # one launch for both
+    assert b["t_photon_s"] > 0 and b["t_electron_s"] > 0
+    assert physics_events(a) == physics_events(b) and a["interactions"] == b["interactions"]
+    rtol = 2 * max(sum(r["deposits"]) for r in res) * np.finfo(float).eps   # any order of all deposits
+    np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
+    assert balance(a) < 1e-12
