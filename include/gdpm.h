@@ -186,7 +186,8 @@ typedef struct {
     double t_total_s;            /* wall time of the call */
     double t_kernel_s;           /* device time of the transport passes (device clock) */
     double t_photon_s, t_electron_s;  /* device time per pass type, when the passes are
-                                         launched apart (0 with fused_passes) */
+                                         launched apart (0 if all ran in one launch with
+                                         the other type's, see fused_passes) */
     uint64_t events[8];          /* GDPM_EV_* counters of the run (for a job of a batch or a
                                     server: the engine's totals, all jobs, when it finished;
                                     events[GDPM_EV_HISTORIES] is the job's own) */
@@ -292,7 +293,9 @@ typedef struct {
  * "photon_waves" wavefronts of each workgroup at first (default -1: half) and
  * the electron pass on the others, each wavefront turning to the other pass
  * when its own has nothing left; each pass then transports what its queue held
- * at the start of the iteration; needs the electron tables staged in LDS;
+ * at the start of the iteration; needs the electron tables staged in LDS: with
+ * "lds_tables" off, or tables that do not fit (more than 6 materials of 1024
+ * nodes at 12 wavefronts), the passes run apart, which t_photon_s shows;
  * 0: the photon pass, then the electron pass).
  * Results do not depend on any of these options (each particle draws from its
  * own random stream), only the speed does. */

@@ -50,7 +50,7 @@ hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, boo
                             bool permuted, Ctl* ctl, const Tables& T, const RunDev& R);
 hipError_t launch_rebin(hipStream_t st, int blocks, Ctl* ctl, const RunDev& R, int ri, int nb,
                         float lo, float inv, int space);
-hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_waves, bool bricks, bool permuted,
+hipError_t launch_fused(hipStream_t st, int ri, int blocks, int threads, int photon_waves, bool bricks, bool permuted,
                         Ctl* ctl, const Tables& T, const RunDev& R);
 hipError_t launch_count_records(hipStream_t st, int blocks, const Ctl* ctl, const RunDev& R,
                                 unsigned long long* counts);
@@ -348,7 +348,7 @@ struct StepGraphKey {
     int lone;            // the one job holding particles (queues not re-binned), or -1
     int blocks, nb, space;     // one workgroup per CU (source, re-binning)
     PassGrid pass[2];    // grid of each pass (fused: the same one)
-    int fused, photon_waves;   // both passes in one launch; its photon-first wavefronts
+    int fused, photon_waves;   // both passes in one launch (2 or 3, see slice_f4; else 0); its photon-first wavefronts
     float blo, binv;
     RunDev R;
     Tables T;
@@ -570,7 +570,7 @@ gdpm_status context_mem(gdpm_context ctx, EngineMem* m) {
 
 int grid_blocks(gdpm_context ctx) { return std::max(1, ctx->cu_count); }
 
-// persistent grid of a transport pass (ri = 2: of both in one launch): one workgroup per
+// persistent grid of a transport pass (ri = 2, 3: of both in one launch): one workgroup per
 // CU of waves_per_cu wavefronts (photons: photon_waves_per_cu), a third more in passes
 // of many records (see PassGrid; not of both in one launch) if the LDS has room; lds: its
 // tables are staged; bricks: the electrons' brick sums have room
@@ -1233,14 +1233,18 @@ gdpm_status Engine::step() {
     k.lone = (k.rebin[0] && k.rebin[1]) ? -1 : lone;
     // both passes in one launch: needs the electron tables staged (the photon
     // tables are read through the caches); not in the one-particle form
-    const PassShape both = pass_shape(ctx, T, 2);
-    k.fused = ctx->fused_passes && !ctx->solo_lanes && both.lds;
-    if (k.fused) {
-        const int waves = (int)both.grid.wide;
-        k.pass[0] = k.pass[1] = both.grid;
-        k.bricks = both.bricks;
-        k.photon_waves = ctx->photon_waves < 0 ? waves / 2 : std::min(ctx->photon_waves, waves);
-        k.lds[0] = 0;
+    if (ctx->fused_passes && !ctx->solo_lanes) {
+        k.fused = 2;
+        PassShape both = pass_shape(ctx, T, k.fused);
+        if (!both.lds) both = pass_shape(ctx, T, k.fused = 3);
+        if (!both.lds) k.fused = 0;
+        if (k.fused) {
+            const int waves = (int)both.grid.wide;
+            k.pass[0] = k.pass[1] = both.grid;
+            k.bricks = both.bricks;
+            k.photon_waves = ctx->photon_waves < 0 ? waves / 2 : std::min(ctx->photon_waves, waves);
+            k.lds[0] = 0;
+        }
     }
     k.R = R;
     k.T = T;
@@ -1342,7 +1346,7 @@ gdpm_status Engine::issue(const StepGraphKey& k) {
     if (k.fused) {
         // both queues set up, then one launch runs both passes
         if ((s = rebin(1))) return s;
-        HIP_TRY(launch_fused(st, (int)k.pass[1].blocks, 64 * (int)k.pass[1].wide, k.photon_waves, k.bricks != 0,
+        HIP_TRY(launch_fused(st, k.fused, (int)k.pass[1].blocks, 64 * (int)k.pass[1].wide, k.photon_waves, k.bricks != 0,
                              k.rebin[0] || k.rebin[1], dc, k.T, k.R));
     } else {
         if ((s = pass(0))) return s;

@@ -1724,11 +1724,14 @@ constexpr uint32_t kBrickF4 = kBrickVoxels * 64u / 2u + 64u * 2u / 16u;
 // columns, and generator words of as many columns more (see photon_pass)
 constexpr uint32_t kPool = 64u, kPhotonCols = 64u + kPool;
 constexpr uint32_t kPoolF4 = 3u * kPool + kPool / 4u;
-// ri: 0 photons, 1 electrons, 2 both (k_transport; its photons have no pool: with one for
-// each wavefront, 12 of them and the electron tables of 4 materials would take 175,248 of
-// the CU's 163,840 bytes)
+// ri: 0 photons, 1 electrons, 2 both (k_transport), 3 both without the photons' pool: with
+// one for each wavefront, 12 of them and the electron tables of 4 materials would take
+// 175,248 of the CU's 163,840 bytes, and without 136,848.  The pool is kept where it fits:
+// with 10 wavefronts, 3e7 photons took 16.7 and 13.9 ms (CTs of 0.2 and 0.4 cm) with it
+// and 17.7 and 14.9 without.
 GDPM_HD uint32_t slice_f4(int ri, bool bricks) {
-    return ri == 0 ? kRngWords * kPhotonCols / 4u + kPoolF4 : kRingF4 + (bricks ? kBrickF4 : 0u);
+    const uint32_t photons = kRngWords * kPhotonCols / 4u + kPoolF4, electrons = kRingF4 + (bricks ? kBrickF4 : 0u);
+    return ri == 0 || (ri == 2 && photons > electrons) ? photons : electrons;
 }
 
 // the device clock at the start of a pass (its completion takes the difference)
@@ -2542,7 +2545,7 @@ __global__ void __launch_bounds__(1024) k_electron(PassArgs) {
 // Each pass reads what its queue held at the set-up: what either pass pushes
 // is transported in the next iteration.
 // ---------------------------------------------------------------------------
-template <bool kPerm>
+template <bool kPerm, bool kPark>
 __global__ void __launch_bounds__(768) k_transport(PassArgs) {
     const Args A = pass_args();
     start_clock(A);
@@ -2551,11 +2554,11 @@ __global__ void __launch_bounds__(768) k_transport(PassArgs) {
     group_clear(group);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ElecLds E = stage_electron_tables(A->T, lds);
-    GDPM_LDS float* ring = (GDPM_LDS float*)(lds + tables_f4(1, A->T) + wave * slice_f4(2, A->bricks));
+    GDPM_LDS float* ring = (GDPM_LDS float*)(lds + tables_f4(1, A->T) + wave * slice_f4(kPark ? 2 : 3, A->bricks));
     for (int k = 0; k < 2; ++k) {
         const bool photons = ((int)wave < A->photon_waves) == (k == 0);
         if (photons)
-            photon_pass<false, kPerm, false, false>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, ring, group);
+            photon_pass<false, kPerm, false, kPark>(A, PhotGlobal{global_f4(A->T.phot)}, nullptr, ring, group);
         else
             electron_pass<false, kPerm>(A, E, ring, group);
     }
@@ -3045,7 +3048,7 @@ hipError_t launch_admit(hipStream_t st, int cus, const JobDev& job, JobDev* jobs
     hipLaunchKernelGGL(k_admit, dim3((unsigned)(need < (size_t)(8 * cus) ? need : (size_t)(8 * cus))), dim3(256), 0, st, a);
     return hipGetLastError();
 }
-// LDS bytes of a pass (ri = 2: both in one launch) with `waves` wavefronts per block
+// LDS bytes of a pass (ri = 2, 3: both in one launch) with `waves` wavefronts per block
 // (lds: its tables staged; bricks: the electrons' brick sums)
 size_t transport_lds_bytes(int ri, const Tables& T, int waves, bool lds, bool bricks) {
     const size_t per_wave = slice_f4(ri, bricks);
@@ -3060,7 +3063,8 @@ hipError_t transport_lds_optin(size_t bytes) {
                              (const void*)k_photon<true, false, true>,  (const void*)k_electron<true, false, true>,
                              (const void*)k_photon<true, true, false>,  (const void*)k_electron<true, true, false>,
                              (const void*)k_photon<true, true, true>,   (const void*)k_electron<true, true, true>,
-                             (const void*)k_transport<false>,           (const void*)k_transport<true>};
+                             (const void*)k_transport<false, false>,    (const void*)k_transport<true, false>,
+                             (const void*)k_transport<false, true>,     (const void*)k_transport<true, true>};
     for (const void* k : kernels) {
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         if (e != hipSuccess) return e;
@@ -3104,15 +3108,14 @@ hipError_t launch_transport(hipStream_t st, int ri, int blocks, int threads, boo
         launch_transport_form<false>(st, ri, blocks, threads, lds, solo, bytes, a);
     return hipGetLastError();
 }
-// both passes in one launch (k_transport)
-hipError_t launch_fused(hipStream_t st, int blocks, int threads, int photon_waves, bool bricks, bool permuted,
+// both passes in one launch (k_transport); ri: 2 or 3, see slice_f4
+hipError_t launch_fused(hipStream_t st, int ri, int blocks, int threads, int photon_waves, bool bricks, bool permuted,
                         Ctl* ctl, const Tables& T, const RunDev& R) {
-    const size_t bytes = transport_lds_bytes(2, T, threads / 64, true, bricks);
+    const size_t bytes = transport_lds_bytes(ri, T, threads / 64, true, bricks);
     const PassArgs a{ctl, T, R, photon_waves, bricks};
-    if (permuted)
-        hipLaunchKernelGGL((k_transport<true>), dim3(blocks), dim3(threads), bytes, st, a);
-    else
-        hipLaunchKernelGGL((k_transport<false>), dim3(blocks), dim3(threads), bytes, st, a);
+    void (*const k)(PassArgs) = ri == 2 ? (permuted ? k_transport<true, true> : k_transport<false, true>)
+                                        : (permuted ? k_transport<true, false> : k_transport<false, false>);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(threads), bytes, st, a);
     return hipGetLastError();
 }
 
