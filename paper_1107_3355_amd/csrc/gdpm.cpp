@@ -581,9 +581,10 @@ struct PassShape {
 PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri) {
     int narrow = ctx->waves_per_cu;
     if (ri == 0 && ctx->photon_waves_per_cu) narrow = std::min(narrow, ctx->photon_waves_per_cu);
-    int waves = ri < 2 ? narrow + narrow / 3 : narrow;
     auto fits = [&](int w, bool lds) { return transport_lds_bytes(ri, T, w, lds, false) <= (size_t)ctx->max_lds; };
-    if (ctx->lds_tables && !fits(waves, true) && fits(narrow, true)) waves = narrow;
+    while (narrow > 1 && !fits(narrow, false)) --narrow;   // (without the opt-in of gdpm_context_create)
+    int waves = ri < 2 ? narrow + narrow / 3 : narrow;
+    if (!fits(waves, false) || (ctx->lds_tables && !fits(waves, true) && fits(narrow, true))) waves = narrow;
     const bool lds = ctx->lds_tables && fits(waves, true);
     const bool bricks = ri != 0 && transport_lds_bytes(ri, T, waves, lds, true) <= (size_t)ctx->max_lds;
     return PassShape{{(uint32_t)grid_blocks(ctx), (uint32_t)waves, (uint32_t)narrow}, lds, bricks};
@@ -1872,10 +1873,11 @@ gdpm_status gdpm_context_create(int hip_device, const char* opts_json, gdpm_cont
         return fail(GDPM_E_INVALID, "photon_waves in [0, waves_per_cu] (or -1: half)");
     HIP_TRY(hipDeviceGetAttribute(&ctx->cu_count, hipDeviceAttributeMultiprocessorCount, hip_device));
     HIP_TRY(hipDeviceGetAttribute(&ctx->max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, hip_device));
-    if (ctx->lds_tables) {
-        // the kernels may use all of it (above 64 KB an opt-in is needed)
-        if (transport_lds_optin((size_t)ctx->max_lds) != hipSuccess) ctx->lds_tables = 0;
+    // The kernels may use all of it; above 64 KB an opt-in is needed, also without tables
+    // (16 wavefronts of the photon pass take 123,008 bytes).
+    if (transport_lds_optin((size_t)ctx->max_lds) != hipSuccess) {
         (void)hipGetLastError();
+        ctx->max_lds = std::min(ctx->max_lds, 1 << 16);
     }
     HIP_TRY(hipStreamCreateWithFlags(&ctx->stream, hipStreamNonBlocking));
     HIP_TRY(ctx->ctl.alloc(sizeof(Ctl)));

@@ -3,6 +3,10 @@ sizes where one form ends and the next begins.  The particles' streams fix every
 history, so the physics events must be the same whole numbers and the doses the
 same up to the order of the FP64 tally additions (a sum of n terms reorders to
 within n ulps; voxel sums here have below 1e4 terms: 1e-12)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -223,3 +227,19 @@ def test_fused_passes(n, n_mat, opts):
     rtol = 2 * max(sum(r["deposits"]) for r in res) * np.finfo(float).eps   # any order of all deposits
     np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
     assert balance(a) < 1e-12
+
+
+# the forms without staged tables take more than 64 KB of LDS too: in a process of their
+# own, where no other context has asked for it
+def test_unstaged_tables_alone(gctx):
+    code = ("from paper_1107_3355_amd import gdpm as G, inputs as I\n"
+            "from tests.gpu_common import gpu_run, physics_events\n"
+            "w = I.water_cube_2mev(40_000)\n"
+            "c = G.Context(0, opts='{\"lds_tables\": 0}', materials=I.MATERIALS)\n"
+            "r = gpu_run(c, w.phantom, w.source, n_hist=40_000, seed=9)\n"
+            "print(physics_events(r))\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                         capture_output=True, text=True, timeout=100)
+    assert out.returncode == 0, out.stderr
+    w = I.water_cube_2mev(40_000)
+    assert out.stdout.strip() == str(physics_events(gpu_run(gctx, w.phantom, w.source, n_hist=40_000, seed=9)))
