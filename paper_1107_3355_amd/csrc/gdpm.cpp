@@ -573,12 +573,17 @@ int grid_blocks(gdpm_context ctx) { return std::max(1, ctx->cu_count); }
 // persistent grid of a transport pass (ri = 2, 3: of both in one launch): one workgroup per
 // CU of waves_per_cu wavefronts (photons: photon_waves_per_cu), a third more in passes
 // of many records (see PassGrid; not of both in one launch) if the LDS has room; lds: its
-// tables are staged; bricks: the electrons' brick sums have room
+// tables are staged; bricks: the electrons' brick sums have room (sums: some job has a
+// tally in bricks).  Electrons give up
+// wavefronts down to waves_per_cu to have the sums beside staged tables: with 5 materials
+// 16 without the sums took 10.0, 6.2 and 12.6 ms (3e7 photons on CTs of 0.2 and 0.4 cm, 3e6
+// electrons on 0.3 cm slabs), 12 with them 8.3, 6.1 and 8.7, and the 13 that fit 8.0, 5.8
+// and 8.6.
 struct PassShape {
     PassGrid grid;
     int lds, bricks;
 };
-PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri) {
+PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri, bool sums) {
     int narrow = ctx->waves_per_cu;
     if (ri == 0 && ctx->photon_waves_per_cu) narrow = std::min(narrow, ctx->photon_waves_per_cu);
     auto fits = [&](int w, bool lds) { return transport_lds_bytes(ri, T, w, lds, false) <= (size_t)ctx->max_lds; };
@@ -586,7 +591,12 @@ PassShape pass_shape(gdpm_context ctx, const Tables& T, int ri) {
     int waves = ri < 2 ? narrow + narrow / 3 : narrow;
     if (!fits(waves, false) || (ctx->lds_tables && !fits(waves, true) && fits(narrow, true))) waves = narrow;
     const bool lds = ctx->lds_tables && fits(waves, true);
-    const bool bricks = ri != 0 && transport_lds_bytes(ri, T, waves, lds, true) <= (size_t)ctx->max_lds;
+    for (int w = waves; sums && lds && ri == 1 && w >= narrow; --w)
+        if (transport_lds_bytes(ri, T, w, true, true) <= (size_t)ctx->max_lds) {
+            waves = w;
+            break;
+        }
+    const bool bricks = sums && ri != 0 && transport_lds_bytes(ri, T, waves, lds, true) <= (size_t)ctx->max_lds;
     return PassShape{{(uint32_t)grid_blocks(ctx), (uint32_t)waves, (uint32_t)narrow}, lds, bricks};
 }
 
@@ -1215,6 +1225,12 @@ gdpm_status Engine::step() {
     k.space = space;
     k.blo = blo;
     k.binv = nb / (bhi - blo);
+    bool sums = false;
+    for (int i = 0; i < n_slots; ++i)
+        if (slots[i] && !slots[i]->done) {
+            const Brick b = slots[i]->brick();
+            sums = sums || b.mx || b.my || b.mz;
+        }
     for (int ri = 0; ri < 2; ++ri) {
         // sort the queue's positions by job (and bin, rebin_bins > 1), dropping
         // empty ones, so that each job's records form a segment of the pass's
@@ -1224,7 +1240,7 @@ gdpm_status Engine::step() {
         // locality), the pass then reads the queue as it is, empty slots included
         k.rebin[ri] = !M.fixed && ((ri == 0 ? ctx->rebin_photons : ctx->rebin_electrons) || holders > 1 || lone < 0);
         if (k.rebin[ri]) tm.passes_rebinned++;
-        const PassShape shape = pass_shape(ctx, T, ri);
+        const PassShape shape = pass_shape(ctx, T, ri, sums);
         k.pass[ri] = shape.grid;
         k.lds[ri] = shape.lds;
         if (ri == 1) k.bricks = shape.bricks;
@@ -1236,8 +1252,8 @@ gdpm_status Engine::step() {
     // tables are read through the caches); not in the one-particle form
     if (ctx->fused_passes && !ctx->solo_lanes) {
         k.fused = 2;
-        PassShape both = pass_shape(ctx, T, k.fused);
-        if (!both.lds) both = pass_shape(ctx, T, k.fused = 3);
+        PassShape both = pass_shape(ctx, T, k.fused, sums);
+        if (!both.lds) both = pass_shape(ctx, T, k.fused = 3, sums);
         if (!both.lds) k.fused = 0;
         if (k.fused) {
             const int waves = (int)both.grid.wide;

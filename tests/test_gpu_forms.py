@@ -243,3 +243,26 @@ def test_unstaged_tables_alone(gctx):
     assert out.returncode == 0, out.stderr
     w = I.water_cube_2mev(40_000)
     assert out.stdout.strip() == str(physics_events(gpu_run(gctx, w.phantom, w.source, n_hist=40_000, seed=9)))
+
+
+# electron passes of many records with tables that leave room for 16, 13 (5 materials)
+# and no wavefronts with brick sums
+@pytest.mark.parametrize("n_mat", [4, 5, 6])
+def test_wide_passes_with_more_materials(n_mat):
+    mats = (list(MATS) + list(MATS))[:n_mat]
+    shape, n = (20, 20, 20), 4_500_000
+    ph = I.Phantom(*shape, 0.1, 0.1, 0.1, (np.arange(8000).reshape(shape) % n_mat).astype(np.uint8),
+                   np.ones(shape, np.float32))
+    src = I.Source(I.ELECTRON, I.mono(0.9), [I.parallel_beam_z(ph, 2.0)])
+    res = []
+    for opts in ('{}', '{"lds_tables": 0, "waves_per_cu": 12, "pass_histories": 500000}'):
+        c = G.Context(0, opts=opts, materials=mats)
+        try:
+            res.append(gpu_run(c, ph, src, n_hist=n, seed=4, n_batches=2))
+        finally:
+            c.close()
+    a, b = res
+    assert physics_events(a) == physics_events(b) and a["interactions"] == b["interactions"]
+    rtol = 2 * max(sum(r["deposits"]) for r in res) * np.finfo(float).eps   # any order of all deposits
+    np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
+    assert balance(a) < 1e-9
