@@ -132,6 +132,9 @@ gdpm_status fail(gdpm_status st, const char* fmt, ...) {
                         #call, hipGetErrorString(e_));                                       \
     } while (0)
 
+// hipMalloc; if memory has run out, once more without the blocks that pools keep
+hipError_t device_malloc(void** p, size_t n);
+
 // device allocation owned by a unique_ptr-like holder
 struct DevBuf {
     void* p = nullptr;
@@ -148,7 +151,7 @@ struct DevBuf {
     hipError_t alloc(size_t n) {
         reset();
         if (n == 0) n = 16;
-        hipError_t e = hipMalloc(&p, n);
+        hipError_t e = device_malloc(&p, n);
         if (e == hipSuccess) bytes = n;
         else p = nullptr;
         return e;
@@ -163,7 +166,8 @@ struct DevBuf {
 // batch of 24.  A block comes back when the job's buffers go, once the device has
 // finished with it: the job's statistics have been reported, or its engine has ended
 // (see ~Engine); at most kMaxHeld bytes are kept, the oldest blocks
-// go first, and all go when the context or a server ends or memory runs out.
+// go first, and all go when the context or a server ends or an allocation of the
+// library, of any context, finds no memory.
 // Jobs of a server end on the server's thread and are released on the caller's,
 // hence the lock.
 struct DevPool {
@@ -176,7 +180,32 @@ struct DevPool {
     std::list<Block> blocks;   // oldest first
     size_t held = 0;
     bool closed = false;
-    ~DevPool() { trim(); }
+    // all pools of the process (locked before a pool is)
+    struct All {
+        std::mutex m;
+        std::vector<DevPool*> pools;
+    };
+    static All& all() {
+        static All* a = new All;   // (pools may outlive static objects)
+        return *a;
+    }
+    DevPool() {
+        std::lock_guard<std::mutex> lk(all().m);
+        all().pools.push_back(this);
+    }
+    DevPool(const DevPool&) = delete;
+    DevPool& operator=(const DevPool&) = delete;
+    ~DevPool() {
+        {
+            std::lock_guard<std::mutex> lk(all().m);
+            all().pools.erase(std::find(all().pools.begin(), all().pools.end(), this));
+        }
+        trim();
+    }
+    static void trim_all() {
+        std::lock_guard<std::mutex> lk(all().m);
+        for (DevPool* p : all().pools) p->trim();
+    }
     void trim() {
         std::lock_guard<std::mutex> lk(m);
         for (auto& b : blocks) (void)hipFree(b.p);
@@ -208,12 +237,7 @@ struct DevPool {
             }
         }
         out->bytes = n;
-        hipError_t e = hipMalloc(&out->p, n);
-        if (e == hipErrorOutOfMemory) {
-            (void)hipGetLastError();
-            trim();
-            e = hipMalloc(&out->p, n);
-        }
+        const hipError_t e = device_malloc(&out->p, n);
         if (e != hipSuccess) *out = Block{nullptr, 0};
         return e;
     }
@@ -236,6 +260,16 @@ struct DevPool {
         return held;
     }
 };
+
+hipError_t device_malloc(void** p, size_t n) {
+    hipError_t e = hipMalloc(p, n);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        DevPool::trim_all();
+        e = hipMalloc(p, n);
+    }
+    return e;
+}
 
 // a job's buffer out of the pool
 struct PoolBuf {

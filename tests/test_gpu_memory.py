@@ -113,3 +113,35 @@ def test_outputs_that_share_an_array(n):
             np.testing.assert_allclose(shared, ref, rtol=1e-9, atol=1e-12 * ref.max())
     finally:
         c.close()
+
+
+def test_kept_memory_is_given_up_for_other_allocations():
+    """With the device full but for half a gibibyte, an allocation that needs what the
+    context keeps of its last job (its tallies: 1.5 GB) gets it."""
+    hip = _hip()
+    c, d = G.Context(0, materials=MATS), G.Context(0, materials=MATS)
+    blocks = []
+    try:
+        ph, src = _water(200, 0.2)
+        p, s = c.phantom(ph), c.source(src)
+        c.run(p, s, n_hist=100, n_batches=24, want_dose=False)
+        d.atomic_rate(1 << 20)
+        spare = C.c_void_p()
+        assert hip.hipMalloc(C.byref(spare), C.c_size_t(256 << 20)) == 0
+        size = 32 << 30
+        while size >= 256 << 20:   # fill the device up to less than that
+            b = C.c_void_p()
+            if hip.hipMalloc(C.byref(b), C.c_size_t(size)) == 0:
+                blocks.append(b)
+            else:
+                hip.hipGetLastError()
+                size //= 2
+        assert hip.hipFree(spare) == 0
+        assert d.atomic_rate(1200 << 20) > 0   # (a buffer of its own, of another context)
+        r = c.run(p, s, n_hist=100, n_batches=2, want_dose=False)
+        assert r["histories"] == 100
+    finally:
+        for b in blocks:
+            hip.hipFree(b)
+        d.close()
+        c.close()
