@@ -298,7 +298,10 @@ typedef struct {
  * nodes at 12 wavefronts), the passes run apart, which t_photon_s shows;
  * 0: the photon pass, then the electron pass).
  * Results do not depend on any of these options (each particle draws from its
- * own random stream), only the speed does. */
+ * own random stream), only the speed does.
+ * A context keeps up to 2 GiB of the device memory of its finished jobs for the
+ * next ones (gdpm_run_noalloc aside), until it or a server on it is destroyed
+ * or an allocation of the library finds no memory. */
 gdpm_status gdpm_context_create(int hip_device, const char* opts_json, gdpm_context* out);
 
 /* The launch settings the context uses now, after any autotuning ("autotune":
@@ -438,7 +441,8 @@ gdpm_status gdpm_run_batch(gdpm_context ctx, int n, const gdpm_job_desc* jobs,
  * budget is admitted when nothing else runs); admitted jobs share every
  * kernel launch (as in gdpm_run_batch) and each leaves as soon as its own
  * uncertainty target or history count is reached, freeing its slot and
- * memory for the next request.  Phantoms, sources and tables stay resident
+ * memory for the next request (memory that the context keeps for it counts
+ * towards the budget too).  Phantoms, sources and tables stay resident
  * on the device.  Jobs must share cutoffs and physics flags (bits 0-5) with
  * the first job submitted. */
 typedef struct gdpm_server_s* gdpm_server;
@@ -449,7 +453,8 @@ typedef struct {
     double footprint_bytes;       /* device bytes held by admitted jobs now */
     double high_water_bytes;      /* largest footprint_bytes so far */
     double resident_bytes;        /* queues, control blocks, tables, phantoms and
-                                     sources of the context */
+                                     sources of the context, and the memory of
+                                     finished jobs that it keeps for the next */
 } gdpm_server_info;
 
 /* max_slots in 1..256; hbm_budget_bytes > 0. */

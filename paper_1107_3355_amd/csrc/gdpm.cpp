@@ -167,7 +167,9 @@ struct DevBuf {
 // finished with it: the job's statistics have been reported, or its engine has ended
 // (see ~Engine); at most kMaxHeld bytes are kept, the oldest blocks
 // go first, and all go when the context or a server ends or an allocation of the
-// library, of any context, finds no memory.
+// library, of any context, finds no memory.  While a server owns the context, what
+// is kept and what its jobs hold stay within the server's budget together.  A block only
+// serves a request of its own size, so that jobs hold what their footprint says.
 // Jobs of a server end on the server's thread and are released on the caller's,
 // hence the lock.
 struct DevPool {
@@ -178,7 +180,8 @@ struct DevPool {
     };
     std::mutex m;
     std::list<Block> blocks;   // oldest first
-    size_t held = 0;
+    size_t held = 0, used = 0; // bytes kept, and bytes taken
+    size_t limit = SIZE_MAX;   // of both together (a server's budget), as long as something is kept
     bool closed = false;
     // all pools of the process (locked before a pool is)
     struct All {
@@ -206,52 +209,64 @@ struct DevPool {
         std::lock_guard<std::mutex> lk(all().m);
         for (DevPool* p : all().pools) p->trim();
     }
+    // frees the oldest blocks until at most n bytes are kept (locked)
+    void keep(size_t n) {
+        while (held > n) {
+            held -= blocks.front().bytes;
+            (void)hipFree(blocks.front().p);
+            blocks.pop_front();
+        }
+    }
     void trim() {
         std::lock_guard<std::mutex> lk(m);
-        for (auto& b : blocks) (void)hipFree(b.p);
-        blocks.clear();
-        held = 0;
+        keep(0);
+    }
+    // what may be kept beside n bytes in use
+    size_t room(size_t n) const { return std::min(kMaxHeld, n < limit ? limit - n : 0); }
+    void set_limit(size_t n) {
+        std::lock_guard<std::mutex> lk(m);
+        limit = n;
+        keep(room(used));
     }
     void close() {
         trim();
         std::lock_guard<std::mutex> lk(m);
         closed = true;
     }
-    // the smallest kept block of n to 2 n bytes (a megabyte more for small
-    // ones), or a new one
+    // a kept block of this size (rounded up), or a new one
     hipError_t take(size_t n, Block* out) {
         const size_t grain = n > ((size_t)1 << 20) ? (size_t)1 << 16 : 4096;
         n = (std::max<size_t>(n, 1) + grain - 1) / grain * grain;
         {
             std::lock_guard<std::mutex> lk(m);
-            auto best = blocks.end();
             for (auto it = blocks.begin(); it != blocks.end(); ++it)
-                if (it->bytes >= n && it->bytes <= 2 * n + ((size_t)1 << 20) &&
-                    (best == blocks.end() || it->bytes < best->bytes))
-                    best = it;
-            if (best != blocks.end()) {
-                *out = *best;
-                held -= best->bytes;
-                blocks.erase(best);
-                return hipSuccess;
-            }
+                if (it->bytes == n) {
+                    *out = *it;
+                    held -= n;
+                    used += n;
+                    blocks.erase(it);
+                    return hipSuccess;
+                }
+            used += n;
+            keep(room(used));
         }
         out->bytes = n;
         const hipError_t e = device_malloc(&out->p, n);
-        if (e != hipSuccess) *out = Block{nullptr, 0};
+        if (e != hipSuccess) {
+            *out = Block{nullptr, 0};
+            std::lock_guard<std::mutex> lk(m);
+            used -= n;
+        }
         return e;
     }
     void give(Block b) {
         std::lock_guard<std::mutex> lk(m);
-        if (closed || b.bytes > kMaxHeld) {
+        used -= b.bytes;
+        if (closed || b.bytes > room(used)) {
             (void)hipFree(b.p);
             return;
         }
-        while (held + b.bytes > kMaxHeld) {
-            held -= blocks.front().bytes;
-            (void)hipFree(blocks.front().p);
-            blocks.pop_front();
-        }
+        keep(room(used) - b.bytes);
         held += b.bytes;
         blocks.push_back(b);
     }
@@ -1814,6 +1829,7 @@ void gdpm_server_s::loop() {
         if (running.empty()) {
             if (stop && pending.empty()) {
                 ctx->pool->trim();
+                ctx->pool->set_limit(SIZE_MAX);
                 break;
             }
             cv_work.wait(lk, [&] { return stop || !pending.empty(); });
@@ -2442,10 +2458,12 @@ gdpm_status gdpm_server_create(gdpm_context ctx, uint64_t hbm_budget_bytes, int 
     srv->budget = hbm_budget_bytes;
     srv->max_slots = max_slots;
     ctx->busy = true;
+    ctx->pool->set_limit(hbm_budget_bytes);
     try {
         srv->th = std::thread([s = srv.get()] { s->loop(); });
     } catch (...) {
         ctx->busy = false;
+        ctx->pool->set_limit(SIZE_MAX);
         return fail(GDPM_E_NOMEM, "cannot start the server thread");
     }
     *out = srv.release();

@@ -145,3 +145,37 @@ def test_kept_memory_is_given_up_for_other_allocations():
             hip.hipFree(b)
         d.close()
         c.close()
+
+
+def test_server_budget_holds_kept_memory():
+    """What a context keeps of finished jobs stays within the budget of the server that
+    owns it, together with what the running jobs hold, also where their sizes differ."""
+    hip = _hip()
+
+    def free():
+        a, b = C.c_size_t(), C.c_size_t()
+        assert hip.hipMemGetInfo(C.byref(a), C.byref(b)) == 0
+        return a.value
+
+    budget, slack = 300 << 20, 24 << 20   # slack: the runtime's own allocations
+    c = G.Context(0, materials=MATS)
+    try:
+        ph, src = _water(128, 0.25)   # 16.8 MB an array
+        p, s = c.phantom(ph), c.source(src)
+        c.run(p, s, n_hist=1000, n_batches=2)     # queues
+        G.Server(c, budget).close()               # gives back what is kept
+        base = free()
+        c.run(p, s, n_hist=1000, n_batches=50, want_dose=False)   # 872 MB, kept
+        assert base - free() > 2 * budget
+        with G.Server(c, budget) as srv:
+            assert base - free() <= budget + slack
+            for nb in (14, 7, 9, 12, 4, 13):
+                jobs = [srv.submit(p, s, n_hist=200_000, n_batches=nb, seed=k) for k in range(3)]
+                for j in jobs:
+                    assert base - free() <= budget + slack, nb
+                    assert j.wait()["histories"] == 200_000
+                assert base - free() <= budget + slack, nb
+            assert srv.info()["high_water_bytes"] <= budget
+        assert base - free() <= slack
+    finally:
+        c.close()
