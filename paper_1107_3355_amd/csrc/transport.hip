@@ -1213,7 +1213,8 @@ GDPM_DEV void setup_pass(Ctl* ctl, const RunDev& R, int ri, int rebinned, int lo
         r.group_waves = group_waves;
         const uint32_t claim = claim_size(count, waves, ri);
         r.first = rebinned ? 0u : claim;
-        r.push = min(max(claim, kPushMin), kPushMax);
+        // (the slots that all wavefronts leave unused are no more with `wide` of them)
+        r.push = min(max(claim, kPushMin), kPushMax * grid.narrow / group_waves);
         r.next_head = r.tail;
         if (!perm) r.permuted = 0u;
     }

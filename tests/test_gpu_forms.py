@@ -266,3 +266,20 @@ def test_wide_passes_with_more_materials(n_mat):
     rtol = 2 * max(sum(r["deposits"]) for r in res) * np.finfo(float).eps   # any order of all deposits
     np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
     assert balance(a) < 1e-9
+
+
+# the slots that wavefronts reserve and leave unused, 128 each on average with 12 per CU: a
+# queue of 2^23 records has room for them beside one electron of each of 7.93e6 photons
+# (0.39e6 slots), with 16 wavefronts as well
+def test_reserved_slots_of_wide_passes():
+    n = 7_930_000
+    ph = I.homogeneous((16, 16, 16), (1.0,) * 3, I.ID_BONE, 2.0e4)
+    src = I.Source(I.PHOTON, I.mono(0.3), [I.parallel_beam_z(ph, 8.0)])
+    c = G.Context(0, opts=f'{{"ring_capacity_log2": 23, "pass_histories": {n}}}', materials=MATS)
+    try:
+        r = gpu_run(c, ph, src, n_hist=n, seed=2, n_batches=2,
+                    flags=G.NO_COMPTON | G.NO_PAIR | G.NO_MOLLER | G.NO_BREMS, want_dose=False)
+    finally:
+        c.close()
+    assert r["events"]["pushes"] == r["interactions"]["photo"] > 0.99 * n
+    assert balance(r) < 1e-9
