@@ -793,17 +793,6 @@ struct WJob {
     uint32_t seg_begin, seg_count;   // the job's records in the running pass
 };
 
-template <class T>
-GDPM_DEV T uniform_copy(const T& v) {
-    static_assert(sizeof(T) % 4 == 0, "word-sized fields");
-    T out;
-    const uint32_t* a = reinterpret_cast<const uint32_t*>(&v);
-    uint32_t* b = reinterpret_cast<uint32_t*>(&out);
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) b[i] = __builtin_amdgcn_readfirstlane(a[i]);
-    return out;
-}
-
 GDPM_DEV void load_job(WJob& w, Args A, int j, int ri) {
     j = __builtin_amdgcn_readfirstlane(j);
     w.p = (JobPtr)A->R.jobs + j;

@@ -283,3 +283,27 @@ def test_reserved_slots_of_wide_passes():
         c.close()
     assert r["events"]["pushes"] == r["interactions"]["photo"] > 0.99 * n
     assert balance(r) < 1e-9
+
+
+# 64 lanes for a chain: a segment of 70 steps of every chain and a few histories more, and
+# the next one, whose chains start at other steps
+def test_metropolis_64_lanes(gctx):
+    n, chains = 2_300_007, 16_384
+    segment = -(-n // 2)                  # two batches
+    lanes = 1
+    while lanes < 64 and 2 * lanes <= segment // chains:
+        lanes *= 2
+    assert lanes == 64
+    ph = I.ct_phantom((32, 32, 16), (1.5, 1.5, 2.0))
+    src = I.Source(I.PHOTON, I.triangular_spectrum(), I.imrt_plan(ph, nb=6), beamlet_sampler=1)
+    kw = dict(n_hist=n, seed=5, n_batches=2, hist0=123)
+    a = gpu_run(gctx, ph, src, **kw)
+    c = G.Context(0, opts=f'{{"pass_histories": {chains - 1}}}', materials=MATS)   # one step at a time
+    try:
+        b = gpu_run(c, ph, src, **kw)
+    finally:
+        c.close()
+    assert physics_events(a) == physics_events(b) and a["interactions"] == b["interactions"]
+    rtol = 2 * max(sum(r["deposits"]) for r in (a, b)) * np.finfo(float).eps   # any order of all deposits
+    np.testing.assert_allclose(a["dose"], b["dose"], rtol=rtol, atol=rtol * b["dose"].max())
+    assert balance(a) < 1e-12
