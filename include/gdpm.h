@@ -235,7 +235,8 @@ typedef struct {
 /* Create a context on HIP device `hip_device`.  opts_json may be NULL or a
  * flat JSON object with any of: "ring_capacity_log2" (queue records per type,
  * 2^k, default 25), "waves_per_cu" (wavefronts of the persistent workgroup
- * each CU runs, 1..12, default 12; passes of many records run a third more),
+ * each CU runs, 1..12, default 12; passes of many records run up to a third
+ * more, as the LDS has room),
  * "photon_waves_per_cu" (the same for the
  * photon pass alone, at most waves_per_cu, 0..12, default 0: waves_per_cu),
  * "rebin_bins" (bins per job of the queue re-binning, 0..64, default 1:

@@ -8,7 +8,8 @@ namespace gdpm {
 
 constexpr int kMaxMaterials = 8;
 constexpr uint32_t kPushMin = 32;       // ring slots a wavefront reserves at a time: its
-constexpr uint32_t kPushMax = 256;      // first claim of the pass, within these bounds
+constexpr uint32_t kPushMax = 256;      // first claim of the pass, within these bounds (the upper
+                                        // one for narrow passes, see setup_pass)
 constexpr uint32_t kClaimMin = 32;      // smallest number of queue items a wavefront claims
                                         // with one atomic, and the largest, per particle type:
 constexpr uint32_t kClaimMaxPhoton = 2048;   // a photon record lasts a few short iterations, so
@@ -63,10 +64,6 @@ struct alignas(16) Particle {
 };
 static_assert(sizeof(Particle) == 64, "particle record is 64 bytes");
 
-// One queue (ring buffer of 2^k records, indices wrap modulo 2^32).  Counters
-// that many wavefronts add to have a cache line of their own each: additions to
-// one line are served one after the other (85 million a second, whatever the
-// address in it), and readers of its other words wait with them.
 // The wavefronts of a pass: `wide` per workgroup are launched, and if the pass has
 // fewer than kWideMin records for each of their lanes, or kWideMinJob in each job,
 // only the first `narrow` of them work.  16 wavefronts per CU instead of 12 hide more of
@@ -82,6 +79,10 @@ struct PassGrid {
     uint32_t blocks, wide, narrow;
 };
 
+// One queue (ring buffer of 2^k records, indices wrap modulo 2^32).  Counters
+// that many wavefronts add to have a cache line of their own each: additions to
+// one line are served one after the other (85 million a second, whatever the
+// address in it), and readers of its other words wait with them.
 struct alignas(128) RingCtl {
     uint32_t tail;                   // records in [head, tail); wavefronts reserve slots here
     uint32_t pad0[31];

@@ -520,7 +520,7 @@ struct gdpm_source_s {
 
 namespace {
 
-constexpr int kMaxWaves = 12;           // wavefronts of the transport kernels' workgroups (launch bound)
+constexpr int kMaxWaves = 12;           // largest waves_per_cu (a third more is 16, the kernels' launch bound)
 constexpr int kMaxGrid = 8192;          // nodes of an interpolation grid
 constexpr size_t kMaxStepGraphs = 32;   // launch settings an engine remembers
 uint64_t pow2_at_least(uint64_t n, uint64_t lo) {

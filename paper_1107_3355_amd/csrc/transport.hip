@@ -1744,9 +1744,10 @@ GDPM_DEV bool group_idle(Args A, int ri) {
 // is read from global memory); ring: the wavefront's generator words and its pool (kPark; without it a
 // lane waits in passes of any length).
 //
-// Vector instructions bound the pass (two thirds of the cycles), and half of them sample
-// interactions, which come in one of four flights.  Sampled as soon as 22 lanes had one,
-// they ran on 26 of 64 lanes and the flights on 50, since the lanes of those waited.
+// Without the pool, vector instructions were issued in two thirds of the cycles, half of
+// them to sample interactions, which come in one of four flights: sampled as soon as 22
+// lanes had one, they ran on 26 of 64 lanes and the flights on 50, since the lanes of those
+// waited.
 // In a pass with several photons per lane they are parked instead, in a pool of 64
 // photons in LDS, and the lane goes on with another photon, until there is one for each
 // lane; then the wavefront exchanges the photons in its lanes for parked ones, samples
@@ -1757,6 +1758,10 @@ GDPM_DEV bool group_idle(Args A, int ri) {
 // of the generator words goes with it): generated again, they took what the fuller
 // lanes gave.  In a pass with few photons a lane waits: they end before the pool fills,
 // and the exchange cost 8% of it (1e5 photons).
+// What bounds the pass now are the latencies of the voxel reads and, on fine grids, the
+// lines that they fetch (13.3 GB in a launch of 2.06 ms on the CT of 0.2 cm): vector
+// instructions are issued in 43% of the cycles there, 52% on 0.4 cm, 42% on slabs, on 70 to
+// 74% of the lanes.
 template <bool kSolo, bool kPerm, bool kMajLds, bool kPark, class PT>
 GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS float* ring, GroupPtr group) {
     const GDPM_CONST RingCtl* rc = ring_const(A0, 0);
@@ -2127,8 +2132,8 @@ __global__ void __launch_bounds__(1024) k_photon(PassArgs) {
 // for 16 with it: what took 15.9, 10.2, 4.6 and 18.4 ms (5e7 photons on CTs of 0.2 and
 // 0.4 cm, 2e7 photons and 5e6 electrons on 0.3 cm slabs) took 13.1, 9.9, 4.4 and 12.5
 // with the former and takes 12.5, 8.9, 4.0 and 13.8 with the latter.  What bounds it now is
-// vector instructions (71% of the cycles) with half of their lanes at work, and
-// the latencies between them.
+// vector instructions (78, 83, 95 and 69% of the cycles in the four) with half of their
+// lanes at work, and the latencies between them.
 template <bool kSolo, bool kPerm, class EL>
 GDPM_DEV void electron_pass(Args A0, const EL E, GDPM_LDS float* ring, GroupPtr group) {
     GDPM_LDS double* const sums = (GDPM_LDS double*)(ring + 4u * kRingF4);
@@ -2531,7 +2536,10 @@ __global__ void __launch_bounds__(1024) k_electron(PassArgs) {
 // the other.  The photon pass mostly waits on its random voxel reads and the
 // electron pass mostly issues vector instructions, so a CU runs one while the
 // other waits.  The electron tables are in
-// LDS; the photon cross sections and majorants are read through the caches.
+// LDS; the photon cross sections and majorants are read through the caches; the photons
+// have their pool where it fits (kPark, see slice_f4).  Measured slower than the passes
+// apart: 16.5, 13.7, 1.13 and 10.7 ms instead of 13.7, 10.6, 1.11 and 10.4 (3e7 photons on
+// CTs of 0.2 and 0.4 cm, 3e5 on the latter, 3e6 electrons on slabs).
 // Each pass reads what its queue held at the set-up: what either pass pushes
 // is transported in the next iteration.
 // ---------------------------------------------------------------------------
