@@ -1759,9 +1759,8 @@ GDPM_DEV bool group_idle(Args A, int ri) {
 // lanes gave.  In a pass with few photons a lane waits: they end before the pool fills,
 // and the exchange cost 8% of it (1e5 photons).
 // What bounds the pass now are the latencies of the voxel reads and, on fine grids, the
-// lines that they fetch (13.3 GB in a launch of 2.06 ms on the CT of 0.2 cm): vector
-// instructions are issued in 43% of the cycles there, 52% on 0.4 cm, 42% on slabs, on 70 to
-// 74% of the lanes.
+// lines that they fetch (6.5 TB/s on the CT of 0.2 cm): vector instructions are issued in
+// 43% of the cycles there, 52% on 0.4 cm, 42% on slabs, on 70 to 74% of the lanes.
 template <bool kSolo, bool kPerm, bool kMajLds, bool kPark, class PT>
 GDPM_DEV void photon_pass(Args A0, const PT ptab, const GDPM_LDS float* lmaj, GDPM_LDS float* ring, GroupPtr group) {
     const GDPM_CONST RingCtl* rc = ring_const(A0, 0);
